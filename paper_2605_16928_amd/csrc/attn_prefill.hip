@@ -455,20 +455,22 @@ __global__ __launch_bounds__(kSelThreads, 2) void prefill_select_kernel(const Pr
   const int tw = t0 + qgroup * 32;                                 // first query of the group
   const bool idle = tw >= a.n_q;                                   // no query in this group (the wave still goes to the barriers)
   const int pos0 = (int)a.q_start_host;
-  const int t = tw + r;
-  const bool qok = t < a.n_q;
+  // The lanes past the last query of a partial group repeat that query (their results are not stored): every lane
+  // then has a causal range that ends where its group's does, and the group's interior tiles need no mask.  (Masking
+  // those lanes instead puts the whole range of a partial group on the masked path of one wave: the search takes 10.7 against 0.9 ms
+  // for a chunk of 333 queries behind 131072 tokens.)
+  const bool qok = tw + r < a.n_q;
+  const int t = max(min(tw + r, a.n_q - 1), 0);
   const int m = pos0 + t;
   const float ninf = -__builtin_huge_valf(), pinf = __builtin_huge_valf();
   const float cs = a.index_scale;
   const uint16_t* kIg = a.kI + (int64_t)j * a.kI_head_stride;
-  u32x4 qIreg = (u32x4){0u, 0u, 0u, 0u};
-  if (qok) qIreg = *reinterpret_cast<const u32x4*>(a.qI + ((int64_t)j * a.n_q + t) * kIndexDim + g * 8);
+  const u32x4 qIreg = *reinterpret_cast<const u32x4*>(a.qI + ((int64_t)j * a.n_q + t) * kIndexDim + g * 8);
   const int n_rows = pos0 + a.n_q;                                 // index-key rows that exist
   const int m_wave_lo = pos0 + tw;
   const int m_wave_hi = pos0 + min(tw + 32, a.n_q) - 1;
-  const bool wave_partial = tw + 32 > a.n_q;
   const int n_tiles = idle ? 0 : m_wave_hi / 32 + 1;
-  const int n_interior = (wave_partial || idle) ? 0 : (m_wave_lo + 1) / 32;  // tiles with nb + 31 <= m_wave_lo
+  const int n_interior = idle ? 0 : (m_wave_lo + 1) / 32;          // tiles with nb + 31 <= m_wave_lo
   double (*hist)[32] = hist_all[qgroup];
   float (*lst)[64] = list_all[wave];
   // this group's row of the tile-maximum table: written in sweep 0 (one entry per pair of key tiles, i.e. per 64
@@ -532,7 +534,7 @@ __global__ __launch_bounds__(kSelThreads, 2) void prefill_select_kernel(const Pr
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const int n = nb + (i >> 2) * 8 + g * 4 + (i & 3);
-        v[i] = (!edge || (qok && n <= m)) ? SI[i] : ninf;
+        v[i] = (!edge || n <= m) ? SI[i] : ninf;
       }
 #pragma unroll
       for (int st = 8; st > 0; st >>= 1)
@@ -549,7 +551,7 @@ __global__ __launch_bounds__(kSelThreads, 2) void prefill_select_kernel(const Pr
         const float tt8 = sel_t(selM8, SI[i], cs8);
         // a repeated sweep takes the candidates at or below the lowered reference only (the others were
         // counted above the open-ended bin); a query that does not repeat has reference -inf and takes none
-        const bool cand = (!edge || (qok && n <= m)) && (phase == 1 || tt8 >= 0.f);
+        const bool cand = (!edge || n <= m) && (phase == 1 || tt8 >= 0.f);
         if (cand) {
           // first digit of q: floor(min(tt * 2^17, 2^21 - 1)) >> 14 == floor(min(tt * 8, (2^21 - 1) / 2^14))
           const int bin = (int)fminf(tt8, 127.99993896484375f);
@@ -569,7 +571,7 @@ __global__ __launch_bounds__(kSelThreads, 2) void prefill_select_kernel(const Pr
       auto member = [&](int i) {
         const int n = nb + (i >> 2) * 8 + g * 4 + (i & 3);
         const bool in = __builtin_amdgcn_fmed3f(SI[i], x_lo, x_top) == SI[i];
-        return edge ? (in && qok && n <= m) : in;
+        return edge ? (in && n <= m) : in;
       };
       bool go = true;
       float reach = 0.f;
@@ -588,7 +590,7 @@ __global__ __launch_bounds__(kSelThreads, 2) void prefill_select_kernel(const Pr
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
           const int n = nb + (i >> 2) * 8 + g * 4 + (i & 3);
-          v[i] = (!edge || (qok && n <= m)) ? SI[i] : ninf;
+          v[i] = (!edge || n <= m) ? SI[i] : ninf;
         }
 #pragma unroll
         for (int st = 8; st > 0; st >>= 1)
@@ -701,9 +703,11 @@ __global__ __launch_bounds__(kSelThreads, 2) void prefill_select_kernel(const Pr
     }
   };
   const int n_plain = n_interior / (2 * kSelRing) * (2 * kSelRing);   // whole rounds of interior tiles run without masks
-  // this wave's share: an equal run of the mask-free rounds; the last wave of the group also takes the edge
-  const int rounds = n_plain / (2 * kSelRing);
-  const int plain_lo = (rounds * part / KS) * (2 * kSelRing), plain_hi = (rounds * (part + 1) / KS) * (2 * kSelRing);
+  // this wave's share: an equal run of the rounds, the masked ones of the edge (one or two) at the end
+  const int plain_rounds = n_plain / (2 * kSelRing), rounds = (n_tiles + 2 * kSelRing - 1) / (2 * kSelRing);
+  const int round_lo = rounds * part / KS, round_hi = rounds * (part + 1) / KS;
+  const int plain_lo = min(round_lo, plain_rounds) * (2 * kSelRing), plain_hi = min(round_hi, plain_rounds) * (2 * kSelRing);
+  const int edge_lo = max(round_lo, plain_rounds) * (2 * kSelRing), edge_hi = round_hi * (2 * kSelRing);
   // Sweeps 2 and 3 over the mask-free range, 512 tiles (256 entries of the maximum table) at a time: where at most
   // a quarter of the tile pairs can hold a member, only those are fetched and looked at -- with a peaked score
   // law that is a handful of pairs in a million keys --; otherwise the streaming sweep above runs over the stretch,
@@ -763,7 +767,7 @@ __global__ __launch_bounds__(kSelThreads, 2) void prefill_select_kernel(const Pr
     constexpr int phase_ = decltype(PH)::value;
     if constexpr (phase_ == 2 || phase_ == 3) sweep_picked(PH, plain_lo, plain_hi);
     else sweep(PH, std::false_type{}, std::false_type{}, plain_lo, plain_hi);
-    if (part == KS - 1) sweep(PH, std::true_type{}, std::true_type{}, n_plain, n_tiles);
+    sweep(PH, std::true_type{}, std::true_type{}, edge_lo, edge_hi);
     if (phase_ == 2 || phase_ == 3) drain_list();
   };
 
@@ -819,7 +823,7 @@ __global__ __launch_bounds__(kSelThreads, 2) void prefill_select_kernel(const Pr
     }
     if (round == 0 || repeat_me) scan((double)a.p * Z);
     // the threshold in the open-ended bin: everything above it is counted (cum), its members go round again
-    repeat_me = (round == 0 || repeat_me) && !idle && qok && bsel == kSelBins - 1 && hsel > 0.0 && round + 1 < kSelMaxRounds;
+    repeat_me = (round == 0 || repeat_me) && !idle && bsel == kSelBins - 1 && hsel > 0.0 && round + 1 < kSelMaxRounds;
     // does any query of the workgroup repeat?  (flags in the lists' memory, idle in this phase; the barrier also
     // says that every wave has read the histograms)
     int* flags = reinterpret_cast<int*>(&list_all[0][0][0]);
@@ -859,8 +863,8 @@ __global__ __launch_bounds__(kSelThreads, 2) void prefill_select_kernel(const Pr
     // rounding error of M = max * scale and may be a hair below zero (a lowered reference keeps its bound:
     // what lies above it has been counted)
     if (qlo == 0 && !rebased) x_top = pinf;
-    xlo_wave = -wave_max_f32((qok && !idle) ? -x_lo : ninf);
-    xlo_wave_top = wave_max_f32((qok && !idle) ? x_lo : ninf);
+    xlo_wave = -wave_max_f32(idle ? ninf : -x_lo);
+    xlo_wave_top = wave_max_f32(idle ? ninf : x_lo);
     shift -= 7;                                                     // of this sweep's digit: 7, then 0
     zero_hist();
     __syncthreads();

@@ -369,3 +369,12 @@ def test_sparse_prefill_threshold_far_below_the_row_maximum(scale, p):
     deep = [r["sel"]["smax"] - r["sel"]["tau"] for r in ref]
     assert max(deep) > 15.875 and (scale > 2.75 or np.median(deep) > 15.875), deep
     assert all(r["sel"]["count"] < r["m"] + 1 for r in ref)
+
+
+@pytest.mark.parametrize("chunk_start,T", [(0, 1), (0, 33), (255, 31), (256, 65), (1000, 97), (2047, 33)])
+def test_sparse_prefill_partial_query_groups(chunk_start, T):
+    """Chunks whose last 32-query group is partial, with causal ranges that end on, one before and one behind the edges of
+    the search's key tiles (32) and rounds (256): the group's spare lanes repeat its last query and must leave no trace."""
+    print(f"[case] sparse prefill, partial group, T {T} behind {chunk_start}", flush=True)
+    w = wl.small_prefill(DEV, p=0.9, chunk_start=chunk_start, T=T, seed=101 + T)
+    _check_sparse_prefill(w, f"partial_{chunk_start}_{T}", 0.9)
