@@ -89,8 +89,8 @@ constexpr float kSelScale = 131072.0f;
 constexpr int kSelQMax = (1 << 21) - 1;
 constexpr int kTileHalfs = kPfK * kKsStride + kHeadDim * kVtStride;   // bf16 elements of one staged K + V^T tile
 constexpr int kSmemDense = kTileHalfs * 2 * 2;                        // two buffers
-constexpr int kSelListCap = 16;      // entries per lane: what one tile can add (lists are emptied after every tile)
-constexpr int kSelMfma = 2;          // index-score MFMAs of a wave in flight (the SIMD's other wave covers their latency)
+constexpr int kSelListCap = 24;      // entries per lane of the member lists: with the histogram 80 KB, two workgroups per compute unit
+constexpr int kSelMfma = 2;          // index-score MFMAs of a wave in flight (the SIMD's other waves cover their latency)
 constexpr int kSelRing = 4;          // index-key tiles in flight per wave during the threshold search
 
 __device__ __forceinline__ int sel_q_of_t(float tt) {       // tt = M - s >= 0
@@ -359,6 +359,19 @@ __global__ __launch_bounds__(kPfThreads, 2) void flash_prefill_kernel(const Pref
   }
 }
 
+// Largest of 16 matrix-core results, none NaN: medians for the first of each half (they make the compiler wait for the
+// matrix core, which it does not do for operands of an assembly statement), then three-operand maxima -- the compiler
+// has no way to one that does not first canonicalise every operand.
+__device__ __forceinline__ float max16_nn(const float (&v)[16]) {
+  float a = max_nn(v[0], v[1]), b = max_nn(v[2], v[3]);
+#pragma unroll
+  for (int i = 4; i < 16; i += 4) {
+    asm("v_max3_f32 %0, %0, %1, %2" : "+v"(a) : "v"(v[i]), "v"(v[i + 1]));
+    asm("v_max3_f32 %0, %0, %1, %2" : "+v"(b) : "v"(v[i + 2]), "v"(v[i + 3]));
+  }
+  return max_nn(a, b);
+}
+
 // ---- per-query top-p threshold search (selecting mode of rtp_sparse_attn_prefill) ---------------------
 // Sec. 3.2, S = Top-P(s(m, .), p), applied to every prefill query over its causal candidates n <= m.
 //
@@ -370,8 +383,7 @@ __global__ __launch_bounds__(kPfThreads, 2) void flash_prefill_kernel(const Pref
 // x 32 queries is ONE MFMA (K = 16) in the transposed layout, so a lane holds 16 keys of its own query.
 //
 // What makes the sweeps cheap:
-//  - index keys are fetched kSelRing tiles ahead into registers (two waves share a SIMD: not enough to
-//    hide a load's latency by themselves);
+//  - index keys are fetched kSelRing tiles ahead into registers, through a scalar base address;
 //  - interior tiles (every key a candidate of every query of the wave) carry no mask arithmetic;
 //  - the histogram of a group is laid out [bin][query]: the 32 queries of a wave sit in 32 different
 //    LDS bank pairs whatever their bins, so an fp64 LDS atomic of the wave sees only the two-way
@@ -379,8 +391,8 @@ __global__ __launch_bounds__(kPfThreads, 2) void flash_prefill_kernel(const Pref
 //  - q is a monotone function of the raw MFMA product x (s = x * index_scale), so "q lies in the digit
 //    prefix" is an interval of x.  Its two end points are found once per query and sweep by bisection
 //    over the float bit patterns, evaluating the very expression that defines q -- the comparisons of
-//    sweeps 2, 3 and of the attention kernel are then exact restatements of that definition, two
-//    (one) compare per pair, and only members do any further arithmetic;
+//    sweeps 2, 3 and of the attention kernel are then exact restatements of that definition, and only members
+//    do any further arithmetic;
 //  - sweep 0 records the largest product of the group in every pair of key tiles, and sweeps 2 and 3 -- whose
 //    members all lie at or above a known bound -- pass over the pairs that cannot hold one.
 // t = M - x * index_scale as ONE fused operation (one rounding): the definition every sweep, the end points
@@ -388,28 +400,44 @@ __global__ __launch_bounds__(kPfThreads, 2) void flash_prefill_kernel(const Pref
 __device__ __forceinline__ float sel_t(float M, float x, float index_scale) { return __builtin_fmaf(-x, index_scale, M); }
 
 // Smallest float x (as a raw product) with sel_t(M, x) < bound; -inf if every finite x qualifies.
-// sel_t is non-increasing in x, so the predicate flips once from false to true.
+// sel_t is non-increasing in x, so the predicate flips once from false to true.  The exact-arithmetic solution is a few
+// ulps of the larger operand away from the flip: two probes on either side of it usually leave a handful of
+// bisection steps of the 32 (a probe only ever narrows the bracket, so a poor guess costs time and nothing else).
 __device__ __forceinline__ float sel_first_below(float M, float index_scale, float bound) {
   if (bound == __builtin_huge_valf()) return -__builtin_huge_valf();
   uint32_t lo = float_key(-__builtin_huge_valf()), hi = float_key(__builtin_huge_valf());
-  while (lo < hi) {
-    const uint32_t mid = lo + ((hi - lo) >> 1);
-    if (sel_t(M, key_float(mid), index_scale) < bound) hi = mid; else lo = mid + 1;
+  auto probe = [&](uint32_t k) {
+    if (sel_t(M, key_float(k), index_scale) < bound) hi = k; else lo = k + 1;
+  };
+  const float guess = (M - bound) / index_scale;
+  if (fabsf(guess) < 1e30f) {
+    const uint32_t kg = float_key(guess);
+#pragma unroll
+    for (uint32_t d = 4096; d >= 32; d >>= 7) {
+      if (kg - d > lo && kg - d < hi) probe(kg - d);
+      if (kg + d > lo && kg + d < hi) probe(kg + d);
+    }
   }
+  while (lo < hi) probe(lo + ((hi - lo) >> 1));
   return key_float(lo);
 }
 
 //
-// KS waves share one group of 32 queries and split its key range between them; a workgroup is eight waves -- two
-// per SIMD, so that one wave's vector instructions issue under the other's latencies -- i.e. 8 / KS groups.  The
-// waves of a group add into ONE histogram (LDS atomics; 32 KB per group); the per-lane member lists of sweeps 2
-// and 3 hold one tile's worth of entries (16) and are emptied after every tile that added one.  All waves of the
-// workgroup meet at barriers around every scan, so the phases are uniform over the workgroup.
-// The library launches KS = 8, one group per workgroup: on score laws that keep thousands of tokens per query it
-// runs as fast as two or four groups per workgroup (25.6 ms against 25.7 and 25.6 on the last 8192-query chunk of
-// a 1,048,576-token context), and when a few queries of a chunk have their threshold deep in the background
-// while the others' sweeps 2 and 3 visit a handful of tiles, short workgroups in four times the number let the
-// dispatcher even the load out (19.0 ms against 24.1).
+// KS waves share one group of 32 queries and split its key range between them; a workgroup is eight waves, i.e.
+// 8 / KS groups, and 128 vector registers and 80 KB of LDS let two workgroups share a compute unit: four waves per
+// SIMD issue under each other's latencies (with two, 221 registers and loads two rounds of eight tiles ahead, the search
+// took 23.7 ms on the last 8192-query chunk of a 1,048,576-token context, 18.2 now; the same code held to 128
+// registers 19.4).  The waves of a group add into ONE histogram (LDS atomics; 32 KB per group); the per-lane member
+// lists of sweeps 2 and 3 are emptied when a half tile might overrun one.  All waves of the workgroup meet at
+// barriers around every scan, so the phases are uniform over the workgroup.
+// What bounds the sweeps there: sweep 0 (2.4 ms) and sweep 3 (2.0, was 4.0) their vector instructions per tile; sweep 1
+// (7.4, was 9.3) the LDS atomics -- an fp64 one holds the compute unit's LDS for 8.4 cycles, i.e. 34 per SIMD and wave of
+// 64 pairs, as many as its seven vector instructions take --; sweep 2 (6.3, was 8.2) the LDS stores (4.3 cycles
+// each whatever the number of lanes) and draining the lists.  Skipping the stores of the pairs without a member by a
+// branch measured slower (7.5).
+// The library launches KS = 8, one group per workgroup: when a few queries of a chunk have their threshold deep in the
+// background while the others' sweeps 2 and 3 visit a handful of tiles, short workgroups let the dispatcher even
+// the load out.
 //
 // A threshold inside the open-ended last coarse bin (candidates 15.875 or more below the row maximum) is not
 // taken as "keep everything": the workgroup repeats sweep 1 with the reference lowered by 15.875 for the queries
@@ -421,15 +449,15 @@ constexpr double kSelLumpScale = 7843180.797657975;   // exp(15.875)
 constexpr int kSelMaxRounds = 24;
 
 template <int KS>
-__global__ __launch_bounds__(kSelThreads, 2) void prefill_select_kernel(const PrefillArgs a) {
+__global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const PrefillArgs a) {
   constexpr int NW = kSelThreads / 64;                             // waves per workgroup
   constexpr int NG = NW / KS;                                      // query groups per workgroup
   constexpr int kSelQ = 32 * NG;                                   // queries per workgroup
   static_assert(NG >= 1 && NG <= 4, "at most four histograms fit");
   __shared__ double hist_all[NG][kSelBins][32];                    // 32 KB per group
-  __shared__ float list_all[NW][kSelListCap][64];                  // per-lane member lists of sweeps 2 and 3 (32 KB)
+  __shared__ float list_all[NW][kSelListCap][64];                  // per-lane member lists of sweeps 2 and 3 (48 KB)
   float (*max_all)[32] = reinterpret_cast<float (*)[32]>(&list_all[0][0][0]);   // sweep 0: the waves' row maxima
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // (tile numbers are scalars)
   const int g = lane >> 5, r = lane & 31;
   // Workgroups go round-robin over the chip's 8 dies, each with its own L2.  The 1-D grid is decoded so
   // that a die works on ONE head (8 / n_heads dies per head): all its waves then stream the same index
@@ -490,6 +518,14 @@ __global__ __launch_bounds__(kSelThreads, 2) void prefill_select_kernel(const Pr
     const int nrow = min(tile * 32 + r, n_rows - 1);               // rows past the chunk are causally masked anyway
     return *reinterpret_cast<const u32x4*>(kIg + (int64_t)nrow * kIndexDim + g * 8);
   };
+  // the same for a tile of the mask-free range, all of whose rows exist (what is fetched ahead past the last whole tile
+  // is not used): a scalar base and one lane offset, no vector arithmetic
+  const uint32_t k_lane = (uint32_t)(r * kIndexDim + g * 8) * 2u;
+  const int last_whole = n_rows / 32 - 1;
+  auto load_k_whole = [&](int tile) {
+    const unsigned char* base = reinterpret_cast<const unsigned char*>(kIg) + (int64_t)min(tile, last_whole) * (32 * kIndexDim * 2);
+    return *reinterpret_cast<const u32x4*>(base + k_lane);
+  };
   // the group's waves clear their histogram together (followed by a barrier at the call sites)
   auto zero_hist = [&]() {
     double* h = &hist[0][0];
@@ -505,44 +541,60 @@ __global__ __launch_bounds__(kSelThreads, 2) void prefill_select_kernel(const Pr
   float selM8 = ninf;               // 8 * selM and 8 * index_scale for sweep 1
   const float cs8 = cs * 8.0f;
   float x_lo = ninf, x_top = pinf;  // sweeps 2, 3: members of the prefix have x_lo <= x <= x_top
+  float x_max = ninf;               // the row's largest raw product
+  float x_mid = 0.f, x_half = 0.f;  // sweep 3: middle of [x_lo, min(x_top, x_max)] and the larger distance of its ends from it
   int shift = 0;
   float mxs[kSelMfma];
 #pragma unroll
   for (int u = 0; u < kSelMfma; ++u) mxs[u] = ninf;
 
-  // Weighs the listed members of every lane: lane-private lists, so the only cross-lane step is the
-  // loop bound.
+  // Weighs the listed members of every lane: lane-private lists, so the only cross-lane step is the loop bound.
+  // Four entries at a time: their reads, exponentials and atomics overlap (one by one, a drain is a chain of LDS round
+  // trips that costs a wave more than the pairs between two drains).
   auto drain_list = [&]() {
-    for (int k = 0; __ballot(k < lcnt) != 0ull; ++k) {
-      if (k < lcnt) {
-        const float tt = sel_t(selM, lst[k][lane], cs);
-        add_mass((sel_q_of_t(tt) >> shift) & (kSelBins - 1), tt);
+#pragma unroll 1
+    for (int k = 0; __ballot(k < lcnt) != 0ull; k += 4) {
+      float x[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) x[u] = lst[k + u][lane];          // (the capacity is a multiple of 4; what lies past the end is not used)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (k + u < lcnt) {
+          const float tt = sel_t(selM, x[u], cs);
+          add_mass((sel_q_of_t(tt) >> shift) & (kSelBins - 1), tt);
+        }
       }
     }
     lcnt = 0;
   };
 
-  // What one tile contributes in phase PH (0: maximum, 1: all candidates, 4: the candidates at or below the
-  // lowered reference of a repeated sweep 1, 2 / 3: members of the digit prefix): SI = its 32 x 32 index
-  // products, nb = its first key.
-  auto tile_work = [&](auto PH, auto EDGE, const f32x16& SI, int nb, float& mxacc) -> float {
+  // Stores x at the LDS address `end` and advances it, in the lanes whose median equals x.
+  auto append_if_member = [](uint32_t& end, float x, float median) {
+    uint64_t lanes;
+    asm volatile("s_mov_b64 %1, exec\n\tv_cmpx_eq_f32_e64 exec, %2, %3\n\tds_write_b32 %0, %2\n\tv_add_u32_e32 %0, 0x100, %0\n\t"
+                 "s_mov_b64 exec, %1"
+                 : "+v"(end), "=&s"(lanes) : "v"(x), "v"(median) : "memory");
+  };
+
+  // What one tile contributes in phase PH (0: maximum, 1: all candidates -- of a repeated sweep 1: those at or below
+  // the lowered reference --, 2 / 3: members of the digit prefix): SI = its 32 x 32 index products, nb = its first
+  // key.  MASKED: causality and the lowered reference are tested pair by pair.
+  float t_least = ninf;             // masked sweep 1: candidates have 8 (M - s) >= t_least
+  auto tile_work = [&](auto PH, auto MASKED, const f32x16& SI, int nb, float& mxacc) -> float {
     constexpr int phase = decltype(PH)::value;
-    constexpr bool edge = decltype(EDGE)::value;
+    constexpr bool masked = decltype(MASKED)::value;
     if (phase == 0) {
       // scaling by a positive constant is monotone, so the maximum is taken on the raw products
       float v[16];
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const int n = nb + (i >> 2) * 8 + g * 4 + (i & 3);
-        v[i] = (!edge || n <= m) ? SI[i] : ninf;
+        v[i] = (!masked || n <= m) ? SI[i] : ninf;
       }
-#pragma unroll
-      for (int st = 8; st > 0; st >>= 1)
-#pragma unroll
-        for (int i = 0; i < st; ++i) v[i] = max_nn(v[i], v[i + st]);
-      mxacc = fmaxf(mxacc, v[0]);
-      return v[0];
-    } else if (phase == 1 || phase == 4) {
+      const float top = max16_nn(v);
+      mxacc = fmaxf(mxacc, top);
+      return top;
+    } else if (phase == 1) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const int n = nb + (i >> 2) * 8 + g * 4 + (i & 3);
@@ -551,8 +603,7 @@ __global__ __launch_bounds__(kSelThreads, 2) void prefill_select_kernel(const Pr
         const float tt8 = sel_t(selM8, SI[i], cs8);
         // a repeated sweep takes the candidates at or below the lowered reference only (the others were
         // counted above the open-ended bin); a query that does not repeat has reference -inf and takes none
-        const bool cand = (!edge || n <= m) && (phase == 1 || tt8 >= 0.f);
-        if (cand) {
+        if (!masked || (n <= m && tt8 >= t_least)) {
           // first digit of q: floor(min(tt * 2^17, 2^21 - 1)) >> 14 == floor(min(tt * 8, (2^21 - 1) / 2^14))
           const int bin = (int)fminf(tt8, 127.99993896484375f);
           // exp(s - M) = exp2(tt * -log2(e)); the constant carries the 1/8, again exactly
@@ -564,53 +615,58 @@ __global__ __launch_bounds__(kSelThreads, 2) void prefill_select_kernel(const Pr
       // sweep 3) are only noted here -- their raw product goes to the lane's list -- and weighed
       // with all lanes busy (drain_list); weighing them where they turn up would run the exponential
       // and the atomic for one or two active lanes at a time.
-      // Membership x_lo <= x <= x_top is one median and one comparison on the vector ALU (going through
-      // scalar condition registers costs a vector-to-scalar hand-off per pair).  Appending is branch-free:
-      // every pair writes its product at the list's end, members advance the end.  Sweep 3 first counts the
-      // tile's members and skips the appends when the whole wave has none (nearly always).
+      // Membership x_lo <= x <= x_top is one median and one comparison, which switches the other lanes off for the
+      // store at the list's end and the step of the end: three vector instructions per pair.
       auto member = [&](int i) {
         const int n = nb + (i >> 2) * 8 + g * 4 + (i & 3);
         const bool in = __builtin_amdgcn_fmed3f(SI[i], x_lo, x_top) == SI[i];
-        return edge ? (in && n <= m) : in;
+        return masked ? (in && n <= m) : in;
       };
       bool go = true;
       float reach = 0.f;
       if (phase == 3) {
-        // does any lane have a member in this tile?  The comparisons' lane masks are OR-ed on the scalar side
-        // (no vector instruction beyond the median and the comparison per pair)
-        uint64_t any = 0;
+        // does any lane have a member in this tile?  Its products' smallest distance from the middle of the lane's
+        // range says so, one and a half vector instructions per pair (rounding is monotone, so a member is
+        // never further away than the range's ends as subtracted the same way; a tile let through for nothing is harmless)
+        if (masked) {
+          uint64_t any = 0;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) any |= __ballot(member(i));
-        go = any != 0ull;
+          for (int i = 0; i < 16; ++i) any |= __ballot(member(i));
+          go = any != 0ull;
+        } else {
+          float d = pinf;
+#pragma unroll
+          for (int i = 0; i < 16; i += 2) d = fminf(fminf(fabsf(SI[i] - x_mid), fabsf(SI[i + 1] - x_mid)), d);
+          go = __ballot(d <= x_half) != 0ull;
+        }
         // can some query of the wave keep a key of this tile?  Its final threshold is at or above x_lo, so a
         // tile whose largest visible product is below x_lo for every query holds no kept pair
         reach = 1.f;
         if (!reach_known) {
-        float v[16];
+          float v[16];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int n = nb + (i >> 2) * 8 + g * 4 + (i & 3);
-          v[i] = (!edge || n <= m) ? SI[i] : ninf;
-        }
-#pragma unroll
-        for (int st = 8; st > 0; st >>= 1)
-#pragma unroll
-          for (int i = 0; i < st; ++i) v[i] = max_nn(v[i], v[i + st]);
-        const float top = v[0];
-        reach = __ballot(top >= x_lo) != 0ull ? 1.f : 0.f;
+          for (int i = 0; i < 16; ++i) {
+            const int n = nb + (i >> 2) * 8 + g * 4 + (i & 3);
+            v[i] = (!masked || n <= m) ? SI[i] : ninf;
+          }
+          reach = __ballot(max16_nn(v) >= x_lo) != 0ull ? 1.f : 0.f;
         }
       }
       if (go) {
-        // The list holds 16 entries per lane; a half tile adds at most 8, so it is emptied when some lane holds
-        // more than 8 before a half tile starts.  The list's end travels as an LDS address.
+        // A half tile adds at most 8 entries, so the lists are emptied when some lane has no room for 8 more.  The list's
+        // end travels as an LDS address.
 #pragma unroll
         for (int hf = 0; hf < 2; ++hf) {
           if (__ballot(lcnt > kSelListCap - 8) != 0ull) drain_list();
           uint32_t end = lst_base + (uint32_t)lcnt * 256u;
 #pragma unroll
           for (int i = hf * 8; i < hf * 8 + 8; ++i) {
-            *reinterpret_cast<float __attribute__((address_space(3)))*>(end) = SI[i];
-            end += member(i) ? 256u : 0u;
+            if (masked) {
+              *reinterpret_cast<float __attribute__((address_space(3)))*>(end) = SI[i];
+              end += member(i) ? 256u : 0u;
+            } else {
+              append_if_member(end, SI[i], __builtin_amdgcn_fmed3f(SI[i], x_lo, x_top));
+            }
           }
           lcnt = (int)((end - lst_base) >> 8);
         }
@@ -620,50 +676,44 @@ __global__ __launch_bounds__(kSelThreads, 2) void prefill_select_kernel(const Pr
     return 0.f;
   };
 
-  // One sweep over the tiles [tile_begin, tile_end) in rounds of 2 * kSelRing: two groups of index-key
-  // registers alternate, each refilled (for two groups ahead) as soon as its MFMAs have read it, so a
-  // load has a whole group's arithmetic to land in; the kSelRing MFMAs of a group are issued together and
-  // their latency hides behind one another.  No tail test: the interior range is a whole number of
-  // rounds, and in the edge range a tile past the last one holds only keys n > m, which the causal mask drops.
-  // LOOK (sweeps 2 and 3): consult the maximum table pair by pair -- skip what cannot hold a member, and in sweep 3
-  // note which pairs a query can keep a key in.  Without it the sweep is the plain streaming one, which is what a
-  // stretch where nearly every pair can hold a member gets (looking would cost more than it saves there; the
-  // pairs keep their maxima in the table, which is the conservative answer).
-  auto sweep = [&](auto PH, auto EDGE, auto LOOK, int tile_begin, int tile_end) {
+  // One sweep over the tiles [tile_begin, tile_end) in rounds of kSelRing: a round's index-key registers are refilled
+  // (for the next round) as soon as its MFMAs have read them, so a load has a round's arithmetic -- of this wave and
+  // of the SIMD's three others -- to land in.  No tail test: the mask-free range is a whole number of rounds, and in
+  // the masked range a tile past the last one holds only keys n > m, which the causal mask drops.
+  // Sweeps 2 and 3 consult the maximum table pair by pair: skip what cannot hold a member, and in sweep 3 note which
+  // pairs a query can keep a key in.  no_look: nearly every pair can hold a member and is needed (see sweep_picked);
+  // the pairs keep their maxima in the table, which is the conservative answer.
+  auto sweep = [&](auto PH, auto MASKED, int tile_begin, int tile_end, bool no_look = false) {
     if (tile_begin >= tile_end) return;
     constexpr int phase_ = decltype(PH)::value;
-    constexpr bool kSkip = (phase_ == 2 || phase_ == 3) && decltype(LOOK)::value;
-    if (!kSkip) reach_known = true;
+    constexpr bool kSkip = phase_ == 2 || phase_ == 3;
     static_assert(kSelMfma == 2, "a batch of MFMAs is one 64-key tile of the maximum table");
-    u32x4 ringA[kSelRing], ringB[kSelRing];
-    float tmA[kSelRing / 2], tmB[kSelRing / 2];                    // the table entries of the tile pairs in the rings
+    constexpr bool masked_ = decltype(MASKED)::value;
+    auto fetch = [&](int tile) { return masked_ ? load_k(tile) : load_k_whole(tile); };
+    u32x4 ring[kSelRing];
+    float tm[kSelRing / 2];                                        // the table entries of the tile pairs in the ring
 #pragma unroll
-    for (int u = 0; u < kSelRing; ++u) {
-      ringA[u] = load_k(tile_begin + u);
-      ringB[u] = load_k(tile_begin + kSelRing + u);
-    }
+    for (int u = 0; u < kSelRing; ++u) ring[u] = fetch(tile_begin + u);
     if (kSkip) {
 #pragma unroll
-      for (int u = 0; u < kSelRing / 2; ++u) {
-        tmA[u] = tmx[(tile_begin >> 1) + u];
-        tmB[u] = tmx[((tile_begin + kSelRing) >> 1) + u];
-      }
+      for (int u = 0; u < kSelRing / 2; ++u) tm[u] = tmx[(tile_begin >> 1) + u];
     }
-    auto group = [&](u32x4 (&ring)[kSelRing], float (&tm)[kSelRing / 2], int first) {
+#pragma unroll 1
+    for (int first = tile_begin; first < tile_end; first += kSelRing) {
 #pragma unroll
       for (int hb = 0; hb < kSelRing; hb += kSelMfma) {            // kSelMfma MFMAs in flight at a time
-        // no member possible in this pair of tiles: only the prefetches for two groups ahead are issued
+        // no member possible in this pair of tiles: only the prefetches for the next round are issued
         bool skip = false;
         if (kSkip) {
           const float pair_max = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(tm[hb / 2])));
-          skip = pair_max < xlo_wave;
+          skip = !no_look && pair_max < xlo_wave;
           // a maximum at or above EVERY query's x_lo is at or above its own query's: no need to look
-          reach_known = pair_max >= xlo_wave_top;
-          tm[hb / 2] = tmx[((first + 2 * kSelRing + hb) >> 1)];
+          reach_known = no_look || pair_max >= xlo_wave_top;
+          tm[hb / 2] = tmx[((first + kSelRing + hb) >> 1)];
         }
         if (skip) {
 #pragma unroll
-          for (int u = 0; u < kSelMfma; ++u) ring[hb + u] = load_k(first + 2 * kSelRing + hb + u);
+          for (int u = 0; u < kSelMfma; ++u) ring[hb + u] = fetch(first + kSelRing + hb + u);
           continue;
         }
         f32x16 SI[kSelMfma];
@@ -675,12 +725,12 @@ __global__ __launch_bounds__(kSelThreads, 2) void prefill_select_kernel(const Pr
                                                           __builtin_bit_cast(bf16x8, qIreg), SI[u], 0, 0, 0);
         }
 #pragma unroll
-        for (int u = 0; u < kSelMfma; ++u) ring[hb + u] = load_k(first + 2 * kSelRing + hb + u);
+        for (int u = 0; u < kSelMfma; ++u) ring[hb + u] = fetch(first + kSelRing + hb + u);
         float tmax = ninf;
 #pragma unroll
         for (int u = 0; u < kSelMfma; ++u) {
           __builtin_amdgcn_sched_barrier(0);       // one tile at a time: hoisting four tiles' operands runs out of registers
-          tmax = fmaxf(tmax, tile_work(PH, EDGE, SI[u], (first + hb + u) * 32, mxs[u]));
+          tmax = fmaxf(tmax, tile_work(PH, MASKED, SI[u], (first + hb + u) * 32, mxs[u]));
         }
         if (phase_ == 0) {                         // the pair's maximum over the wave's 32 queries x 64 keys
           const float wm = wave_max_f32(tmax);
@@ -695,19 +745,14 @@ __global__ __launch_bounds__(kSelThreads, 2) void prefill_select_kernel(const Pr
         }
         __builtin_amdgcn_sched_barrier(0);
       }
-    };
-#pragma unroll 1
-    for (int base = tile_begin; base < tile_end; base += 2 * kSelRing) {
-      group(ringA, tmA, base);
-      group(ringB, tmB, base + kSelRing);
     }
   };
-  const int n_plain = n_interior / (2 * kSelRing) * (2 * kSelRing);   // whole rounds of interior tiles run without masks
+  const int n_plain = n_interior / kSelRing * kSelRing;            // whole rounds of interior tiles run without masks
   // this wave's share: an equal run of the rounds, the masked ones of the edge (one or two) at the end
-  const int plain_rounds = n_plain / (2 * kSelRing), rounds = (n_tiles + 2 * kSelRing - 1) / (2 * kSelRing);
+  const int plain_rounds = n_plain / kSelRing, rounds = (n_tiles + kSelRing - 1) / kSelRing;
   const int round_lo = rounds * part / KS, round_hi = rounds * (part + 1) / KS;
-  const int plain_lo = min(round_lo, plain_rounds) * (2 * kSelRing), plain_hi = min(round_hi, plain_rounds) * (2 * kSelRing);
-  const int edge_lo = max(round_lo, plain_rounds) * (2 * kSelRing), edge_hi = round_hi * (2 * kSelRing);
+  const int plain_lo = min(round_lo, plain_rounds) * kSelRing, plain_hi = min(round_hi, plain_rounds) * kSelRing;
+  const int edge_lo = max(round_lo, plain_rounds) * kSelRing, edge_hi = round_hi * kSelRing;
   // Sweeps 2 and 3 over the mask-free range, 512 tiles (256 entries of the maximum table) at a time: where at most
   // a quarter of the tile pairs can hold a member, only those are fetched and looked at -- with a peaked score
   // law that is a handful of pairs in a million keys --; otherwise the streaming sweep above runs over the stretch,
@@ -719,40 +764,34 @@ __global__ __launch_bounds__(kSelThreads, 2) void prefill_select_kernel(const Pr
 #pragma unroll 1
     for (int tb = tile_begin; tb < tile_end; tb += 512) {
       const int te = min(tb + 512, tile_end);
-      float tmv[4];
-      uint64_t on[4];
+      auto entry = [&](int k) {
+        const int pair = (tb >> 1) + k * 64 + lane;
+        return pair < (te >> 1) ? tmx[pair] : ninf;
+      };
       int n_on = 0;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int pair = (tb >> 1) + k * 64 + lane;
-        tmv[k] = pair < (te >> 1) ? tmx[pair] : ninf;
-        on[k] = __ballot(tmv[k] >= xlo_wave);
-        n_on += __popcll(on[k]);
-      }
-      // next to nothing to skip, and (sweep 3) the pairs looked at so far nearly all turned out to be needed:
-      // stream, do not look
-      if (n_on > 240 && (phase_ == 2 || (n_looked >= 64 && 10 * n_needed >= 9 * n_looked))) {
-        sweep(PH, std::false_type{}, std::false_type{}, tb, te);
-        continue;
-      }
+      for (int k = 0; k < 4; ++k) n_on += __popcll(__ballot(entry(k) >= xlo_wave));
       if (n_on > 64) {
-        sweep(PH, std::false_type{}, std::true_type{}, tb, te);
+        // next to nothing to skip, and (sweep 3) the pairs looked at so far nearly all turned out to be needed: do not look
+        const bool no_look = n_on > 240 && (phase_ == 2 || (n_looked >= 64 && 10 * n_needed >= 9 * n_looked));
+        sweep(PH, std::false_type{}, tb, te, no_look);
         continue;
       }
-#pragma unroll
+#pragma unroll 1
       for (int k = 0; k < 4; ++k) {
-        uint64_t todo = on[k];
+        const float tmv = entry(k);
+        uint64_t todo = __ballot(tmv >= xlo_wave);
         while (todo != 0ull) {
           const int pl = __builtin_ctzll(todo);
           todo &= todo - 1ull;
           const int tile = tb + 2 * (k * 64 + pl);
-          reach_known = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(tmv[k]), pl)) >= xlo_wave_top;
+          reach_known = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(tmv), pl)) >= xlo_wave_top;
           f32x16 SI[2];
 #pragma unroll
           for (int u = 0; u < 2; ++u) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) SI[u][i] = 0.f;
-            SI[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, load_k(tile + u)),
+            SI[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, load_k_whole(tile + u)),
                                                             __builtin_bit_cast(bf16x8, qIreg), SI[u], 0, 0, 0);
           }
           float tmax = ninf;
@@ -766,8 +805,8 @@ __global__ __launch_bounds__(kSelThreads, 2) void prefill_select_kernel(const Pr
   auto sweep_all = [&](auto PH) {
     constexpr int phase_ = decltype(PH)::value;
     if constexpr (phase_ == 2 || phase_ == 3) sweep_picked(PH, plain_lo, plain_hi);
-    else sweep(PH, std::false_type{}, std::false_type{}, plain_lo, plain_hi);
-    sweep(PH, std::true_type{}, std::true_type{}, edge_lo, edge_hi);
+    else sweep(PH, std::false_type{}, plain_lo, plain_hi);
+    sweep(PH, std::true_type{}, edge_lo, edge_hi);
     if (phase_ == 2 || phase_ == 3) drain_list();
   };
 
@@ -777,18 +816,54 @@ __global__ __launch_bounds__(kSelThreads, 2) void prefill_select_kernel(const Pr
   float cut = pinf;               // keep a candidate iff reference - s < cut
   double cum = 0.0, hsel = 0.0;
   int bsel = kSelBins - 1;
-  // this query's bins from the top of the score range (bin 0) down; both lanes of the pair and every wave of
-  // the group run the same scan on the same numbers
-  auto scan = [&](double target) {
+  // The threshold bin: this query's bins from the top of the score range (bin 0) down.  The two lanes of the query and
+  // every wave of the group take one run of bins each and leave its sum; every one of them then goes through the
+  // runs' sums and the bins of the run that crosses, on the same numbers in the same order.  (All of them going through
+  // all 128 bins is a chain of LDS reads and additions of 32000 cycles, three times per workgroup.)  One barrier; the
+  // sums live in the lists' memory, idle between sweeps.  `whole`: the histogram holds all candidates, take Z from it.
+  constexpr int kRuns = 2 * KS, kRunBins = kSelBins / kRuns;
+  double (*run_sum)[32] = reinterpret_cast<double (*)[32]>(&list_all[0][0][0]) + qgroup * kRuns;
+  static_assert(kSelBins % kRuns == 0 && sizeof(double) * 32 * kRuns * NG + sizeof(int) * NW <= sizeof(list_all), "runs of equal length");
+  auto scan = [&](bool whole, bool take) {
+    {
+      double h[kRunBins], sum = 0.0;
+#pragma unroll
+      for (int i = 0; i < kRunBins; ++i) h[i] = hist[(part * 2 + g) * kRunBins + i][r];
+#pragma unroll
+      for (int i = 0; i < kRunBins; ++i) sum += h[i];
+      run_sum[part * 2 + g][r] = sum;
+    }
+    __syncthreads();
+    if (!take) return;
+    double rs[kRuns];
+#pragma unroll
+    for (int i = 0; i < kRuns; ++i) rs[i] = run_sum[i][r];
+    if (whole) {
+      Z = 0.0;
+#pragma unroll
+      for (int i = 0; i < kRuns; ++i) Z += rs[i];
+    }
+    const double target = (double)a.p * Z;
     cum = above;
+    int run = kRuns - 1;
+    bool found = false;
+#pragma unroll
+    for (int i = 0; i < kRuns - 1; ++i) {
+      found = found || cum + rs[i] >= target;
+      if (!found) cum += rs[i];
+      else run = min(run, i);
+    }
     hsel = 0.0;
     bsel = kSelBins - 1;
-    bool found = false;
-    for (int i = 0; i < kSelBins; ++i) {
-      const double hv = hist[i][r];
+    found = false;
+    double h[kRunBins];
+#pragma unroll
+    for (int i = 0; i < kRunBins; ++i) h[i] = hist[run * kRunBins + i][r];
+#pragma unroll
+    for (int i = 0; i < kRunBins; ++i) {
       if (!found) {
-        if (cum + hv >= target) { bsel = i; hsel = hv; found = true; }
-        else cum += hv;
+        if (cum + h[i] >= target) { bsel = run * kRunBins + i; hsel = h[i]; found = true; }
+        else cum += h[i];
       }
     }
   };
@@ -805,6 +880,7 @@ __global__ __launch_bounds__(kSelThreads, 2) void prefill_select_kernel(const Pr
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < KS; ++k) mx = fmaxf(mx, max_all[qgroup * KS + k][r]);
+    x_max = mx;
     selM = mx * cs;
   }
   __syncthreads();                                                  // the maxima are read: the lists' memory is free again
@@ -814,19 +890,20 @@ __global__ __launch_bounds__(kSelThreads, 2) void prefill_select_kernel(const Pr
   bool repeat_me = false, rebased = false;
   for (int round = 0; round < kSelMaxRounds; ++round) {
     selM8 = (round == 0 || repeat_me) ? selM * 8.0f : ninf;         // (exact unless it overflows)
-    if (round == 0) sweep_all(std::integral_constant<int, 1>{});
-    else sweep_all(std::integral_constant<int, 4>{});
-    __syncthreads();                                                // every wave of the group has added its masses
     if (round == 0) {
-      Z = 0.0;
-      for (int i = 0; i < kSelBins; ++i) Z += hist[i][r];
+      sweep_all(std::integral_constant<int, 1>{});
+    } else {
+      t_least = 0.f;                                                // (no mask-free form: repeats are rare)
+      sweep(std::integral_constant<int, 1>{}, std::true_type{}, plain_lo, plain_hi);
+      sweep(std::integral_constant<int, 1>{}, std::true_type{}, edge_lo, edge_hi);
     }
-    if (round == 0 || repeat_me) scan((double)a.p * Z);
+    __syncthreads();                                                // every wave of the group has added its masses
+    scan(round == 0, round == 0 || repeat_me);
     // the threshold in the open-ended bin: everything above it is counted (cum), its members go round again
     repeat_me = (round == 0 || repeat_me) && !idle && bsel == kSelBins - 1 && hsel > 0.0 && round + 1 < kSelMaxRounds;
     // does any query of the workgroup repeat?  (flags in the lists' memory, idle in this phase; the barrier also
     // says that every wave has read the histograms)
-    int* flags = reinterpret_cast<int*>(&list_all[0][0][0]);
+    int* flags = reinterpret_cast<int*>(reinterpret_cast<double (*)[32]>(&list_all[0][0][0]) + NG * kRuns);
     const bool mine = __ballot(repeat_me) != 0ull;
     if (lane == 0) flags[wave] = mine ? 1 : 0;
     __syncthreads();
@@ -863,6 +940,11 @@ __global__ __launch_bounds__(kSelThreads, 2) void prefill_select_kernel(const Pr
     // rounding error of M = max * scale and may be a hair below zero (a lowered reference keeps its bound:
     // what lies above it has been counted)
     if (qlo == 0 && !rebased) x_top = pinf;
+    {
+      const float hi = fminf(x_top, x_max), lo = fmaxf(x_lo, -1e38f);
+      x_mid = 0.5f * lo + 0.5f * hi;
+      x_half = fmaxf(hi - x_mid, x_mid - lo);
+    }
     xlo_wave = -wave_max_f32(idle ? ninf : -x_lo);
     xlo_wave_top = wave_max_f32(idle ? ninf : x_lo);
     shift -= 7;                                                     // of this sweep's digit: 7, then 0
@@ -871,7 +953,7 @@ __global__ __launch_bounds__(kSelThreads, 2) void prefill_select_kernel(const Pr
     if (phase == 2) sweep_all(std::integral_constant<int, 2>{});
     else sweep_all(std::integral_constant<int, 3>{});
     __syncthreads();
-    scan((double)a.p * Z);
+    scan(false, true);
     prefix = (prefix << 7) | bsel;
     above = cum;
     __syncthreads();                                                // every wave has read the histograms
