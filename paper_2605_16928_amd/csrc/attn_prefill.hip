@@ -50,14 +50,15 @@ struct PrefillArgs {
   float* lse;
   int32_t n_heads;
   uint8_t heads[128];           // query heads this launch computes
-  int32_t n_splits;             // dense mode: key range of every query tile cut into this many parts
-  float* part;                  // n_splits > 1: partial results [split, head slot, query, kPfPart]
+  int32_t n_splits;             // wide kernel: key range of every query tile cut into this many parts
+  int32_t n_sub;                // ... and every part into this many sub-ranges that share the part's reference maxima
+  float* part;                  // n_splits * n_sub > 1: partial results [range, head slot, query, kPfPart]
   // sparse mode only (per-query top-p over the indexer scores):
   const uint16_t* qI;           // bf16 [n_ret, n_q, 16]
   const uint16_t* kI;           // bf16 [n_ret, >= pos0 + n_q, 16]
   int64_t kI_head_stride;
   float p, index_scale;
-  float* tau;                   // optional [n_ret, n_q]
+  float* tau;                   // optional [n_ret, n_q] (the three also in dense mode, where they are known without a search)
   int32_t* count;
   float* mass;
   float* sel_thr;               // [n_ret, n_q]: a candidate is kept iff its raw index product is >= this
@@ -995,7 +996,17 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
 // repeats its keys with the classical running-maximum recurrence (exact_pass).  Real score rows
 // have their maximum at the first tokens; the repeat exists for correctness, not for speed.
 // K/V tiles rotate through three LDS buffers (the PV of a tile's last block reads its V^T while the
-// next tile is current), one workgroup barrier per 64-key tile.
+// next tile is current), two workgroup barriers per 64-key tile.
+//
+// Tiles that every query of the workgroup sees in full -- all but the first and the four or five on the diagonal --
+// run in a loop without a branch (steady, below), the others block by block with element masks and nothing
+// interleaved.  Inside the branches that served both before, the register allocator moved accumulators at the joins,
+// and every stream began by waiting for its first LDS operands, all eight waves at once; in the loop a stream reads
+// the next one's first operands.  Attention launch of 4 heads x 4096 queries at 128K tokens: 1300 -> 1090 us selecting,
+// 1250 -> 970 us dense (1.14 PFLOP/s); last 8192-query chunk of 1M tokens, selecting: 20.3 -> 17.6 ms (operands three
+// and two steps ahead instead of five and four: 17.7 and 1141 us).  What bounds it now is the sum of what the
+// two waves of a SIMD issue -- 16 MFMAs of 32 cycles and about 110 vector, LDS and scalar instructions per 32 x 32
+// block -- and the transposing V reads, which keep the LDS busy for two thirds of that time.
 constexpr int kPwQ = 256;
 constexpr int kPwStages = 3;
 // One staged tile: 64 K rows then 64 V rows, 256 bytes each, no padding -- the tiles are written by
@@ -1023,15 +1034,16 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
   __shared__ __attribute__((aligned(16))) unsigned char smem[kSmemWide];
   unsigned char* const Ls = smem;       // stage s: K rows at Ls + s * kPwTileBytes, V rows 16 KiB further
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // (the branches on a wave's queries are scalar)
   const int g = lane >> 5, r = lane & 31;
   // A selecting launch behind a threshold search (one sequence) is laid out (key range, query tile, head slot): the
   // query tiles' lists differ wildly in length, and with the key range as the fastest index the ranges of a long
   // list go round all eight dies (workgroups are dealt to the dies in turn) instead of piling up on one.
   // The grid of such a launch is sized for the finer cut; the ranges really used (listed_splits) take the
   // first workgroups of the grid in the same (key range, query tile, head slot) order, the others leave.
-  const bool listed = SPARSE && a.p < 1.f;
-  const int n_splits = LOCAL ? 1 : (listed ? listed_splits(a) : a.n_splits);
+  constexpr bool listed = SPARSE;
+  const int n_parts = LOCAL ? 1 : (listed ? listed_splits(a) : a.n_splits), n_sub = LOCAL ? 1 : a.n_sub;
+  const int n_splits = n_parts * n_sub;
   int hslot = blockIdx.x, split, qt_rev = blockIdx.y, b = 0;
   if (listed) {
     const int lin = (int)blockIdx.x + (int)gridDim.x * ((int)blockIdx.y + (int)gridDim.y * (int)blockIdx.z);
@@ -1112,7 +1124,7 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
     for (int qb = 0; qb < QB; ++qb) {
       if (qok[qb]) {
         qIreg[qb] = *reinterpret_cast<const u32x4*>(a.qI + ((int64_t)j * a.n_q + tq[qb]) * kIndexDim + g * 8);
-        if (a.p < 1.f) selThr[qb] = a.sel_thr[(int64_t)j * a.n_q + tq[qb]];
+        selThr[qb] = a.sel_thr[(int64_t)j * a.n_q + tq[qb]];
       }
     }
   }
@@ -1143,7 +1155,6 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
   // repeat that key: they are masked for every query, and real data keeps 0 * V finite) ----
   // Load j (0..GH-1: K, GH..2GH-1: V) of a wave covers rows RG * (j % GH) + 4 * wave + lane / 16 of the
   // tile, lane % 16 is the 16-byte position inside the row; the lane fetches the chunk that belongs there.
-  const int uwave = __builtin_amdgcn_readfirstlane(wave);
   const uint32_t lds_base = (uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char*)Ls;
   const int ld_row = 4 * wave + (lane >> 4);
   const int ld_pos = lane & 15;
@@ -1153,7 +1164,7 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
     const int jj = j % GH;
     const int n = min(n0 + RG * jj + ld_row, m_hi);
     const uint16_t* src = (j < GH ? Kg + ld_ck * 8 : Vg + ld_cv * 8) + (int64_t)n * a.row_stride;
-    const uint32_t dst = lds_base + slot * kPwTileBytes + (j < GH ? 0 : kPwTileBytes / 2) + (jj * NW + uwave) * 1024;
+    const uint32_t dst = lds_base + slot * kPwTileBytes + (j < GH ? 0 : kPwTileBytes / 2) + (jj * NW + wave) * 1024;
     // Written as assembly on purpose: through the compiler's own intrinsic every later LDS read waits
     // for ALL outstanding direct loads (it cannot tell the buffers apart), which serialises the
     // pipeline; completion is awaited explicitly (loads_landed) before the barrier that publishes a tile.
@@ -1169,10 +1180,11 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
     off_k[jj] = (uint32_t)(((int64_t)(RG * jj + ld_row) * a.row_stride + ld_ck * 8) * 2);
     off_v[jj] = (uint32_t)(((int64_t)(RG * jj + ld_row) * a.row_stride + ld_cv * 8) * 2);
   }
-  auto load_piece_full = [&](int n0, int slot, int j) __attribute__((always_inline)) {
+  auto load_piece_full = [&](int n0_any, int slot, int j) __attribute__((always_inline)) {
+    const int n0 = __builtin_amdgcn_readfirstlane(n0_any);   // (a listed tile's number was loaded from memory)
     const int jj = j % GH;
     const unsigned char* base = reinterpret_cast<const unsigned char*>((j < GH ? Kg : Vg) + (int64_t)n0 * a.row_stride);
-    const uint32_t dst = lds_base + slot * kPwTileBytes + (j < GH ? 0 : kPwTileBytes / 2) + (jj * NW + uwave) * 1024;
+    const uint32_t dst = lds_base + slot * kPwTileBytes + (j < GH ? 0 : kPwTileBytes / 2) + (jj * NW + wave) * 1024;
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(j < GH ? off_k[jj] : off_v[jj]), "s"(base)
                  : "memory", "m0");
   };
@@ -1211,20 +1223,32 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
       for (int qb = 0; qb < QB; ++qb) S[qb] = mfma32<F16>(ka, qreg[qb][kk], S[qb]);
     }
   };
-  // The same MFMAs with their K operands read three steps ahead and a slice of other work (issuing
-  // the loads of a later tile) between every pair; scheduling fences keep the order.
+  // The same MFMAs with their K operands read kAheadK steps ahead and a slice of other work (issuing the loads of a
+  // later tile) between every pair; scheduling fences keep the order.  In the steady loop the first operands were
+  // read during the stream before (ka_first; likewise va_first for the PV stream): with every wave of the workgroup at
+  // the same place (two barriers per tile) nothing else covers their LDS latency.
+  constexpr int kAheadK = 5, kAheadV = 4;
+  u32x4 ka_first[kAheadK];
+  s16x8 va_first[kAheadV];
+  auto first_k = [&](const unsigned char* tile, int kb) __attribute__((always_inline)) {
+#pragma unroll
+    for (int kk = 0; kk < kAheadK; ++kk) ka_first[kk] = read_k(tile, kb, kk);
+  };
+  auto first_v = [&](const unsigned char* tile, int kb) __attribute__((always_inline)) {
+#pragma unroll
+    for (int k = 0; k < kAheadV; ++k) va_first[k] = read_v(tile, kb, k >> 2, k & 3);
+  };
   auto scores_beside = [&](const unsigned char* tile, int kb, f32x16 (&S)[QB], auto&& work) __attribute__((always_inline)) {
     u32x4 ka[8];
-    ka[0] = read_k(tile, kb, 0);
-    ka[1] = read_k(tile, kb, 1);
-    ka[2] = read_k(tile, kb, 2);
+#pragma unroll
+    for (int kk = 0; kk < kAheadK; ++kk) ka[kk] = ka_first[kk];
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
       for (int i = 0; i < 16; ++i) S[qb][i] = 0.f;
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) {
-      if (kk + 3 < 8) ka[kk + 3] = read_k(tile, kb, kk + 3);
+      if (kk + kAheadK < 8) ka[kk + kAheadK] = read_k(tile, kb, kk + kAheadK);
 #pragma unroll
       for (int qb = 0; qb < QB; ++qb) {
         S[qb] = mfma32<F16>(ka[kk], qreg[qb][kk], S[qb]);
@@ -1297,11 +1321,12 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
   // The steady-state step: the PV MFMAs of the previous block and the softmax of the current block as
   // ONE hand-interleaved instruction sequence -- per MFMA (32 cycles of the matrix pipe) one pair of
   // probabilities (2 fma, 2 exp, 1 convert, 1 packed dot product on the vector ALU); scheduling fences
-  // keep the compiler from regrouping it, V^T operands are read two steps ahead.  SEL (the selecting
-  // mode): the block's index-score MFMAs in front and every probability gated by its query's keep test
+  // keep the compiler from regrouping it, V^T operands are read kAheadV steps ahead (the first ones are in va_first)
+  // and, at its end, the first K operands of the score MFMAs that follow (block next_kb of next_tile).  SEL (the
+  // selecting mode): the block's index-score MFMAs in front and every probability gated by its query's keep test
   // (one compare, one select, one add for the count per probability).
   auto pv_beside_softmax = [&](auto sel_tag, const unsigned char* tile, int kb, const uint32_t (&Pin)[QB][8], const f32x16 (&S)[QB],
-                               uint32_t (&Pout)[QB][8], const u32x4 ki) __attribute__((always_inline)) {
+                               uint32_t (&Pout)[QB][8], const u32x4 ki, const unsigned char* next_tile, int next_kb) __attribute__((always_inline)) {
     constexpr bool SEL = decltype(sel_tag)::value;
     f32x16 SI[QB];
     float mc[QB], l[QB];
@@ -1319,12 +1344,13 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
     }
     s16x8 va[8];
     auto read_va = [&](int k) __attribute__((always_inline)) { va[k] = read_v(tile, kb, k >> 2, k & 3); };   // k = tt * 4 + db
-    read_va(0);
-    read_va(1);
+#pragma unroll
+    for (int k = 0; k < kAheadV; ++k) va[k] = va_first[k];
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
       const int tt = k >> 2, db = k & 3;
-      if (k + 2 < 8) read_va(k + 2);
+      if (k + kAheadV < 8) read_va(k + kAheadV);
+      if (k == 8 - kAheadV) first_k(next_tile, next_kb);
 #pragma unroll
       for (int qb = 0; qb < QB; ++qb) {
         const u32x4 pb = (u32x4){Pin[qb][4 * tt], Pin[qb][4 * tt + 1], Pin[qb][4 * tt + 2], Pin[qb][4 * tt + 3]};
@@ -1370,11 +1396,13 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
   };
 
   auto tile_n0 = [&](int it) __attribute__((always_inline)) {
-    if (SPARSE && listed) return alist[it] * kPfK;
+    if (listed) return alist[it] * kPfK;
     return (it < ks_end ? it : kt_w0 + (it - ks_end)) * kPfK;
   };
-  const int it_lo = (int)((int64_t)n_tiles * split / n_splits);
-  const int it_hi = (int)((int64_t)n_tiles * (split + 1) / n_splits);
+  const int p_lo = (int)((int64_t)n_tiles * (split / n_sub) / n_parts), p_hi = (int)((int64_t)n_tiles * (split / n_sub + 1) / n_parts);
+  const int sub = split % n_sub;
+  const int it_lo = p_lo + (int)((int64_t)(p_hi - p_lo) * sub / n_sub);
+  const int it_hi = p_lo + (int)((int64_t)(p_hi - p_lo) * (sub + 1) / n_sub);
   auto slot_of = [&](int it) __attribute__((always_inline)) { return (it - it_lo) % kPwStages; };
   auto tile_at = [&](int it) __attribute__((always_inline)) { return Ls + slot_of(it) * kPwTileBytes; };
 
@@ -1396,14 +1424,18 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
     int n_t3 = tile_n0(min(it_lo + 3, it_hi - 1));
     load_tile(n_t0, 0);
     load_tile(n_t1, 1);
+    // reference maxima: the largest score of the part's first tile, masks ignored (always finite).  A sub-range further
+    // on takes the same reference -- its probabilities are rounded to 16 bits exactly as if the part were
+    // walked in one go -- from a copy of that tile in the buffer that is free until half 1 of its own first tile.
+    const unsigned char* const t_ref = it_lo == p_lo ? Ls : Ls + 2 * kPwTileBytes;
+    if (it_lo != p_lo) load_tile(tile_n0(p_lo), 2);
     loads_landed();
     __syncthreads();
-    // reference maxima: the largest score of the first tile, masks ignored (always finite)
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) mrow[qb] = ninf;
 #pragma unroll
     for (int kb = 1; kb >= 0; --kb) {
-      mfma_S(Ls, kb, S);
+      mfma_S(t_ref, kb, S);
 #pragma unroll
       for (int qb = 0; qb < QB; ++qb) {
         float mx = S[qb][0];
@@ -1411,7 +1443,8 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
         for (int i = 1; i < 16; ++i) mx = fmaxf(mx, S[qb][i]);
         mrow[qb] = fmaxf(mrow[qb], fmaxf(mx, __shfl_xor(mx, 32)));
       }
-    }                                                    // S now holds block (it_lo, 0)
+    }
+    if (it_lo != p_lo) mfma_S(Ls, 0, S);                 // S now holds block (it_lo, 0)
 
     // Invariant at the start of half hf of tile it: S holds the scores of that block if it is active
     // for this wave; if `pend`, the probabilities of the last active block wait in P1 (hf = 0, V in
@@ -1424,21 +1457,23 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
       ki0 = load_ki(n_t0);
       ki1 = load_ki(n_t0 + 32);
     }
+    auto next_tiles = [&](int it) __attribute__((always_inline)) {
+      n_t0 = n_t1;
+      n_t1 = n_t2;
+      n_t2 = n_t3;
+      n_t3 = tile_n0(min(it + 4, it_hi - 1));
+    };
+    // one half of a tile that some query may not see in full (masks by element, nothing interleaved)
     auto half = [&](int it, auto hf_tag) __attribute__((always_inline)) {
       constexpr int hf = decltype(hf_tag)::value;
       const int nb0 = n_t0 + hf * 32;
       const unsigned char* t_pend = hf == 0 ? tile_at(it - 1) : tile_at(it);
       const uint32_t (&Pin)[QB][8] = hf == 0 ? P1 : P0;
       uint32_t (&Pout)[QB][8] = hf == 0 ? P0 : P1;
-      if (!is_active(nb0)) {
-        if (pend) mfma_PV(t_pend, 1 - hf, Pin);
-        pend = false;
-      } else if (pend && !needs_mask(nb0)) {
-        // steady state: PV of the previous block beside the softmax of this one
-        pv_beside_softmax(std::integral_constant<bool, SPARSE>{}, t_pend, 1 - hf, Pin, S, Pout, hf == 0 ? ki0 : ki1);
-      } else {
-        if (pend) mfma_PV(t_pend, 1 - hf, Pin);
-        mask_block(S, nb0);
+      if (pend) mfma_PV(t_pend, 1 - hf, Pin);
+      pend = false;
+      if (is_active(nb0)) {
+        if (needs_mask(nb0)) mask_block(S, nb0);
         if (SPARSE) select_block(S, hf == 0 ? ki0 : ki1);
         softmax_fixed(S, Pout);
         pend = true;
@@ -1448,36 +1483,59 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
         ki1 = load_ki(n_t1 + 32);
       }
       if (hf == 0) {
-        if (is_active(nb0 + 32)) scores_beside(tile_at(it), 1, S, [&](int) __attribute__((always_inline)) {});
+        if (is_active(nb0 + 32)) mfma_S(tile_at(it), 1, S);
         loads_landed();
         __syncthreads();
       } else {
         // past the last tile the same loads re-fetch it into a buffer nobody reads: no branches
-        const int n2 = n_t2;
-        const int s2 = slot_of(it + 2);
-        const bool next_active = it + 1 < it_hi && is_active(n_t1);
-        if (n2 + kPfK - 1 <= m_hi) {                       // a whole tile (all but the last of the range)
-          if (next_active) {
-            scores_beside(tile_at(it + 1), 0, S, [&](int kk) __attribute__((always_inline)) { if (kk < 2 * GH) load_piece_full(n2, s2, kk); });
-          } else {
-#pragma unroll
-            for (int j = 0; j < 2 * GH; ++j) load_piece_full(n2, s2, j);
-          }
-        } else if (next_active) {
-          scores_beside(tile_at(it + 1), 0, S, [&](int kk) __attribute__((always_inline)) { if (kk < 2 * GH) load_piece(n2, s2, kk); });
-        } else {
-          load_tile(n2, s2);
-        }
+        load_tile(n_t2, slot_of(it + 2));
+        if (it + 1 < it_hi && is_active(n_t1)) mfma_S(tile_at(it + 1), 0, S);
       }
     };
-    for (int it = it_lo; it < it_hi; ++it) {
+    int it = it_lo;
+    auto edge_tile = [&]() __attribute__((always_inline)) {
       half(it, std::integral_constant<int, 0>{});
       half(it, std::integral_constant<int, 1>{});
-      n_t0 = n_t1;
-      n_t1 = n_t2;
-      n_t2 = n_t3;
-      n_t3 = tile_n0(min(it + 4, it_hi - 1));
+      next_tiles(it);
+      ++it;
+    };
+    edge_tile();
+    // The steady loop: tiles every query of the workgroup sees in full, the tile to fetch a whole one.  The tile
+    // before was visible as well, so every wave with queries has probabilities pending; a wave without queries only
+    // fetches its share of the tiles.
+    auto steady = [&]() __attribute__((always_inline)) { return it < it_hi && n_t0 + kPfK - 1 <= m_lo && n_t2 + kPfK - 1 <= m_hi; };
+    if (!LOCAL && steady()) {
+      if (m_w_hi >= m_w_lo) {
+        first_v(tile_at(it - 1), 1);
+        do {
+          pv_beside_softmax(std::integral_constant<bool, SPARSE>{}, tile_at(it - 1), 1, P1, S, P0, ki0, tile_at(it), 1);
+          scores_beside(tile_at(it), 1, S, [&](int) __attribute__((always_inline)) {});
+          first_v(tile_at(it), 0);
+          loads_landed();
+          __syncthreads();
+          pv_beside_softmax(std::integral_constant<bool, SPARSE>{}, tile_at(it), 0, P0, S, P1, ki1, tile_at(it + 1), 0);
+          if (SPARSE) {                                    // the next tile's index keys: a tile's time to arrive
+            ki0 = load_ki(n_t1);
+            ki1 = load_ki(n_t1 + 32);
+          }
+          const int n2 = n_t2, s2 = slot_of(it + 2);
+          scores_beside(tile_at(it + 1), 0, S, [&](int kk) __attribute__((always_inline)) { if (kk < 2 * GH) load_piece_full(n2, s2, kk); });
+          first_v(tile_at(it), 1);
+          next_tiles(it);
+          ++it;
+        } while (steady());
+      } else {
+        do {
+          loads_landed();
+          __syncthreads();
+#pragma unroll
+          for (int j = 0; j < 2 * GH; ++j) load_piece_full(n_t2, slot_of(it + 2), j);
+          next_tiles(it);
+          ++it;
+        } while (steady());
+      }
     }
+    while (it < it_hi) edge_tile();
     if (pend) mfma_PV(tile_at(it_hi - 1), 1, P1);        // drain: PV of the last block
     loads_landed();
 
@@ -1560,10 +1618,11 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
     if (!qok[qb]) continue;
     const float mfin = (it_lo < it_hi && ltot > 0.f) ? mrow[qb] : ninf;
     const int kept = sel_cnt[qb] + __shfl_xor(sel_cnt[qb], 32);
-    if (SPARSE && g == 0 && split == 0 && !(a.p < 1.f)) {   // keep-all: the threshold search did not run
+    if (MODE == kModeDense && g == 0 && split == 0) {       // the statistics of the rule that keeps every candidate
       const int64_t o = (int64_t)hslot * a.n_q + tq[qb];
       if (a.mass) a.mass[o] = 1.f;
       if (a.tau) a.tau[o] = ninf;
+      if (a.count) a.count[o] = mq[qb] + 1;
     }
     if (n_splits > 1) {
       float* prow = a.part + (((int64_t)split * a.n_heads + hslot) * a.n_q + tq[qb]) * kPfPart;
@@ -1668,33 +1727,85 @@ __global__ __launch_bounds__(256) void index_project_kernel(const ProjectArgs a)
   a.out[((int64_t)j * a.n_q + t) * kIndexDim + i] = f64_to_bf16_rne(acc);
 }
 
-// Merges the key-range partials of one (query, head): thread = output dim, two queries per block.
+// Merges the key-range partials of a (query, head): SLICES groups of 32 lanes walk the ranges slice, slice + SLICES, ...,
+// four partials in flight each, a lane owns 4 of the 128 output dims; LDS merges the slices.  8 / SLICES rows per
+// workgroup: two slices where there are few ranges (24 us for 16384 rows of 4 ranges with a thread per dim going through
+// the ranges one by one, 11 now), all eight where a short chunk's keys are cut into dozens (43 and 5 us for 256 rows of 64).
+template <int SLICES>
 __global__ __launch_bounds__(256) void prefill_combine_kernel(const PrefillArgs a) {
-  const int t = blockIdx.x * 2 + (threadIdx.x >> 7), d = threadIdx.x & 127, hs = blockIdx.y;
-  if (t >= a.n_q) return;
+  __shared__ float sh_m[8], sh_l[8];
+  __shared__ int sh_kept[8];
+  __shared__ __attribute__((aligned(16))) float sh_acc[8][kHeadDim];
+  const int tid = threadIdx.x, d4 = tid & 31, grp = tid >> 5, slice = grp % SLICES, hs = blockIdx.y;
+  const int t = blockIdx.x * (8 / SLICES) + grp / SLICES;
+  const bool row = t < a.n_q;
   const float ninf = -__builtin_huge_valf();
-  const int n_splits = a.act_range ? listed_splits(a) : a.n_splits;     // (a listed launch decides on the device)
-  float M = ninf;
-  for (int s = 0; s < n_splits; ++s) M = fmaxf(M, a.part[(((int64_t)s * a.n_heads + hs) * a.n_q + t) * kPfPart]);
-  if (a.count && d == 0) {                                 // selecting mode: kept keys over all key ranges
-    int kept = 0;
-    for (int s = 0; s < n_splits; ++s) kept += __float_as_int(a.part[(((int64_t)s * a.n_heads + hs) * a.n_q + t) * kPfPart + 2]);
-    a.count[(int64_t)hs * a.n_q + t] = kept;
+  const int n_splits = (a.act_range ? listed_splits(a) : a.n_splits) * a.n_sub;   // (a listed launch decides on the device)
+  const int64_t step = (int64_t)a.n_heads * a.n_q * kPfPart;            // from one range's partials to the next
+  const float* part = a.part + ((int64_t)hs * a.n_q + (row ? t : 0)) * kPfPart;
+  float M = ninf, L = 0.f;
+  float4 A = make_float4(0.f, 0.f, 0.f, 0.f);
+  int kept = 0;
+  for (int s0 = slice; row && s0 < n_splits; s0 += 4 * SLICES) {
+    float pm[4], pl[4];
+    int pk[4];
+    float4 pv[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int s = s0 + u * SLICES;
+      pm[u] = ninf; pl[u] = 0.f; pk[u] = 0; pv[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (s < n_splits) {
+        const float* p = part + s * step;
+        const float4 h = *reinterpret_cast<const float4*>(p);
+        pm[u] = h.x; pl[u] = h.y; pk[u] = __float_as_int(h.z);
+        pv[u] = *reinterpret_cast<const float4*>(p + 4 + d4 * 4);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      kept += pk[u];
+      const float Mn = fmaxf(M, pm[u]);
+      if (Mn != ninf) {
+        const float c0 = fast_exp2((M - Mn) * a.scale_log2), c1 = fast_exp2((pm[u] - Mn) * a.scale_log2);
+        L = L * c0 + pl[u] * c1;
+        A.x = A.x * c0 + pv[u].x * c1; A.y = A.y * c0 + pv[u].y * c1;
+        A.z = A.z * c0 + pv[u].z * c1; A.w = A.w * c0 + pv[u].w * c1;
+        M = Mn;
+      }
+    }
   }
-  float L = 0.f, A = 0.f;
-  if (M != ninf) {
-    for (int s = 0; s < n_splits; ++s) {
-      const float* p = a.part + (((int64_t)s * a.n_heads + hs) * a.n_q + t) * kPfPart;
-      if (p[0] == ninf) continue;
-      const float cw = fast_exp2((p[0] - M) * a.scale_log2);
-      L += p[1] * cw;
-      A += p[4 + d] * cw;
+  if (d4 == 0) { sh_m[grp] = M; sh_l[grp] = L; sh_kept[grp] = kept; }
+  *reinterpret_cast<float4*>(&sh_acc[grp][d4 * 4]) = A;
+  __syncthreads();
+  if (slice != 0 || !row) return;
+  float Mt = ninf, Lt = 0.f;
+  float4 At = make_float4(0.f, 0.f, 0.f, 0.f);
+  kept = 0;
+#pragma unroll
+  for (int k = 0; k < SLICES; ++k) { Mt = fmaxf(Mt, sh_m[grp + k]); kept += sh_kept[grp + k]; }
+  if (Mt != ninf) {
+#pragma unroll
+    for (int k = 0; k < SLICES; ++k) {
+      const float cw = fast_exp2((sh_m[grp + k] - Mt) * a.scale_log2);
+      const float4 v = *reinterpret_cast<const float4*>(&sh_acc[grp + k][d4 * 4]);
+      Lt += sh_l[grp + k] * cw;
+      At.x += v.x * cw; At.y += v.y * cw; At.z += v.z * cw; At.w += v.w * cw;
     }
   }
   const int h = a.heads[hs];
   const int64_t o = (int64_t)t * a.n_q_heads + h;        // single sequence
-  a.out[o * kHeadDim + d] = f32_to_16(L > 0.f ? A / L : 0.f, a.f16 != 0);
-  if (a.lse && d == 0) a.lse[o] = L > 0.f ? M * a.scale + logf(L) : ninf;
+  const float inv = Lt > 0.f ? 1.f / Lt : 0.f;
+  const u32x2 w = a.f16 ? (u32x2){pack16<true>(At.x * inv, At.y * inv), pack16<true>(At.z * inv, At.w * inv)}
+                        : (u32x2){pack16<false>(At.x * inv, At.y * inv), pack16<false>(At.z * inv, At.w * inv)};
+  *reinterpret_cast<u32x2*>(a.out + o * kHeadDim + d4 * 4) = w;
+  if (d4 != 0) return;
+  if (a.lse) a.lse[o] = Lt > 0.f ? Mt * a.scale + logf(Lt) : ninf;
+  if (a.act_range && a.count) a.count[(int64_t)hs * a.n_q + t] = kept;   // selecting mode: kept keys over all key ranges
+}
+
+static void launch_prefill_combine(const PrefillArgs& a, hipStream_t s) {
+  if (a.n_splits * a.n_sub > 8) RTP_LAUNCH(prefill_combine_kernel<8>, dim3((unsigned)a.n_q, (unsigned)a.n_heads), dim3(256), 0, s, a);
+  else RTP_LAUNCH(prefill_combine_kernel<2>, dim3((unsigned)((a.n_q + 3) / 4), (unsigned)a.n_heads), dim3(256), 0, s, a);
 }
 
 // Compute units of the current device (256 on the target; also the answer where no device is visible,
@@ -1749,22 +1860,34 @@ static int choose_splits_listed(int n_heads, int32_t T, int64_t chunk_start) {
   return s > base ? (int)s : base;
 }
 
+// Sub-ranges per key range for launches that leave compute units idle all the same (short chunks): as many as fill
+// them, of at least 8 tiles, at most 64 ranges in all.  A sub-range repeats the score product of one tile for its
+// reference and leaves one more partial to merge.  Chunks of 64 queries behind 60000 tokens: 113 -> 26 us for the
+// attention launch, 333 queries behind 131072 (search and lists): 453 -> 145, a 2037-query prompt: 65 -> 25.
+static int choose_sub(int n_heads, int32_t T, int64_t chunk_start, int n_base, int n_splits) {
+  const int64_t wgs = (int64_t)n_heads * ((T + kPwQ - 1) / kPwQ) * n_base;
+  const int64_t max_tiles = (chunk_start + T - 1) / kPfK + 1;
+  if (wgs <= 0) return 1;
+  const int64_t s = std::min(std::min((int64_t)compute_units() / wgs, max_tiles / (8 * n_base)), (int64_t)64 / n_splits);
+  return s > 1 ? (int)s : 1;
+}
+
 static int32_t launch_prefill(const char* who, bool local, PrefillArgs& a, int32_t B, hipStream_t s) {
   if (a.n_heads == 0) return RTP_OK;
   if (a.n_splits < 1) a.n_splits = 1;
+  if (a.n_sub < 1) a.n_sub = 1;
   // dense launches take the wide kernel; the local band (a few dozen key tiles per query tile, many of
   // them masked) stays on the 128-query kernel, whose masked tiles cost less (the wide kernel takes
   // twice as long for the band: its masked blocks leave the pipelined path)
   const int qt = local ? kPfQ : kPwQ;
-  dim3 grid((unsigned)a.n_heads, (unsigned)((a.n_q + qt - 1) / qt), (unsigned)(B * (local ? 1 : a.n_splits)));
+  dim3 grid((unsigned)a.n_heads, (unsigned)((a.n_q + qt - 1) / qt), (unsigned)(B * (local ? 1 : a.n_splits * a.n_sub)));
   if (grid.y > 65535 || grid.z > 65535) return fail(RTP_ERR_INVALID_ARG, "%s: n_q / B too large for one launch", who);
   if (local) {
     if (a.f16) RTP_LAUNCH((flash_prefill_kernel<kModeLocal, true>), grid, dim3(kPfThreads), 0, s, a);
     else RTP_LAUNCH(flash_prefill_kernel<kModeLocal>, grid, dim3(kPfThreads), 0, s, a);
   } else if (a.f16) RTP_LAUNCH((flash_prefill_wide_kernel<kModeDense, 1, true>), grid, dim3(512), 0, s, a);
   else RTP_LAUNCH((flash_prefill_wide_kernel<kModeDense, 1>), grid, dim3(512), 0, s, a);
-  if (!local && a.n_splits > 1)
-    RTP_LAUNCH(prefill_combine_kernel, dim3((unsigned)((a.n_q + 1) / 2), (unsigned)a.n_heads), dim3(256), 0, s, a);
+  if (!local && a.n_splits * a.n_sub > 1) launch_prefill_combine(a, s);
   return check_launch(who);
 }
 
@@ -1834,6 +1957,20 @@ static PrefillTileWs prefill_tile_ws(int32_t n_ret, int32_t T, int64_t chunk_sta
   return w;
 }
 
+// Key ranges of a launch for the retrieval heads under either rule, and the number the workspace has room for.
+struct PrefillRanges {
+  int dense, dense_sub, listed, listed_sub, ws_ranges;
+};
+static PrefillRanges prefill_ranges(int n_ret, int32_t T, int64_t chunk_start) {
+  PrefillRanges r;
+  r.dense = choose_splits(n_ret, T, chunk_start);
+  r.listed = choose_splits_listed(n_ret, T, chunk_start);
+  r.dense_sub = choose_sub(n_ret, T, chunk_start, r.dense, r.dense);
+  r.listed_sub = choose_sub(n_ret, T, chunk_start, r.dense, r.listed);
+  r.ws_ranges = std::max(r.dense * r.dense_sub, r.listed * r.listed_sub);
+  return r;
+}
+
 }  // namespace rtp
 
 using namespace rtp;
@@ -1844,7 +1981,7 @@ extern "C" size_t rtp_sparse_attn_prefill_workspace_bytes(const rtp_layer_desc* 
   const size_t proj = align_up((size_t)layer->n_ret * T * kIndexDim * sizeof(uint16_t), 256);
   const size_t state = align_up((size_t)layer->n_ret * T * sizeof(float), 256);
   // both rules: key-range partials
-  const int ns = choose_splits_listed(layer->n_ret, T, chunk_start < 0 ? 0 : chunk_start);   // (the larger of the two rules)
+  const int ns = prefill_ranges(layer->n_ret, T, chunk_start < 0 ? 0 : chunk_start).ws_ranges;
   const size_t part = ns > 1 ? align_up((size_t)ns * layer->n_ret * T * kPfPart * sizeof(float), 256) : 0;
   // selecting mode: the tile-maximum table and the query tiles' lists of tiles to visit
   const PrefillTileWs tw = prefill_tile_ws(layer->n_ret, T, chunk_start < 0 ? 0 : chunk_start);
@@ -1901,11 +2038,16 @@ extern "C" int32_t rtp_sparse_attn_prefill(const rtp_layer_desc* layer, const vo
   a.lse = lse;
   a.n_heads = layer->n_ret;
   for (int j = 0; j < layer->n_ret; ++j) a.heads[j] = (uint8_t)layer->ret_heads[j];
-  if (!sparse) {                                     // the paper's dense prefill rule
-    a.n_splits = choose_splits(layer->n_ret, T, chunk_start);
-    if (a.n_splits > 1) {
+  a.tau = tau;
+  a.count = count;
+  a.mass = mass;
+  const PrefillRanges ranges = prefill_ranges(layer->n_ret, T, chunk_start);
+  if (!(p < 1.f)) {                                  // the paper's dense prefill rule: nothing to score, nothing to select
+    a.n_splits = ranges.dense;
+    a.n_sub = ranges.dense_sub;
+    if (a.n_splits * a.n_sub > 1) {
       const size_t need = rtp_sparse_attn_prefill_workspace_bytes(layer, T, chunk_start);
-      if (!ws || ((uintptr_t)ws & 255) || ws_bytes < need) a.n_splits = 1;   // no scratch: run unsplit
+      if (!ws || ((uintptr_t)ws & 255) || ws_bytes < need) a.n_splits = a.n_sub = 1;   // no scratch: run unsplit
       a.part = (float*)ws;
     }
     return launch_prefill(who, false, a, 1, (hipStream_t)stream);
@@ -1931,51 +2073,40 @@ extern "C" int32_t rtp_sparse_attn_prefill(const rtp_layer_desc* layer, const vo
   a.kI_head_stride = kI_head_stride;
   a.p = p;
   a.index_scale = index_scale_of(layer);
-  a.tau = tau;
-  a.count = count;
-  a.mass = mass;
   const size_t proj_bytes = align_up((size_t)layer->n_ret * T * kIndexDim * sizeof(uint16_t), 256);
   const size_t state_bytes = align_up((size_t)layer->n_ret * T * sizeof(float), 256);
   a.sel_thr = (float*)((char*)ws + proj_bytes);
   a.part = (float*)((char*)ws + proj_bytes + state_bytes);
-  a.n_splits = p < 1.f ? choose_splits_listed(layer->n_ret, T, chunk_start) : choose_splits(layer->n_ret, T, chunk_start);
+  a.n_splits = ranges.listed;
+  a.n_sub = ranges.listed_sub;
   {
-    // (the layout does not depend on p: the partials' region has the size of the larger rule)
-    const int ns_ws = choose_splits_listed(layer->n_ret, T, chunk_start);
-    const size_t part_bytes = ns_ws > 1 ? align_up((size_t)ns_ws * layer->n_ret * T * kPfPart * sizeof(float), 256) : 0;
+    const size_t part_bytes = ranges.ws_ranges > 1 ? align_up((size_t)ranges.ws_ranges * layer->n_ret * T * kPfPart * sizeof(float), 256) : 0;
     const PrefillTileWs tw = prefill_tile_ws(layer->n_ret, T, chunk_start);
     char* at = (char*)ws + proj_bytes + state_bytes + part_bytes;
     a.n_t64 = tw.n_t64;
     a.tile_max = (float*)at;
     a.act_list = (int32_t*)(at + tw.table_bytes);
     a.act_count = (int32_t*)(at + tw.table_bytes + tw.list_bytes);
-    if (p < 1.f) {
-      // (the last two ints of the counts' region)
-      a.act_range = a.act_count + (tw.count_bytes / sizeof(int32_t) - 2);
-      a.n_splits_even = std::max(2, choose_splits(layer->n_ret, T, chunk_start));
-    }
+    // (the last two ints of the counts' region)
+    a.act_range = a.act_count + (tw.count_bytes / sizeof(int32_t) - 2);
+    a.n_splits_even = std::max(2, ranges.dense);
   }
-  if (p < 1.f) {
-    constexpr int ks = 8;                                  // waves per 32-query group (see the kernel's header)
-    static_assert(ks == 8, "the launch below names the instantiation");
-    const unsigned n_qtiles = (unsigned)((T + 256 / ks - 1) / (256 / ks));
-    // 1-D grid, padded so that every die gets whole (head, query tile) columns (see the kernel's decoding)
-    unsigned wgs = (unsigned)a.n_heads * n_qtiles;
-    if (a.n_heads <= 8 && 8 % a.n_heads == 0) {
-      const unsigned per_head = 8u / (unsigned)a.n_heads;
-      wgs = 8u * ((n_qtiles + per_head - 1) / per_head);
-    }
-    RTP_LAUNCH(prefill_select_kernel<8>, dim3(wgs), dim3(kSelThreads), 0, (hipStream_t)stream, a);
-    RTP_LAUNCH(prefill_active_tiles_kernel, dim3((unsigned)((T + kPwQ - 1) / kPwQ), (unsigned)a.n_heads), dim3(256), 0,
-               (hipStream_t)stream, a);
+  constexpr int ks = 8;                                    // waves per 32-query group (see the kernel's header)
+  static_assert(ks == 8, "the launch below names the instantiation");
+  const unsigned n_qtiles = (unsigned)((T + 256 / ks - 1) / (256 / ks));
+  // 1-D grid, padded so that every die gets whole (head, query tile) columns (see the kernel's decoding)
+  unsigned wgs = (unsigned)a.n_heads * n_qtiles;
+  if (a.n_heads <= 8 && 8 % a.n_heads == 0) {
+    const unsigned per_head = 8u / (unsigned)a.n_heads;
+    wgs = 8u * ((n_qtiles + per_head - 1) / per_head);
   }
-  dim3 grid((unsigned)a.n_heads, (unsigned)((T + kPwQ - 1) / kPwQ), (unsigned)a.n_splits);
-  if (p < 1.f) grid = dim3((unsigned)a.n_splits, (unsigned)((T + kPwQ - 1) / kPwQ), (unsigned)a.n_heads);
+  RTP_LAUNCH(prefill_select_kernel<8>, dim3(wgs), dim3(kSelThreads), 0, (hipStream_t)stream, a);
+  const unsigned n_wide = (unsigned)((T + kPwQ - 1) / kPwQ);
+  RTP_LAUNCH(prefill_active_tiles_kernel, dim3(n_wide, (unsigned)a.n_heads), dim3(256), 0, (hipStream_t)stream, a);
+  const dim3 grid((unsigned)(a.n_splits * a.n_sub), n_wide, (unsigned)a.n_heads);
   if (a.f16) RTP_LAUNCH((flash_prefill_wide_kernel<kModeSparse, 1, true>), grid, dim3(512), 0, (hipStream_t)stream, a);
   else RTP_LAUNCH((flash_prefill_wide_kernel<kModeSparse, 1>), grid, dim3(512), 0, (hipStream_t)stream, a);
-  if (a.n_splits > 1)
-    RTP_LAUNCH(prefill_combine_kernel, dim3((unsigned)((T + 1) / 2), (unsigned)a.n_heads), dim3(256), 0,
-                       (hipStream_t)stream, a);
+  if (a.n_splits * a.n_sub > 1) launch_prefill_combine(a, (hipStream_t)stream);
   return check_launch(who);
 }
 

@@ -378,3 +378,40 @@ def test_sparse_prefill_partial_query_groups(chunk_start, T):
     print(f"[case] sparse prefill, partial group, T {T} behind {chunk_start}", flush=True)
     w = wl.small_prefill(DEV, p=0.9, chunk_start=chunk_start, T=T, seed=101 + T)
     _check_sparse_prefill(w, f"partial_{chunk_start}_{T}", 0.9)
+
+
+@pytest.mark.parametrize("chunk_start,T", [(0, 257), (63, 130), (191, 257), (256, 256), (449, 65), (640, 511)])
+@pytest.mark.parametrize("kv_dtype", ["bf16", "fp16"])
+def test_prefill_dense_rule_around_the_steady_loop(chunk_start, T, kv_dtype):
+    """Key ranges whose mask-free part begins, ends or is cut short on, before and behind the edges of the 64-key tiles
+    and of the 256-query tiles; partial query tiles leave waves without a query.  The dense rule with statistics."""
+    print(f"[case] dense rule, T {T} behind {chunk_start}, {kv_dtype}", flush=True)
+    w = wl.small_prefill(DEV, chunk_start=chunk_start, T=T, n_q_heads=4, n_kv_heads=2, ret_heads=(1,), seed=111 + T, kv_dtype=kv_dtype)
+    _check_dense_rule(w, f"{chunk_start}+{T}")
+
+
+@pytest.mark.parametrize("chunk_start,T", [(9000, 1), (4000, 64), (3000, 300), (505, 9)])
+def test_prefill_dense_rule_short_chunks_in_many_key_ranges(chunk_start, T):
+    """Short chunks cut their keys into up to 64 ranges (512 keys at the least) and merge them."""
+    print(f"[case] dense rule, T {T} behind {chunk_start}", flush=True)
+    w = wl.small_prefill(DEV, chunk_start=chunk_start, T=T, n_q_heads=4, n_kv_heads=2, ret_heads=(1,), seed=131 + T)
+    _check_dense_rule(w, f"{chunk_start}+{T}")
+    _check_sparse_prefill(w, f"{chunk_start}+{T}", 0.9)
+
+
+def _check_dense_rule(w, what):
+    L = w.layer
+    run = PrefillRun(w)
+    run.sparse_prefill(p=1.0)
+    torch.cuda.synchronize()
+    oi = prefill_oracle_inputs(w)
+    rows = [(t, h) for t in range(w.T) for h in L.ret_heads]
+    ref = orc.dense_rows(rows=rows, q_bits=oi["q_bits"], K_bits=oi["K_bits"], V_bits=oi["V_bits"], chunk_start=w.chunk_start,
+                         n_q_heads=L.n_q_heads, n_kv_heads=L.n_kv_heads, kv_dtype=L.kv_dtype)
+    got = run.out.float().cpu().numpy().astype(np.float64)
+    lse = run.lse.cpu().numpy()
+    for r in ref:
+        check_out(got[r["t"], r["h"]], r["out"], f"{what} t{r['t']} h{r['h']}", tight="mfma")
+        assert abs(lse[r["t"], r["h"]] - r["lse"]) < 3e-3
+    assert np.array_equal(run.count.cpu().numpy(), np.tile(w.chunk_start + np.arange(w.T) + 1, (L.n_ret, 1)))
+    assert np.all(run.mass.cpu().numpy() == 1.0) and np.all(np.isneginf(run.tau.cpu().numpy()))
