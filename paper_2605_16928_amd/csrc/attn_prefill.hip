@@ -70,6 +70,18 @@ struct PrefillArgs {
   int32_t* act_count;           // [n_ret, ceil(n_q / 256)]
   int32_t* act_range;           // {longest list, shortest list} of the launch (the search resets, the list kernel updates)
   int32_t n_splits_even;        // key ranges per query tile when the lists are about equally long
+  // a threshold search cut into launches, n_slice workgroups per 32-query group (short chunks; see prefill_select_kernel)
+  int32_t n_slice;
+  float* sl_max;                // [groups, n_slice, 32]: the slices' row maxima
+  double* sl_hist;              // [2, groups, n_slice, 128, 32]: the slices' histograms, of the current sweep and the one before
+  struct SelState* sl_state;    // [2, groups, 32]: what a scan found, read by the next launch
+  int32_t* sl_again;            // [groups]: 1 = some query's threshold lies in the open-ended bin, the last launch searches the group
+};
+
+struct SelState {               // one query between two launches of a sliced search
+  double Z, above;
+  float selM, x_max;
+  int32_t prefix, pad;
 };
 
 // Key ranges a selecting launch behind a threshold search really uses: the grid is sized for lists that differ
@@ -439,6 +451,12 @@ __device__ __forceinline__ float sel_first_below(float M, float index_scale, flo
 // The library launches KS = 8, one group per workgroup: when a few queries of a chunk have their threshold deep in the
 // background while the others' sweeps 2 and 3 visit a handful of tiles, short workgroups let the dispatcher even
 // the load out.
+// A chunk of few groups leaves most of the chip idle that way (333 queries of 4 heads: 44 workgroups, 0.88 ms at 128K
+// tokens).  Then the search runs as five launches with n_slice workgroups per group, each sweeping a slice of the
+// group's keys: STEP = 0 .. 3 are the sweeps -- a launch first merges what the slices of the launch before left
+// (maxima, histograms: plain stores and sums in slice order, no atomics) and repeats the scan in every slice -- and
+// kSelFinish scans the last histogram; the kernel boundaries are the only synchronisation.  Every sum has the same
+// terms as in one workgroup, in fp64.  0.88 -> 0.20 ms there.
 //
 // A threshold inside the open-ended last coarse bin (candidates 15.875 or more below the row maximum) is not
 // taken as "keep everything": the workgroup repeats sweep 1 with the reference lowered by 15.875 for the queries
@@ -448,9 +466,12 @@ constexpr int kSelThreads = 512;
 constexpr float kSelLumpT = 15.875f;               // (kSelBins - 1) / 8: where the open-ended bin starts
 constexpr double kSelLumpScale = 7843180.797657975;   // exp(15.875)
 constexpr int kSelMaxRounds = 24;
+constexpr int kSelAll = -1, kSelFinish = 4;        // STEP of prefill_select_kernel beside the sweeps 0 .. 3
 
-template <int KS>
+template <int KS, int STEP>
 __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const PrefillArgs a) {
+  constexpr bool kSliced = STEP >= 0 && STEP < kSelFinish;             // this launch sweeps a slice of the group's keys
+  constexpr bool kWhole = STEP == kSelAll || STEP == kSelFinish;       // ... or can run the whole search
   constexpr int NW = kSelThreads / 64;                             // waves per workgroup
   constexpr int NG = NW / KS;                                      // query groups per workgroup
   constexpr int kSelQ = 32 * NG;                                   // queries per workgroup
@@ -465,6 +486,7 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
   // keys and meet in that L2.
   int j, qtile;
   const int n_qtiles = (a.n_q + kSelQ - 1) / kSelQ;
+  const int n_slice = kSliced ? a.n_slice : 1;
   if (a.n_heads <= 8 && 8 % a.n_heads == 0) {
     const int per_head = 8 / a.n_heads;                            // dies per head
     const int die = blockIdx.x & 7, k = blockIdx.x >> 3;
@@ -474,11 +496,13 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
     j = blockIdx.x % a.n_heads;
     qtile = blockIdx.x / a.n_heads;
   }
-  if (blockIdx.x == 0 && tid == 0) {                               // for prefill_active_tiles_kernel, which runs next
+  if (kWhole && blockIdx.x == 0 && tid == 0) {                     // for prefill_active_tiles_kernel, which runs next
     a.act_range[0] = 0;
     a.act_range[1] = 0x7fffffff;
   }
-  if (qtile >= n_qtiles) return;                                   // (the whole workgroup)
+  if (qtile >= n_qtiles * n_slice) return;                         // (the whole workgroup)
+  const int slice = qtile / n_qtiles;
+  qtile -= slice * n_qtiles;
   const int t0 = (n_qtiles - 1 - qtile) * kSelQ;                   // long rows first
   const int qgroup = wave / KS, part = wave - qgroup * KS;         // this wave's queries and its share of their keys
   const int tw = t0 + qgroup * 32;                                 // first query of the group
@@ -515,7 +539,7 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
   int lcnt = 0;                     // entries in this lane's member list
   const uint32_t lst_base = (uint32_t)(size_t)(__attribute__((address_space(3))) float*)&lst[0][lane];
 
-  auto load_k = [&](int tile) {
+  auto load_k = [&](int tile) __attribute__((always_inline)) {
     const int nrow = min(tile * 32 + r, n_rows - 1);               // rows past the chunk are causally masked anyway
     return *reinterpret_cast<const u32x4*>(kIg + (int64_t)nrow * kIndexDim + g * 8);
   };
@@ -523,17 +547,17 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
   // is not used): a scalar base and one lane offset, no vector arithmetic
   const uint32_t k_lane = (uint32_t)(r * kIndexDim + g * 8) * 2u;
   const int last_whole = n_rows / 32 - 1;
-  auto load_k_whole = [&](int tile) {
+  auto load_k_whole = [&](int tile) __attribute__((always_inline)) {
     const unsigned char* base = reinterpret_cast<const unsigned char*>(kIg) + (int64_t)min(tile, last_whole) * (32 * kIndexDim * 2);
     return *reinterpret_cast<const u32x4*>(base + k_lane);
   };
   // the group's waves clear their histogram together (followed by a barrier at the call sites)
-  auto zero_hist = [&]() {
+  auto zero_hist = [&]() __attribute__((always_inline)) {
     double* h = &hist[0][0];
     for (int i = part * 64 + lane; i < kSelBins * 32; i += KS * 64) h[i] = 0.0;
   };
   // One candidate's mass into bin `bin` of this lane's query.
-  auto add_mass = [&](int bin, float tt) {
+  auto add_mass = [&](int bin, float tt) __attribute__((always_inline)) {
     const float wgt = fast_exp2(tt * -1.4426950408889634f);        // exp(s - M)
     atomicAdd(&hist[bin][r], (double)wgt);
   };
@@ -552,7 +576,7 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
   // Weighs the listed members of every lane: lane-private lists, so the only cross-lane step is the loop bound.
   // Four entries at a time: their reads, exponentials and atomics overlap (one by one, a drain is a chain of LDS round
   // trips that costs a wave more than the pairs between two drains).
-  auto drain_list = [&]() {
+  auto drain_list = [&]() __attribute__((always_inline)) {
 #pragma unroll 1
     for (int k = 0; __ballot(k < lcnt) != 0ull; k += 4) {
       float x[4];
@@ -570,7 +594,7 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
   };
 
   // Stores x at the LDS address `end` and advances it, in the lanes whose median equals x.
-  auto append_if_member = [](uint32_t& end, float x, float median) {
+  auto append_if_member = [](uint32_t& end, float x, float median) __attribute__((always_inline)) {
     uint64_t lanes;
     asm volatile("s_mov_b64 %1, exec\n\tv_cmpx_eq_f32_e64 exec, %2, %3\n\tds_write_b32 %0, %2\n\tv_add_u32_e32 %0, 0x100, %0\n\t"
                  "s_mov_b64 exec, %1"
@@ -581,7 +605,7 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
   // the lowered reference --, 2 / 3: members of the digit prefix): SI = its 32 x 32 index products, nb = its first
   // key.  MASKED: causality and the lowered reference are tested pair by pair.
   float t_least = ninf;             // masked sweep 1: candidates have 8 (M - s) >= t_least
-  auto tile_work = [&](auto PH, auto MASKED, const f32x16& SI, int nb, float& mxacc) -> float {
+  auto tile_work = [&](auto PH, auto MASKED, const f32x16& SI, int nb, float& mxacc) __attribute__((always_inline)) -> float {
     constexpr int phase = decltype(PH)::value;
     constexpr bool masked = decltype(MASKED)::value;
     if (phase == 0) {
@@ -684,7 +708,7 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
   // Sweeps 2 and 3 consult the maximum table pair by pair: skip what cannot hold a member, and in sweep 3 note which
   // pairs a query can keep a key in.  no_look: nearly every pair can hold a member and is needed (see sweep_picked);
   // the pairs keep their maxima in the table, which is the conservative answer.
-  auto sweep = [&](auto PH, auto MASKED, int tile_begin, int tile_end, bool no_look = false) {
+  auto sweep = [&](auto PH, auto MASKED, int tile_begin, int tile_end, bool no_look = false) __attribute__((always_inline)) {
     if (tile_begin >= tile_end) return;
     constexpr int phase_ = decltype(PH)::value;
     constexpr bool kSkip = phase_ == 2 || phase_ == 3;
@@ -751,7 +775,8 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
   const int n_plain = n_interior / kSelRing * kSelRing;            // whole rounds of interior tiles run without masks
   // this wave's share: an equal run of the rounds, the masked ones of the edge (one or two) at the end
   const int plain_rounds = n_plain / kSelRing, rounds = (n_tiles + kSelRing - 1) / kSelRing;
-  const int round_lo = rounds * part / KS, round_hi = rounds * (part + 1) / KS;
+  const int share = slice * KS + part, shares = n_slice * KS;
+  const int round_lo = (int)((int64_t)rounds * share / shares), round_hi = (int)((int64_t)rounds * (share + 1) / shares);
   const int plain_lo = min(round_lo, plain_rounds) * kSelRing, plain_hi = min(round_hi, plain_rounds) * kSelRing;
   const int edge_lo = max(round_lo, plain_rounds) * kSelRing, edge_hi = round_hi * kSelRing;
   // Sweeps 2 and 3 over the mask-free range, 512 tiles (256 entries of the maximum table) at a time: where at most
@@ -760,7 +785,7 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
   // consulting the table per pair unless that can skip next to nothing and, in sweep 3, nine in ten of the pairs
   // the wave has looked at turned out to hold a product some query can keep (a group with one moderately hard query
   // among easy ones is not such a case: looking tells which pairs that query really keeps a key in).
-  auto sweep_picked = [&](auto PH, int tile_begin, int tile_end) {
+  auto sweep_picked = [&](auto PH, int tile_begin, int tile_end) __attribute__((always_inline)) {
     constexpr int phase_ = decltype(PH)::value;
 #pragma unroll 1
     for (int tb = tile_begin; tb < tile_end; tb += 512) {
@@ -803,7 +828,7 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
       }
     }
   };
-  auto sweep_all = [&](auto PH) {
+  auto sweep_all = [&](auto PH) __attribute__((always_inline)) {
     constexpr int phase_ = decltype(PH)::value;
     if constexpr (phase_ == 2 || phase_ == 3) sweep_picked(PH, plain_lo, plain_hi);
     else sweep(PH, std::false_type{}, plain_lo, plain_hi);
@@ -825,7 +850,7 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
   constexpr int kRuns = 2 * KS, kRunBins = kSelBins / kRuns;
   double (*run_sum)[32] = reinterpret_cast<double (*)[32]>(&list_all[0][0][0]) + qgroup * kRuns;
   static_assert(kSelBins % kRuns == 0 && sizeof(double) * 32 * kRuns * NG + sizeof(int) * NW <= sizeof(list_all), "runs of equal length");
-  auto scan = [&](bool whole, bool take) {
+  auto scan = [&](bool whole, bool take) __attribute__((always_inline)) {
     {
       double h[kRunBins], sum = 0.0;
 #pragma unroll
@@ -870,8 +895,9 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
   };
 
   // ---- sweep 0: the row maxima ----
-  sweep_all(std::integral_constant<int, 0>{});
-  {
+  // (of this workgroup's share of the keys, in every wave)
+  auto row_maxima = [&]() __attribute__((always_inline)) {
+    sweep_all(std::integral_constant<int, 0>{});
     float mx = mxs[0];
 #pragma unroll
     for (int u = 1; u < kSelMfma; ++u) mx = fmaxf(mx, mxs[u]);
@@ -883,50 +909,57 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
     for (int k = 0; k < KS; ++k) mx = fmaxf(mx, max_all[qgroup * KS + k][r]);
     x_max = mx;
     selM = mx * cs;
-  }
-  __syncthreads();                                                  // the maxima are read: the lists' memory is free again
-
-  // ---- sweep 1: the first digit; repeated with a lowered reference while some query's threshold lies in the
-  // open-ended bin ----
-  bool repeat_me = false, rebased = false;
-  for (int round = 0; round < kSelMaxRounds; ++round) {
-    selM8 = (round == 0 || repeat_me) ? selM * 8.0f : ninf;         // (exact unless it overflows)
-    if (round == 0) {
-      sweep_all(std::integral_constant<int, 1>{});
-    } else {
-      t_least = 0.f;                                                // (no mask-free form: repeats are rare)
-      sweep(std::integral_constant<int, 1>{}, std::true_type{}, plain_lo, plain_hi);
-      sweep(std::integral_constant<int, 1>{}, std::true_type{}, edge_lo, edge_hi);
-    }
-    __syncthreads();                                                // every wave of the group has added its masses
-    scan(round == 0, round == 0 || repeat_me);
-    // the threshold in the open-ended bin: everything above it is counted (cum), its members go round again
-    repeat_me = (round == 0 || repeat_me) && !idle && bsel == kSelBins - 1 && hsel > 0.0 && round + 1 < kSelMaxRounds;
-    // does any query of the workgroup repeat?  (flags in the lists' memory, idle in this phase; the barrier also
-    // says that every wave has read the histograms)
+    __syncthreads();                                                // the maxima are read: the lists' memory is free again
+  };
+  bool rebased = false;
+  // after a scan of sweep 1: is this query's threshold in the open-ended bin?
+  auto in_open_bin = [&]() __attribute__((always_inline)) { return !idle && bsel == kSelBins - 1 && hsel > 0.0; };
+  // the same for any query of the workgroup (flags in the lists' memory, idle in this phase; the barrier also says
+  // that every wave has read the histograms)
+  auto any_of = [&](bool mine_) __attribute__((always_inline)) {
     int* flags = reinterpret_cast<int*>(reinterpret_cast<double (*)[32]>(&list_all[0][0][0]) + NG * kRuns);
-    const bool mine = __ballot(repeat_me) != 0ull;
+    const bool mine = __ballot(mine_) != 0ull;
     if (lane == 0) flags[wave] = mine ? 1 : 0;
     __syncthreads();
     int any = 0;
 #pragma unroll
     for (int w = 0; w < NW; ++w) any |= flags[w];
-    if (!any) break;
-    if (repeat_me) {
-      rebased = true;
-      selM -= kSelLumpT;
-      Z *= kSelLumpScale;
-      above = cum * kSelLumpScale;
+    return any != 0;
+  };
+
+  // ---- sweep 1: the first digit; repeated with a lowered reference while some query's threshold lies in the
+  // open-ended bin ----
+  auto first_digit = [&]() __attribute__((always_inline)) {
+    bool repeat_me = false;
+    for (int round = 0; round < kSelMaxRounds; ++round) {
+      selM8 = (round == 0 || repeat_me) ? selM * 8.0f : ninf;       // (exact unless it overflows)
+      if (round == 0) {
+        sweep_all(std::integral_constant<int, 1>{});
+      } else {
+        t_least = 0.f;                                              // (no mask-free form: repeats are rare)
+        sweep(std::integral_constant<int, 1>{}, std::true_type{}, plain_lo, plain_hi);
+        sweep(std::integral_constant<int, 1>{}, std::true_type{}, edge_lo, edge_hi);
+      }
+      __syncthreads();                                              // every wave of the group has added its masses
+      scan(round == 0, round == 0 || repeat_me);
+      // the threshold in the open-ended bin: everything above it is counted (cum), its members go round again
+      repeat_me = (round == 0 || repeat_me) && in_open_bin() && round + 1 < kSelMaxRounds;
+      if (!any_of(repeat_me)) break;
+      if (repeat_me) {
+        rebased = true;
+        selM -= kSelLumpT;
+        Z *= kSelLumpScale;
+        above = cum * kSelLumpScale;
+      }
+      zero_hist();
+      __syncthreads();
     }
-    zero_hist();
-    __syncthreads();
-  }
-  prefix = bsel;
-  above = cum;
+    prefix = bsel;
+    above = cum;
+  };
 
   // ---- sweeps 2 and 3: the second and third digit among the members of the prefix ----
-#pragma unroll 1
-  for (int phase = 2; phase < 4; ++phase) {
+  auto member_range = [&](int phase) __attribute__((always_inline)) {
     // members of the prefix: prefix << shift <= q < (prefix + 1) << shift; for the non-negative
     // tt = M - s of a candidate that is qlo / 2^17 <= tt < qhi / 2^17 (the last bin is open-ended),
     // and in terms of the raw product x: first x with tt < hi bound <= x < first x with tt < lo bound
@@ -949,15 +982,94 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
     xlo_wave = -wave_max_f32(idle ? ninf : -x_lo);
     xlo_wave_top = wave_max_f32(idle ? ninf : x_lo);
     shift -= 7;                                                     // of this sweep's digit: 7, then 0
-    zero_hist();
+  };
+
+  // a sliced search: the histogram of the group from what its slices left in the launch before
+  const int groups = a.n_heads * n_qtiles, grp = j * n_qtiles + qtile;
+  constexpr int kHistN = kSelBins * 32, kHistPer = kHistN / kSelThreads;
+  auto merge_slices = [&](int n) __attribute__((always_inline)) {
+    const double* old = a.sl_hist + ((int64_t)(1 - (STEP & 1)) * groups + grp) * n * kHistN + tid;
+    double sum[kHistPer];
+#pragma unroll
+    for (int i = 0; i < kHistPer; ++i) sum[i] = 0.0;
+#pragma unroll 4
+    for (int k = 0; k < n; ++k) {
+#pragma unroll
+      for (int i = 0; i < kHistPer; ++i) sum[i] += old[(int64_t)k * kHistN + i * kSelThreads];
+    }
+#pragma unroll
+    for (int i = 0; i < kHistPer; ++i) (&hist[0][0])[tid + i * kSelThreads] = sum[i];
     __syncthreads();
-    if (phase == 2) sweep_all(std::integral_constant<int, 2>{});
-    else sweep_all(std::integral_constant<int, 3>{});
+  };
+  if constexpr (kSliced) {
+    const int64_t mine_at = (int64_t)grp * n_slice + slice;
+    double* const own = a.sl_hist + ((int64_t)(STEP & 1) * groups * n_slice + mine_at) * kHistN;          // written by this launch
+    if constexpr (STEP == 0) {
+      row_maxima();
+      if (tid < 32) a.sl_max[mine_at * 32 + r] = x_max;
+      return;
+    }
+    if constexpr (STEP == 1) {
+      x_max = ninf;
+      for (int k = 0; k < n_slice; ++k) x_max = fmaxf(x_max, a.sl_max[((int64_t)grp * n_slice + k) * 32 + r]);
+      selM = x_max * cs;
+      selM8 = selM * 8.0f;
+      zero_hist();
+      __syncthreads();
+      sweep_all(std::integral_constant<int, 1>{});
+    } else if constexpr (STEP >= 2) {
+      if (STEP == 3 && a.sl_again[grp] != 0) return;                  // (the same for the whole workgroup)
+      merge_slices(n_slice);
+      if (STEP == 2) {
+        x_max = ninf;
+        for (int k = 0; k < n_slice; ++k) x_max = fmaxf(x_max, a.sl_max[((int64_t)grp * n_slice + k) * 32 + r]);
+        selM = x_max * cs;
+      } else {
+        const SelState st = a.sl_state[(int64_t)grp * 32 + r];
+        Z = st.Z; above = st.above; selM = st.selM; x_max = st.x_max; prefix = st.prefix;
+      }
+      scan(STEP == 2, true);
+      if (STEP == 2) {
+        const bool again = any_of(in_open_bin());
+        if (slice == 0 && tid == 0) a.sl_again[grp] = again ? 1 : 0;
+        if (again) return;
+      }
+      prefix = STEP == 2 ? bsel : (prefix << 7) | bsel;
+      above = cum;
+      if (slice == 0 && tid < 32) a.sl_state[((int64_t)(STEP - 2) * groups + grp) * 32 + r] = SelState{Z, above, selM, x_max, prefix, 0};
+      __syncthreads();                                              // every wave has read the histogram
+      member_range(STEP);
+      zero_hist();
+      __syncthreads();
+      sweep_all(std::integral_constant<int, STEP>{});
+    }
     __syncthreads();
+    for (int i = tid; i < kHistN; i += kSelThreads) own[i] = (&hist[0][0])[i];
+    return;
+  }
+
+  if (STEP == kSelFinish && a.sl_again[grp] == 0) {
+    const SelState st = a.sl_state[((int64_t)groups + grp) * 32 + r];
+    Z = st.Z; above = st.above; selM = st.selM; x_max = st.x_max; prefix = st.prefix;
+    merge_slices(a.n_slice);
     scan(false, true);
     prefix = (prefix << 7) | bsel;
-    above = cum;
-    __syncthreads();                                                // every wave has read the histograms
+  } else {
+    row_maxima();
+    first_digit();
+#pragma unroll 1
+    for (int phase = 2; phase < 4; ++phase) {
+      member_range(phase);
+      zero_hist();
+      __syncthreads();
+      if (phase == 2) sweep_all(std::integral_constant<int, 2>{});
+      else sweep_all(std::integral_constant<int, 3>{});
+      __syncthreads();
+      scan(false, true);
+      prefix = (prefix << 7) | bsel;
+      above = cum;
+      __syncthreads();                                              // every wave has read the histograms
+    }
   }
   // a threshold inside the open-ended last coarse bin (only after the last repeat) keeps every candidate
   const bool lump = (prefix >> 14) == kSelBins - 1;
@@ -1290,22 +1402,6 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
       }
     }
   };
-  // probabilities against the fixed reference; masked scores are -inf and give exactly 0
-  auto softmax_fixed = [&](const f32x16 (&S)[QB], uint32_t (&P)[QB][8]) __attribute__((always_inline)) {
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      const float mc = mrow[qb] * c;
-      float lsum = 0.f;
-#pragma unroll
-      for (int i = 0; i < 16; i += 2) {
-        const float p0 = fast_exp2(fmaf(S[qb][i], c, -mc));
-        const float p1 = fast_exp2(fmaf(S[qb][i + 1], c, -mc));
-        lsum += p0 + p1;
-        P[qb][i >> 1] = pack16<F16>(p0, p1);
-      }
-      lrow[qb] += lsum;
-    }
-  };
   // l += both halves of a packed pair of probabilities, i.e. the values as rounded to bf16 (what the PV
   // product multiplies): one instruction, and of a kind the compiler leaves where it is written (plain
   // additions get collected behind the last MFMA of the sequence, where nothing hides them)
@@ -1317,6 +1413,24 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
   auto row_sum_add = [&](float& l, uint32_t pk) __attribute__((always_inline)) {
     if constexpr (F16) asm volatile("v_dot2c_f32_f16 %0, %1, %2" : "+v"(l) : "v"(pk), "v"(0x3c003c00u));
     else asm volatile("v_dot2c_f32_bf16 %0, %1, %2" : "+v"(l) : "v"(pk), "v"(0x3f803f80u));
+  };
+  // probabilities against the fixed reference; masked scores are -inf and give exactly 0
+  // (summed as rounded to 16 bits, like everywhere: a row of few tokens then divides by what it was multiplied with)
+  auto softmax_fixed = [&](const f32x16 (&S)[QB], uint32_t (&P)[QB][8]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      const float mc = mrow[qb] * c;
+      float lsum = 0.f;
+#pragma unroll
+      for (int i = 0; i < 16; i += 2) {
+        const float p0 = fast_exp2(fmaf(S[qb][i], c, -mc));
+        const float p1 = fast_exp2(fmaf(S[qb][i + 1], c, -mc));
+        P[qb][i >> 1] = pack16<F16>(p0, p1);
+        row_sum_add(lsum, P[qb][i >> 1]);
+      }
+      row_sum_settled(lsum);
+      lrow[qb] += lsum;
+    }
   };
   // The steady-state step: the PV MFMAs of the previous block and the softmax of the current block as
   // ONE hand-interleaved instruction sequence -- per MFMA (32 cycles of the matrix pipe) one pair of
@@ -1941,6 +2055,30 @@ int32_t prefill_range_attn(const char* who, bool dense, const rtp_layer_desc* L,
   return launch_prefill(who, !dense, a, B, s);
 }
 
+// Workgroups per 32-query group of the threshold search: as many as fill two workgroups per compute unit, each with at
+// least 4096 keys of the longest range, at most 16.  The five launches cost about 60 us beside the sweeps, what one
+// workgroup needs for 9000 keys of a broad score law: the slices have to save more than that (1 to 64 queries behind
+// 60000 tokens: 82 to 93 us against some 400 in one launch; 1000 queries behind 5000 tokens stay at 62 in one).
+static int search_slices(int n_ret, int32_t T, int64_t chunk_start) {
+  const int64_t groups = (int64_t)n_ret * ((T + 31) / 32), keys = chunk_start + T;
+  const int64_t s = std::min(2 * (int64_t)compute_units() / groups, std::min(keys / 4096, (int64_t)16));
+  return s >= 2 && keys - keys / s > 9000 ? (int)s : 1;
+}
+struct SearchWs {
+  size_t max_bytes, hist_bytes, state_bytes, again_bytes;
+  size_t total() const { return max_bytes + hist_bytes + state_bytes + again_bytes; }
+};
+static SearchWs search_ws(int n_ret, int32_t T, int n_slice) {
+  const size_t groups = (size_t)n_ret * ((T + 31) / 32);
+  SearchWs w = {};
+  if (n_slice < 2) return w;
+  w.max_bytes = align_up(groups * n_slice * 32 * sizeof(float), 256);
+  w.hist_bytes = align_up(groups * n_slice * 2 * kSelBins * 32 * sizeof(double), 256);
+  w.state_bytes = align_up(groups * 2 * 32 * sizeof(SelState), 256);
+  w.again_bytes = align_up(groups * sizeof(int32_t), 256);
+  return w;
+}
+
 // Sizes of the tile bookkeeping of a selecting launch.  A table row has one entry per 64 keys of the context, plus
 // the entries the threshold search touches past a group's last tile (its sweeps run in whole rounds of 8 tiles of
 // 32 keys and read the table one round ahead).
@@ -1985,7 +2123,10 @@ extern "C" size_t rtp_sparse_attn_prefill_workspace_bytes(const rtp_layer_desc* 
   const size_t part = ns > 1 ? align_up((size_t)ns * layer->n_ret * T * kPfPart * sizeof(float), 256) : 0;
   // selecting mode: the tile-maximum table and the query tiles' lists of tiles to visit
   const PrefillTileWs tw = prefill_tile_ws(layer->n_ret, T, chunk_start < 0 ? 0 : chunk_start);
-  return proj + state + part + tw.table_bytes + tw.list_bytes + tw.count_bytes;
+  // ... and what the launches of a sliced search hand on
+  const int64_t c0 = chunk_start < 0 ? 0 : chunk_start;
+  const size_t sliced = search_ws(layer->n_ret, T, search_slices(layer->n_ret, T, c0)).total();
+  return proj + state + part + sliced + tw.table_bytes + tw.list_bytes + tw.count_bytes;
 }
 
 extern "C" int32_t rtp_sparse_attn_prefill(const rtp_layer_desc* layer, const void* q_pre, const void* q, const float* WQ,
@@ -2083,6 +2224,13 @@ extern "C" int32_t rtp_sparse_attn_prefill(const rtp_layer_desc* layer, const vo
     const size_t part_bytes = ranges.ws_ranges > 1 ? align_up((size_t)ranges.ws_ranges * layer->n_ret * T * kPfPart * sizeof(float), 256) : 0;
     const PrefillTileWs tw = prefill_tile_ws(layer->n_ret, T, chunk_start);
     char* at = (char*)ws + proj_bytes + state_bytes + part_bytes;
+    a.n_slice = search_slices(layer->n_ret, T, chunk_start);
+    const SearchWs sw = search_ws(layer->n_ret, T, a.n_slice);
+    a.sl_max = (float*)at;
+    a.sl_hist = (double*)(at + sw.max_bytes);
+    a.sl_state = (SelState*)(at + sw.max_bytes + sw.hist_bytes);
+    a.sl_again = (int32_t*)(at + sw.max_bytes + sw.hist_bytes + sw.state_bytes);
+    at += sw.total();
     a.n_t64 = tw.n_t64;
     a.tile_max = (float*)at;
     a.act_list = (int32_t*)(at + tw.table_bytes);
@@ -2094,13 +2242,23 @@ extern "C" int32_t rtp_sparse_attn_prefill(const rtp_layer_desc* layer, const vo
   constexpr int ks = 8;                                    // waves per 32-query group (see the kernel's header)
   static_assert(ks == 8, "the launch below names the instantiation");
   const unsigned n_qtiles = (unsigned)((T + 256 / ks - 1) / (256 / ks));
-  // 1-D grid, padded so that every die gets whole (head, query tile) columns (see the kernel's decoding)
-  unsigned wgs = (unsigned)a.n_heads * n_qtiles;
-  if (a.n_heads <= 8 && 8 % a.n_heads == 0) {
+  // 1-D grid, padded so that every die gets whole (head, query tile, slice) columns (see the kernel's decoding)
+  auto search_grid = [&](unsigned slices) {
+    if (a.n_heads > 8 || 8 % a.n_heads != 0) return dim3((unsigned)a.n_heads * n_qtiles * slices);
     const unsigned per_head = 8u / (unsigned)a.n_heads;
-    wgs = 8u * ((n_qtiles + per_head - 1) / per_head);
+    return dim3(8u * ((n_qtiles * slices + per_head - 1) / per_head));
+  };
+  hipStream_t s = (hipStream_t)stream;
+  if (a.n_slice > 1) {
+    const dim3 grid = search_grid((unsigned)a.n_slice);
+    RTP_LAUNCH((prefill_select_kernel<8, 0>), grid, dim3(kSelThreads), 0, s, a);
+    RTP_LAUNCH((prefill_select_kernel<8, 1>), grid, dim3(kSelThreads), 0, s, a);
+    RTP_LAUNCH((prefill_select_kernel<8, 2>), grid, dim3(kSelThreads), 0, s, a);
+    RTP_LAUNCH((prefill_select_kernel<8, 3>), grid, dim3(kSelThreads), 0, s, a);
+    RTP_LAUNCH((prefill_select_kernel<8, kSelFinish>), search_grid(1), dim3(kSelThreads), 0, s, a);
+  } else {
+    RTP_LAUNCH((prefill_select_kernel<8, kSelAll>), search_grid(1), dim3(kSelThreads), 0, s, a);
   }
-  RTP_LAUNCH(prefill_select_kernel<8>, dim3(wgs), dim3(kSelThreads), 0, (hipStream_t)stream, a);
   const unsigned n_wide = (unsigned)((T + kPwQ - 1) / kPwQ);
   RTP_LAUNCH(prefill_active_tiles_kernel, dim3(n_wide, (unsigned)a.n_heads), dim3(256), 0, (hipStream_t)stream, a);
   const dim3 grid((unsigned)(a.n_splits * a.n_sub), n_wide, (unsigned)a.n_heads);

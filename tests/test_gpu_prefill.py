@@ -415,3 +415,22 @@ def _check_dense_rule(w, what):
         assert abs(lse[r["t"], r["h"]] - r["lse"]) < 3e-3
     assert np.array_equal(run.count.cpu().numpy(), np.tile(w.chunk_start + np.arange(w.T) + 1, (L.n_ret, 1)))
     assert np.all(run.mass.cpu().numpy() == 1.0) and np.all(np.isneginf(run.tau.cpu().numpy()))
+
+
+@pytest.mark.parametrize("chunk_start,T,kw,p", [
+    (13000, 1, {}, 0.9), (20000, 33, {}, 0.8), (14335, 40, dict(own_frac=0.99, pick_run=32), 0.9), (30001, 70, dict(index_mode="proj"), 0.95)])
+def test_sparse_prefill_sliced_search(chunk_start, T, kw, p):
+    """Short chunks behind long prefixes: the threshold search runs as one launch per sweep with several workgroups per
+    query group, whose maxima and histograms the next launch merges."""
+    print(f"[case] sliced search, T {T} behind {chunk_start}", flush=True)
+    w = wl.small_prefill(DEV, p=p, chunk_start=chunk_start, T=T, seed=151 + T, n_q_heads=4, n_kv_heads=2, ret_heads=(1,), **kw)
+    _check_sparse_prefill(w, f"sliced_{chunk_start}_{T}", p)
+
+
+def test_sparse_prefill_sliced_search_with_a_threshold_in_the_open_ended_bin():
+    """A query group with a threshold more than 15.875 below a row maximum leaves the sliced form: its last launch searches
+    the group from the start."""
+    print("[case] sliced search, threshold far below the maximum", flush=True)
+    w = wl.small_prefill("cpu", p=0.999999, chunk_start=13000, T=40, seed=98)
+    w.layer.index_scale = 2.5
+    _check_sparse_prefill(w.to(DEV), "sliced_far", 0.999999)
