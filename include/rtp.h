@@ -113,7 +113,8 @@ const char* rtp_version(void);
  * after allocation; rtp_topp_select with level1_ready = 1 leaves it initialised again).  When given,
  * the score pass also accumulates the first level of the selector's mass histogram while the scores
  * are in registers, and the following rtp_topp_select(..., level1_ready = 1, same workspace, row_len =
- * ctx_len of each row, max_len = max_ctx) skips its first two launches.
+ * ctx_len of each row, max_len = max_ctx) skips its first two launches.  With max_ctx <= 8192 the selection is one launch
+ * that needs nothing but the scores; the score pass then leaves the workspace as it is.
  */
 int32_t rtp_index_score(const rtp_layer_desc* layer, const void* q_in, const float* WQ,
                         const void* kI, int64_t kI_head_stride,
@@ -148,6 +149,7 @@ int32_t rtp_index_score(const rtp_layer_desc* layer, const void* q_in, const flo
  *   level1_ready  0: the call is self-contained and the workspace contents do not matter.
  *             1: rtp_index_score has accumulated the first histogram level into this (initialised)
  *             workspace; the call starts at level 2 and leaves the workspace initialised for the next step.
+ *             (max_len <= 8192: either way one launch that does not use the workspace's contents.)
  */
 size_t rtp_topp_workspace_bytes(int32_t R, int64_t max_len);
 /* Zero-fills a top-p workspace (needed once before it is first handed to rtp_index_score). */

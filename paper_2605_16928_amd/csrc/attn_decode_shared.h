@@ -86,10 +86,11 @@ __device__ __forceinline__ float row_share(float x) {      // every lane reads l
 // The work items first_item, first_item + item_step, ... of a workgroup of THREADS threads, TILES tiles per wave
 // in flight (alone in its launch the kernel runs 256 threads and 2 tiles: 1, 3 and 4 measured slower).
 // PAGED: token position p of sequence b lives in pool row page_table[b][p >> page_shift] * page_size + p % page_size
-// (rows of a bounded cache are never paged).
+// (rows of a bounded cache are never paged).  direct: an item holds all of its unit's tokens (n_splits == 1) and writes
+// the local heads' results instead of partials.
 template <int G, int SRC, int THREADS, int TILES, bool F16 = false, bool PAGED = false>
 __device__ __forceinline__ void gqa_decode_items(const AttnDecodeArgs& a, const int first_item, const int item_step,
-                                                 const int item_end = -1) {
+                                                 const int item_end = -1, const bool direct = false) {
   static_assert(SRC != kSrcSparse && G >= 2 && G <= 16, "range sources, GQA groups");
   constexpr int kTile = 16;                 // tokens per MFMA tile
   constexpr int kTilesInFlight = TILES;     // 8 x 16-byte loads per lane and tile in flight
@@ -108,7 +109,16 @@ __device__ __forceinline__ void gqa_decode_items(const AttnDecodeArgs& a, const 
     const int b = unit / a.n_kv_heads, kvh = unit - b * a.n_kv_heads, h0 = kvh * G;
     const int n_tok = unit_tokens<SRC>(a, unit);
     const int t_begin = split * ST, t_end = min(n_tok, t_begin + ST);
-    if (t_begin >= n_tok) continue;
+    if (t_begin >= n_tok) {
+      if (direct) {                           // a sequence without tokens
+        for (int e = tid; e < G * kHeadDim; e += kAdThreads) {
+          if (a.is_ret[h0 + (e >> 7)]) continue;
+          a.out[((int64_t)b * a.n_q_heads + h0) * kHeadDim + e] = 0;
+          if (a.lse && (e & 127) == 0) a.lse[(int64_t)b * a.n_q_heads + h0 + (e >> 7)] = ninf;
+        }
+      }
+      continue;
+    }
     int s0 = 0, w0 = 0;
     if (SRC == kSrcLocal) {
       const int n = a.ctx_len[b];
@@ -258,6 +268,13 @@ __device__ __forceinline__ void gqa_decode_items(const AttnDecodeArgs& a, const 
           L += sh_l[w][hh] * cw;
           A += sh_acc[w][hh][d] * cw;
         }
+      }
+      if (direct) {
+        if (a.is_ret[h0 + hh]) continue;
+        const int64_t o = (int64_t)b * a.n_q_heads + h0 + hh;
+        a.out[o * kHeadDim + d] = f32_to_16(L > 0.f ? A / L : 0.f, a.f16 != 0);
+        if (a.lse && d == 0) a.lse[o] = L > 0.f ? (M + log2f(L)) * 0.6931471805599453f : ninf;
+        continue;
       }
       pout[hh * kPartStride + 4 + d] = A;
       if (d == 0) { pout[hh * kPartStride] = M; pout[hh * kPartStride + 1] = L; }

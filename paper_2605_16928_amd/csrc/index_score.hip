@@ -189,7 +189,7 @@ static int32_t run_index_score(const char* who, bool probe, const rtp_layer_desc
     if (((uintptr_t)topp_ws & 255) || topp_ws_bytes < l.total)
       return fail(RTP_ERR_WORKSPACE, "%s: top-p workspace of %zu bytes (256-byte aligned) required, got %zu", who,
                   l.total, topp_ws_bytes);
-    hist = (uint64_t*)((char*)topp_ws + l.hist_off);
+    if (max_ctx > kTpChunk) hist = (uint64_t*)((char*)topp_ws + l.hist_off);   // (shorter rows: see kTpChunk)
     hist_stride = l.hist_stride;
     n_sub = l.n_sub;
   }

@@ -30,6 +30,7 @@
 
 #include <stdlib.h>
 
+#include <algorithm>
 #include <mutex>
 
 namespace rtp {
@@ -41,7 +42,7 @@ namespace rtp {
 // run their phases in step and share its vector ALUs: fewer, larger workgroups repeat less (and start
 // sooner: a launch of 1024 workgroups takes 2.5 us to get them all going), smaller ones balance better.
 constexpr int kTpThreads = 512;
-constexpr int kTpChunk = 8192;             // scores per workgroup
+// (kTpChunk = 8192 scores per workgroup: topp_common.h)
 constexpr int kTpVec = kTpChunk / (kTpThreads * 4);   // float4 loads per thread
 
 struct RowState {          // one per row and launch (levels 2 and 3 leave one each)
@@ -78,6 +79,7 @@ struct TopPArgs {
   uint64_t* hist;          // [R, hist_stride]
   int64_t hist_stride;
   int32_t n_sub;           // copies of level 1 per row (topp_common.h)
+  int32_t n_copy;          // rows of one chunk: workgroups that share a row's gather (1 everywhere else)
   RowState* state;         // [R, 3]
   int32_t* bucket_n;       // [R]: scores that share the level-2 prefix (may exceed kBucketCap)
   uint2* bucket;           // [R, kBucketCap]: (key, position) of the first kBucketCap of them
@@ -630,6 +632,7 @@ struct GatherArgs {
   uint16_t* out;
   float* lse;
   int32_t f16;             // q, K, V and out are fp16 (else bf16)
+  int32_t max_copy;        // rows of one chunk: partials per row that `part` has room for
   const int32_t* page_table;   // paged cache: [B, pt_stride] pool pages (NULL: contiguous sequences at seq_start)
   int64_t pt_stride;
   int32_t page_shift;
@@ -640,6 +643,126 @@ constexpr int kScanCost = 128;             // repeating a chunk's compaction cos
 constexpr int kSaInFlight = 8;             // K/V rows in flight per 16-lane group (two register sets taking turns,
                                            // or more rows, measured no faster: the gather is bandwidth-bound)
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// Attention of row r over the `kept_here` positions in `list` (LDS; complete once the barrier in here is passed): groups of
+// 16 lanes, one K/V row (256 bytes) per group and load, kSaInFlight rows per group in flight; a lane owns 8 of the
+// 128 dims.  Threads 0 .. 127 get the softmax state (M, L) and their dim's unnormalised output A (in as -inf, 0, 0).
+template <bool F16, bool PAGED>
+__device__ __forceinline__ void attend_list(const GatherArgs& ga, const int r, const int32_t* list, int32_t* rows_lds,
+                                            const int kept_here, float& M, float& L, float& A) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const float ninf = -__builtin_huge_valf();
+  __shared__ float sh_m[kTpThreads / 64], sh_l[kTpThreads / 64];
+  __shared__ float sh_acc[kTpThreads / 64][kHeadDim];
+  __syncthreads();                           // the list is complete
+  const int grp = wave * 4 + (lane >> 4), piece = lane & 15;
+  const int b = r / ga.n_ret;
+  const int h = ga.ret_heads[r - b * ga.n_ret];
+  const int kvh = h / (ga.n_q_heads / ga.n_kv_heads);
+  const int64_t seq0 = PAGED ? 0 : ga.seq_start[b];
+  const uint16_t* Kb = ga.K + (int64_t)kvh * ga.head_stride + seq0 * ga.row_stride + piece * 8;
+  const uint16_t* Vb = ga.V + (int64_t)kvh * ga.head_stride + seq0 * ga.row_stride + piece * 8;
+  if (PAGED) {
+    const int32_t* pt = ga.page_table + (int64_t)b * ga.pt_stride;
+    const int mask = (1 << ga.page_shift) - 1;
+    for (int i = tid; i < kept_here; i += kTpThreads) {
+      const int p = list[i];
+      rows_lds[i] = (pt[p >> ga.page_shift] << ga.page_shift) | (p & mask);
+    }
+    __syncthreads();
+  }
+  const int32_t* rows = PAGED ? rows_lds : list;
+  float qv[8];
+  unpack8<F16>(*reinterpret_cast<const u32x4*>(ga.q + ((int64_t)b * ga.n_q_heads + h) * kHeadDim + piece * 8), qv);
+#pragma unroll
+  for (int d = 0; d < 8; ++d) qv[d] *= ga.scale_log2;
+  float m = ninf, l = 0.f, acc[8];
+#pragma unroll
+  for (int d = 0; d < 8; ++d) acc[d] = 0.f;
+  constexpr int kGroups = kTpThreads / 16;   // 16-lane groups of the workgroup, one K/V row each per load
+  for (int base = 0; base < kept_here; base += kGroups * kSaInFlight) {
+    u32x4 kr[kSaInFlight], vr[kSaInFlight];
+    bool ok[kSaInFlight];
+#pragma unroll
+    for (int u = 0; u < kSaInFlight; ++u) {
+      const int i = base + u * kGroups + grp;
+      ok[u] = i < kept_here;
+      if (ok[u]) {
+        const int64_t pos = rows[i];
+        kr[u] = *reinterpret_cast<const u32x4*>(Kb + pos * ga.row_stride);
+        vr[u] = *reinterpret_cast<const u32x4*>(Vb + pos * ga.row_stride);
+      } else {
+        kr[u] = (u32x4){0u, 0u, 0u, 0u};
+        vr[u] = (u32x4){0u, 0u, 0u, 0u};
+      }
+    }
+    float sc[kSaInFlight];
+    float mx = ninf;
+#pragma unroll
+    for (int u = 0; u < kSaInFlight; ++u) {
+      float kf[8];
+      unpack8<F16>(kr[u], kf);
+      float d = kf[0] * qv[0];
+#pragma unroll
+      for (int e = 1; e < 8; ++e) d = fmaf(kf[e], qv[e], d);
+      d = row16_sum(d);
+      sc[u] = ok[u] ? d : ninf;
+      mx = fmaxf(mx, sc[u]);
+    }
+    const float mn = fmaxf(m, mx);
+    if (mn != ninf) {
+      const float corr = fast_exp2(m - mn);
+      l *= corr;
+#pragma unroll
+      for (int d = 0; d < 8; ++d) acc[d] *= corr;
+      m = mn;
+    }
+#pragma unroll
+    for (int u = 0; u < kSaInFlight; ++u) {
+      float vf[8];
+      unpack8<F16>(vr[u], vf);
+      const float pw = (sc[u] == ninf) ? 0.f : fast_exp2(sc[u] - m);
+      l += pw;
+#pragma unroll
+      for (int d = 0; d < 8; ++d) acc[d] = fmaf(pw, vf[d], acc[d]);
+    }
+  }
+  // the four groups of a wave in registers, the four waves through LDS
+#pragma unroll
+  for (int o = 16; o <= 32; o <<= 1) {
+    const float mo = __shfl_xor(m, o), lo = __shfl_xor(l, o);
+    float ao[8];
+#pragma unroll
+    for (int d = 0; d < 8; ++d) ao[d] = __shfl_xor(acc[d], o);
+    const float M = fmaxf(m, mo);
+    if (M != ninf) {
+      const float ca = fast_exp2(m - M), cb = fast_exp2(mo - M);
+      l = l * ca + lo * cb;
+#pragma unroll
+      for (int d = 0; d < 8; ++d) acc[d] = acc[d] * ca + ao[d] * cb;
+      m = M;
+    }
+  }
+  if (lane < 16) {
+    if (piece == 0) { sh_m[wave] = m; sh_l[wave] = l; }
+#pragma unroll
+    for (int d = 0; d < 8; ++d) sh_acc[wave][piece * 8 + d] = acc[d];
+  }
+  __syncthreads();
+  if (tid < kHeadDim) {
+    M = sh_m[0];
+#pragma unroll
+    for (int w = 1; w < kTpThreads / 64; ++w) M = fmaxf(M, sh_m[w]);
+    if (M != ninf) {
+#pragma unroll
+      for (int w = 0; w < kTpThreads / 64; ++w) {
+        const float cw = fast_exp2(sh_m[w] - M);
+        L += sh_l[w] * cw;
+        A += sh_acc[w][tid] * cw;
+      }
+    }
+  }
+}
 
 // PAGED (ATTEND only): the K/V rows of a sequence live in pool pages; the kept positions are translated to pool
 // rows once, into a second LDS list, before the gather starts.
@@ -843,119 +966,10 @@ __global__ __launch_bounds__(kTpThreads) void topp_write_kernel(const TopPArgs a
     return;
   }
 
-  // ---- attention over this chunk's kept positions: groups of 16 lanes, one K/V row (256 bytes) per
-  // group and load, kSaInFlight rows per group in flight; a lane owns 8 of the 128 dims ----
-  __shared__ float sh_m[kTpThreads / 64], sh_l[kTpThreads / 64];
-  __shared__ float sh_acc[kTpThreads / 64][kHeadDim];
-  __syncthreads();                           // the list is complete
-  const int lane = tid & 63, wave = tid >> 6;
-  const int grp = wave * 4 + (lane >> 4), piece = lane & 15;
-  const int b = r / ga.n_ret;
-  const int h = ga.ret_heads[r - b * ga.n_ret];
-  const int kvh = h / (ga.n_q_heads / ga.n_kv_heads);
-  const int64_t seq0 = PAGED ? 0 : ga.seq_start[b];
-  const uint16_t* Kb = ga.K + (int64_t)kvh * ga.head_stride + seq0 * ga.row_stride + piece * 8;
-  const uint16_t* Vb = ga.V + (int64_t)kvh * ga.head_stride + seq0 * ga.row_stride + piece * 8;
-  if (PAGED) {
-    const int32_t* pt = ga.page_table + (int64_t)b * ga.pt_stride;
-    const int mask = (1 << ga.page_shift) - 1;
-    for (int i = tid; i < kept_here; i += kTpThreads) {
-      const int p = sh_list[i];
-      sh_rows[i] = (pt[p >> ga.page_shift] << ga.page_shift) | (p & mask);
-    }
-    __syncthreads();
-  }
-  const int32_t* rows = PAGED ? sh_rows : sh_list;
-  float qv[8];
-  unpack8<F16>(*reinterpret_cast<const u32x4*>(ga.q + ((int64_t)b * ga.n_q_heads + h) * kHeadDim + piece * 8), qv);
-#pragma unroll
-  for (int d = 0; d < 8; ++d) qv[d] *= ga.scale_log2;
-  float m = ninf, l = 0.f, acc[8];
-#pragma unroll
-  for (int d = 0; d < 8; ++d) acc[d] = 0.f;
-  constexpr int kGroups = kTpThreads / 16;   // 16-lane groups of the workgroup, one K/V row each per load
-  for (int base = 0; base < kept_here; base += kGroups * kSaInFlight) {
-    u32x4 kr[kSaInFlight], vr[kSaInFlight];
-    bool ok[kSaInFlight];
-#pragma unroll
-    for (int u = 0; u < kSaInFlight; ++u) {
-      const int i = base + u * kGroups + grp;
-      ok[u] = i < kept_here;
-      if (ok[u]) {
-        const int64_t pos = rows[i];
-        kr[u] = *reinterpret_cast<const u32x4*>(Kb + pos * ga.row_stride);
-        vr[u] = *reinterpret_cast<const u32x4*>(Vb + pos * ga.row_stride);
-      } else {
-        kr[u] = (u32x4){0u, 0u, 0u, 0u};
-        vr[u] = (u32x4){0u, 0u, 0u, 0u};
-      }
-    }
-    float sc[kSaInFlight];
-    float mx = ninf;
-#pragma unroll
-    for (int u = 0; u < kSaInFlight; ++u) {
-      float kf[8];
-      unpack8<F16>(kr[u], kf);
-      float d = kf[0] * qv[0];
-#pragma unroll
-      for (int e = 1; e < 8; ++e) d = fmaf(kf[e], qv[e], d);
-      d = row16_sum(d);
-      sc[u] = ok[u] ? d : ninf;
-      mx = fmaxf(mx, sc[u]);
-    }
-    const float mn = fmaxf(m, mx);
-    if (mn != ninf) {
-      const float corr = fast_exp2(m - mn);
-      l *= corr;
-#pragma unroll
-      for (int d = 0; d < 8; ++d) acc[d] *= corr;
-      m = mn;
-    }
-#pragma unroll
-    for (int u = 0; u < kSaInFlight; ++u) {
-      float vf[8];
-      unpack8<F16>(vr[u], vf);
-      const float pw = (sc[u] == ninf) ? 0.f : fast_exp2(sc[u] - m);
-      l += pw;
-#pragma unroll
-      for (int d = 0; d < 8; ++d) acc[d] = fmaf(pw, vf[d], acc[d]);
-    }
-  }
-  // the four groups of a wave in registers, the four waves through LDS
-#pragma unroll
-  for (int o = 16; o <= 32; o <<= 1) {
-    const float mo = __shfl_xor(m, o), lo = __shfl_xor(l, o);
-    float ao[8];
-#pragma unroll
-    for (int d = 0; d < 8; ++d) ao[d] = __shfl_xor(acc[d], o);
-    const float M = fmaxf(m, mo);
-    if (M != ninf) {
-      const float ca = fast_exp2(m - M), cb = fast_exp2(mo - M);
-      l = l * ca + lo * cb;
-#pragma unroll
-      for (int d = 0; d < 8; ++d) acc[d] = acc[d] * ca + ao[d] * cb;
-      m = M;
-    }
-  }
-  if (lane < 16) {
-    if (piece == 0) { sh_m[wave] = m; sh_l[wave] = l; }
-#pragma unroll
-    for (int d = 0; d < 8; ++d) sh_acc[wave][piece * 8 + d] = acc[d];
-  }
-  __syncthreads();
+  // ---- attention over this chunk's kept positions ----
+  float M = ninf, L = 0.f, A = 0.f;
+  attend_list<F16, PAGED>(ga, r, sh_list, sh_rows, kept_here, M, L, A);
   if (tid < kHeadDim) {
-    float M = sh_m[0];
-#pragma unroll
-    for (int w = 1; w < kTpThreads / 64; ++w) M = fmaxf(M, sh_m[w]);
-    float L = 0.f, A = 0.f;
-    if (M != ninf) {
-#pragma unroll
-      for (int w = 0; w < kTpThreads / 64; ++w) {
-        const float cw = fast_exp2(sh_m[w] - M);
-        L += sh_l[w] * cw;
-        A += sh_acc[w][tid] * cw;
-      }
-    }
     float* pout = ga.part + ((int64_t)r * a.n_chunks + c) * kSaPart;
     pout[4 + tid] = A;
     if (tid == 0) { pout[0] = M; pout[1] = L; }
@@ -988,7 +1002,7 @@ __global__ __launch_bounds__(256) void select_attend_combine_kernel(const TopPAr
   const int r = blockIdx.x, tid = threadIdx.x;
   const float ninf = -__builtin_huge_valf();
   const int n = a.row_len[r];
-  const int n_row_chunks = n > 0 ? (n + kTpChunk - 1) / kTpChunk : 0;
+  const int n_row_chunks = n > 0 ? (a.n_copy > 1 ? a.n_copy : (n + kTpChunk - 1) / kTpChunk) : 0;
   const int d4 = tid & 31, slice = tid >> 5;
   float M = ninf, L = 0.f;
   float4 A = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -1041,6 +1055,169 @@ __global__ __launch_bounds__(256) void select_attend_combine_kernel(const TopPAr
   }
 }
 
+// ---- rows of one chunk: the whole selection (and attention) in one launch -----------------------------
+// A row of at most kTpChunk scores is one workgroup's chunk, so nothing has to cross a launch: the scores stay in
+// registers through all three levels, the histograms never leave LDS (the score pass leaves the workspace alone for such
+// rows: a level-1 histogram by the way costs it more than it costs the 512 threads here), the chunk's offset is 0 and,
+// with ATTEND, its partial softmax state is the row's result.  The same bins, weights, scans and compaction as in the
+// launches above give the same numbers.  RIDE_G > 0: the last n_ride workgroups run the local heads' work items of the
+// step (rtp_decode_attention).  n_copy workgroups per row repeat the selection and share the gather where a merge launch
+// follows for the local heads anyway.
+// Latency-bound throughout: a step of one sequence of 4096 tokens 38.7 -> 23 us of kernels, the selector alone 27 -> 11 us.
+template <bool ATTEND, int RIDE_G, bool F16 = false, bool PAGED = false>
+__global__ __launch_bounds__(kTpThreads) void topp_row_kernel(const TopPArgs a, const GatherArgs ga, const AttnDecodeArgs la,
+                                                              const int n_ride, const int direct) {
+  const int n_row_wgs = a.R * a.n_copy;
+  if constexpr (RIDE_G > 0) {
+    if ((int)blockIdx.x >= n_row_wgs) {
+      gqa_decode_items<RIDE_G, kSrcLocal, kTpThreads, 1, F16, PAGED>(la, (int)blockIdx.x - n_row_wgs, n_ride, n_ride, direct != 0);
+      return;
+    }
+  }
+  const int r = (int)blockIdx.x / a.n_copy, copy = (int)blockIdx.x - r * a.n_copy;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const float ninf = -__builtin_huge_valf();
+  const bool by_count = a.kcount != nullptr;
+  const int n = max(min(a.row_len[r], kTpChunk), 0);
+  float4 v[kTpVec];
+  load_chunk(reinterpret_cast<const float4*>(a.scores + (int64_t)r * a.score_stride), n, tid, v);
+  uint64_t bins[kBins1 / kTpThreads];
+  __shared__ uint64_t lh[kBins1];
+  __shared__ int32_t sh_list[kTpChunk];              // level 2: the members' scores; then the kept positions
+  __shared__ int32_t sh_rows[(ATTEND && PAGED) ? kTpChunk : 1];
+  __shared__ uint64_t sh_part[kTpThreads / 64], sh_res[3], sh_tot[kTpThreads / 64][2];
+  __shared__ double sh_d[kTpThreads / 64], sh_dres[3], tab[256];
+  __shared__ int sh_i[kTpThreads / 64], sh_n;
+  fill_exp_table(tab);
+  auto clear_bins = [&]() {
+    for (int i = tid; i < kBins1; i += kTpThreads) lh[i] = 0;
+  };
+  clear_bins();
+  if (tid == 0) sh_n = 0;
+  const float pr = by_count ? 0.5f : a.p[r];
+  const int kc = by_count ? a.kcount[r] : 1;
+  int flags = by_count ? (kc > 0 ? 0 : -1) : (pr >= 1.f ? 1 : (pr > 0.f ? 0 : -1));
+  const int shift = fixed_shift(n);
+  auto score = [&](int u, int k) { return k == 0 ? v[u].x : (k == 1 ? v[u].y : (k == 2 ? v[u].z : v[u].w)); };
+  __syncthreads();
+
+  // ---- level 1 ----
+  uint32_t prefix = 0;
+  float ref = 0.f;
+  uint64_t target = 1;
+  double above_base = 0.0, total_d = 1.0;
+  if (flags == 0) {
+#pragma unroll
+    for (int u = 0; u < kTpVec; ++u)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float s = score(u, k);
+        if ((u * kTpThreads + tid) * 4 + k >= n) continue;
+        if (!by_count) level1_add(lh, s, shift, tab);
+        else if (s != ninf) atomicAdd((unsigned long long*)&lh[float_key(s) >> 21], 1ull);
+      }
+    __syncthreads();
+    load_bins<kBins1>(lh, bins);
+    if (by_count) {
+      const ScanResult s1 = scan_from_top<kBins1>(bins, 0, (uint64_t)kc, sh_part, sh_res);
+      if (s1.total == 0) flags = 2;
+      else if ((uint64_t)kc >= s1.total) flags = 1;
+      else { prefix = (uint32_t)s1.bin; target = (uint64_t)kc - s1.above; }
+    } else {
+      const Scan1Result s1 = scan_level1(bins, pr, sh_d, sh_i, sh_dres, tab);
+      if (s1.bin < 0) flags = 2;
+      else if (level1_bin_is_wide(s1.top)) flags = -2;
+      else { prefix = (uint32_t)s1.bin; ref = s1.ref; target = s1.target; above_base = s1.above_base; total_d = s1.total_d; }
+    }
+  }
+  float res_tau = ninf, res_mass = 1.f;
+  uint32_t tkey = 0;
+  if (flags == 0) {
+    // ---- level 2: the members of the level-1 bin, packed into LDS and weighed densely ----
+    clear_bins();
+    uint32_t member = 0;
+#pragma unroll
+    for (int u = 0; u < kTpVec; ++u)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float s = score(u, k);
+        const bool in = (u * kTpThreads + tid) * 4 + k < n && (float_key(s) >> 21) == prefix && s != ninf;
+        member |= (in ? 1u : 0u) << (u * 4 + k);
+      }
+    const int cnt = __popc(member), incl = wave_incl_scan(cnt);
+    int base = 0;
+    if (lane == 63 && incl > 0) base = atomicAdd(&sh_n, incl);
+    int pos = wave_last(base) + incl - cnt;
+    float* packed = reinterpret_cast<float*>(sh_list);
+#pragma unroll
+    for (int u = 0; u < kTpVec; ++u)
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (member & (1u << (u * 4 + k))) packed[pos++] = score(u, k);
+    __syncthreads();
+    const int n_member = sh_n;
+    for (int i = tid; i < n_member; i += kTpThreads) {
+      const float s = packed[i];
+      const uint64_t w = by_count ? 1ull : fixed_weight(s, ref, shift, tab);
+      if (w) atomicAdd((unsigned long long*)&lh[(float_key(s) >> 10) & (kBins2 - 1)], (unsigned long long)w);
+    }
+    __syncthreads();
+    load_bins<kBins2>(lh, bins);
+    const ScanResult s2 = scan_from_top<kBins2>(bins, 0, target, sh_part, sh_res);
+    prefix = (prefix << 11) | (uint32_t)s2.bin;
+    // ---- level 3: the few that share the 22-bit prefix ----
+    clear_bins();
+    __syncthreads();
+    for (int i = tid; i < n_member; i += kTpThreads) {
+      const float s = packed[i];
+      const uint32_t key = float_key(s);
+      if ((key >> 10) != prefix) continue;
+      const uint64_t w = by_count ? 1ull : fixed_weight(s, ref, shift, tab);
+      if (w) atomicAdd((unsigned long long*)&lh[key & (kBins3 - 1)], (unsigned long long)w);
+    }
+    __syncthreads();
+    uint64_t bins3[kBins3 / kTpThreads];
+    load_bins<kBins3>(lh, bins3);
+    const ScanResult s3 = scan_from_top<kBins3>(bins3, s2.above, target, sh_part, sh_res);
+    tkey = (prefix << 10) | (uint32_t)s3.bin;
+    res_tau = key_float(tkey);
+    res_mass = by_count ? __builtin_nanf("") : (float)((above_base + (double)(s3.above + s3.bin_mass)) / total_d);
+  }
+  int kept = 0;
+  if (n > 0 && (flags == 0 || flags == 1)) {
+    const uint32_t keep = keep_mask(v, n, tid, flags == 1, tkey);
+    kept = write_ranked(keep, 0, ATTEND ? nullptr : a.sel_idx + (int64_t)r * a.sel_stride, 0, sh_tot, ATTEND ? sh_list : nullptr);
+  } else {
+    res_tau = (flags < 0 && n > 0) ? __builtin_nanf("") : ninf;
+    res_mass = 0.f;
+  }
+  if (ATTEND) {
+    // this copy's share of the kept positions
+    const int k_lo = kept * copy / a.n_copy, k_hi = kept * (copy + 1) / a.n_copy;
+    float M = ninf, L = 0.f, A = 0.f;
+    attend_list<F16, PAGED>(ga, r, sh_list + k_lo, sh_rows, k_hi - k_lo, M, L, A);
+    if (tid < kHeadDim) {
+      if (a.n_copy > 1) {
+        float* pout = ga.part + ((int64_t)r * a.n_copy + copy) * kSaPart;
+        pout[4 + tid] = A;
+        if (tid == 0) { pout[0] = M; pout[1] = L; }
+      } else {
+        const int b = r / ga.n_ret;
+        const int64_t o = (int64_t)b * ga.n_q_heads + ga.ret_heads[r - b * ga.n_ret];
+        ga.out[o * kHeadDim + tid] = f32_to_16(L > 0.f ? A / L : 0.f, ga.f16 != 0);
+        if (ga.lse && tid == 0) ga.lse[o] = L > 0.f ? (M + log2f(L)) * 0.6931471805599453f : ninf;
+      }
+    }
+    int32_t* dst = a.sel_idx + (int64_t)r * a.sel_stride;
+    for (int i = k_lo + tid; i < k_hi; i += kTpThreads) dst[i] = sh_list[i];
+  }
+  if (copy == 0 && tid == 0) {
+    a.sel_count[r] = (flags < 0 && n > 0) ? flags : kept;
+    if (a.tau) a.tau[r] = res_tau;
+    if (a.mass) a.mass[r] = res_mass;
+  }
+}
+
 }  // namespace rtp
 
 using namespace rtp;
@@ -1058,6 +1235,59 @@ extern "C" int32_t rtp_topp_workspace_init(void* ws, size_t ws_bytes, void* stre
   const int64_t n = (int64_t)(ws_bytes / 8);
   RTP_LAUNCH(topp_zero_kernel, dim3((unsigned)((n + kTpThreads - 1) / kTpThreads)), dim3(kTpThreads), 0,
                      (hipStream_t)stream, (uint64_t*)ws, n);
+  return check_launch(who);
+}
+
+// Rows of at most one chunk (max_len <= kTpChunk): see topp_row_kernel.  Local heads on board: with at most
+// kDirectTokens tokens per unit a unit is one work item whose workgroup writes the heads' results itself (a few load
+// rounds, shorter than the row's own work), else the plan's items and a launch that merges them.
+constexpr int kDirectTokens = 1024;
+// Workgroups that share the gather of a row of one chunk when a merge launch follows anyway (a set of thousands of tokens
+// keeps one workgroup busy for 33 us): up to four, about one workgroup per compute unit in all.
+static int row_copies(int32_t R) { return R <= 64 ? 4 : (R <= 128 ? 2 : 1); }
+template <int RIDE_G, bool F16, bool PAGED>
+static void launch_rows_t(TopPArgs a, const GatherArgs& ga, AttnDecodeArgs la, hipStream_t s) {
+  int n_ride = 0;
+  bool direct = true;
+  if (RIDE_G > 0) {
+    direct = la.split_tokens * la.n_splits <= kDirectTokens;
+    if (direct) { la.split_tokens *= la.n_splits; la.n_splits = 1; }
+    n_ride = la.units * la.n_splits;
+    // (one workgroup per compute unit with groups of 8 or a second list, two otherwise: no copies that would wait)
+    const int room = (RIDE_G == 8 || PAGED ? 256 : 512) - n_ride;
+    if (!direct) a.n_copy = std::max(1, std::min(ga.max_copy, room / a.R));
+  }
+  RTP_LAUNCH((topp_row_kernel<true, RIDE_G, F16, PAGED>), dim3((unsigned)(n_ride + a.R * a.n_copy)), dim3(kTpThreads), 0, s, a, ga, la,
+             n_ride, direct ? 1 : 0);
+  if constexpr (RIDE_G > 0) {
+    if (direct) return;
+    TopPArgs rows = a;                               // one copy: the rows are finished, only local heads are merged
+    rows.n_chunks = a.n_copy;
+    if (a.n_copy == 1) rows.R = 0;
+    RTP_LAUNCH(select_attend_combine_kernel<RIDE_G>, dim3((unsigned)(rows.R + la.units * RIDE_G)), dim3(256), 0, s, rows, ga, la);
+  }
+}
+static int32_t launch_rows(const char* who, const TopPArgs& a, const GatherArgs* attend, const AttnDecodeArgs* ride, int ride_G,
+                           hipStream_t s) {
+  if (!attend) {
+    RTP_LAUNCH((topp_row_kernel<false, 0>), dim3((unsigned)a.R), dim3(kTpThreads), 0, s, a, GatherArgs{}, AttnDecodeArgs{}, 0, 0);
+    return check_launch(who);
+  }
+  const AttnDecodeArgs la = ride ? *ride : AttnDecodeArgs{};
+  const int G = ride ? ride_G : 0;
+  const bool paged = attend->page_table != nullptr;
+#define RTP_ROWS(GG)                                                                          \
+  do {                                                                                         \
+    if (attend->f16 && paged) launch_rows_t<GG, true, true>(a, *attend, la, s);  \
+    else if (attend->f16) launch_rows_t<GG, true, false>(a, *attend, la, s);     \
+    else if (paged) launch_rows_t<GG, false, true>(a, *attend, la, s);           \
+    else launch_rows_t<GG, false, false>(a, *attend, la, s);                     \
+  } while (0)
+  if (G == 0) RTP_ROWS(0);
+  else if (G == 2) RTP_ROWS(2);
+  else if (G == 4) RTP_ROWS(4);
+  else RTP_ROWS(8);
+#undef RTP_ROWS
   return check_launch(who);
 }
 
@@ -1102,11 +1332,13 @@ static int32_t run_select(const char* who, const float* scores, int64_t score_st
   a.hist = (uint64_t*)((char*)ws + l.hist_off);
   a.hist_stride = l.hist_stride;
   a.n_sub = l.n_sub;
+  a.n_copy = 1;
   a.state = (RowState*)((char*)ws + l.state_off);
   a.bucket_n = (int32_t*)((char*)ws + l.bn_off);
   a.bucket = (uint2*)((char*)ws + l.bucket_off);
 
   hipStream_t s = (hipStream_t)stream;
+  if (a.n_chunks == 1) return launch_rows(who, a, attend, ride, ride_G, s);
   dim3 grid((unsigned)a.n_chunks, (unsigned)R), block(kTpThreads);
   if (!level1_ready) {
     const int64_t nz = (int64_t)R * l.hist_stride;
@@ -1225,7 +1457,7 @@ extern "C" int32_t rtp_topk_select(const float* scores, int64_t score_stride, co
 
 extern "C" size_t rtp_select_attend_decode_workspace_bytes(const rtp_layer_desc* layer, int32_t B, int64_t max_ctx) {
   if (!layer || B <= 0 || max_ctx <= 0 || layer->n_ret <= 0) return 256;
-  const int64_t n_chunks = (max_ctx + kTpChunk - 1) / kTpChunk;
+  const int64_t n_chunks = max_ctx <= kTpChunk ? row_copies(B * layer->n_ret) : (max_ctx + kTpChunk - 1) / kTpChunk;
   return align_up((size_t)B * layer->n_ret * n_chunks * kSaPart * sizeof(float), 256);
 }
 
@@ -1252,7 +1484,9 @@ static int32_t prepare_select_attend(const char* who, const rtp_layer_desc* laye
   *R = (int64_t)B * layer->n_ret;
   if (*R > 65535) return fail(RTP_ERR_INVALID_ARG, "%s: B * n_ret is limited to 65535", who);
   if (layer->n_ret == 0) return RTP_OK;
-  const size_t need = rtp_select_attend_decode_workspace_bytes(layer, B, max_ctx);
+  const size_t one_each = align_up((size_t)B * layer->n_ret * kSaPart * sizeof(float), 256);
+  const size_t full = rtp_select_attend_decode_workspace_bytes(layer, B, max_ctx);
+  const size_t need = max_ctx <= kTpChunk ? one_each : full;     // (short rows: more room is for workgroups that share a gather)
   if (!attn_ws || ((uintptr_t)attn_ws & 255) || attn_ws_bytes < need)
     return fail(RTP_ERR_WORKSPACE, "%s: attention workspace of %zu bytes (256-byte aligned) required, got %zu", who, need,
                 attn_ws_bytes);
@@ -1270,6 +1504,7 @@ static int32_t prepare_select_attend(const char* who, const rtp_layer_desc* laye
   ga->out = (uint16_t*)out;
   ga->lse = lse;
   ga->f16 = layer->kv_dtype == RTP_DTYPE_FP16;
+  ga->max_copy = max_ctx <= kTpChunk && attn_ws_bytes >= full ? row_copies((int32_t)*R) : 1;
   ga->page_table = pages ? pages->table : nullptr;
   ga->pt_stride = pages ? pages->stride : 0;
   ga->page_shift = page_shift;

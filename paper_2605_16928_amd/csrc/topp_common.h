@@ -14,6 +14,10 @@
 
 namespace rtp {
 
+// Scores of a row per workgroup of the selector.  Rows of at most that many are selected in one launch, from the scores
+// alone: the score pass then leaves the selector's workspace untouched.
+constexpr int kTpChunk = 8192;
+
 constexpr int kBins1 = 2048, kBins2 = 2048, kBins3 = 1024;
 constexpr int kBinsTotal = kBins1 + kBins2 + kBins3;
 

@@ -581,3 +581,29 @@ def test_select_attend_with_clustered_kept_tokens():
         s64 = s_gpu[r, :n].astype(np.float64)
         p = float(w.p_rows[r])
         check_selection(sets[r], s64, orc.topp_select(s64, p), p, f"clustered row {r}")
+
+
+@pytest.mark.parametrize("G,kv_dtype", [(1, "bf16"), (2, "bf16"), (4, "fp16"), (8, "bf16")])
+@pytest.mark.parametrize("ctx,window,p", [((8192, 8191, 1, 33), 2048, 0.98), ((8193, 5, 4097), 600, 0.9), ((2049, 511, 513), 100, 0.5)])
+def test_decode_step_around_one_chunk_per_row(G, kv_dtype, ctx, window, p):
+    """Contexts up to 8192 tokens take the one-launch selection (rows finished in it, or shared by several workgroups and merged
+    with the local heads); one token more takes the launch per level.  One-call and separate-call forms against the oracle."""
+    print(f"[case] rows around one chunk, G {G}, {kv_dtype}, contexts {ctx}", flush=True)
+    w = wl.small_decode("cpu", seed=201 + G, ctx=ctx, n_q_heads=2 * G if G > 1 else 4, n_kv_heads=2 if G > 1 else 4,
+                        ret_heads=(0, 1), window=window, p=(p,), kv_dtype=kv_dtype, n_planted=4).to(DEV)
+    ref = orc.decode_layer(**oracle_inputs(w))
+    for one_call in (True, False):
+        run = DecodeRun(w)
+        run.out.fill_(7.0)
+        if one_call:
+            run.step_one_stream()
+            run.out.fill_(7.0)
+            run.step_one_stream()                 # the workspace of the first step serves the second
+        else:
+            run.step(fused=False)
+        sets, cnt = run.sel_sets()
+        scores = run.scores.cpu().numpy().astype(np.float64)
+        for r in range(run.R):
+            s64, pr = scores[r, :w.ctx_len[r // w.layer.n_ret]], float(w.p_rows[r])
+            check_selection(sets[r], s64, orc.topp_select(s64, pr), pr, f"row {r}")
+        check_layer(run.out_f64(), run.lse.cpu().numpy(), w, oracle_inputs(w), ref, sets, f"one call {one_call}")
