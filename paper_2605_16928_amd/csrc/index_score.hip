@@ -19,6 +19,12 @@ namespace rtp {
 // (measured on batch 8 x 131072: 27.5 us against 28.4 us with 2048; the plain pass prefers 2048)
 constexpr int kIsThreads = 256;
 constexpr int kIsChunkPlain = 8 * kIsThreads, kIsChunkHist = 16 * kIsThreads;
+// Few workgroups: 1024 tokens, so that a chunk's weights (a few hundred cycles for every two tokens of a lane) are spread over
+// the chip.  The line lies at one workgroup of 4096 tokens per compute unit (batch 1 x 262144, 4 heads: 12.0 us against 13.5;
+// x 131072: 7.9 against 11.1; x 32768: 5.5 against 9.8) and, for rows of at most 65536 tokens, at two (8 x 65536: 17.4 against
+// 18.9; 12 ragged rows to 30011: 10.6 against 13.2).  Beyond, the flushes of a row's many chunks into its few copies of the
+// histogram cost more than the spreading gives (2 x 262144: 21.7 against 19.2; 8 x 98304: 24.8 against 23.7).
+constexpr int kIsChunkHistSmall = 4 * kIsThreads;
 constexpr int kIsBatch = 16;             // 16-byte loads in flight per lane
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -56,9 +62,9 @@ __device__ __forceinline__ float dot8(const u32x4 v, const float (&q)[8]) {
 
 // PROBE: the same grid, loads and stores with the arithmetic taken out (the stored word is a piece of the key
 // row): what the chip sustains for this traffic mix, 32 bytes read for every 4 written.
-template <bool HIST, bool PROBE = false>
+template <bool HIST, bool PROBE = false, int kIsChunk = HIST ? kIsChunkHist : kIsChunkPlain>
 __global__ __launch_bounds__(kIsThreads) void index_score_kernel(const IndexScoreArgs a) {
-  constexpr int kIsChunk = HIST ? kIsChunkHist : kIsChunkPlain;
+  constexpr int kIsBatch = rtp::kIsBatch < 2 * kIsChunk / kIsThreads ? rtp::kIsBatch : 2 * kIsChunk / kIsThreads;
   static_assert((kIsChunk * 2) % (kIsThreads * kIsBatch) == 0, "a chunk is a whole number of load batches");
   const int bj = blockIdx.z;
   const int b = bj / a.n_ret, j = bj - b * a.n_ret, t = blockIdx.y;
@@ -216,9 +222,12 @@ static int32_t run_index_score(const char* who, bool probe, const rtp_layer_desc
   a.qI_out = (uint16_t*)qI_out;
   for (int j = 0; j < 64; ++j) a.ret_heads[j] = j < layer->n_ret ? layer->ret_heads[j] : 0;
 
-  const int64_t chunk = hist ? kIsChunkHist : kIsChunkPlain;
+  const int64_t big = (max_ctx + kIsChunkHist - 1) / kIsChunkHist * n_q * B * layer->n_ret;     // workgroups with long chunks
+  const bool small = hist && (big <= 256 || (big <= 512 && max_ctx <= 65536));
+  const int64_t chunk = small ? kIsChunkHistSmall : (hist ? kIsChunkHist : kIsChunkPlain);
   dim3 grid((unsigned)((max_ctx + chunk - 1) / chunk), (unsigned)n_q, (unsigned)(B * layer->n_ret));
   if (probe) RTP_LAUNCH((index_score_kernel<false, true>), grid, dim3(kIsThreads), 0, (hipStream_t)stream, a);
+  else if (small) RTP_LAUNCH((index_score_kernel<true, false, kIsChunkHistSmall>), grid, dim3(kIsThreads), 0, (hipStream_t)stream, a);
   else if (hist) RTP_LAUNCH(index_score_kernel<true>, grid, dim3(kIsThreads), 0, (hipStream_t)stream, a);
   else RTP_LAUNCH(index_score_kernel<false>, grid, dim3(kIsThreads), 0, (hipStream_t)stream, a);
   return check_launch(who);

@@ -607,3 +607,23 @@ def test_decode_step_around_one_chunk_per_row(G, kv_dtype, ctx, window, p):
             s64, pr = scores[r, :w.ctx_len[r // w.layer.n_ret]], float(w.p_rows[r])
             check_selection(sets[r], s64, orc.topp_select(s64, pr), pr, f"row {r}")
         check_layer(run.out_f64(), run.lse.cpu().numpy(), w, oracle_inputs(w), ref, sets, f"one call {one_call}")
+
+
+@pytest.mark.parametrize("ctx", [(8193, 1023, 1024, 1025, 1), (12289, 4095, 4096, 4097), (65537,), (8193,) + (300,) * 84, (8193,) + (300,) * 85])
+def test_level1_in_score_pass_around_the_chunks(ctx):
+    """Score passes of few workgroups take shorter chunks (the last two cases lie on either side of that line): the scores and
+    the selection carry the same bits as with the histogram made by the selector."""
+    print(f"[case] score pass chunks, {len(ctx)} contexts to {ctx[0]}", flush=True)
+    w = wl.small_decode("cpu", seed=211, ctx=ctx, p=(0.9,)).to(DEV)
+    res = []
+    for fuse in (False, True):
+        run = DecodeRun(w, fuse_level1=fuse)
+        for rep in range(2):
+            run.sel_idx.fill_(-1)
+            run.index_score()
+            run.topp()
+            torch.cuda.synchronize()
+        res.append((run.scores, run.sel_idx, run.sel_count, run.tau, run.mass))
+    assert int(res[0][2].min()) > 0
+    for a, b in zip(*res):
+        assert torch.equal(a.nan_to_num(), b.nan_to_num()) if a.dtype == torch.float32 else torch.equal(a, b)
