@@ -83,6 +83,40 @@ __device__ __forceinline__ float row_share(float x) {      // every lane reads l
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x150 + H, 0xf, 0xf, false));
 }
 
+// The same with a lane number that unrolling makes a constant (one DPP move where a shuffle is a trip through the LDS pipe).
+__device__ __forceinline__ float row_share_of(const float x, const int h) {
+  switch (h) {
+    case 0: return row_share<0>(x);
+    case 1: return row_share<1>(x);
+    case 2: return row_share<2>(x);
+    case 3: return row_share<3>(x);
+    case 4: return row_share<4>(x);
+    case 5: return row_share<5>(x);
+    case 6: return row_share<6>(x);
+    case 7: return row_share<7>(x);
+  }
+  return __shfl(x, h);
+}
+
+// Reductions over the four 16-lane rows of a wave (lanes l, l + 16, l + 32, l + 48) by row swaps: an item of few tiles is a
+// chain of latencies, and a swap costs a few cycles where a shuffle through the LDS pipe costs about 120 (level-2 launch with
+// carried items, groups of 8: 27.2 us with shuffles, 24.3 with swaps; groups of 4, batch 8 x 131072: 24.8 and 23.6).
+__device__ __forceinline__ float max_over_rows(const float x) {
+  const uint32_t u = __float_as_uint(x);
+  const auto s = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const uint32_t h = __float_as_uint(fmaxf(__uint_as_float(s[0]), __uint_as_float(s[1])));
+  const auto t = __builtin_amdgcn_permlane32_swap(h, h, false, false);
+  return fmaxf(__uint_as_float(t[0]), __uint_as_float(t[1]));
+}
+// row 0 receives the sum of a over the rows, row 1 that of b, row 2 of c, row 3 of d: (r0 + r1) + (r2 + r3) each
+__device__ __forceinline__ float sum_rows(const float a, const float b, const float c, const float d) {
+  const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  const auto t = __builtin_amdgcn_permlane16_swap(__float_as_uint(c), __float_as_uint(d), false, false);
+  const float ab = __uint_as_float(s[0]) + __uint_as_float(s[1]), cd = __uint_as_float(t[0]) + __uint_as_float(t[1]);
+  const auto u = __builtin_amdgcn_permlane32_swap(__float_as_uint(ab), __float_as_uint(cd), false, false);
+  return __uint_as_float(u[0]) + __uint_as_float(u[1]);
+}
+
 // The work items first_item, first_item + item_step, ... of a workgroup of THREADS threads, TILES tiles per wave
 // in flight (alone in its launch the kernel runs 256 threads and 2 tiles: 1, 3 and 4 measured slower).
 // PAGED: token position p of sequence b lives in pool row page_table[b][p >> page_shift] * page_size + p % page_size
@@ -195,8 +229,7 @@ __device__ __forceinline__ void gqa_decode_items(const AttnDecodeArgs& a, const 
           sc[i] = (tb + 4 * grp + i < t_end) ? S[i] * a.scale_log2 : ninf;
           mx = fmaxf(mx, sc[i]);
         }
-        mx = fmaxf(mx, __shfl_xor(mx, 16));
-        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        mx = max_over_rows(mx);
         const float m_new = fmaxf(m_run, mx);                       // finite: the tile has a valid token
         const float corr = fast_exp2(m_run - m_new);                // 0 on the first tile (m_run = -inf)
         float pw[4];
@@ -212,7 +245,7 @@ __device__ __forceinline__ void gqa_decode_items(const AttnDecodeArgs& a, const 
         if (__ballot(corr != 1.f) != 0ull) {
 #pragma unroll
           for (int hh = 0; hh < G; ++hh) {
-            const float ch = __shfl(corr, hh);
+            const float ch = row_share_of(corr, hh);
 #pragma unroll
             for (int c = 0; c < 8; ++c) acc[hh][c] *= ch;
           }
@@ -236,22 +269,14 @@ __device__ __forceinline__ void gqa_decode_items(const AttnDecodeArgs& a, const 
     }
 
     // ---- the wave's result: sums over its four lane groups (they share the head maxima), then LDS ----
-    l_run += __shfl_xor(l_run, 16);
-    l_run += __shfl_xor(l_run, 32);
-#pragma unroll
-    for (int hh = 0; hh < G; ++hh)
-#pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        acc[hh][c] += __shfl_xor(acc[hh][c], 16);
-        acc[hh][c] += __shfl_xor(acc[hh][c], 32);
-      }
+    l_run = sum_rows(l_run, l_run, l_run, l_run);
     __syncthreads();   // previous item's readers are done with the LDS buffers
     if (lane < G) { sh_m[wave][lane] = m_run; sh_l[wave][lane] = l_run; }
-    if (lane < 16) {
 #pragma unroll
-      for (int hh = 0; hh < G; ++hh)
-#pragma unroll
-        for (int c = 0; c < 8; ++c) sh_acc[wave][hh][piece * 8 + c] = acc[hh][c];
+    for (int hh = 0; hh < G; ++hh) {       // lane group grp ends with dims 2 * grp and 2 * grp + 1 of the lane's eight
+      const float e0 = sum_rows(acc[hh][0], acc[hh][2], acc[hh][4], acc[hh][6]);
+      const float e1 = sum_rows(acc[hh][1], acc[hh][3], acc[hh][5], acc[hh][7]);
+      *reinterpret_cast<float2*>(&sh_acc[wave][hh][piece * 8 + 2 * grp]) = make_float2(e0, e1);
     }
     __syncthreads();
     float* pout = a.part + (int64_t)item * G * kPartStride;
