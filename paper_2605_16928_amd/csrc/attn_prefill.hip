@@ -1414,9 +1414,10 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
     if constexpr (F16) asm volatile("v_dot2c_f32_f16 %0, %1, %2" : "+v"(l) : "v"(pk), "v"(0x3c003c00u));
     else asm volatile("v_dot2c_f32_bf16 %0, %1, %2" : "+v"(l) : "v"(pk), "v"(0x3f803f80u));
   };
-  // probabilities against the fixed reference; masked scores are -inf and give exactly 0
-  // (summed as rounded to 16 bits, like everywhere: a row of few tokens then divides by what it was multiplied with)
-  auto softmax_fixed = [&](const f32x16 (&S)[QB], uint32_t (&P)[QB][8]) __attribute__((always_inline)) {
+  // probabilities against the fixed reference; masked scores are -inf and give exactly 0.  Summed as rounded to 16 bits where
+  // the steady loop could have run the block, unrounded where it could not: rows of few tokens live in such blocks, and their
+  // log-sum would carry the rounding (chunk of 172 tokens at position 0: 2.2e-4 instead of 1.2e-4 off).
+  auto softmax_fixed = [&](const f32x16 (&S)[QB], uint32_t (&P)[QB][8], const bool rounded) __attribute__((always_inline)) {
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
       const float mc = mrow[qb] * c;
@@ -1425,10 +1426,15 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
       for (int i = 0; i < 16; i += 2) {
         const float p0 = fast_exp2(fmaf(S[qb][i], c, -mc));
         const float p1 = fast_exp2(fmaf(S[qb][i + 1], c, -mc));
+        lsum += p0 + p1;
         P[qb][i >> 1] = pack16<F16>(p0, p1);
-        row_sum_add(lsum, P[qb][i >> 1]);
       }
-      row_sum_settled(lsum);
+      if (rounded) {                                       // (the same for the whole wave)
+        lsum = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) row_sum_add(lsum, P[qb][i]);
+        row_sum_settled(lsum);
+      }
       lrow[qb] += lsum;
     }
   };
@@ -1585,11 +1591,15 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
       const uint32_t (&Pin)[QB][8] = hf == 0 ? P1 : P0;
       uint32_t (&Pout)[QB][8] = hf == 0 ? P0 : P1;
       if (pend) mfma_PV(t_pend, 1 - hf, Pin);
+      bool rounded = pend || (hf == 0 && it == it_lo && it_lo != p_lo);    // some block of the part was before
       pend = false;
       if (is_active(nb0)) {
-        if (needs_mask(nb0)) mask_block(S, nb0);
+        if (needs_mask(nb0)) {
+          mask_block(S, nb0);
+          rounded = false;
+        }
         if (SPARSE) select_block(S, hf == 0 ? ki0 : ki1);
-        softmax_fixed(S, Pout);
+        softmax_fixed(S, Pout, rounded);
         pend = true;
       }
       if (SPARSE && hf == 1) {                             // the next tile's index keys: a tile's time to arrive

@@ -434,3 +434,20 @@ def test_sparse_prefill_sliced_search_with_a_threshold_in_the_open_ended_bin():
     w = wl.small_prefill("cpu", p=0.999999, chunk_start=13000, T=40, seed=98)
     w.layer.index_scale = 2.5
     _check_sparse_prefill(w.to(DEV), "sliced_far", 0.999999)
+
+
+@pytest.mark.parametrize("p", [0.9, 1.0])
+@pytest.mark.parametrize("kv_dtype", ["bf16", "fp16"])
+def test_prefill_log_sums_of_masked_rows_carry_no_rounding(p, kv_dtype):
+    """Rows whose keys all lie in a part's first block or in masked ones sum unrounded probabilities: at most 32 terms in fp32
+    against a score error of 128 products in fp32 (|score| < 16), so 2^-24 * (32 + 128 * 16) < 1.3e-4 at the very worst; the
+    rounded sum of a few bf16 terms is off by up to 2^-9 = 2e-3 (fp16: 2^-12 = 2.4e-4)."""
+    print(f"[case] log-sums of masked rows, p {p}, {kv_dtype}", flush=True)
+    w = wl.small_prefill(DEV, chunk_start=0, T=172, seed=161, n_q_heads=4, n_kv_heads=2, ret_heads=(1, 2), kv_dtype=kv_dtype)
+    run = PrefillRun(w)
+    run.sparse_prefill(p=p)
+    torch.cuda.synchronize()
+    lse = run.lse.cpu().numpy().astype(np.float64)
+    ref = orc.prefill_rows(rows=[(t, h) for t in range(32) for h in w.layer.ret_heads], p=p, **prefill_oracle_inputs(w))
+    worst = max(abs(lse[r["t"], r["h"]] - r["lse"]) for r in ref)
+    assert worst < 1.3e-4, worst
