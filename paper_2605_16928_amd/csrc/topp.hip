@@ -79,7 +79,7 @@ struct TopPArgs {
   uint64_t* hist;          // [R, hist_stride]
   int64_t hist_stride;
   int32_t n_sub;           // copies of level 1 per row (topp_common.h)
-  int32_t n_copy;          // rows of one chunk: workgroups that share a row's gather (1 everywhere else)
+  int32_t n_copy;          // gathering launches: workgroups that share a chunk's gather
   RowState* state;         // [R, 3]
   int32_t* bucket_n;       // [R]: scores that share the level-2 prefix (may exceed kBucketCap)
   uint2* bucket;           // [R, kBucketCap]: (key, position) of the first kBucketCap of them
@@ -632,7 +632,7 @@ struct GatherArgs {
   uint16_t* out;
   float* lse;
   int32_t f16;             // q, K, V and out are fp16 (else bf16)
-  int32_t max_copy;        // rows of one chunk: partials per row that `part` has room for
+  int32_t max_copy;        // partials per chunk that `part` has room for
   const int32_t* page_table;   // paged cache: [B, pt_stride] pool pages (NULL: contiguous sequences at seq_start)
   int64_t pt_stride;
   int32_t page_shift;
@@ -768,7 +768,9 @@ __device__ __forceinline__ void attend_list(const GatherArgs& ga, const int r, c
 // rows once, into a second LDS list, before the gather starts.
 template <bool ATTEND, bool F16 = false, bool PAGED = false>
 __global__ __launch_bounds__(kTpThreads) void topp_write_kernel(const TopPArgs a, const GatherArgs ga) {
-  const int r = blockIdx.y, c = blockIdx.x, tid = threadIdx.x;
+  const int r = blockIdx.y, tid = threadIdx.x;
+  const int n_copy = ATTEND ? a.n_copy : 1;
+  const int c = (int)blockIdx.x / n_copy, copy = (int)blockIdx.x - c * n_copy;
   __shared__ int32_t sh_list[ATTEND ? kTpChunk : 1];
   __shared__ int32_t sh_rows[(ATTEND && PAGED) ? kTpChunk : 1];
   // Levels 1 and 2 were last read by the level-2 / level-3 launches; every workgroup of the grid clears its
@@ -778,15 +780,15 @@ __global__ __launch_bounds__(kTpThreads) void topp_write_kernel(const TopPArgs a
   int res_count = 0;
   bool have_res = false;
   auto rezero = [&]() {
-    if (have_res && c == 0 && tid == 0) {
+    if (have_res && blockIdx.x == 0 && tid == 0) {
       a.sel_count[r] = res_count;
       if (a.tau) a.tau[r] = res_tau;
       if (a.mass) a.mass[r] = res_mass;
     }
     if (!a.rezero) return;
     uint64_t* h = a.hist + (int64_t)r * a.hist_stride;
-    for (int i = c * kTpThreads + tid; i < kBins1 + kBins2; i += a.n_chunks * kTpThreads) h[i] = 0;
-    for (int i = kBinsTotal + c * kTpThreads + tid; i < a.hist_stride; i += a.n_chunks * kTpThreads) h[i] = 0;
+    for (int i = blockIdx.x * kTpThreads + tid; i < kBins1 + kBins2; i += gridDim.x * kTpThreads) h[i] = 0;
+    for (int i = kBinsTotal + blockIdx.x * kTpThreads + tid; i < a.hist_stride; i += gridDim.x * kTpThreads) h[i] = 0;
   };
   // what the level-3 launch left for this row, in flight before anything else: its histogram, the per-chunk
   // counts (one per thread: that covers rows of kTpThreads chunks) and the row's short list
@@ -821,7 +823,7 @@ __global__ __launch_bounds__(kTpThreads) void topp_write_kernel(const TopPArgs a
   // level 2 always leaves st[0]; level 3 leaves st[1] (a copy of st[0] for rows that carry no search)
   const RowState prev = a.state[(int64_t)r * 3 + 1];
 
-  int kept_here = 0, kept_base = 0;
+  int kept_here = 0, kept_base = 0, list_lo = 0;
   bool balanced = false;          // ATTEND: gather an equal share of the row's ranks instead of this chunk's own tokens
   const bool empty_row = prev.flags < 0 || prev.flags == 2;      // the same in every workgroup of the row
   if (empty_row) {
@@ -906,9 +908,11 @@ __global__ __launch_bounds__(kTpThreads) void topp_write_kernel(const TopPArgs a
     // gather starts behind a barrier, and every wait for a K/V row would also wait for stores in flight)
     kept_here = write_ranked(keep, before, ATTEND ? nullptr : a.sel_idx + (int64_t)r * a.sel_stride, n0, sh_tot,
                              ATTEND ? sh_list : nullptr);
-    kept_base = before;
+    list_lo = kept_here * copy / n_copy;                 // this copy's share of the chunk's list
+    kept_base = before + list_lo;
+    kept_here = kept_here * (copy + 1) / n_copy - list_lo;
   } else {
-    write_ranked(keep, before, a.sel_idx + (int64_t)r * a.sel_stride, n0, sh_tot, nullptr);   // this chunk's part of the list
+    if (copy == 0) write_ranked(keep, before, a.sel_idx + (int64_t)r * a.sel_stride, n0, sh_tot, nullptr);   // this chunk's part of the list
     // exact kept count of every chunk: the level-3 launch's count + the kept members of the short list
     sh_cnt[tid] = tid < n_row_chunks ? cc_mine : 0;
     __syncthreads();
@@ -936,7 +940,8 @@ __global__ __launch_bounds__(kTpThreads) void topp_write_kernel(const TopPArgs a
     const int q0 = (int)(excl >> 32);                    // cost before this thread's chunk
     sh_pre[tid] = (int)(uint32_t)excl;                   // kept tokens before it
     const int64_t cost_all = (int64_t)(all >> 32);
-    const int w_lo = (int)(cost_all * c / n_row_chunks), w_hi = (int)(cost_all * (c + 1) / n_row_chunks);
+    const int share = c * n_copy + copy, n_shares = n_row_chunks * n_copy;
+    const int w_lo = (int)(cost_all * share / n_shares), w_hi = (int)(cost_all * (share + 1) / n_shares);
     // ranks below a point x of the cost axis: this chunk's share, summed over the chunks
     auto below = [&](int x) { return min(max(x - q0 - my_scan, 0), mine); };
     const int lo_w = wave_sum(below(w_lo)), hi_w = wave_sum(below(w_hi));
@@ -968,15 +973,15 @@ __global__ __launch_bounds__(kTpThreads) void topp_write_kernel(const TopPArgs a
 
   // ---- attention over this chunk's kept positions ----
   float M = ninf, L = 0.f, A = 0.f;
-  attend_list<F16, PAGED>(ga, r, sh_list, sh_rows, kept_here, M, L, A);
+  attend_list<F16, PAGED>(ga, r, sh_list + list_lo, sh_rows, kept_here, M, L, A);
   if (tid < kHeadDim) {
-    float* pout = ga.part + ((int64_t)r * a.n_chunks + c) * kSaPart;
+    float* pout = ga.part + ((int64_t)r * gridDim.x + blockIdx.x) * kSaPart;
     pout[4 + tid] = A;
     if (tid == 0) { pout[0] = M; pout[1] = L; }
   }
   if (!balanced) {   // the chunk's positions, in one coalesced piece (after the last barrier)
     int32_t* dst = a.sel_idx + (int64_t)r * a.sel_stride + kept_base;
-    for (int i = tid; i < kept_here; i += kTpThreads) dst[i] = sh_list[i];
+    for (int i = tid; i < kept_here; i += kTpThreads) dst[i] = sh_list[list_lo + i];
   }
   rezero();
 }
@@ -1002,7 +1007,7 @@ __global__ __launch_bounds__(256) void select_attend_combine_kernel(const TopPAr
   const int r = blockIdx.x, tid = threadIdx.x;
   const float ninf = -__builtin_huge_valf();
   const int n = a.row_len[r];
-  const int n_row_chunks = n > 0 ? (a.n_copy > 1 ? a.n_copy : (n + kTpChunk - 1) / kTpChunk) : 0;
+  const int n_row_chunks = n > 0 ? (n + kTpChunk - 1) / kTpChunk * a.n_copy : 0;   // partials of the row
   const int d4 = tid & 31, slice = tid >> 5;
   float M = ninf, L = 0.f;
   float4 A = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -1015,7 +1020,7 @@ __global__ __launch_bounds__(256) void select_attend_combine_kernel(const TopPAr
       const int i = i0 + u * 8;
       pm[u] = ninf; pl[u] = 0.f; pv[u] = make_float4(0.f, 0.f, 0.f, 0.f);
       if (i < n_row_chunks) {
-        const float* p = ga.part + ((int64_t)r * a.n_chunks + i) * kSaPart;
+        const float* p = ga.part + ((int64_t)r * a.n_chunks * a.n_copy + i) * kSaPart;
         pm[u] = p[0]; pl[u] = p[1];
         pv[u] = *reinterpret_cast<const float4*>(p + 4 + d4 * 4);
       }
@@ -1242,9 +1247,18 @@ extern "C" int32_t rtp_topp_workspace_init(void* ws, size_t ws_bytes, void* stre
 // kDirectTokens tokens per unit a unit is one work item whose workgroup writes the heads' results itself (a few load
 // rounds, shorter than the row's own work), else the plan's items and a launch that merges them.
 constexpr int kDirectTokens = 1024;
-// Workgroups that share the gather of a row of one chunk when a merge launch follows anyway (a set of thousands of tokens
-// keeps one workgroup busy for 33 us): up to four, about one workgroup per compute unit in all.
-static int row_copies(int32_t R) { return R <= 64 ? 4 : (R <= 128 ? 2 : 1); }
+// Workgroups that share the gather of a chunk's kept tokens (each repeats the rest of the chunk's work): what the attention
+// workspace is sized for, and with less room there is one.
+// One chunk per row, when a merge launch follows anyway (a set of thousands of tokens keeps one workgroup busy for 33 us): up
+// to four, about one workgroup per compute unit in all.
+// More chunks: four while they leave the chip a quarter full (1 x 32768, 4 heads: 15.3 -> 11.0 us; 3 x 32768: 15.5 -> 12.5),
+// fewer where a row would have more than the 32 partials that the merge reads in one round (1 x 131072: write and merge 19.4 us
+// with one, 18.2 with two, 18.7 with four; 1 x 262144: 20.5 with one, 22.0 with four).  Beyond 64 workgroups the copies only
+// compete for the memory (5 x 65536: 17.7 us with one, 19.8 with two; 12 ragged rows to 30011: 15.3 and 18.0).
+static int gather_copies(int64_t R, int64_t n_chunks) {
+  if (n_chunks == 1) return R <= 64 ? 4 : (R <= 128 ? 2 : 1);
+  return R * n_chunks > 64 ? 1 : (n_chunks <= 8 ? 4 : (n_chunks <= 16 ? 2 : 1));
+}
 template <int RIDE_G, bool F16, bool PAGED>
 static void launch_rows_t(TopPArgs a, const GatherArgs& ga, AttnDecodeArgs la, hipStream_t s) {
   int n_ride = 0;
@@ -1262,7 +1276,6 @@ static void launch_rows_t(TopPArgs a, const GatherArgs& ga, AttnDecodeArgs la, h
   if constexpr (RIDE_G > 0) {
     if (direct) return;
     TopPArgs rows = a;                               // one copy: the rows are finished, only local heads are merged
-    rows.n_chunks = a.n_copy;
     if (a.n_copy == 1) rows.R = 0;
     RTP_LAUNCH(select_attend_combine_kernel<RIDE_G>, dim3((unsigned)(rows.R + la.units * RIDE_G)), dim3(256), 0, s, rows, ga, la);
   }
@@ -1371,10 +1384,12 @@ static int32_t run_select(const char* who, const float* scores, int64_t score_st
   }
   if (attend) {
     const bool paged = attend->page_table != nullptr;
-    if (attend->f16 && paged) RTP_LAUNCH((topp_write_kernel<true, true, true>), grid, block, 0, s, a, *attend);
-    else if (attend->f16) RTP_LAUNCH((topp_write_kernel<true, true>), grid, block, 0, s, a, *attend);
-    else if (paged) RTP_LAUNCH((topp_write_kernel<true, false, true>), grid, block, 0, s, a, *attend);
-    else RTP_LAUNCH(topp_write_kernel<true>, grid, block, 0, s, a, *attend);
+    a.n_copy = attend->max_copy;
+    const dim3 ggrid((unsigned)(a.n_chunks * a.n_copy), (unsigned)R);
+    if (attend->f16 && paged) RTP_LAUNCH((topp_write_kernel<true, true, true>), ggrid, block, 0, s, a, *attend);
+    else if (attend->f16) RTP_LAUNCH((topp_write_kernel<true, true>), ggrid, block, 0, s, a, *attend);
+    else if (paged) RTP_LAUNCH((topp_write_kernel<true, false, true>), ggrid, block, 0, s, a, *attend);
+    else RTP_LAUNCH(topp_write_kernel<true>, ggrid, block, 0, s, a, *attend);
     if (ride) {
       const dim3 cgrid((unsigned)(R + ride->units * ride_G));
       if (ride_G == 2) RTP_LAUNCH(select_attend_combine_kernel<2>, cgrid, dim3(256), 0, s, a, *attend, *ride);
@@ -1457,8 +1472,8 @@ extern "C" int32_t rtp_topk_select(const float* scores, int64_t score_stride, co
 
 extern "C" size_t rtp_select_attend_decode_workspace_bytes(const rtp_layer_desc* layer, int32_t B, int64_t max_ctx) {
   if (!layer || B <= 0 || max_ctx <= 0 || layer->n_ret <= 0) return 256;
-  const int64_t n_chunks = max_ctx <= kTpChunk ? row_copies(B * layer->n_ret) : (max_ctx + kTpChunk - 1) / kTpChunk;
-  return align_up((size_t)B * layer->n_ret * n_chunks * kSaPart * sizeof(float), 256);
+  const int64_t R = (int64_t)B * layer->n_ret, n_chunks = (max_ctx + kTpChunk - 1) / kTpChunk;
+  return align_up((size_t)(R * n_chunks * gather_copies(R, n_chunks)) * kSaPart * sizeof(float), 256);
 }
 
 // Argument checks of the selection + attention call and its gather arguments (shared by the two entry points).
@@ -1484,9 +1499,9 @@ static int32_t prepare_select_attend(const char* who, const rtp_layer_desc* laye
   *R = (int64_t)B * layer->n_ret;
   if (*R > 65535) return fail(RTP_ERR_INVALID_ARG, "%s: B * n_ret is limited to 65535", who);
   if (layer->n_ret == 0) return RTP_OK;
-  const size_t one_each = align_up((size_t)B * layer->n_ret * kSaPart * sizeof(float), 256);
-  const size_t full = rtp_select_attend_decode_workspace_bytes(layer, B, max_ctx);
-  const size_t need = max_ctx <= kTpChunk ? one_each : full;     // (short rows: more room is for workgroups that share a gather)
+  // one partial per chunk; the size function's full answer is for workgroups that share a gather
+  const int64_t n_chunks = (max_ctx + kTpChunk - 1) / kTpChunk;
+  const size_t need = align_up((size_t)(*R * n_chunks) * kSaPart * sizeof(float), 256);
   if (!attn_ws || ((uintptr_t)attn_ws & 255) || attn_ws_bytes < need)
     return fail(RTP_ERR_WORKSPACE, "%s: attention workspace of %zu bytes (256-byte aligned) required, got %zu", who, need,
                 attn_ws_bytes);
@@ -1504,7 +1519,7 @@ static int32_t prepare_select_attend(const char* who, const rtp_layer_desc* laye
   ga->out = (uint16_t*)out;
   ga->lse = lse;
   ga->f16 = layer->kv_dtype == RTP_DTYPE_FP16;
-  ga->max_copy = max_ctx <= kTpChunk && attn_ws_bytes >= full ? row_copies((int32_t)*R) : 1;
+  ga->max_copy = attn_ws_bytes >= rtp_select_attend_decode_workspace_bytes(layer, B, max_ctx) ? gather_copies(*R, n_chunks) : 1;
   ga->page_table = pages ? pages->table : nullptr;
   ga->pt_stride = pages ? pages->stride : 0;
   ga->page_shift = page_shift;
