@@ -1011,32 +1011,38 @@ __global__ __launch_bounds__(256) void select_attend_combine_kernel(const TopPAr
   const int d4 = tid & 31, slice = tid >> 5;
   float M = ninf, L = 0.f;
   float4 A = make_float4(0.f, 0.f, 0.f, 0.f);
-  // four partials in flight per slice: a long row has hundreds of chunks and each load is a round trip
-  for (int i0 = slice; i0 < n_row_chunks; i0 += 8 * 4) {
-    float pm[4], pl[4];
-    float4 pv[4];
+  // each load is a round trip: four partials in flight per slice, 16 for rows of more than 32 (a row of 1M tokens has 128;
+  // with 8 of them this launch takes 8.7 us with four in flight, 4.7 with 16).  The same order of sums either way.
+  auto walk = [&](auto in_flight) __attribute__((always_inline)) {
+    constexpr int U = decltype(in_flight)::value;
+    for (int i0 = slice; i0 < n_row_chunks; i0 += 8 * U) {
+      float pm[U], pl[U];
+      float4 pv[U];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int i = i0 + u * 8;
-      pm[u] = ninf; pl[u] = 0.f; pv[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (i < n_row_chunks) {
-        const float* p = ga.part + ((int64_t)r * a.n_chunks * a.n_copy + i) * kSaPart;
-        pm[u] = p[0]; pl[u] = p[1];
-        pv[u] = *reinterpret_cast<const float4*>(p + 4 + d4 * 4);
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + u * 8;
+        pm[u] = ninf; pl[u] = 0.f; pv[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (i < n_row_chunks) {
+          const float* p = ga.part + ((int64_t)r * a.n_chunks * a.n_copy + i) * kSaPart;
+          pm[u] = p[0]; pl[u] = p[1];
+          pv[u] = *reinterpret_cast<const float4*>(p + 4 + d4 * 4);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const float Mn = fmaxf(M, pm[u]);
+        if (Mn != ninf) {
+          const float c0 = fast_exp2(M - Mn), c1 = fast_exp2(pm[u] - Mn);
+          L = L * c0 + pl[u] * c1;
+          A.x = A.x * c0 + pv[u].x * c1; A.y = A.y * c0 + pv[u].y * c1;
+          A.z = A.z * c0 + pv[u].z * c1; A.w = A.w * c0 + pv[u].w * c1;
+          M = Mn;
+        }
       }
     }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const float Mn = fmaxf(M, pm[u]);
-      if (Mn != ninf) {
-        const float c0 = fast_exp2(M - Mn), c1 = fast_exp2(pm[u] - Mn);
-        L = L * c0 + pl[u] * c1;
-        A.x = A.x * c0 + pv[u].x * c1; A.y = A.y * c0 + pv[u].y * c1;
-        A.z = A.z * c0 + pv[u].z * c1; A.w = A.w * c0 + pv[u].w * c1;
-        M = Mn;
-      }
-    }
-  }
+  };
+  if (n_row_chunks > 32) walk(std::integral_constant<int, 16>{});
+  else walk(std::integral_constant<int, 4>{});
   if (d4 == 0) { sh_m[slice] = M; sh_l[slice] = L; }
   *reinterpret_cast<float4*>(&sh_acc[slice][d4 * 4]) = A;
   __syncthreads();
@@ -1252,9 +1258,9 @@ constexpr int kDirectTokens = 1024;
 // One chunk per row, when a merge launch follows anyway (a set of thousands of tokens keeps one workgroup busy for 33 us): up
 // to four, about one workgroup per compute unit in all.
 // More chunks: four while they leave the chip a quarter full (1 x 32768, 4 heads: 15.3 -> 11.0 us; 3 x 32768: 15.5 -> 12.5),
-// fewer where a row would have more than the 32 partials that the merge reads in one round (1 x 131072: write and merge 19.4 us
-// with one, 18.2 with two, 18.7 with four; 1 x 262144: 20.5 with one, 22.0 with four).  Beyond 64 workgroups the copies only
-// compete for the memory (5 x 65536: 17.7 us with one, 19.8 with two; 12 ragged rows to 30011: 15.3 and 18.0).
+// fewer where a row would have more partials than the merge's short form reads in one round, 32 (1 x 131072: write and merge
+// 19.4 us with one, 18.2 with two, 18.7 with four).  Beyond 64 workgroups the copies only compete for the memory (5 x 65536:
+// 17.7 us with one, 19.8 with two; 12 ragged rows to 30011: 15.3 and 18.0).
 static int gather_copies(int64_t R, int64_t n_chunks) {
   if (n_chunks == 1) return R <= 64 ? 4 : (R <= 128 ? 2 : 1);
   return R * n_chunks > 64 ? 1 : (n_chunks <= 8 ? 4 : (n_chunks <= 16 ? 2 : 1));

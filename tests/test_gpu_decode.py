@@ -629,11 +629,11 @@ def test_level1_in_score_pass_around_the_chunks(ctx):
         assert torch.equal(a.nan_to_num(), b.nan_to_num()) if a.dtype == torch.float32 else torch.equal(a, b)
 
 
-@pytest.mark.parametrize("ctx", [(40000, 9000), (65536,), (65537,), (131073,), (8193, 16384, 100, 16385)])
+@pytest.mark.parametrize("ctx", [(40000, 9000), (65536,), (65537,), (131073,), (262145, 262144), (8193, 16384, 100, 16385)])
 @pytest.mark.parametrize("clustered", [False, True])
 def test_gather_shared_by_several_workgroups(ctx, clustered):
     """Small batches of long rows: several workgroups per 8192-score chunk share its gather where the workspace has room for
-    their partials.  The selection is that of the separate calls bit for bit, with either workspace; the outputs differ only
+    their partials (rows of 33 chunks: more than 32 partials to merge).  The selection is that of the separate calls bit for bit, with either workspace; the outputs differ only
     by the order of fp32 sums and one rounding to 16 bits."""
     print(f"[case] shared gather, contexts {ctx}, clustered {clustered}", flush=True)
     w = wl.small_decode("cpu", seed=221, ctx=ctx, p=(0.95,)).to(DEV)
