@@ -451,3 +451,19 @@ def test_prefill_log_sums_of_masked_rows_carry_no_rounding(p, kv_dtype):
     ref = orc.prefill_rows(rows=[(t, h) for t in range(32) for h in w.layer.ret_heads], p=p, **prefill_oracle_inputs(w))
     worst = max(abs(lse[r["t"], r["h"]] - r["lse"]) for r in ref)
     assert worst < 1.3e-4, worst
+
+
+@pytest.mark.parametrize("chunk_start,window", [(200, 64), (255, 40), (128, 100), (191, 30)])
+def test_local_prefill_infinite_value_of_the_last_key(chunk_start, window):
+    """The rows a ragged last tile stages past the last key take part with probability 0 and value 0: an infinite value of the
+    last key gives its own query infinity, not NaN."""
+    print(f"[case] local prefill, infinite last value, {chunk_start}", flush=True)
+    w = wl.small_prefill(DEV, chunk_start=chunk_start, T=1, sink=4, window=window, seed=171)
+    w.V[:, chunk_start, 3] = float("inf")
+    run = PrefillRun(w)
+    run.local_attn()
+    torch.cuda.synchronize()
+    heads = [h for h in range(w.layer.n_q_heads) if h not in w.layer.ret_heads]
+    out = run.out[0, heads].float()
+    assert torch.isposinf(out[:, 3]).all()
+    assert torch.isfinite(out[:, :3]).all() and torch.isfinite(out[:, 4:]).all()
