@@ -632,7 +632,7 @@ struct GatherArgs {
   uint16_t* out;
   float* lse;
   int32_t f16;             // q, K, V and out are fp16 (else bf16)
-  int32_t max_copy;        // partials per chunk that `part` has room for
+  int32_t max_copy;        // workgroups per chunk at most (`part` has room for their partials)
   const int32_t* page_table;   // paged cache: [B, pt_stride] pool pages (NULL: contiguous sequences at seq_start)
   int64_t pt_stride;
   int32_t page_shift;
@@ -1253,8 +1253,8 @@ extern "C" int32_t rtp_topp_workspace_init(void* ws, size_t ws_bytes, void* stre
 // kDirectTokens tokens per unit a unit is one work item whose workgroup writes the heads' results itself (a few load
 // rounds, shorter than the row's own work), else the plan's items and a launch that merges them.
 constexpr int kDirectTokens = 1024;
-// Workgroups that share the gather of a chunk's kept tokens (each repeats the rest of the chunk's work): what the attention
-// workspace is sized for, and with less room there is one.
+// Workgroups that share the gather of a chunk's kept tokens (each repeats the rest of the chunk's work).  The attention
+// workspace has room for their partials.
 // One chunk per row, when a merge launch follows anyway (a set of thousands of tokens keeps one workgroup busy for 33 us): up
 // to four, about one workgroup per compute unit in all.
 // More chunks: four while they leave the chip a quarter full (1 x 32768, 4 heads: 15.3 -> 11.0 us; 3 x 32768: 15.5 -> 12.5),
@@ -1479,7 +1479,9 @@ extern "C" int32_t rtp_topk_select(const float* scores, int64_t score_stride, co
 extern "C" size_t rtp_select_attend_decode_workspace_bytes(const rtp_layer_desc* layer, int32_t B, int64_t max_ctx) {
   if (!layer || B <= 0 || max_ctx <= 0 || layer->n_ret <= 0) return 256;
   const int64_t R = (int64_t)B * layer->n_ret, n_chunks = (max_ctx + kTpChunk - 1) / kTpChunk;
-  return align_up((size_t)(R * n_chunks * gather_copies(R, n_chunks)) * kSaPart * sizeof(float), 256);
+  // one partial per chunk, or four up to the 256 that gather_copies ever asks for: never less for more rows or longer ones
+  const int64_t parts = std::max(R * n_chunks, std::min<int64_t>(4 * R * n_chunks, 256));
+  return align_up((size_t)parts * kSaPart * sizeof(float), 256);
 }
 
 // Argument checks of the selection + attention call and its gather arguments (shared by the two entry points).
@@ -1505,9 +1507,8 @@ static int32_t prepare_select_attend(const char* who, const rtp_layer_desc* laye
   *R = (int64_t)B * layer->n_ret;
   if (*R > 65535) return fail(RTP_ERR_INVALID_ARG, "%s: B * n_ret is limited to 65535", who);
   if (layer->n_ret == 0) return RTP_OK;
-  // one partial per chunk; the size function's full answer is for workgroups that share a gather
   const int64_t n_chunks = (max_ctx + kTpChunk - 1) / kTpChunk;
-  const size_t need = align_up((size_t)(*R * n_chunks) * kSaPart * sizeof(float), 256);
+  const size_t need = rtp_select_attend_decode_workspace_bytes(layer, B, max_ctx);
   if (!attn_ws || ((uintptr_t)attn_ws & 255) || attn_ws_bytes < need)
     return fail(RTP_ERR_WORKSPACE, "%s: attention workspace of %zu bytes (256-byte aligned) required, got %zu", who, need,
                 attn_ws_bytes);
@@ -1525,7 +1526,7 @@ static int32_t prepare_select_attend(const char* who, const rtp_layer_desc* laye
   ga->out = (uint16_t*)out;
   ga->lse = lse;
   ga->f16 = layer->kv_dtype == RTP_DTYPE_FP16;
-  ga->max_copy = attn_ws_bytes >= rtp_select_attend_decode_workspace_bytes(layer, B, max_ctx) ? gather_copies(*R, n_chunks) : 1;
+  ga->max_copy = gather_copies(*R, n_chunks);
   ga->page_table = pages ? pages->table : nullptr;
   ga->pt_stride = pages ? pages->stride : 0;
   ga->page_shift = page_shift;
