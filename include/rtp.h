@@ -213,8 +213,12 @@ int32_t rtp_sparse_attn_decode(const rtp_layer_desc* layer, const void* q,
  * For p < 1 the attention visits only the 64-key tiles in which some query of a 256-query tile can keep a key (the
  * search leaves, per 32-query group and tile, whether a product reaches the group's thresholds); outputs, counts and
  * sums are those of visiting every tile.  The workspace holds that table (4 B per group and 64 keys of context),
- * the tile lists and the key-range partials: about 630 MB for T = 8192 at chunk_start = 1,040,384 with 4
- * retrieval heads, 40 MB for T = 4096 at 126,976.
+ * the tile lists, and the key-range partials or, before them, what the launches of a short chunk's search hand on: about
+ * 630 MB for T = 8192 at chunk_start = 1,040,384 with 4 retrieval heads, 40 MB for T = 4096 at 126,976, 35 MB for T = 333
+ * at 131,072.  The size function answers what every chunk of at most T queries ending at chunk_start + T takes at full
+ * speed, so it never answers less for a longer chunk with the same end.  A short chunk needs far less (T = 333 at
+ * 131,072: 6 MB) and uses of a smaller workspace what there is, at the price of idle compute units.  p >= 1 without
+ * statistics keeps nothing but partials there and needs no workspace at all.
  */
 size_t rtp_sparse_attn_prefill_workspace_bytes(const rtp_layer_desc* layer, int32_t T, int64_t chunk_start);
 int32_t rtp_sparse_attn_prefill(const rtp_layer_desc* layer, const void* q_pre, const void* q, const float* WQ,
@@ -230,7 +234,8 @@ int32_t rtp_sparse_attn_prefill(const rtp_layer_desc* layer, const void* q_pre, 
  * index score of every 32-query group in every 64-key tile, and the attention launch visits a tile only if some
  * query of its 256-query tile can keep a key there).  layer, T and chunk_start as in that call; waits for `stream`,
  * then writes two host values: tiles_visited (64-key tiles visited, summed over retrieval heads and 256-query
- * tiles) and tiles_causal (what plain causal attention visits).  Allocates nothing on the device.
+ * tiles) and tiles_causal (what plain causal attention visits).  ws_bytes: at least the size function's answer.
+ * Allocates nothing on the device.
  */
 int32_t rtp_sparse_attn_prefill_tile_stats(const rtp_layer_desc* layer, int32_t T, int64_t chunk_start,
                                            const void* ws, size_t ws_bytes, void* stream,

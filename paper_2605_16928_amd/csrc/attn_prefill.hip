@@ -2055,24 +2055,24 @@ int32_t prefill_range_attn(const char* who, bool dense, const rtp_layer_desc* L,
 // least 4096 keys of the longest range, at most 16.  The five launches cost about 60 us beside the sweeps, what one
 // workgroup needs for 9000 keys of a broad score law: the slices have to save more than that (1 to 64 queries behind
 // 60000 tokens: 82 to 93 us against some 400 in one launch; 1000 queries behind 5000 tokens stay at 62 in one).
-static int search_slices(int n_ret, int32_t T, int64_t chunk_start) {
-  const int64_t groups = (int64_t)n_ret * ((T + 31) / 32), keys = chunk_start + T;
-  const int64_t s = std::min(2 * (int64_t)compute_units() / groups, std::min(keys / 4096, (int64_t)16));
-  return s >= 2 && keys - keys / s > 9000 ? (int)s : 1;
-}
+// `room`: bytes there are for what the launches hand on; fewer slices where it holds no more.
 struct SearchWs {
   size_t max_bytes, hist_bytes, state_bytes, again_bytes;
   size_t total() const { return max_bytes + hist_bytes + state_bytes + again_bytes; }
 };
-static SearchWs search_ws(int n_ret, int32_t T, int n_slice) {
-  const size_t groups = (size_t)n_ret * ((T + 31) / 32);
+static SearchWs search_ws(int64_t groups, int64_t workgroups) {
   SearchWs w = {};
-  if (n_slice < 2) return w;
-  w.max_bytes = align_up(groups * n_slice * 32 * sizeof(float), 256);
-  w.hist_bytes = align_up(groups * n_slice * 2 * kSelBins * 32 * sizeof(double), 256);
-  w.state_bytes = align_up(groups * 2 * 32 * sizeof(SelState), 256);
-  w.again_bytes = align_up(groups * sizeof(int32_t), 256);
+  w.max_bytes = align_up((size_t)workgroups * 32 * sizeof(float), 256);
+  w.hist_bytes = align_up((size_t)workgroups * 2 * kSelBins * 32 * sizeof(double), 256);
+  w.state_bytes = align_up((size_t)groups * 2 * 32 * sizeof(SelState), 256);
+  w.again_bytes = align_up((size_t)groups * sizeof(int32_t), 256);
   return w;
+}
+static int search_slices(int n_ret, int32_t T, int64_t chunk_start, size_t room) {
+  const int64_t groups = (int64_t)n_ret * ((T + 31) / 32), keys = chunk_start + T;
+  int64_t s = std::min(2 * (int64_t)compute_units() / groups, std::min(keys / 4096, (int64_t)16));
+  while (s >= 2 && search_ws(groups, groups * s).total() > room) --s;
+  return s >= 2 && keys - keys / s > 9000 ? (int)s : 1;
 }
 
 // Sizes of the tile bookkeeping of a selecting launch.  A table row has one entry per 64 keys of the context, plus
@@ -2091,9 +2091,9 @@ static PrefillTileWs prefill_tile_ws(int32_t n_ret, int32_t T, int64_t chunk_sta
   return w;
 }
 
-// Key ranges of a launch for the retrieval heads under either rule, and the number the workspace has room for.
+// Key ranges of a launch for the retrieval heads under either rule.
 struct PrefillRanges {
-  int dense, dense_sub, listed, listed_sub, ws_ranges;
+  int dense, dense_sub, listed, listed_sub;
 };
 static PrefillRanges prefill_ranges(int n_ret, int32_t T, int64_t chunk_start) {
   PrefillRanges r;
@@ -2101,8 +2101,45 @@ static PrefillRanges prefill_ranges(int n_ret, int32_t T, int64_t chunk_start) {
   r.listed = choose_splits_listed(n_ret, T, chunk_start);
   r.dense_sub = choose_sub(n_ret, T, chunk_start, r.dense, r.dense);
   r.listed_sub = choose_sub(n_ret, T, chunk_start, r.dense, r.listed);
-  r.ws_ranges = std::max(r.dense * r.dense_sub, r.listed * r.listed_sub);
   return r;
+}
+static size_t range_bytes(int n_ret, int32_t T) { return (size_t)n_ret * T * kPfPart * sizeof(float); }   // one range's partials
+static size_t partial_bytes(int ranges, int n_ret, int32_t T) { return ranges > 1 ? align_up(ranges * range_bytes(n_ret, T), 256) : 0; }
+
+// The workspace: projected index queries | one threshold per (retrieval head, query) | tile-maximum table, tile lists and
+// their lengths | scratch.  The scratch first carries what the launches of a sliced search hand on and then, when the
+// search is over, the key-range partials.  A call needs room for the partials of its ranges (prefill_needed); how many
+// slices and sub-ranges it takes follows from the scratch it was given, so that a short chunk runs in the workspace of a
+// long one.
+struct PrefillWs {
+  size_t proj, state, tiles;             // bytes of the parts in front of the scratch
+  PrefillTileWs tw;
+  size_t front() const { return proj + state + tiles; }
+};
+static PrefillWs prefill_ws(int n_ret, int32_t T, int64_t chunk_start) {
+  PrefillWs w;
+  w.proj = align_up((size_t)n_ret * T * kIndexDim * sizeof(uint16_t), 256);
+  w.state = align_up((size_t)n_ret * T * sizeof(float), 256);
+  w.tw = prefill_tile_ws(n_ret, T, chunk_start);
+  w.tiles = w.tw.table_bytes + w.tw.list_bytes + w.tw.count_bytes;
+  return w;
+}
+static size_t prefill_needed(int n_ret, int32_t T, int64_t chunk_start) {
+  return prefill_ws(n_ret, T, chunk_start).front() + partial_bytes(choose_splits_listed(n_ret, T, chunk_start), n_ret, T);
+}
+// The scratch that lets every chunk of at most T queries that ends where this one does run at full speed: the largest
+// partials of any of them (they grow with the queries as long as the number of 256-query tiles stays) and the most a
+// sliced search takes.  The size function therefore never answers less for a longer chunk with the same end.
+static size_t prefill_scratch(int n_ret, int32_t T, int64_t chunk_start) {
+  const int64_t end = chunk_start + T, groups = (int64_t)n_ret * ((T + 31) / 32);
+  size_t most = 0;
+  for (int64_t t = std::min<int64_t>(T, kPwQ);; t = std::min<int64_t>(T, t + kPwQ)) {
+    const PrefillRanges r = prefill_ranges(n_ret, (int32_t)t, end - t);
+    most = std::max(most, partial_bytes(std::max(r.dense * r.dense_sub, r.listed * r.listed_sub), n_ret, (int32_t)t));
+    if (t == T) break;
+  }
+  const int64_t cus = compute_units(), wgs = std::min(groups * std::min(end / 4096, (int64_t)16), 2 * cus);
+  return std::max(most, end > 9000 ? search_ws(std::min(groups, cus), wgs).total() : 0);
 }
 
 }  // namespace rtp
@@ -2111,18 +2148,8 @@ using namespace rtp;
 
 extern "C" size_t rtp_sparse_attn_prefill_workspace_bytes(const rtp_layer_desc* layer, int32_t T, int64_t chunk_start) {
   if (!layer || T <= 0 || layer->n_ret <= 0) return 256;
-  // selecting mode: projected index queries, then one threshold per (retrieval head, query)
-  const size_t proj = align_up((size_t)layer->n_ret * T * kIndexDim * sizeof(uint16_t), 256);
-  const size_t state = align_up((size_t)layer->n_ret * T * sizeof(float), 256);
-  // both rules: key-range partials
-  const int ns = prefill_ranges(layer->n_ret, T, chunk_start < 0 ? 0 : chunk_start).ws_ranges;
-  const size_t part = ns > 1 ? align_up((size_t)ns * layer->n_ret * T * kPfPart * sizeof(float), 256) : 0;
-  // selecting mode: the tile-maximum table and the query tiles' lists of tiles to visit
-  const PrefillTileWs tw = prefill_tile_ws(layer->n_ret, T, chunk_start < 0 ? 0 : chunk_start);
-  // ... and what the launches of a sliced search hand on
   const int64_t c0 = chunk_start < 0 ? 0 : chunk_start;
-  const size_t sliced = search_ws(layer->n_ret, T, search_slices(layer->n_ret, T, c0)).total();
-  return proj + state + part + sliced + tw.table_bytes + tw.list_bytes + tw.count_bytes;
+  return prefill_ws(layer->n_ret, T, c0).front() + prefill_scratch(layer->n_ret, T, c0);
 }
 
 extern "C" int32_t rtp_sparse_attn_prefill(const rtp_layer_desc* layer, const void* q_pre, const void* q, const float* WQ,
@@ -2147,7 +2174,7 @@ extern "C" int32_t rtp_sparse_attn_prefill(const rtp_layer_desc* layer, const vo
     if (((uintptr_t)q_pre & 15) || ((uintptr_t)kI & 15) || (kI_head_stride & 7) || kI_head_stride < 0)
       return fail(RTP_ERR_INVALID_ARG, "%s: index tensors must be 16-byte aligned, kI_head_stride a multiple of 8", who);
     if (layer->n_ret > 0) {
-      const size_t need = rtp_sparse_attn_prefill_workspace_bytes(layer, T, chunk_start);
+      const size_t need = prefill_needed(layer->n_ret, T, chunk_start);
       if (!ws || ((uintptr_t)ws & 255) || ws_bytes < need)
         return fail(RTP_ERR_WORKSPACE, "%s: workspace of %zu bytes (256-byte aligned) required, got %zu", who, need, ws_bytes);
     }
@@ -2180,13 +2207,12 @@ extern "C" int32_t rtp_sparse_attn_prefill(const rtp_layer_desc* layer, const vo
   a.mass = mass;
   const PrefillRanges ranges = prefill_ranges(layer->n_ret, T, chunk_start);
   if (!(p < 1.f)) {                                  // the paper's dense prefill rule: nothing to score, nothing to select
-    a.n_splits = ranges.dense;
-    a.n_sub = ranges.dense_sub;
-    if (a.n_splits * a.n_sub > 1) {
-      const size_t need = rtp_sparse_attn_prefill_workspace_bytes(layer, T, chunk_start);
-      if (!ws || ((uintptr_t)ws & 255) || ws_bytes < need) a.n_splits = a.n_sub = 1;   // no scratch: run unsplit
-      a.part = (float*)ws;
-    }
+    // (the partials are all this rule keeps in the workspace; without room for them: one range)
+    const size_t room = ws && !((uintptr_t)ws & 255) ? ws_bytes / range_bytes(layer->n_ret, T) : 0;
+    const bool split = room >= (size_t)ranges.dense;
+    a.n_splits = split ? ranges.dense : 1;
+    a.n_sub = split ? (int32_t)std::min<size_t>(ranges.dense_sub, room / ranges.dense) : 1;
+    a.part = (float*)ws;
     return launch_prefill(who, false, a, 1, (hipStream_t)stream);
   }
 
@@ -2210,29 +2236,28 @@ extern "C" int32_t rtp_sparse_attn_prefill(const rtp_layer_desc* layer, const vo
   a.kI_head_stride = kI_head_stride;
   a.p = p;
   a.index_scale = index_scale_of(layer);
-  const size_t proj_bytes = align_up((size_t)layer->n_ret * T * kIndexDim * sizeof(uint16_t), 256);
-  const size_t state_bytes = align_up((size_t)layer->n_ret * T * sizeof(float), 256);
-  a.sel_thr = (float*)((char*)ws + proj_bytes);
-  a.part = (float*)((char*)ws + proj_bytes + state_bytes);
+  const PrefillWs w = prefill_ws(layer->n_ret, T, chunk_start);
+  char* const tiles = (char*)ws + w.proj + w.state;
+  char* const scratch = (char*)ws + w.front();
+  const size_t room = ws_bytes - w.front();
+  a.sel_thr = (float*)((char*)ws + w.proj);
+  a.part = (float*)scratch;
   a.n_splits = ranges.listed;
-  a.n_sub = ranges.listed_sub;
+  a.n_sub = (int32_t)std::max<size_t>(std::min<size_t>(ranges.listed_sub, room / range_bytes(layer->n_ret, T) / ranges.listed), 1);
+  a.n_slice = search_slices(layer->n_ret, T, chunk_start, room);
   {
-    const size_t part_bytes = ranges.ws_ranges > 1 ? align_up((size_t)ranges.ws_ranges * layer->n_ret * T * kPfPart * sizeof(float), 256) : 0;
-    const PrefillTileWs tw = prefill_tile_ws(layer->n_ret, T, chunk_start);
-    char* at = (char*)ws + proj_bytes + state_bytes + part_bytes;
-    a.n_slice = search_slices(layer->n_ret, T, chunk_start);
-    const SearchWs sw = search_ws(layer->n_ret, T, a.n_slice);
-    a.sl_max = (float*)at;
-    a.sl_hist = (double*)(at + sw.max_bytes);
-    a.sl_state = (SelState*)(at + sw.max_bytes + sw.hist_bytes);
-    a.sl_again = (int32_t*)(at + sw.max_bytes + sw.hist_bytes + sw.state_bytes);
-    at += sw.total();
-    a.n_t64 = tw.n_t64;
-    a.tile_max = (float*)at;
-    a.act_list = (int32_t*)(at + tw.table_bytes);
-    a.act_count = (int32_t*)(at + tw.table_bytes + tw.list_bytes);
+    const int64_t groups = (int64_t)layer->n_ret * ((T + 31) / 32);
+    const SearchWs sw = search_ws(groups, groups * a.n_slice);
+    a.sl_max = (float*)scratch;
+    a.sl_hist = (double*)(scratch + sw.max_bytes);
+    a.sl_state = (SelState*)(scratch + sw.max_bytes + sw.hist_bytes);
+    a.sl_again = (int32_t*)(scratch + sw.max_bytes + sw.hist_bytes + sw.state_bytes);
+    a.n_t64 = w.tw.n_t64;
+    a.tile_max = (float*)tiles;
+    a.act_list = (int32_t*)(tiles + w.tw.table_bytes);
+    a.act_count = (int32_t*)(tiles + w.tw.table_bytes + w.tw.list_bytes);
     // (the last two ints of the counts' region)
-    a.act_range = a.act_count + (tw.count_bytes / sizeof(int32_t) - 2);
+    a.act_range = a.act_count + (w.tw.count_bytes / sizeof(int32_t) - 2);
     a.n_splits_even = std::max(2, ranges.dense);
   }
   constexpr int ks = 8;                                    // waves per 32-query group (see the kernel's header)
@@ -2281,11 +2306,10 @@ extern "C" int32_t rtp_sparse_attn_prefill_tile_stats(const rtp_layer_desc* laye
   if (!ws || ((uintptr_t)ws & 255) || ws_bytes < need)
     return fail(RTP_ERR_WORKSPACE, "%s: the workspace of the rtp_sparse_attn_prefill call (%zu bytes) is required", who, need);
   clear_error();
-  const PrefillTileWs tw = prefill_tile_ws(layer->n_ret, T, chunk_start);
+  const PrefillWs w = prefill_ws(layer->n_ret, T, chunk_start);
   const int n_qt = (T + kPwQ - 1) / kPwQ;
   std::vector<int32_t> counts((size_t)layer->n_ret * n_qt);
-  // the counts are the last region of the workspace
-  const char* at = (const char*)ws + need - tw.count_bytes;
+  const char* at = (const char*)ws + w.front() - w.tw.count_bytes;       // the lists' lengths end the part in front of the scratch
   hipError_t e = hipStreamSynchronize((hipStream_t)stream);
   if (e == hipSuccess) e = hipMemcpy(counts.data(), at, counts.size() * sizeof(int32_t), hipMemcpyDeviceToHost);
   if (e != hipSuccess) return fail(RTP_ERR_HIP, "%s: %s", who, hipGetErrorString(e));

@@ -369,3 +369,16 @@ def test_prefill_tile_statistics_argument_checks():
     L0 = _layer(ret_heads=[])
     rc = lib.rtp_sparse_attn_prefill_tile_stats(C.byref(L0), 300, 3000, None, 0, None, C.byref(vis), C.byref(causal))
     assert rc == rtp.RTP_OK and vis.value == 0 and causal.value == 0
+
+
+@pytest.mark.parametrize("hq,hkv,n_ret,T0,N", [
+    (32, 8, 4, 4096, 32768), (32, 8, 4, 4096, 65536), (32, 8, 4, 4096, 131072), (8, 2, 2, 8192, 65536), (64, 8, 8, 1024, 131072),
+    (64, 8, 8, 2048, 131072), (8, 2, 1, 2048, 4096), (8, 2, 2, 4096, 8192)])
+def test_prefill_workspace_of_a_chunk_covers_shorter_chunks(hq, hkv, n_ret, T0, N):
+    """A prompt of N tokens is prefilled in chunks of T0: one workspace of the size named for a whole chunk that ends at N is
+    enough for every shorter chunk that ends there."""
+    L = _layer(n_q_heads=hq, n_kv_heads=hkv, ret_heads=list(range(n_ret)))
+    need = rtp.rtp_sparse_attn_prefill_workspace_bytes
+    whole = need(L, T0, N - T0)
+    over = [t for t in range(1, T0) if need(L, t, N - t) > whole]
+    assert not over, (len(over), over[:3])

@@ -467,3 +467,63 @@ def test_local_prefill_infinite_value_of_the_last_key(chunk_start, window):
     out = run.out[0, heads].float()
     assert torch.isposinf(out[:, 3]).all()
     assert torch.isfinite(out[:, :3]).all() and torch.isfinite(out[:, 4:]).all()
+
+
+def _launches(call):
+    rtp.rtp_profile_start(64)
+    try:
+        call()
+    finally:
+        recorded = rtp.rtp_profile_stop(64)
+    return [name for name, _ in recorded]
+
+
+@pytest.mark.parametrize("p", [0.9, 1.0])
+def test_short_chunk_in_the_workspace_of_a_whole_chunk(p):
+    """The last 333 queries of a prompt in the workspace that served its chunks of 4096: the same launches as with a workspace of
+    their own, and the same result.  In the least workspace there is the short chunk runs in fewer workgroups: the same selection,
+    outputs that differ by the order of fp32 sums and one rounding to 16 bits."""
+    print(f"[case] short chunk, long chunk's workspace, p {p}", flush=True)
+    w = wl.make_prefill("tail", wl.Layer(32, 8, [0, 8, 16, 24], sink=4, window=256), 131072, 333, p, 181, DEV, cluster_len=32)
+    run = PrefillRun(w)
+    size = lambda T, c: rtp.rtp_sparse_attn_prefill_workspace_bytes(run.desc, T, c)
+    args = (run.desc, w.qI, w.q, None, w.kI, w.N * 16, run.Kp, run.Vp, run.rs, run.hs, w.chunk_start, w.T, p)
+
+    def go(n_bytes):
+        ws = torch.full((n_bytes,), 0xAB, dtype=torch.uint8, device=DEV)
+        o, l = torch.zeros_like(run.out), torch.zeros_like(run.lse)
+        st = (run.tau, run.count, run.mass) if p < 1.0 else (None, None, None)
+        for t in st:
+            if t is not None:
+                t.fill_(-5)
+        names = _launches(lambda: rtp.rtp_sparse_attn_prefill(*args, o, l, *st, ws))
+        torch.cuda.synchronize()
+        return names, o[:, w.layer.ret_heads].float(), l[:, w.layer.ret_heads], [t.clone() for t in st if t is not None]
+
+    one_range = w.layer.n_ret * w.T * 132 * 4
+    if p < 1.0:
+        lo, hi = 0, size(w.T, w.chunk_start) // 256          # the least accepted size, in units of 256 bytes
+        while hi - lo > 1:
+            mid = (lo + hi) // 2
+            try:
+                go(mid * 256)
+                hi = mid
+            except rtp.RtpError as e:
+                assert e.code == rtp.RTP_ERR_WORKSPACE
+                lo = mid
+        least = hi * 256
+        assert least < 7 << 20
+    else:
+        least = 8 * one_range
+    own, whole, small = go(size(w.T, w.chunk_start)), go(size(4096, w.chunk_start - 4096)), go(least)
+    assert own[0] == whole[0] and any("combine" in n for n in own[0])
+    assert sum("select_kernel" in n for n in own[0]) == (5 if p < 1.0 else 0)
+    for names, o, l, st in (whole, small):
+        assert any("combine" in n for n in names)
+        assert ((o - own[1]).abs() <= 2.0 ** -7 * torch.maximum(o.abs(), own[1].abs()) + 1e-5).all()
+        assert (l - own[2]).abs().max() < 1e-4
+        if p < 1.0:
+            assert torch.equal(st[0], own[3][0]) and torch.equal(st[1], own[3][1]) and (st[2] - own[3][2]).abs().max() < 1e-6
+    if p >= 1.0:
+        names, o, l, _ = go(one_range - 256)
+        assert len(names) == 1 and (l - own[2]).abs().max() < 1e-4
