@@ -15,6 +15,7 @@
 // Workgroup = 4 waves = 128 queries of one (sequence, head); key tiles of 64; heads of one KV group
 // are adjacent in the grid so that they meet in L2; late (long) query tiles are scheduled first.
 #include "common.h"
+#include "prefill_scan.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -858,28 +859,10 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
       for (int i = 0; i < kRuns; ++i) Z += rs[i];
     }
     const double target = (double)a.p * Z;
-    cum = above;
-    int run = kRuns - 1;
-    bool found = false;
-#pragma unroll
-    for (int i = 0; i < kRuns - 1; ++i) {
-      found = found || cum + rs[i] >= target;
-      if (!found) cum += rs[i];
-      else run = min(run, i);
-    }
-    hsel = 0.0;
-    bsel = kSelBins - 1;
-    found = false;
-    double h[kRunBins];
-#pragma unroll
-    for (int i = 0; i < kRunBins; ++i) h[i] = hist[run * kRunBins + i][r];
-#pragma unroll
-    for (int i = 0; i < kRunBins; ++i) {
-      if (!found) {
-        if (cum + h[i] >= target) { bsel = run * kRunBins + i; hsel = h[i]; found = true; }
-        else cum += h[i];
-      }
-    }
+    const ThresholdBin t = threshold_bin<kRuns, kRunBins>(above, target, rs, [&](int i) __attribute__((always_inline)) { return hist[i][r]; });
+    bsel = t.bin;
+    cum = t.above;
+    hsel = t.mass;
   };
 
   // ---- sweep 0: the row maxima ----
