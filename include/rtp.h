@@ -114,7 +114,8 @@ const char* rtp_version(void);
  * the score pass also accumulates the first level of the selector's mass histogram while the scores
  * are in registers, and the following rtp_topp_select(..., level1_ready = 1, same workspace, row_len =
  * ctx_len of each row, max_len = max_ctx) skips its first two launches.  With max_ctx <= 8192 the selection is one launch
- * that needs nothing but the scores; the score pass then leaves the workspace as it is.
+ * that needs nothing but the scores; the score pass then leaves the workspace as it is.  (Bounds on either side of 8192 are
+ * sorted out by the selector, which leaves the workspace initialised in any case.)
  */
 int32_t rtp_index_score(const rtp_layer_desc* layer, const void* q_in, const float* WQ,
                         const void* kI, int64_t kI_head_stride,

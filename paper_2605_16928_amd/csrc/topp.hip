@@ -331,7 +331,7 @@ __device__ __forceinline__ void level_body(const TopPArgs& a, const int c, const
   __shared__ uint64_t sh_res[3];
   __shared__ double sh_d[kTpThreads / 64];
   __shared__ double sh_dres[3];
-  __shared__ int sh_i[kTpThreads / 64];
+  __shared__ int sh_i[kTpThreads / 64], sh_n;
   __shared__ double tab[256];
   fill_exp_table(tab);
   uint64_t* hrow = a.hist + (int64_t)r * a.hist_stride;
@@ -381,6 +381,26 @@ __device__ __forceinline__ void level_body(const TopPArgs& a, const int c, const
       }
       s.flags = flags;
     } else if (flags == 0) {
+      if (__builtin_expect(a.rezero && n <= kTpChunk, 0)) {
+        // A score pass that was given a bound of at most kTpChunk scores leaves no level 1 (topp_common.h), and the bound
+        // given here may be a larger one all the same: rows that short lie in this workgroup as a whole.
+        uint64_t some = 0;
+#pragma unroll
+        for (int i = 0; i < kBins1 / kTpThreads; ++i) some |= prev_bins[i];
+        if (tid == 0) sh_n = 0;
+        __syncthreads();
+        if (some) sh_n = 1;
+        __syncthreads();
+        if (__builtin_expect(sh_n == 0, 0)) {
+          for (int i = tid; i < kBins; i += kTpThreads) lh[i] = 0;
+          __syncthreads();
+          const float* row = a.scores + (int64_t)r * a.score_stride;
+#pragma unroll 1
+          for (int i = tid; i < n; i += kTpThreads) level1_add(lh, row[i], shift, tab);
+          __syncthreads();
+          load_bins<kBins1>(lh, prev_bins);
+        }
+      }
       const Scan1Result s1 = scan_level1(prev_bins, pr, sh_d, sh_i, sh_dres, tab);
       if (s1.bin < 0) {
         flags = 2;
@@ -440,7 +460,6 @@ __device__ __forceinline__ void level_body(const TopPArgs& a, const int c, const
   // into an LDS list (order is irrelevant: integer masses) and then weighed densely.  At level 3 almost
   // every slot is empty and skipped as it is; packing costs more than it saves there.
   __shared__ float sh_list[LEVEL == 2 ? kTpChunk : 1];
-  __shared__ int sh_n;
   static_assert(kTpVec * 4 <= 32, "member mask is one 32-bit word");
   for (int i = tid; i < kBins; i += kTpThreads) lh[i] = 0;
   if (tid == 0) sh_n = 0;
@@ -1115,7 +1134,7 @@ __global__ __launch_bounds__(kTpThreads) void topp_row_kernel(const TopPArgs a, 
   // ---- level 1 ----
   uint32_t prefix = 0;
   float ref = 0.f;
-  uint64_t target = 1;
+  uint64_t target = 1, left_there = 0;
   double above_base = 0.0, total_d = 1.0;
   if (flags == 0) {
 #pragma unroll
@@ -1139,6 +1158,9 @@ __global__ __launch_bounds__(kTpThreads) void topp_row_kernel(const TopPArgs a, 
       if (s1.bin < 0) flags = 2;
       else if (level1_bin_is_wide(s1.top)) flags = -2;
       else { prefix = (uint32_t)s1.bin; ref = s1.ref; target = s1.target; above_base = s1.above_base; total_d = s1.total_d; }
+      // A score pass that was given a bound of more than kTpChunk scores has left a level 1 that nothing here needs but the
+      // workspace must not keep.  The bin of the row's largest score tells, in whichever copy it is (looked at on the way out).
+      if (a.rezero && copy == 0 && tid < a.n_sub && s1.bin >= 0) left_there = a.hist[(int64_t)r * a.hist_stride + level1_copy_offset(tid) + s1.top];
     }
   }
   float res_tau = ninf, res_mass = 1.f;
@@ -1221,6 +1243,11 @@ __global__ __launch_bounds__(kTpThreads) void topp_row_kernel(const TopPArgs a, 
     }
     int32_t* dst = a.sel_idx + (int64_t)r * a.sel_stride;
     for (int i = k_lo + tid; i < k_hi; i += kTpThreads) dst[i] = sh_list[i];
+  }
+  if (a.rezero && copy == 0 && (flags != 0 || __ballot(left_there != 0) != 0ull)) {     // (flags == 0: the first wave alone)
+    uint64_t* h = a.hist + (int64_t)r * a.hist_stride;
+    for (int sub = 0; sub < a.n_sub; ++sub)
+      for (int i = tid; i < kBins1; i += flags != 0 ? kTpThreads : 64) h[level1_copy_offset(sub) + i] = 0;
   }
   if (copy == 0 && tid == 0) {
     a.sel_count[r] = (flags < 0 && n > 0) ? flags : kept;

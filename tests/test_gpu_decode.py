@@ -7,7 +7,7 @@ import torch
 from oracle import rtp_oracle as orc
 from paper_2605_16928_amd import rtp, workloads as wl
 from gpu_util import (DEV, DecodeRun, oracle_inputs, check_scores, check_selection, check_selection_valid, check_out,
-                      check_layer, attend_reference, i32)
+                      check_layer, attend_reference, i32, ws_alloc)
 
 pytestmark = pytest.mark.gpu
 
@@ -662,3 +662,32 @@ def test_gather_shared_by_several_workgroups(ctx, clustered):
     a, b = run.out[:, L.ret_heads].float(), two.out[:, L.ret_heads].float()
     assert ((a - b).abs() <= 2.0 ** -7 * torch.maximum(a.abs(), b.abs()) + 1e-5).all()
     assert (run.lse[:, L.ret_heads] - two.lse[:, L.ret_heads]).abs().max() < 1e-4
+
+
+@pytest.mark.parametrize("score_bound,select_bound", [(5000, 20000), (20000, 5000)])
+@pytest.mark.parametrize("R", [2, 20])
+def test_level1_with_bounds_on_either_side_of_one_chunk(score_bound, select_bound, R):
+    """The bound handed to the score pass and the selector's differ, one of them at most 8192: rows of one chunk are selected all
+    the same, and the workspace of the first step serves the steps behind it, whichever bound they name."""
+    print(f"[case] score pass bound {score_bound}, selector bound {select_bound}, {R} rows", flush=True)
+    w = wl.small_decode("cpu", seed=231 + R, ctx=(5000, 4097, 300, 1, 2049, 4999, 777, 5000, 64, 4000)[:R // 2], p=(0.9,), ret_heads=(0, 5)).to(DEV)
+    ref = DecodeRun(w, fuse_level1=False)
+    ref.index_score()
+    ref.topp()
+    run = DecodeRun(w)
+    run.stride = 20000
+    run.scores = torch.full((run.R, run.stride), float("nan"), device=DEV)
+    run.sel_idx = torch.full((run.R, run.stride), -7, dtype=torch.int32, device=DEV)
+    run.ws_topp = ws_alloc(rtp.rtp_topp_workspace_bytes(run.R, 20000))
+    rtp.rtp_topp_workspace_init(run.ws_topp)
+    for a, b in ((score_bound, select_bound), (20000, 20000), (score_bound, select_bound), (score_bound, score_bound)):
+        run.sel_count.fill_(-7)
+        run.max_ctx = a
+        run.index_score()
+        run.max_ctx = b
+        run.topp()
+        torch.cuda.synchronize()
+        assert torch.equal(run.sel_count, ref.sel_count) and torch.equal(run.tau, ref.tau) and torch.equal(run.mass, ref.mass), (a, b)
+        for r in range(run.R):
+            n = int(run.sel_count[r])
+            assert n > 0 and torch.equal(run.sel_idx[r, :n], ref.sel_idx[r, :n]), (a, b, r)
