@@ -91,7 +91,7 @@ __device__ __forceinline__ int listed_splits(const PrefillArgs& a) {
   return (2 * shortest >= longest) ? min(a.n_splits_even, a.n_splits) : a.n_splits;
 }
 
-enum { kModeDense = 0, kModeLocal = 1, kModeSparse = 2 };
+enum { kModeDense = 0, kModeSparse = 1 };
 // Per-query threshold search of the sparse mode: a score s is mapped to the integer
 // q = floor((M - s) * 2^17) (M = row maximum; q clamps at 2^21 - 1, i.e. 16 below the maximum) and
 // the threshold is the smallest q whose cumulative mass from q = 0 reaches p * Z, found digit by
@@ -445,7 +445,8 @@ __device__ __forceinline__ float sel_first_below(float M, float index_scale, flo
 // group's keys: STEP = 0 .. 3 are the sweeps -- a launch first merges what the slices of the launch before left
 // (maxima, histograms: plain stores and sums in slice order, no atomics) and repeats the scan in every slice -- and
 // kSelFinish scans the last histogram; the kernel boundaries are the only synchronisation.  Every sum has the same
-// terms as in one workgroup, in fp64.  0.88 -> 0.20 ms there.
+// terms as in one workgroup, in fp64.  0.88 -> 0.20 ms there.  (A group with a query whose threshold lies in the open-ended
+// bin, see below, leaves that form: its sweeps 0 and 1 are thrown away and one workgroup of the last launch searches it as a whole.)
 //
 // A threshold inside the open-ended last coarse bin (candidates 15.875 or more below the row maximum) is not
 // taken as "keep everything": the workgroup repeats sweep 1 with the reference lowered by 15.875 for the queries
@@ -1079,7 +1080,8 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
 // repeats its keys with the classical running-maximum recurrence (exact_pass).  Real score rows
 // have their maximum at the first tokens; the repeat exists for correctness, not for speed.
 // K/V tiles rotate through three LDS buffers (the PV of a tile's last block reads its V^T while the
-// next tile is current), two workgroup barriers per 64-key tile.
+// next tile is current).  One workgroup barrier per 64-key tile, in its middle: it publishes tile it + 1, whose loads every
+// wave has waited for, and behind it every wave is done with tile it - 1, whose buffer the loads of tile it + 2 fill.
 //
 // Tiles that every query of the workgroup sees in full -- all but the first and the four or five on the diagonal --
 // run in a loop without a branch (steady, below), the others block by block with element masks and nothing
@@ -1110,7 +1112,6 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
   constexpr int NW = 8 / QB;                 // waves per workgroup; each owns QB blocks of 32 queries
   constexpr int RG = 4 * NW;                 // tile rows one load instruction of the whole workgroup covers
   constexpr int GH = 64 / RG;                // such loads per wave for the K rows of a tile (and as many for V)
-  constexpr bool LOCAL = MODE == kModeLocal;
   constexpr bool SPARSE = MODE == kModeSparse;
   __shared__ __attribute__((aligned(16))) unsigned char smem[kSmemWide];
   unsigned char* const Ls = smem;       // stage s: K rows at Ls + s * kPwTileBytes, V rows 16 KiB further
@@ -1123,7 +1124,7 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
   // The grid of such a launch is sized for the finer cut; the ranges really used (listed_splits) take the
   // first workgroups of the grid in the same (key range, query tile, head slot) order, the others leave.
   constexpr bool listed = SPARSE;
-  const int n_parts = LOCAL ? 1 : (listed ? listed_splits(a) : a.n_splits), n_sub = LOCAL ? 1 : a.n_sub;
+  const int n_parts = listed ? listed_splits(a) : a.n_splits, n_sub = a.n_sub;
   const int n_splits = n_parts * n_sub;
   int hslot = blockIdx.x, split, qt_rev = blockIdx.y, b = 0;
   if (listed) {
@@ -1163,17 +1164,11 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
   const int m_lo = pos0 + t0;
   const int m_hi = pos0 + min(t0 + kPwQ, a.n_q) - 1;
   const int kt_end = m_hi / kPfK;                       // inclusive
-  int kt_w0 = 0, ks_end = 0;
-  if (LOCAL) {
-    const int lo = max(a.sink, m_lo - a.window + 1);
-    kt_w0 = lo / kPfK;
-    ks_end = min((a.sink + kPfK - 1) / kPfK, kt_w0);    // sink tiles not already inside the band
-  }
   // selecting mode with a threshold search in front: only the tiles on this query tile's list (ascending
   // 64-key tile numbers, written by prefill_active_tiles_kernel) can hold a kept pair
   const int qt_list = (int)gridDim.y - 1 - qt_rev;
   const int32_t* const alist = listed ? a.act_list + ((int64_t)hslot * gridDim.y + qt_list) * a.n_t64 : nullptr;
-  const int n_tiles = listed ? a.act_count[(int64_t)hslot * gridDim.y + qt_list] : ks_end + (kt_end - kt_w0 + 1);
+  const int n_tiles = listed ? a.act_count[(int64_t)hslot * gridDim.y + qt_list] : kt_end + 1;
   const uint16_t* Kg = a.K + (int64_t)kvh * a.head_stride + tok0 * a.row_stride;
   const uint16_t* Vg = a.V + (int64_t)kvh * a.head_stride + tok0 * a.row_stride;
 
@@ -1307,7 +1302,7 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
   // The same MFMAs with their K operands read kAheadK steps ahead and a slice of other work (issuing the loads of a
   // later tile) between every pair; scheduling fences keep the order.  In the steady loop the first operands were
   // read during the stream before (ka_first; likewise va_first for the PV stream): with every wave of the workgroup at
-  // the same place (two barriers per tile) nothing else covers their LDS latency.
+  // the same place (the barrier in every tile) nothing else covers their LDS latency.
   constexpr int kAheadK = 5, kAheadV = 4;
   u32x4 ka_first[kAheadK];
   s16x8 va_first[kAheadV];
@@ -1354,20 +1349,16 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
     }
   };
   // per-element visibility without control flow: key nb0 + off, off = (i / 4) * 8 + g * 4 + i % 4, is
-  // visible iff off <= hi and (LOCAL) off > lo or off < sk, three per-lane bounds
+  // visible iff off <= hi, a per-lane bound
   auto mask_block = [&](f32x16 (&S)[QB], int nb0) __attribute__((always_inline)) {
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
       const int base = nb0 + g * 4;
       const int hi = qok[qb] ? mq[qb] - base : -1;
-      const int lo = mq[qb] - a.window - base;
-      const int sk = a.sink - base;
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const int off = (i >> 2) * 8 + (i & 3);
-        bool ok = off <= hi;
-        if (LOCAL) ok = ok & ((off > lo) | (off < sk));
-        S[qb][i] = ok ? S[qb][i] : ninf;
+        S[qb][i] = off <= hi ? S[qb][i] : ninf;
       }
     }
   };
@@ -1473,20 +1464,17 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
     for (int qb = 0; qb < QB; ++qb) {
       const int m_b_lo = m_w_lo + qb * 32;
       const int m_b_hi = min(m_b_lo + 31, q_last);
-      e = e || (m_b_hi < m_b_lo) || (nb0 + 31 > m_b_lo) || (LOCAL && !(nb0 > m_b_hi - a.window || nb0 + 31 < a.sink));
+      e = e || (m_b_hi < m_b_lo) || (nb0 + 31 > m_b_lo);
     }
     return e;
   };
   // can some query of this wave see a key of the block at all?
   auto is_active = [&](int nb0) __attribute__((always_inline)) {
-    if (m_w_hi < m_w_lo || nb0 > m_w_hi) return false;
-    if (LOCAL && nb0 >= a.sink && nb0 + 31 <= m_w_lo - a.window) return false;
-    return true;
+    return !(m_w_hi < m_w_lo || nb0 > m_w_hi);
   };
 
   auto tile_n0 = [&](int it) __attribute__((always_inline)) {
-    if (listed) return alist[it] * kPfK;
-    return (it < ks_end ? it : kt_w0 + (it - ks_end)) * kPfK;
+    return (listed ? alist[it] : it) * kPfK;
   };
   const int p_lo = (int)((int64_t)n_tiles * (split / n_sub) / n_parts), p_hi = (int)((int64_t)n_tiles * (split / n_sub + 1) / n_parts);
   const int sub = split % n_sub;
@@ -1597,7 +1585,7 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
     // before was visible as well, so every wave with queries has probabilities pending; a wave without queries only
     // fetches its share of the tiles.
     auto steady = [&]() __attribute__((always_inline)) { return it < it_hi && n_t0 + kPfK - 1 <= m_lo && n_t2 + kPfK - 1 <= m_hi; };
-    if (!LOCAL && steady()) {
+    if (steady()) {
       if (m_w_hi >= m_w_lo) {
         first_v(tile_at(it - 1), 1);
         do {
@@ -1641,7 +1629,7 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
       const float ltot = lrow[qb] + __shfl_xor(lrow[qb], 32);
       // selecting mode: a query that kept no key of this range legitimately sums to zero
       const bool sees_key = SPARSE ? (sel_cnt[qb] + __shfl_xor(sel_cnt[qb], 32) > 0)
-                                   : (qok[qb] && (LOCAL || tile_n0(it_lo) <= mq[qb]));
+                                   : (qok[qb] && tile_n0(it_lo) <= mq[qb]);
       // (fp16 probabilities: nothing above 65504 -- a larger one is infinite and shows in the sum -- and a
       // row whose largest probability is below 2^-6 has most of its mass in subnormals or flushed to zero)
       bad = bad || (sees_key && !(ltot > (F16 ? 0x1p-6f : 0x1p-60f) && ltot < 0x1p100f));
@@ -2059,8 +2047,8 @@ static int search_slices(int n_ret, int32_t T, int64_t chunk_start, size_t room)
 }
 
 // Sizes of the tile bookkeeping of a selecting launch.  A table row has one entry per 64 keys of the context, plus
-// the entries the threshold search touches past a group's last tile (its sweeps run in whole rounds of 8 tiles of
-// 32 keys and read the table one round ahead).
+// the entries the threshold search touches past a group's last tile (its sweeps run in whole rounds of kSelRing tiles of
+// 32 keys and read the table one round ahead: four entries at most, sixteen are there).
 struct PrefillTileWs {
   int32_t n_t64;
   size_t table_bytes, list_bytes, count_bytes;
