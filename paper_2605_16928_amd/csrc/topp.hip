@@ -398,7 +398,10 @@ __device__ __forceinline__ void level_body(const TopPArgs& a, const int c, const
 #pragma unroll 1
           for (int i = tid; i < n; i += kTpThreads) level1_add(lh, row[i], shift, tab);
           __syncthreads();
-          load_bins<kBins1>(lh, prev_bins);
+          // (through memory: with a second source in LDS the compiler splits the loads of every other row's bins)
+          for (int i = tid; i < kBins1; i += kTpThreads) hrow[i] = lh[i];
+          __syncthreads();
+          load_bins<kBins1>(hrow, prev_bins);
         }
       }
       const Scan1Result s1 = scan_level1(prev_bins, pr, sh_d, sh_i, sh_dres, tab);
