@@ -1056,19 +1056,16 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
 }
 
 // ---- the wide kernel: dense and selecting modes ------------------------------------------------------
-// Same data flow as above for a workgroup of 256 queries whose waves share every staged K/V tile, in
-// one of two shapes (QB = 32-query column blocks per wave):
-//   QB = 1 (default): eight waves of 32 queries, two per SIMD, at most 256 registers each;
-//   QB = 2: four waves of 64 queries, one per SIMD.  Every A operand read from LDS (a K row block, a
-//           V^T row block) feeds two MFMAs, which halves the LDS operand traffic per flop; the price is
-//           registers (2 x 64 output accumulators, 64 for the two Q operand sets).
-// Measured on the chip: a lone wave on a SIMD issues an independent 32x32x16 MFMA every 38 cycles and
-// a vector instruction every ~6, two waves reach the pipes' 32 and 4; in this kernel's own address
-// patterns eight waves read K rows from LDS at ~250 bytes per clock and V^T (the transposing read) at
-// ~96, four waves at ~160 and ~63 -- enough for either shape, so the second instruction stream wins:
-// QB = 1 is 3 to 16 % faster than QB = 2 at every depth of the 131072- and 1048576-token configurations.
+// Same data flow as above for a workgroup of 256 queries whose eight waves of 32, two per SIMD at at most 256 registers
+// each, share every staged K/V tile.  (Built and measured as four waves of 64 queries, one per SIMD, too: every A operand
+// read from LDS -- a K row block, a V^T row block -- then feeds two MFMAs, which halves the LDS operand traffic per flop, at the
+// price of registers, 2 x 64 output accumulators and 64 for the two Q operand sets.  A lone wave on a SIMD issues an
+// independent 32x32x16 MFMA every 38 cycles and a vector instruction every ~6, two waves reach the pipes' 32 and 4; in this
+// kernel's own address patterns eight waves read K rows from LDS at ~250 bytes per clock and V^T (the transposing read) at
+// ~96, four waves at ~160 and ~63 -- enough for either shape, so the second instruction stream wins: eight waves were 3 to
+// 16 % faster at every depth of the 131072- and 1048576-token configurations.)
 //
-// Nothing hides latency by itself at one or two waves per SIMD, so the loop is software-pipelined over
+// Nothing hides latency by itself at two waves per SIMD, so the loop is software-pipelined over
 // 32-key blocks: while the softmax of block i runs on the vector ALU, the matrix pipe executes the PV
 // MFMAs of block i-1; the two are independent instruction streams inside one basic block and are
 // interleaved with scheduling-group hints.  For that the accumulators must never be touched by the
@@ -1090,9 +1087,11 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
 // the next one's first operands.  Attention launch of 4 heads x 4096 queries at 128K tokens: 1300 -> 1090 us selecting,
 // 1250 -> 970 us dense (1.14 PFLOP/s); last 8192-query chunk of 1M tokens, selecting: 20.3 -> 17.6 ms (operands three
 // and two steps ahead instead of five and four: 17.7 and 1141 us).  What bounds it now is the sum of what the
-// two waves of a SIMD issue -- 16 MFMAs of 32 cycles and about 110 vector, LDS and scalar instructions per 32 x 32
-// block -- and the transposing V reads, which keep the LDS busy for two thirds of that time.
+// two waves of a SIMD issue -- per 32 x 32 block 16 MFMAs of 32 cycles, 24 LDS reads and, by the counters, 64 (dense) or 122
+// (selecting) other vector instructions --, with the matrix pipe busy 59 and 48 % of the cycles and the LDS, at the rates
+// of these reads, about half of them.
 constexpr int kPwQ = 256;
+constexpr int kPwThreads = 512;
 constexpr int kPwStages = 3;
 // One staged tile: 64 K rows then 64 V rows, 256 bytes each, no padding -- the tiles are written by
 // direct global->LDS loads (16 bytes per lane, a wave's 64 lanes fill 1 KiB contiguously), so bank
@@ -1107,9 +1106,9 @@ constexpr int kPwTileBytes = 2 * kPfK * kHeadDim * 2;
 constexpr int kSmemWide = kPwTileBytes * kPwStages;
 
 
-template <int MODE, int QB, bool F16 = false>
-__global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_wide_kernel(const PrefillArgs a) {
-  constexpr int NW = 8 / QB;                 // waves per workgroup; each owns QB blocks of 32 queries
+template <int MODE, bool F16 = false>
+__global__ __launch_bounds__(kPwThreads, 2) void flash_prefill_wide_kernel(const PrefillArgs a) {
+  constexpr int NW = kPwThreads / 64;        // waves per workgroup; each owns 32 queries
   constexpr int RG = 4 * NW;                 // tile rows one load instruction of the whole workgroup covers
   constexpr int GH = 64 / RG;                // such loads per wave for the K rows of a tile (and as many for V)
   constexpr bool SPARSE = MODE == kModeSparse;
@@ -1144,21 +1143,15 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
   const int64_t tok0 = a.seq_start ? a.seq_start[b] : 0;
   const float ninf = -__builtin_huge_valf();
 
-  // ---- this lane's queries (column r of each of the wave's QB blocks) ----
-  int tq[QB], mq[QB];
-  bool qok[QB];
-  int64_t qrow[QB];
-  u32x4 qreg[QB][8];
+  // ---- this lane's query (column r of the wave's 32) ----
+  const int tq = t0 + wave * 32 + r;
+  const bool qok = tq < a.n_q;
+  const int mq = pos0 + tq;
+  const int64_t qrow = (((int64_t)b * a.n_q + tq) * a.n_q_heads + h) * kHeadDim;
+  u32x4 qreg[8];
 #pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    tq[qb] = t0 + wave * (32 * QB) + qb * 32 + r;
-    qok[qb] = tq[qb] < a.n_q;
-    mq[qb] = pos0 + tq[qb];
-    qrow[qb] = (((int64_t)b * a.n_q + tq[qb]) * a.n_q_heads + h) * kHeadDim;
-#pragma unroll
-    for (int kk = 0; kk < 8; ++kk)
-      qreg[qb][kk] = qok[qb] ? *reinterpret_cast<const u32x4*>(a.q + qrow[qb] + kk * 16 + g * 8) : (u32x4){0u, 0u, 0u, 0u};
-  }
+  for (int kk = 0; kk < 8; ++kk)
+    qreg[kk] = qok ? *reinterpret_cast<const u32x4*>(a.q + qrow + kk * 16 + g * 8) : (u32x4){0u, 0u, 0u, 0u};
 
   // ---- key tiles this workgroup needs ----
   const int m_lo = pos0 + t0;
@@ -1172,36 +1165,27 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
   const uint16_t* Kg = a.K + (int64_t)kvh * a.head_stride + tok0 * a.row_stride;
   const uint16_t* Vg = a.V + (int64_t)kvh * a.head_stride + tok0 * a.row_stride;
 
-  f32x16 O[QB][4];
-  float mrow[QB], lrow[QB];
+  f32x16 O[4];
+  float mrow = ninf, lrow = 0.f;
   const float c = a.scale_log2;
   const int q_last = pos0 + a.n_q - 1;
-  const int m_w_lo = pos0 + t0 + wave * (32 * QB);             // the wave's first query position
-  const int m_w_hi = min(m_w_lo + 32 * QB - 1, q_last);          // and its last (< m_w_lo: the wave has no queries)
+  const int m_w_lo = pos0 + t0 + wave * 32;                      // the wave's first query position
+  const int m_w_hi = min(m_w_lo + 31, q_last);          // and its last (< m_w_lo: the wave has no queries)
 
   // ---- selecting mode: a key is kept by a query iff the raw index product reaches the query's
   // threshold (found by prefill_select_kernel; -inf keeps every candidate).  The index-score block of
   // 32 keys x 32 queries is one MFMA (K = 16) in the layout of the attention scores. ----
-  u32x4 qIreg[QB];
-  float selThr[QB];
-  int sel_cnt[QB];
-#pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    qIreg[qb] = (u32x4){0u, 0u, 0u, 0u};
-    selThr[qb] = ninf;
-    sel_cnt[qb] = 0;
-  }
+  u32x4 qIreg = (u32x4){0u, 0u, 0u, 0u};
+  float selThr = ninf;
+  int sel_cnt = 0;
   const uint16_t* kIg = nullptr;
   const int n_rows = pos0 + a.n_q;                      // index-key rows that exist
   if (SPARSE) {
     const int j = hslot;
     kIg = a.kI + (int64_t)j * a.kI_head_stride;
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      if (qok[qb]) {
-        qIreg[qb] = *reinterpret_cast<const u32x4*>(a.qI + ((int64_t)j * a.n_q + tq[qb]) * kIndexDim + g * 8);
-        selThr[qb] = a.sel_thr[(int64_t)j * a.n_q + tq[qb]];
-      }
+    if (qok) {
+      qIreg = *reinterpret_cast<const u32x4*>(a.qI + ((int64_t)j * a.n_q + tq) * kIndexDim + g * 8);
+      selThr = a.sel_thr[(int64_t)j * a.n_q + tq];
     }
   }
   // index keys of the 32-key block at nb0 (rows past the chunk repeat the last one: causally masked anyway)
@@ -1211,19 +1195,16 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
   };
   // drops the keys a query does not keep from its scores and counts the kept ones; run AFTER mask_block
   // (causality shows as -inf there)
-  auto select_block = [&](f32x16 (&S)[QB], const u32x4 ki) __attribute__((always_inline)) {
+  auto select_block = [&](f32x16& S, const u32x4 ki) __attribute__((always_inline)) {
+    f32x16 SI;
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      f32x16 SI;
+    for (int i = 0; i < 16; ++i) SI[i] = 0.f;
+    SI = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ki), __builtin_bit_cast(bf16x8, qIreg), SI, 0, 0, 0);
 #pragma unroll
-      for (int i = 0; i < 16; ++i) SI[i] = 0.f;
-      SI = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ki), __builtin_bit_cast(bf16x8, qIreg[qb]), SI, 0, 0, 0);
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const bool keep = SI[i] >= selThr[qb] && S[qb][i] != ninf;
-        sel_cnt[qb] += keep ? 1 : 0;
-        S[qb][i] = keep ? S[qb][i] : ninf;
-      }
+    for (int i = 0; i < 16; ++i) {
+      const bool keep = SI[i] >= selThr && S[i] != ninf;
+      sel_cnt += keep ? 1 : 0;
+      S[i] = keep ? S[i] : ninf;
     }
   };
 
@@ -1287,16 +1268,13 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
 
   // ---- MFMA streams ----
   // scores of key block kb of the staged tile, for the wave's query blocks
-  auto mfma_S = [&](const unsigned char* tile, int kb, f32x16 (&S)[QB]) __attribute__((always_inline)) {
+  auto mfma_S = [&](const unsigned char* tile, int kb, f32x16& S) __attribute__((always_inline)) {
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) S[qb][i] = 0.f;
+    for (int i = 0; i < 16; ++i) S[i] = 0.f;
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) {
       const u32x4 ka = read_k(tile, kb, kk);
-#pragma unroll
-      for (int qb = 0; qb < QB; ++qb) S[qb] = mfma32<F16>(ka, qreg[qb][kk], S[qb]);
+      S = mfma32<F16>(ka, qreg[kk], S);
     }
   };
   // The same MFMAs with their K operands read kAheadK steps ahead and a slice of other work (issuing the loads of a
@@ -1314,52 +1292,41 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
 #pragma unroll
     for (int k = 0; k < kAheadV; ++k) va_first[k] = read_v(tile, kb, k >> 2, k & 3);
   };
-  auto scores_beside = [&](const unsigned char* tile, int kb, f32x16 (&S)[QB], auto&& work) __attribute__((always_inline)) {
+  auto scores_beside = [&](const unsigned char* tile, int kb, f32x16& S, auto&& work) __attribute__((always_inline)) {
     u32x4 ka[8];
 #pragma unroll
     for (int kk = 0; kk < kAheadK; ++kk) ka[kk] = ka_first[kk];
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) S[qb][i] = 0.f;
+    for (int i = 0; i < 16; ++i) S[i] = 0.f;
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) {
       if (kk + kAheadK < 8) ka[kk + kAheadK] = read_k(tile, kb, kk + kAheadK);
-#pragma unroll
-      for (int qb = 0; qb < QB; ++qb) {
-        S[qb] = mfma32<F16>(ka[kk], qreg[qb][kk], S[qb]);
-        if (qb == 0) work(kk);
-        __builtin_amdgcn_sched_barrier(0);
-      }
+      S = mfma32<F16>(ka[kk], qreg[kk], S);
+      work(kk);
+      __builtin_amdgcn_sched_barrier(0);
     }
   };
   // O^T += V^T P^T for key block kb of the staged tile
-  auto mfma_PV = [&](const unsigned char* tile, int kb, const uint32_t (&P)[QB][8]) __attribute__((always_inline)) {
+  auto mfma_PV = [&](const unsigned char* tile, int kb, const uint32_t (&P)[8]) __attribute__((always_inline)) {
 #pragma unroll
     for (int tt = 0; tt < 2; ++tt) {
 #pragma unroll
       for (int db = 0; db < 4; ++db) {
         const u32x4 va = __builtin_bit_cast(u32x4, read_v(tile, kb, tt, db));
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
-          const u32x4 pb = (u32x4){P[qb][4 * tt], P[qb][4 * tt + 1], P[qb][4 * tt + 2], P[qb][4 * tt + 3]};
-          O[qb][db] = mfma32<F16>(va, pb, O[qb][db]);
-        }
+        const u32x4 pb = (u32x4){P[4 * tt], P[4 * tt + 1], P[4 * tt + 2], P[4 * tt + 3]};
+        O[db] = mfma32<F16>(va, pb, O[db]);
       }
     }
   };
   // per-element visibility without control flow: key nb0 + off, off = (i / 4) * 8 + g * 4 + i % 4, is
   // visible iff off <= hi, a per-lane bound
-  auto mask_block = [&](f32x16 (&S)[QB], int nb0) __attribute__((always_inline)) {
+  auto mask_block = [&](f32x16& S, int nb0) __attribute__((always_inline)) {
+    const int base = nb0 + g * 4;
+    const int hi = qok ? mq - base : -1;
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      const int base = nb0 + g * 4;
-      const int hi = qok[qb] ? mq[qb] - base : -1;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int off = (i >> 2) * 8 + (i & 3);
-        S[qb][i] = off <= hi ? S[qb][i] : ninf;
-      }
+    for (int i = 0; i < 16; ++i) {
+      const int off = (i >> 2) * 8 + (i & 3);
+      S[i] = off <= hi ? S[i] : ninf;
     }
   };
   // l += both halves of a packed pair of probabilities, i.e. the values as rounded to bf16 (what the PV
@@ -1377,26 +1344,23 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
   // probabilities against the fixed reference; masked scores are -inf and give exactly 0.  Summed as rounded to 16 bits where
   // the steady loop could have run the block, unrounded where it could not: rows of few tokens live in such blocks, and their
   // log-sum would carry the rounding (chunk of 172 tokens at position 0: 2.2e-4 instead of 1.2e-4 off).
-  auto softmax_fixed = [&](const f32x16 (&S)[QB], uint32_t (&P)[QB][8], const bool rounded) __attribute__((always_inline)) {
+  auto softmax_fixed = [&](const f32x16& S, uint32_t (&P)[8], const bool rounded) __attribute__((always_inline)) {
+    const float mc = mrow * c;
+    float lsum = 0.f;
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      const float mc = mrow[qb] * c;
-      float lsum = 0.f;
-#pragma unroll
-      for (int i = 0; i < 16; i += 2) {
-        const float p0 = fast_exp2(fmaf(S[qb][i], c, -mc));
-        const float p1 = fast_exp2(fmaf(S[qb][i + 1], c, -mc));
-        lsum += p0 + p1;
-        P[qb][i >> 1] = pack16<F16>(p0, p1);
-      }
-      if (rounded) {                                       // (the same for the whole wave)
-        lsum = 0.f;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) row_sum_add(lsum, P[qb][i]);
-        row_sum_settled(lsum);
-      }
-      lrow[qb] += lsum;
+    for (int i = 0; i < 16; i += 2) {
+      const float p0 = fast_exp2(fmaf(S[i], c, -mc));
+      const float p1 = fast_exp2(fmaf(S[i + 1], c, -mc));
+      lsum += p0 + p1;
+      P[i >> 1] = pack16<F16>(p0, p1);
     }
+    if (rounded) {                                       // (the same for the whole wave)
+      lsum = 0.f;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) row_sum_add(lsum, P[i]);
+      row_sum_settled(lsum);
+    }
+    lrow += lsum;
   };
   // The steady-state step: the PV MFMAs of the previous block and the softmax of the current block as
   // ONE hand-interleaved instruction sequence -- per MFMA (32 cycles of the matrix pipe) one pair of
@@ -1405,22 +1369,17 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
   // and, at its end, the first K operands of the score MFMAs that follow (block next_kb of next_tile).  SEL (the
   // selecting mode): the block's index-score MFMAs in front and every probability gated by its query's keep test
   // (one compare, one select, one add for the count per probability).
-  auto pv_beside_softmax = [&](auto sel_tag, const unsigned char* tile, int kb, const uint32_t (&Pin)[QB][8], const f32x16 (&S)[QB],
-                               uint32_t (&Pout)[QB][8], const u32x4 ki, const unsigned char* next_tile, int next_kb) __attribute__((always_inline)) {
+  auto pv_beside_softmax = [&](auto sel_tag, const unsigned char* tile, int kb, const uint32_t (&Pin)[8], const f32x16& S,
+                               uint32_t (&Pout)[8], const u32x4 ki, const unsigned char* next_tile, int next_kb) __attribute__((always_inline)) {
     constexpr bool SEL = decltype(sel_tag)::value;
-    f32x16 SI[QB];
-    float mc[QB], l[QB];
-    int cnt[QB];
+    f32x16 SI;
+    const float mc = mrow * c;
+    float l = 0.f;
+    int cnt = 0;
+    if (SEL) {
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      mc[qb] = mrow[qb] * c;
-      l[qb] = 0.f;
-      cnt[qb] = 0;
-      if (SEL) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) SI[qb][i] = 0.f;
-        SI[qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ki), __builtin_bit_cast(bf16x8, qIreg[qb]), SI[qb], 0, 0, 0);
-      }
+      for (int i = 0; i < 16; ++i) SI[i] = 0.f;
+      SI = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ki), __builtin_bit_cast(bf16x8, qIreg), SI, 0, 0, 0);
     }
     s16x8 va[8];
     auto read_va = [&](int k) __attribute__((always_inline)) { va[k] = read_v(tile, kb, k >> 2, k & 3); };   // k = tt * 4 + db
@@ -1431,42 +1390,29 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
       const int tt = k >> 2, db = k & 3;
       if (k + kAheadV < 8) read_va(k + kAheadV);
       if (k == 8 - kAheadV) first_k(next_tile, next_kb);
-#pragma unroll
-      for (int qb = 0; qb < QB; ++qb) {
-        const u32x4 pb = (u32x4){Pin[qb][4 * tt], Pin[qb][4 * tt + 1], Pin[qb][4 * tt + 2], Pin[qb][4 * tt + 3]};
-        O[qb][db] = mfma32<F16>(__builtin_bit_cast(u32x4, va[k]), pb, O[qb][db]);
-        {
-          float p0 = fast_exp2(fmaf(S[qb][2 * k], c, -mc[qb]));
-          float p1 = fast_exp2(fmaf(S[qb][2 * k + 1], c, -mc[qb]));
-          if (SEL) {
-            const bool k0 = SI[qb][2 * k] >= selThr[qb], k1 = SI[qb][2 * k + 1] >= selThr[qb];
-            p0 = k0 ? p0 : 0.f;
-            p1 = k1 ? p1 : 0.f;
-            cnt[qb] += (k0 ? 1 : 0) + (k1 ? 1 : 0);
-          }
-          Pout[qb][k] = pack16<F16>(p0, p1);
-          row_sum_add(l[qb], Pout[qb][k]);
+      const u32x4 pb = (u32x4){Pin[4 * tt], Pin[4 * tt + 1], Pin[4 * tt + 2], Pin[4 * tt + 3]};
+      O[db] = mfma32<F16>(__builtin_bit_cast(u32x4, va[k]), pb, O[db]);
+      {
+        float p0 = fast_exp2(fmaf(S[2 * k], c, -mc));
+        float p1 = fast_exp2(fmaf(S[2 * k + 1], c, -mc));
+        if (SEL) {
+          const bool k0 = SI[2 * k] >= selThr, k1 = SI[2 * k + 1] >= selThr;
+          p0 = k0 ? p0 : 0.f;
+          p1 = k1 ? p1 : 0.f;
+          cnt += (k0 ? 1 : 0) + (k1 ? 1 : 0);
         }
-        __builtin_amdgcn_sched_barrier(0);
+        Pout[k] = pack16<F16>(p0, p1);
+        row_sum_add(l, Pout[k]);
       }
+      __builtin_amdgcn_sched_barrier(0);
     }
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      row_sum_settled(l[qb]);
-      lrow[qb] += l[qb];
-      if (SEL) sel_cnt[qb] += cnt[qb];
-    }
+    row_sum_settled(l);
+    lrow += l;
+    if (SEL) sel_cnt += cnt;
   };
   // does the 32-key block starting at nb0 need per-element masks for some query of this wave?
   auto needs_mask = [&](int nb0) __attribute__((always_inline)) {
-    bool e = false;
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      const int m_b_lo = m_w_lo + qb * 32;
-      const int m_b_hi = min(m_b_lo + 31, q_last);
-      e = e || (m_b_hi < m_b_lo) || (nb0 + 31 > m_b_lo);
-    }
-    return e;
+    return m_w_hi < m_w_lo || nb0 + 31 > m_w_lo;
   };
   // can some query of this wave see a key of the block at all?
   auto is_active = [&](int nb0) __attribute__((always_inline)) {
@@ -1485,16 +1431,13 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
 
   bool redo = false;
   if (it_lo < it_hi) {
-    f32x16 S[QB];
-    uint32_t P0[QB][8], P1[QB][8];
+    f32x16 S;
+    uint32_t P0[8], P1[8];
+    lrow = 0.f;
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      lrow[qb] = 0.f;
+    for (int db = 0; db < 4; ++db)
 #pragma unroll
-      for (int db = 0; db < 4; ++db)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) O[qb][db][i] = 0.f;
-    }
+      for (int i = 0; i < 16; ++i) O[db][i] = 0.f;
     // first keys of tiles it, it + 1, it + 2 (clamped to the range's last tile) and, one iteration ahead of its
     // first use, it + 3: a listed tile's number comes from memory
     int n_t0 = tile_n0(it_lo), n_t1 = tile_n0(min(it_lo + 1, it_hi - 1)), n_t2 = tile_n0(min(it_lo + 2, it_hi - 1));
@@ -1508,18 +1451,14 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
     if (it_lo != p_lo) load_tile(tile_n0(p_lo), 2);
     loads_landed();
     __syncthreads();
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) mrow[qb] = ninf;
+    mrow = ninf;
 #pragma unroll
     for (int kb = 1; kb >= 0; --kb) {
       mfma_S(t_ref, kb, S);
+      float mx = S[0];
 #pragma unroll
-      for (int qb = 0; qb < QB; ++qb) {
-        float mx = S[qb][0];
-#pragma unroll
-        for (int i = 1; i < 16; ++i) mx = fmaxf(mx, S[qb][i]);
-        mrow[qb] = fmaxf(mrow[qb], fmaxf(mx, __shfl_xor(mx, 32)));
-      }
+      for (int i = 1; i < 16; ++i) mx = fmaxf(mx, S[i]);
+      mrow = fmaxf(mrow, fmaxf(mx, __shfl_xor(mx, 32)));
     }
     if (it_lo != p_lo) mfma_S(Ls, 0, S);                 // S now holds block (it_lo, 0)
 
@@ -1545,8 +1484,8 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
       constexpr int hf = decltype(hf_tag)::value;
       const int nb0 = n_t0 + hf * 32;
       const unsigned char* t_pend = hf == 0 ? tile_at(it - 1) : tile_at(it);
-      const uint32_t (&Pin)[QB][8] = hf == 0 ? P1 : P0;
-      uint32_t (&Pout)[QB][8] = hf == 0 ? P0 : P1;
+      const uint32_t (&Pin)[8] = hf == 0 ? P1 : P0;
+      uint32_t (&Pout)[8] = hf == 0 ? P0 : P1;
       if (pend) mfma_PV(t_pend, 1 - hf, Pin);
       bool rounded = pend || (hf == 0 && it == it_lo && it_lo != p_lo);    // some block of the part was before
       pend = false;
@@ -1624,33 +1563,27 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
     // the whole band of a local launch; from the range's first key on, in a dense one) must have a sum
     // in the comfortable middle of the fp32 range; everything else (0, tiny, huge, inf, NaN) repeats.
     bool bad = false;
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      const float ltot = lrow[qb] + __shfl_xor(lrow[qb], 32);
-      // selecting mode: a query that kept no key of this range legitimately sums to zero
-      const bool sees_key = SPARSE ? (sel_cnt[qb] + __shfl_xor(sel_cnt[qb], 32) > 0)
-                                   : (qok[qb] && tile_n0(it_lo) <= mq[qb]);
-      // (fp16 probabilities: nothing above 65504 -- a larger one is infinite and shows in the sum -- and a
-      // row whose largest probability is below 2^-6 has most of its mass in subnormals or flushed to zero)
-      bad = bad || (sees_key && !(ltot > (F16 ? 0x1p-6f : 0x1p-60f) && ltot < 0x1p100f));
-    }
+    const float ltot = lrow + __shfl_xor(lrow, 32);
+    // selecting mode: a query that kept no key of this range legitimately sums to zero
+    const bool sees_key = SPARSE ? (sel_cnt + __shfl_xor(sel_cnt, 32) > 0)
+                                 : (qok && tile_n0(it_lo) <= mq);
+    // (fp16 probabilities: nothing above 65504 -- a larger one is infinite and shows in the sum -- and a
+    // row whose largest probability is below 2^-6 has most of its mass in subnormals or flushed to zero)
+    bad = bad || (sees_key && !(ltot > (F16 ? 0x1p-6f : 0x1p-60f) && ltot < 0x1p100f));
     redo = __syncthreads_or(bad ? 1 : 0) != 0;
   }
 
   if (redo) {
     // ---- exact pass: running maximum, accumulators rescaled in place; no pipelining (rare) ----
-    f32x16 S[QB];
-    uint32_t P[QB][8];
+    f32x16 S;
+    uint32_t P[8];
+    mrow = ninf;
+    lrow = 0.f;
+    sel_cnt = 0;
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      mrow[qb] = ninf;
-      lrow[qb] = 0.f;
-      sel_cnt[qb] = 0;
+    for (int db = 0; db < 4; ++db)
 #pragma unroll
-      for (int db = 0; db < 4; ++db)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) O[qb][db][i] = 0.f;
-    }
+      for (int i = 0; i < 16; ++i) O[db][i] = 0.f;
     for (int it = it_lo; it < it_hi; ++it) {
       __syncthreads();
       load_tile(tile_n0(it), 0);
@@ -1662,78 +1595,72 @@ __global__ __launch_bounds__(64 * (8 / QB), QB == 1 ? 2 : 1) void flash_prefill_
         if (kb == 0) mfma_S(Ls, 0, S); else mfma_S(Ls, 1, S);
         mask_block(S, nb0);
         if (SPARSE) select_block(S, load_ki(nb0));
+        float mx = S[0];
 #pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
-          float mx = S[qb][0];
+        for (int i = 1; i < 16; ++i) mx = fmaxf(mx, S[i]);
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        const float mnew = fmaxf(mrow, mx);
+        const float msafe = mnew == ninf ? 0.f : mnew;
+        const float mc = msafe * c;
+        float lsum = 0.f;
 #pragma unroll
-          for (int i = 1; i < 16; ++i) mx = fmaxf(mx, S[qb][i]);
-          mx = fmaxf(mx, __shfl_xor(mx, 32));
-          const float mnew = fmaxf(mrow[qb], mx);
-          const float msafe = mnew == ninf ? 0.f : mnew;
-          const float mc = msafe * c;
-          float lsum = 0.f;
-#pragma unroll
-          for (int i = 0; i < 16; i += 2) {
-            const float p0 = fast_exp2(fmaf(S[qb][i], c, -mc));
-            const float p1 = fast_exp2(fmaf(S[qb][i + 1], c, -mc));
-            lsum += p0 + p1;
-            P[qb][i >> 1] = pack16<F16>(p0, p1);
-          }
-          const float corr = fast_exp2((mrow[qb] - msafe) * c);
-          lrow[qb] = lrow[qb] * corr + lsum;
-#pragma unroll
-          for (int db = 0; db < 4; ++db)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) O[qb][db][i] *= corr;
-          mrow[qb] = mnew;
+        for (int i = 0; i < 16; i += 2) {
+          const float p0 = fast_exp2(fmaf(S[i], c, -mc));
+          const float p1 = fast_exp2(fmaf(S[i + 1], c, -mc));
+          lsum += p0 + p1;
+          P[i >> 1] = pack16<F16>(p0, p1);
         }
+        const float corr = fast_exp2((mrow - msafe) * c);
+        lrow = lrow * corr + lsum;
+#pragma unroll
+        for (int db = 0; db < 4; ++db)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) O[db][i] *= corr;
+        mrow = mnew;
         if (kb == 0) mfma_PV(Ls, 0, P); else mfma_PV(Ls, 1, P);
       }
     }
   }
 
   // ---- normalise and store ----
-#pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    const float ltot = (it_lo < it_hi) ? lrow[qb] + __shfl_xor(lrow[qb], 32) : 0.f;
-    if (!qok[qb]) continue;
-    const float mfin = (it_lo < it_hi && ltot > 0.f) ? mrow[qb] : ninf;
-    const int kept = sel_cnt[qb] + __shfl_xor(sel_cnt[qb], 32);
-    if (MODE == kModeDense && g == 0 && split == 0) {       // the statistics of the rule that keeps every candidate
-      const int64_t o = (int64_t)hslot * a.n_q + tq[qb];
-      if (a.mass) a.mass[o] = 1.f;
-      if (a.tau) a.tau[o] = ninf;
-      if (a.count) a.count[o] = mq[qb] + 1;
-    }
-    if (n_splits > 1) {
-      float* prow = a.part + (((int64_t)split * a.n_heads + hslot) * a.n_q + tq[qb]) * kPfPart;
-      if (g == 0) { prow[0] = mfin; prow[1] = ltot; prow[2] = __int_as_float(kept); }
-#pragma unroll
-      for (int db = 0; db < 4; ++db)
-#pragma unroll
-        for (int i4 = 0; i4 < 4; ++i4)
-          *reinterpret_cast<float4*>(prow + 4 + db * 32 + i4 * 8 + g * 4) =
-              ltot > 0.f ? make_float4(O[qb][db][i4 * 4], O[qb][db][i4 * 4 + 1], O[qb][db][i4 * 4 + 2], O[qb][db][i4 * 4 + 3])
-                         : make_float4(0.f, 0.f, 0.f, 0.f);
-      continue;
-    }
-    const float inv = ltot > 0.f ? 1.f / ltot : 0.f;
-    uint16_t* orow = a.out + qrow[qb];
-#pragma unroll
-    for (int db = 0; db < 4; ++db) {
-#pragma unroll
-      for (int i4 = 0; i4 < 4; ++i4) {
-        const u32x2 w = ltot > 0.f ? (u32x2){pack16<F16>(O[qb][db][i4 * 4] * inv, O[qb][db][i4 * 4 + 1] * inv),
-                                             pack16<F16>(O[qb][db][i4 * 4 + 2] * inv, O[qb][db][i4 * 4 + 3] * inv)}
-                                   : (u32x2){0u, 0u};
-        *reinterpret_cast<u32x2*>(orow + db * 32 + i4 * 8 + g * 4) = w;
-      }
-    }
-    if (a.lse && g == 0) {
-      a.lse[((int64_t)b * a.n_q + tq[qb]) * a.n_q_heads + h] = ltot > 0.f ? mfin * a.scale + logf(ltot) : ninf;
-    }
-    if (SPARSE && a.count && g == 0) a.count[(int64_t)hslot * a.n_q + tq[qb]] = kept;
+  const float ltot = (it_lo < it_hi) ? lrow + __shfl_xor(lrow, 32) : 0.f;
+  if (!qok) return;
+  const float mfin = (it_lo < it_hi && ltot > 0.f) ? mrow : ninf;
+  const int kept = sel_cnt + __shfl_xor(sel_cnt, 32);
+  if (MODE == kModeDense && g == 0 && split == 0) {       // the statistics of the rule that keeps every candidate
+    const int64_t o = (int64_t)hslot * a.n_q + tq;
+    if (a.mass) a.mass[o] = 1.f;
+    if (a.tau) a.tau[o] = ninf;
+    if (a.count) a.count[o] = mq + 1;
   }
+  if (n_splits > 1) {
+    float* prow = a.part + (((int64_t)split * a.n_heads + hslot) * a.n_q + tq) * kPfPart;
+    if (g == 0) { prow[0] = mfin; prow[1] = ltot; prow[2] = __int_as_float(kept); }
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+#pragma unroll
+      for (int i4 = 0; i4 < 4; ++i4)
+        *reinterpret_cast<float4*>(prow + 4 + db * 32 + i4 * 8 + g * 4) =
+            ltot > 0.f ? make_float4(O[db][i4 * 4], O[db][i4 * 4 + 1], O[db][i4 * 4 + 2], O[db][i4 * 4 + 3])
+                       : make_float4(0.f, 0.f, 0.f, 0.f);
+    return;
+  }
+  const float inv = ltot > 0.f ? 1.f / ltot : 0.f;
+  uint16_t* orow = a.out + qrow;
+#pragma unroll
+  for (int db = 0; db < 4; ++db) {
+#pragma unroll
+    for (int i4 = 0; i4 < 4; ++i4) {
+      const u32x2 w = ltot > 0.f ? (u32x2){pack16<F16>(O[db][i4 * 4] * inv, O[db][i4 * 4 + 1] * inv),
+                                           pack16<F16>(O[db][i4 * 4 + 2] * inv, O[db][i4 * 4 + 3] * inv)}
+                                 : (u32x2){0u, 0u};
+      *reinterpret_cast<u32x2*>(orow + db * 32 + i4 * 8 + g * 4) = w;
+    }
+  }
+  if (a.lse && g == 0) {
+    a.lse[((int64_t)b * a.n_q + tq) * a.n_q_heads + h] = ltot > 0.f ? mfin * a.scale + logf(ltot) : ninf;
+  }
+  if (SPARSE && a.count && g == 0) a.count[(int64_t)hslot * a.n_q + tq] = kept;
 }
 
 // The 64-key tiles a 256-query tile of the selecting attention launch has to visit: tile n is on the list iff, for
@@ -1966,8 +1893,8 @@ static int32_t launch_prefill(const char* who, bool local, PrefillArgs& a, int32
   if (local) {
     if (a.f16) RTP_LAUNCH(flash_prefill_local_kernel<true>, grid, dim3(kPfThreads), 0, s, a);
     else RTP_LAUNCH(flash_prefill_local_kernel<false>, grid, dim3(kPfThreads), 0, s, a);
-  } else if (a.f16) RTP_LAUNCH((flash_prefill_wide_kernel<kModeDense, 1, true>), grid, dim3(512), 0, s, a);
-  else RTP_LAUNCH((flash_prefill_wide_kernel<kModeDense, 1>), grid, dim3(512), 0, s, a);
+  } else if (a.f16) RTP_LAUNCH((flash_prefill_wide_kernel<kModeDense, true>), grid, dim3(kPwThreads), 0, s, a);
+  else RTP_LAUNCH(flash_prefill_wide_kernel<kModeDense>, grid, dim3(kPwThreads), 0, s, a);
   if (!local && a.n_splits * a.n_sub > 1) launch_prefill_combine(a, s);
   return check_launch(who);
 }
@@ -2254,8 +2181,8 @@ extern "C" int32_t rtp_sparse_attn_prefill(const rtp_layer_desc* layer, const vo
   const unsigned n_wide = (unsigned)((T + kPwQ - 1) / kPwQ);
   RTP_LAUNCH(prefill_active_tiles_kernel, dim3(n_wide, (unsigned)a.n_heads), dim3(256), 0, (hipStream_t)stream, a);
   const dim3 grid((unsigned)(a.n_splits * a.n_sub), n_wide, (unsigned)a.n_heads);
-  if (a.f16) RTP_LAUNCH((flash_prefill_wide_kernel<kModeSparse, 1, true>), grid, dim3(512), 0, (hipStream_t)stream, a);
-  else RTP_LAUNCH((flash_prefill_wide_kernel<kModeSparse, 1>), grid, dim3(512), 0, (hipStream_t)stream, a);
+  if (a.f16) RTP_LAUNCH((flash_prefill_wide_kernel<kModeSparse, true>), grid, dim3(kPwThreads), 0, (hipStream_t)stream, a);
+  else RTP_LAUNCH(flash_prefill_wide_kernel<kModeSparse>, grid, dim3(kPwThreads), 0, (hipStream_t)stream, a);
   if (a.n_splits * a.n_sub > 1) launch_prefill_combine(a, (hipStream_t)stream);
   return check_launch(who);
 }
