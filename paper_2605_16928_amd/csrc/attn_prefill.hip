@@ -424,20 +424,18 @@ __device__ __forceinline__ float sel_first_below(float M, float index_scale, flo
   return key_float(lo);
 }
 
-//
-// KS waves share one group of 32 queries and split its key range between them; a workgroup is eight waves, i.e.
-// 8 / KS groups, and 128 vector registers and 80 KB of LDS let two workgroups share a compute unit: four waves per
-// SIMD issue under each other's latencies (with two, 221 registers and loads two rounds of eight tiles ahead, the search
+// A workgroup is the eight waves of one group, which split its key range between them; 128 vector registers and 80 KB of
+// LDS let two workgroups share a compute unit: four waves per SIMD (3.5 on average, by the counters) issue under each other's latencies (with two, 221 registers and loads two rounds of eight tiles ahead, the search
 // took 23.7 ms on the last 8192-query chunk of a 1,048,576-token context, 18.2 now; the same code held to 128
-// registers 19.4).  The waves of a group add into ONE histogram (LDS atomics; 32 KB per group); the per-lane member
-// lists of sweeps 2 and 3 are emptied when a half tile might overrun one.  All waves of the workgroup meet at
+// registers 19.4).  The waves add into ONE histogram (LDS atomics; 32 KB); the per-lane member
+// lists of sweeps 2 and 3 are emptied when a half tile might overrun one.  All waves meet at
 // barriers around every scan, so the phases are uniform over the workgroup.
 // What bounds the sweeps there: sweep 0 (2.4 ms) and sweep 3 (2.0, was 4.0) their vector instructions per tile; sweep 1
 // (7.4, was 9.3) the LDS atomics -- an fp64 one holds the compute unit's LDS for 8.4 cycles, i.e. 34 per SIMD and wave of
 // 64 pairs, as many as its seven vector instructions take --; sweep 2 (6.3, was 8.2) the LDS stores (4.3 cycles
 // each whatever the number of lanes) and draining the lists.  Skipping the stores of the pairs without a member by a
 // branch measured slower (7.5).
-// The library launches KS = 8, one group per workgroup: when a few queries of a chunk have their threshold deep in the
+// One group per workgroup: when a few queries of a chunk have their threshold deep in the
 // background while the others' sweeps 2 and 3 visit a handful of tiles, short workgroups let the dispatcher even
 // the load out.
 // A chunk of few groups leaves most of the chip idle that way (333 queries of 4 heads: 44 workgroups, 0.88 ms at 128K
@@ -458,15 +456,12 @@ constexpr double kSelLumpScale = 7843180.797657975;   // exp(15.875)
 constexpr int kSelMaxRounds = 24;
 constexpr int kSelAll = -1, kSelFinish = 4;        // STEP of prefill_select_kernel beside the sweeps 0 .. 3
 
-template <int KS, int STEP>
+template <int STEP>
 __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const PrefillArgs a) {
   constexpr bool kSliced = STEP >= 0 && STEP < kSelFinish;             // this launch sweeps a slice of the group's keys
   constexpr bool kWhole = STEP == kSelAll || STEP == kSelFinish;       // ... or can run the whole search
-  constexpr int NW = kSelThreads / 64;                             // waves per workgroup
-  constexpr int NG = NW / KS;                                      // query groups per workgroup
-  constexpr int kSelQ = 32 * NG;                                   // queries per workgroup
-  static_assert(NG >= 1 && NG <= 4, "at most four histograms fit");
-  __shared__ double hist_all[NG][kSelBins][32];                    // 32 KB per group
+  constexpr int NW = kSelThreads / 64;                             // waves of the workgroup
+  __shared__ double hist[kSelBins][32];                            // 32 KB
   __shared__ float list_all[NW][kSelListCap][64];                  // per-lane member lists of sweeps 2 and 3 (48 KB)
   float (*max_all)[32] = reinterpret_cast<float (*)[32]>(&list_all[0][0][0]);   // sweep 0: the waves' row maxima
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // (tile numbers are scalars)
@@ -475,7 +470,7 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
   // that a die works on ONE head (8 / n_heads dies per head): all its waves then stream the same index
   // keys and meet in that L2.
   int j, qtile;
-  const int n_qtiles = (a.n_q + kSelQ - 1) / kSelQ;
+  const int n_qtiles = (a.n_q + 31) / 32;
   const int n_slice = kSliced ? a.n_slice : 1;
   if (a.n_heads <= 8 && 8 % a.n_heads == 0) {
     const int per_head = 8 / a.n_heads;                            // dies per head
@@ -493,35 +488,31 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
   if (qtile >= n_qtiles * n_slice) return;                         // (the whole workgroup)
   const int slice = qtile / n_qtiles;
   qtile -= slice * n_qtiles;
-  const int t0 = (n_qtiles - 1 - qtile) * kSelQ;                   // long rows first
-  const int qgroup = wave / KS, part = wave - qgroup * KS;         // this wave's queries and its share of their keys
-  const int tw = t0 + qgroup * 32;                                 // first query of the group
-  const bool idle = tw >= a.n_q;                                   // no query in this group (the wave still goes to the barriers)
+  const int t0 = (n_qtiles - 1 - qtile) * 32;                      // first query of the group; long rows first
   const int pos0 = (int)a.q_start_host;
   // The lanes past the last query of a partial group repeat that query (their results are not stored): every lane
   // then has a causal range that ends where its group's does, and the group's interior tiles need no mask.  (Masking
   // those lanes instead puts the whole range of a partial group on the masked path of one wave: the search takes 10.7 against 0.9 ms
   // for a chunk of 333 queries behind 131072 tokens.)
-  const bool qok = tw + r < a.n_q;
-  const int t = max(min(tw + r, a.n_q - 1), 0);
+  const bool qok = t0 + r < a.n_q;
+  const int t = min(t0 + r, a.n_q - 1);
   const int m = pos0 + t;
   const float ninf = -__builtin_huge_valf(), pinf = __builtin_huge_valf();
   const float cs = a.index_scale;
   const uint16_t* kIg = a.kI + (int64_t)j * a.kI_head_stride;
   const u32x4 qIreg = *reinterpret_cast<const u32x4*>(a.qI + ((int64_t)j * a.n_q + t) * kIndexDim + g * 8);
   const int n_rows = pos0 + a.n_q;                                 // index-key rows that exist
-  const int m_wave_lo = pos0 + tw;
-  const int m_wave_hi = pos0 + min(tw + 32, a.n_q) - 1;
-  const int n_tiles = idle ? 0 : m_wave_hi / 32 + 1;
-  const int n_interior = idle ? 0 : (m_wave_lo + 1) / 32;          // tiles with nb + 31 <= m_wave_lo
-  double (*hist)[32] = hist_all[qgroup];
+  const int m_lo = pos0 + t0;
+  const int m_hi = pos0 + min(t0 + 32, a.n_q) - 1;
+  const int n_tiles = m_hi / 32 + 1;
+  const int n_interior = (m_lo + 1) / 32;                          // tiles with nb + 31 <= m_lo
   float (*lst)[64] = list_all[wave];
   // this group's row of the tile-maximum table: written in sweep 0 (one entry per pair of key tiles, i.e. per 64
   // keys), read in sweeps 2 and 3, whose members all lie at or above x_lo -- a tile pair whose maximum is below
   // every query's x_lo holds none.  Sweep 3 replaces the entries of the pairs it visits by +inf (some query of
   // the group has a product at or above its own x_lo there, so it may keep a key) or -inf (none can); the pairs
   // it skips keep a maximum below every x_lo.  The attention launch's tile lists are built from the result.
-  float* tmx = a.tile_max + ((int64_t)j * ((a.n_q + 31) / 32) + (idle ? 0 : tw / 32)) * a.n_t64;
+  float* tmx = a.tile_max + ((int64_t)j * ((a.n_q + 31) / 32) + t0 / 32) * a.n_t64;
   float xlo_wave = ninf;            // smallest x_lo over the wave's queries
   float xlo_wave_top = ninf;        // and the largest
   bool reach_known = false;         // sweep 3: the tile in hand is certain to hold a product at or above its query's x_lo
@@ -544,7 +535,7 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
   // the group's waves clear their histogram together (followed by a barrier at the call sites)
   auto zero_hist = [&]() __attribute__((always_inline)) {
     double* h = &hist[0][0];
-    for (int i = part * 64 + lane; i < kSelBins * 32; i += KS * 64) h[i] = 0.0;
+    for (int i = tid; i < kSelBins * 32; i += kSelThreads) h[i] = 0.0;
   };
   // One candidate's mass into bin `bin` of this lane's query.
   auto add_mass = [&](int bin, float tt) __attribute__((always_inline)) {
@@ -765,7 +756,7 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
   const int n_plain = n_interior / kSelRing * kSelRing;            // whole rounds of interior tiles run without masks
   // this wave's share: an equal run of the rounds, the masked ones of the edge (one or two) at the end
   const int plain_rounds = n_plain / kSelRing, rounds = (n_tiles + kSelRing - 1) / kSelRing;
-  const int share = slice * KS + part, shares = n_slice * KS;
+  const int share = slice * NW + wave, shares = n_slice * NW;
   const int round_lo = (int)((int64_t)rounds * share / shares), round_hi = (int)((int64_t)rounds * (share + 1) / shares);
   const int plain_lo = min(round_lo, plain_rounds) * kSelRing, plain_hi = min(round_hi, plain_rounds) * kSelRing;
   const int edge_lo = max(round_lo, plain_rounds) * kSelRing, edge_hi = round_hi * kSelRing;
@@ -837,17 +828,17 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
   // runs' sums and the bins of the run that crosses, on the same numbers in the same order.  (All of them going through
   // all 128 bins is a chain of LDS reads and additions of 32000 cycles, three times per workgroup.)  One barrier; the
   // sums live in the lists' memory, idle between sweeps.  `whole`: the histogram holds all candidates, take Z from it.
-  constexpr int kRuns = 2 * KS, kRunBins = kSelBins / kRuns;
-  double (*run_sum)[32] = reinterpret_cast<double (*)[32]>(&list_all[0][0][0]) + qgroup * kRuns;
-  static_assert(kSelBins % kRuns == 0 && sizeof(double) * 32 * kRuns * NG + sizeof(int) * NW <= sizeof(list_all), "runs of equal length");
+  constexpr int kRuns = 2 * NW, kRunBins = kSelBins / kRuns;
+  double (*run_sum)[32] = reinterpret_cast<double (*)[32]>(&list_all[0][0][0]);
+  static_assert(kSelBins % kRuns == 0 && sizeof(double) * 32 * kRuns + sizeof(int) * NW <= sizeof(list_all), "runs of equal length");
   auto scan = [&](bool whole, bool take) __attribute__((always_inline)) {
     {
       double h[kRunBins], sum = 0.0;
 #pragma unroll
-      for (int i = 0; i < kRunBins; ++i) h[i] = hist[(part * 2 + g) * kRunBins + i][r];
+      for (int i = 0; i < kRunBins; ++i) h[i] = hist[(wave * 2 + g) * kRunBins + i][r];
 #pragma unroll
       for (int i = 0; i < kRunBins; ++i) sum += h[i];
-      run_sum[part * 2 + g][r] = sum;
+      run_sum[wave * 2 + g][r] = sum;
     }
     __syncthreads();
     if (!take) return;
@@ -878,18 +869,18 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
     zero_hist();
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < KS; ++k) mx = fmaxf(mx, max_all[qgroup * KS + k][r]);
+    for (int k = 0; k < NW; ++k) mx = fmaxf(mx, max_all[k][r]);
     x_max = mx;
     selM = mx * cs;
     __syncthreads();                                                // the maxima are read: the lists' memory is free again
   };
   bool rebased = false;
   // after a scan of sweep 1: is this query's threshold in the open-ended bin?
-  auto in_open_bin = [&]() __attribute__((always_inline)) { return !idle && bsel == kSelBins - 1 && hsel > 0.0; };
+  auto in_open_bin = [&]() __attribute__((always_inline)) { return bsel == kSelBins - 1 && hsel > 0.0; };
   // the same for any query of the workgroup (flags in the lists' memory, idle in this phase; the barrier also says
   // that every wave has read the histograms)
   auto any_of = [&](bool mine_) __attribute__((always_inline)) {
-    int* flags = reinterpret_cast<int*>(reinterpret_cast<double (*)[32]>(&list_all[0][0][0]) + NG * kRuns);
+    int* flags = reinterpret_cast<int*>(reinterpret_cast<double (*)[32]>(&list_all[0][0][0]) + kRuns);
     const bool mine = __ballot(mine_) != 0ull;
     if (lane == 0) flags[wave] = mine ? 1 : 0;
     __syncthreads();
@@ -951,8 +942,8 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
       x_mid = 0.5f * lo + 0.5f * hi;
       x_half = fmaxf(hi - x_mid, x_mid - lo);
     }
-    xlo_wave = -wave_max_f32(idle ? ninf : -x_lo);
-    xlo_wave_top = wave_max_f32(idle ? ninf : x_lo);
+    xlo_wave = -wave_max_f32(-x_lo);
+    xlo_wave_top = wave_max_f32(x_lo);
     shift -= 7;                                                     // of this sweep's digit: 7, then 0
   };
 
@@ -1047,7 +1038,7 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
   const bool lump = (prefix >> 14) == kSelBins - 1;
   cut = lump ? pinf : (float)(prefix + 1) * (1.0f / kSelScale);
   sel_mass = (lump || !(Z > 0.0)) ? 1.f : (float)((cum + hsel) / Z);
-  if (!qok || g != 0 || part != 0) return;
+  if (!qok || g != 0 || wave != 0) return;
   const int64_t o = (int64_t)j * a.n_q + t;
   a.sel_thr[o] = sel_first_below(selM, cs, cut);
   if (a.mass) a.mass[o] = sel_mass;
@@ -2158,9 +2149,7 @@ extern "C" int32_t rtp_sparse_attn_prefill(const rtp_layer_desc* layer, const vo
     a.act_range = a.act_count + (w.tw.count_bytes / sizeof(int32_t) - 2);
     a.n_splits_even = std::max(2, ranges.dense);
   }
-  constexpr int ks = 8;                                    // waves per 32-query group (see the kernel's header)
-  static_assert(ks == 8, "the launch below names the instantiation");
-  const unsigned n_qtiles = (unsigned)((T + 256 / ks - 1) / (256 / ks));
+  const unsigned n_qtiles = (unsigned)((T + 31) / 32);
   // 1-D grid, padded so that every die gets whole (head, query tile, slice) columns (see the kernel's decoding)
   auto search_grid = [&](unsigned slices) {
     if (a.n_heads > 8 || 8 % a.n_heads != 0) return dim3((unsigned)a.n_heads * n_qtiles * slices);
@@ -2170,13 +2159,13 @@ extern "C" int32_t rtp_sparse_attn_prefill(const rtp_layer_desc* layer, const vo
   hipStream_t s = (hipStream_t)stream;
   if (a.n_slice > 1) {
     const dim3 grid = search_grid((unsigned)a.n_slice);
-    RTP_LAUNCH((prefill_select_kernel<8, 0>), grid, dim3(kSelThreads), 0, s, a);
-    RTP_LAUNCH((prefill_select_kernel<8, 1>), grid, dim3(kSelThreads), 0, s, a);
-    RTP_LAUNCH((prefill_select_kernel<8, 2>), grid, dim3(kSelThreads), 0, s, a);
-    RTP_LAUNCH((prefill_select_kernel<8, 3>), grid, dim3(kSelThreads), 0, s, a);
-    RTP_LAUNCH((prefill_select_kernel<8, kSelFinish>), search_grid(1), dim3(kSelThreads), 0, s, a);
+    RTP_LAUNCH(prefill_select_kernel<0>, grid, dim3(kSelThreads), 0, s, a);
+    RTP_LAUNCH(prefill_select_kernel<1>, grid, dim3(kSelThreads), 0, s, a);
+    RTP_LAUNCH(prefill_select_kernel<2>, grid, dim3(kSelThreads), 0, s, a);
+    RTP_LAUNCH(prefill_select_kernel<3>, grid, dim3(kSelThreads), 0, s, a);
+    RTP_LAUNCH(prefill_select_kernel<kSelFinish>, search_grid(1), dim3(kSelThreads), 0, s, a);
   } else {
-    RTP_LAUNCH((prefill_select_kernel<8, kSelAll>), search_grid(1), dim3(kSelThreads), 0, s, a);
+    RTP_LAUNCH(prefill_select_kernel<kSelAll>, search_grid(1), dim3(kSelThreads), 0, s, a);
   }
   const unsigned n_wide = (unsigned)((T + kPwQ - 1) / kPwQ);
   RTP_LAUNCH(prefill_active_tiles_kernel, dim3(n_wide, (unsigned)a.n_heads), dim3(256), 0, (hipStream_t)stream, a);
