@@ -148,7 +148,7 @@ __device__ __forceinline__ float max16_nn(const float (&v)[16]) {
 // The local heads' band.  What bounds it is each wave's chain through a tile (scores, maximum, probabilities, PV: about 2.3 us
 // with one wave per SIMD, where 16 + 16 MFMAs take 0.4), overlapped only with the other workgroup of the compute unit.
 // Staging by direct loads and transposing reads instead of through registers, the first PV operands read under the softmax
-// and maxima in two short chains: 4096 queries at 128K, 28 heads: 241 -> 205 us (590 TFLOP/s); 333 queries: 89 -> 82 us; a
+// and maxima in two short chains: 4096 queries at 128K, 28 heads: 241 -> 175 to 205 us (590 to 690 TFLOP/s); 333 queries: 89 -> 82 us; a
 // prompt of 2037 with 6 heads: 31.5 -> 29 us.  Measured without gain: four buffers, three tiles ahead (92 and 32 us: memory
 // latency is not the limit); the band on the wide kernel (twice as long: its masked blocks leave the pipelined path).
 template <bool F16>
@@ -426,7 +426,7 @@ __device__ __forceinline__ float sel_first_below(float M, float index_scale, flo
 
 // A workgroup is the eight waves of one group, which split its key range between them; 128 vector registers and 80 KB of
 // LDS let two workgroups share a compute unit: four waves per SIMD (3.5 on average, by the counters) issue under each other's latencies (with two, 221 registers and loads two rounds of eight tiles ahead, the search
-// took 23.7 ms on the last 8192-query chunk of a 1,048,576-token context, 18.2 now; the same code held to 128
+// took 23.7 ms on the last 8192-query chunk of a 1,048,576-token context, 18.4 to 19.5 now; the same code held to 128
 // registers 19.4).  The waves add into ONE histogram (LDS atomics; 32 KB); the per-lane member
 // lists of sweeps 2 and 3 are emptied when a half tile might overrun one.  All waves meet at
 // barriers around every scan, so the phases are uniform over the workgroup.
@@ -1075,8 +1075,8 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
 // run in a loop without a branch (steady, below), the others block by block with element masks and nothing
 // interleaved.  Inside the branches that served both before, the register allocator moved accumulators at the joins,
 // and every stream began by waiting for its first LDS operands, all eight waves at once; in the loop a stream reads
-// the next one's first operands.  Attention launch of 4 heads x 4096 queries at 128K tokens: 1300 -> 1090 us selecting,
-// 1250 -> 970 us dense (1.14 PFLOP/s); last 8192-query chunk of 1M tokens, selecting: 20.3 -> 17.6 ms (operands three
+// the next one's first operands.  Attention launch of 4 heads x 4096 queries at 128K tokens: 1300 -> 1066 us selecting,
+// 1250 -> 918 us dense (1.18 PFLOP/s); last 8192-query chunk of 1M tokens, selecting: 20.3 -> 17.3 to 17.7 ms (operands three
 // and two steps ahead instead of five and four: 17.7 and 1141 us).  What bounds it now is the sum of what the
 // two waves of a SIMD issue -- per 32 x 32 block 16 MFMAs of 32 cycles, 24 LDS reads and, by the counters, 64 (dense) or 122
 // (selecting) other vector instructions --, with the matrix pipe busy 59 and 48 % of the cycles and the LDS, at the rates
