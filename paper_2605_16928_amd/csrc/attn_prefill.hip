@@ -2017,15 +2017,20 @@ static size_t prefill_needed(int n_ret, int32_t T, int64_t chunk_start) {
   return prefill_ws(n_ret, T, chunk_start).front() + partial_bytes(choose_splits_listed(n_ret, T, chunk_start), n_ret, T);
 }
 // The scratch that lets every chunk of at most T queries that ends where this one does run at full speed: the largest
-// partials of any of them (they grow with the queries as long as the number of 256-query tiles stays) and the most a
-// sliced search takes.  The size function therefore never answers less for a longer chunk with the same end.
+// partials of any of them and the most a sliced search takes.  For as many 256-query tiles the ranges follow from the average
+// depth alone, which moves by two key tiles: the first and the last such chunk show every choice.  The size function therefore
+// never answers less for a longer chunk with the same end.
 static size_t prefill_scratch(int n_ret, int32_t T, int64_t chunk_start) {
   const int64_t end = chunk_start + T, groups = (int64_t)n_ret * ((T + 31) / 32);
   size_t most = 0;
-  for (int64_t t = std::min<int64_t>(T, kPwQ);; t = std::min<int64_t>(T, t + kPwQ)) {
-    const PrefillRanges r = prefill_ranges(n_ret, (int32_t)t, end - t);
-    most = std::max(most, partial_bytes(std::max(r.dense * r.dense_sub, r.listed * r.listed_sub), n_ret, (int32_t)t));
-    if (t == T) break;
+  for (int64_t first = 1; first <= T; first += kPwQ) {
+    const int32_t last = (int32_t)std::min<int64_t>(T, first + kPwQ - 1);
+    int ranges = 1;
+    for (const int64_t t : {first, (int64_t)last}) {
+      const PrefillRanges r = prefill_ranges(n_ret, (int32_t)t, end - t);
+      ranges = std::max(ranges, std::max(r.dense * r.dense_sub, r.listed * r.listed_sub));
+    }
+    most = std::max(most, partial_bytes(ranges, n_ret, last));
   }
   const int64_t cus = compute_units(), wgs = std::min(groups * std::min(end / 4096, (int64_t)16), 2 * cus);
   return std::max(most, end > 9000 ? search_ws(std::min(groups, cus), wgs).total() : 0);

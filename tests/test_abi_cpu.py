@@ -373,7 +373,8 @@ def test_prefill_tile_statistics_argument_checks():
 
 @pytest.mark.parametrize("hq,hkv,n_ret,T0,N", [
     (32, 8, 4, 4096, 32768), (32, 8, 4, 4096, 65536), (32, 8, 4, 4096, 131072), (8, 2, 2, 8192, 65536), (64, 8, 8, 1024, 131072),
-    (64, 8, 8, 2048, 131072), (8, 2, 1, 2048, 4096), (8, 2, 2, 4096, 8192)])
+    (64, 8, 8, 2048, 131072), (8, 2, 1, 2048, 4096), (8, 2, 2, 4096, 8192), (8, 2, 1, 3329, 7705), (64, 8, 8, 5121, 8626),
+    (32, 8, 3, 8192, 14196)])
 def test_prefill_workspace_of_a_chunk_covers_shorter_chunks(hq, hkv, n_ret, T0, N):
     """A prompt of N tokens is prefilled in chunks of T0: one workspace of the size named for a whole chunk that ends at N is
     enough for every shorter chunk that ends there."""
