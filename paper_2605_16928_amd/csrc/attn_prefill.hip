@@ -15,6 +15,7 @@
 // Workgroup = 4 waves = 128 queries of one (sequence, head); key tiles of 64; heads of one KV group
 // are adjacent in the grid so that they meet in L2; late (long) query tiles are scheduled first.
 #include "common.h"
+#include "index_project.h"
 #include "prefill_scan.h"
 
 #include <algorithm>
@@ -1705,27 +1706,6 @@ __global__ __launch_bounds__(256) void prefill_active_tiles_kernel(const Prefill
   }
 }
 
-// qI[j, t, :] = bf16( W[j] . x[t, ret_heads[j], :] ), the 128-term sums in fp64, one rounding
-// (Sec. 3.2, indexer equation, query side).  16 queries per workgroup: thread = (query, output dim).
-struct ProjectArgs {
-  const float* W;
-  const uint16_t* x;
-  uint16_t* out;
-  int32_t n_q, n_q_heads, n_ret;
-  int32_t ret_heads[64];
-};
-
-__global__ __launch_bounds__(256) void index_project_kernel(const ProjectArgs a) {
-  const int j = blockIdx.y;
-  const int t = blockIdx.x * 16 + (threadIdx.x >> 4), i = threadIdx.x & 15;
-  if (t >= a.n_q) return;
-  const float* w = a.W + ((int64_t)j * kIndexDim + i) * kHeadDim;
-  const uint16_t* x = a.x + ((int64_t)t * a.n_q_heads + a.ret_heads[j]) * kHeadDim;
-  double acc = 0.0;
-  for (int c = 0; c < kHeadDim; ++c) acc = fma((double)w[c], (double)bf16_to_f32(x[c]), acc);
-  a.out[((int64_t)j * a.n_q + t) * kIndexDim + i] = f64_to_bf16_rne(acc);
-}
-
 // Merges the key-range partials of a (query, head): SLICES groups of 32 lanes walk the ranges slice, slice + SLICES, ...,
 // four partials in flight each, a lane owns 4 of the 128 output dims; LDS merges the slices.  8 / SLICES rows per
 // workgroup: two slices where there are few ranges (24 us for 16384 rows of 4 ranges with a thread per dim going through
@@ -2113,16 +2093,16 @@ extern "C" int32_t rtp_sparse_attn_prefill(const rtp_layer_desc* layer, const vo
   // index queries: given, or projected in fp64 into the workspace first
   const uint16_t* qI = (const uint16_t*)q_pre;
   if (WQ) {
-    ProjectArgs pa;
+    IndexProjectArgs pa;
     pa.W = WQ;
     pa.x = (const uint16_t*)q_pre;
     pa.out = (uint16_t*)ws;
-    pa.n_q = T;
-    pa.n_q_heads = layer->n_q_heads;
-    pa.n_ret = layer->n_ret;
-    for (int j = 0; j < 64; ++j) pa.ret_heads[j] = j < layer->n_ret ? layer->ret_heads[j] : 0;
-    RTP_LAUNCH(index_project_kernel, dim3((unsigned)((T + 15) / 16), (unsigned)layer->n_ret), dim3(256), 0,
-                       (hipStream_t)stream, pa);
+    pa.out_head_stride = (int64_t)T * kIndexDim;
+    pa.out_t0 = 0;
+    pa.T = T;
+    pa.n_x_heads = layer->n_q_heads;
+    for (int j = 0; j < 64; ++j) pa.x_head[j] = j < layer->n_ret ? layer->ret_heads[j] : 0;
+    launch_index_project(pa, layer->n_ret, (hipStream_t)stream);
     qI = (const uint16_t*)ws;
   }
   a.qI = qI;
