@@ -37,6 +37,9 @@ def kernel_algorithmic_bytes(R, N, sel_total, bytes_local, G):
         "topp_level_kernel<2>": scores,
         "topp_level_kernel<3>": scores,
         f"topp_level_ride_kernel<2, {G}>": scores + bytes_local,
+        f"topp_select_rows_ride_kernel<{G}>": 2 * scores + sel_total * 4 + bytes_local,
+        "topp_select_rows_kernel": 2 * scores + sel_total * 4,
+        "gather_lists_kernel<false, false>": sel_total * 516,
         "topp_write_kernel<true>": scores + sel_total * 516,
         "topp_write_kernel<false>": scores + sel_total * 4,
     }

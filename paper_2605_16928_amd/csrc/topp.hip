@@ -109,7 +109,8 @@ struct Scan1Result {       // level 1: bins carry different references, the scan
   float ref;
 };
 
-// Every thread gets the result; all workgroups of a row compute the same numbers in the same order.
+// Every thread gets the result; all workgroups of a row compute the same numbers in the same order (waves past the first
+// kTpThreads / 64 bring no bins and only take part in the barriers).
 // Threads own `per` consecutive bins in order FROM THE TOP of the score range (thread 0 the highest bins),
 // so "the mass above" is an ordinary inclusive prefix sum over lanes and waves.
 // The bins arrive in registers (load_bins): a kernel issues those loads first thing, so that they are in
@@ -119,6 +120,15 @@ __device__ __forceinline__ void load_bins(const uint64_t* __restrict__ h, uint64
   const int first = (kTpThreads - 1 - (int)threadIdx.x) * (NBINS / kTpThreads);
 #pragma unroll
   for (int i = 0; i < NBINS / kTpThreads; ++i) loc[i] = h[first + i];
+}
+template <int NBINS, int THREADS>
+__device__ __forceinline__ void load_bins_of(const uint64_t* __restrict__ h, uint64_t (&loc)[NBINS / kTpThreads]) {
+  if (THREADS == kTpThreads || (int)threadIdx.x < kTpThreads) {
+    load_bins<NBINS>(h, loc);
+  } else {
+#pragma unroll
+    for (int i = 0; i < NBINS / kTpThreads; ++i) loc[i] = 0;
+  }
 }
 
 __device__ __forceinline__ Scan1Result scan_level1(const uint64_t (&loc)[kBins1 / kTpThreads], float p, double* sh_d /*[4]*/,
@@ -133,7 +143,7 @@ __device__ __forceinline__ Scan1Result scan_level1(const uint64_t (&loc)[kBins1 
     if (loc[i]) top = first + i;
   }
   top = wave_max_ge_m1(top);
-  if (lane == 0) sh_i[wave] = top;
+  if (lane == 0 && wave < kTpThreads / 64) sh_i[wave] = top;
   __syncthreads();
   top = sh_i[0];
 #pragma unroll
@@ -155,7 +165,7 @@ __device__ __forceinline__ Scan1Result scan_level1(const uint64_t (&loc)[kBins1 
     sum += md[i];
   }
   double incl = wave_incl_scan(sum);                  // this thread's bins and every higher bin of the wave
-  if (lane == 63) sh_d[wave] = incl;
+  if (lane == 63 && wave < kTpThreads / 64) sh_d[wave] = incl;
   // defaults (nobody crosses): the top bin, nothing above it -- left by the thread that owns that bin
   if (top >= first && top < first + per) {
     uint64_t lt = loc[0];
@@ -233,7 +243,7 @@ __device__ __forceinline__ ScanResult scan_from_top(const uint64_t (&loc)[NBINS 
 #pragma unroll
   for (int i = 0; i < per; ++i) sum += loc[i];
   uint64_t incl = wave_incl_scan(sum);                // this thread's bins and every higher bin of the wave
-  if (lane == 63) sh_w[wave] = incl;
+  if (lane == 63 && wave < kTpThreads / 64) sh_w[wave] = incl;
   if (first == 0) { sh_res[0] = 0; sh_res[1] = above; sh_res[2] = loc[0]; }   // defaults: bin 0
   __syncthreads();
   uint64_t before = 0, total = above;
@@ -1259,6 +1269,343 @@ __global__ __launch_bounds__(kTpThreads) void topp_row_kernel(const TopPArgs a, 
   }
 }
 
+// ---- rows of a few chunks: one workgroup selects a whole row ------------------------------------------
+// Behind level 1 a row's scores are looked at twice (out of the cache) and its histograms never leave LDS, so what the launches
+// above hand to each other (level histograms, chunk counts, short lists) does not exist.
+//  * pass 1 packs the members of the level-1 bin into a queue per wave and weighs them 64 at a time (level 2);
+//  * pass 2 notes who lies at or above the 22-bit prefix, one bit per score in registers (a wave owns a contiguous part
+//    of the row, 32 scores per lane and word), and lists and weighs the handful that share the prefix (level 3);
+//  * the exact threshold strikes those below it off the bits, and the kept positions are written from the bits alone.
+// A score takes part in a key comparison with two instructions: with x = bits ^ (0 or 0x7fffffff, by the sign of the range)
+// key >= K is the signed comparison x >= K ^ 0x80000000 for both signs of the score.
+constexpr int kQueue = 64 + 512;                                    // a wave's queue: weighed down to 63, then two load rounds
+constexpr int kEqCap = 512;                                         // listed scores that share the 22-bit prefix
+
+struct KeyRange {
+  uint32_t flip;
+  int32_t lo, hi;              // as signed x, both ends included
+};
+// keys first .. last, never minus infinity or below (keys up to 0x007fffff)
+__device__ __forceinline__ KeyRange key_range(uint32_t first, uint32_t last) {
+  first = max(first, 0x00800000u);
+  last = max(last, first);
+  KeyRange k;
+  k.flip = (first & 0x80000000u) ? 0u : 0x7fffffffu;
+  k.lo = (int32_t)(first ^ 0x80000000u);
+  k.hi = (int32_t)(last ^ 0x80000000u);
+  return k;
+}
+
+// WORDS: words of 32 scores per lane, rows of up to 32 * WORDS * THREADS.
+template <int THREADS, int WORDS>
+__device__ __forceinline__ void select_row(const TopPArgs& a, const int r) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  constexpr int NW = THREADS / 64;
+  const float ninf = -__builtin_huge_valf();
+  __shared__ uint64_t lh[kBins1];
+  __shared__ float queue[NW][kQueue];
+  __shared__ uint2 eq[kEqCap];                                      // (key, position)
+  __shared__ uint64_t sh_part[NW], sh_res[3];
+  __shared__ double sh_d[NW], sh_dres[3], tab[256];
+  __shared__ int sh_i[NW], sh_n;
+  uint64_t* const hrow = a.hist + (int64_t)r * a.hist_stride;
+  const int n_row = a.row_len[r];
+  const int n = max(min(n_row, a.n_chunks * kTpChunk), 0);
+  const float* const row = a.scores + (int64_t)r * a.score_stride;
+  // the level-1 bins, and behind them the first scores of the wave's part of the row: whole load rounds of 256 scores, eight
+  // rounds (a word of 32 scores per lane) at a time; scores past the row's end are -inf
+  const float pr = a.p[r];
+  uint64_t bins[kBins1 / kTpThreads];
+  load_bins_of<kBins1, THREADS>(hrow, bins);
+  const int rounds = (n + 255) >> 8;
+  const int rd0 = rounds * wave / NW, rd1 = rounds * (wave + 1) / NW, words = (rd1 - rd0 + 7) >> 3;
+  float4 next[8];
+  auto fetch = [&](int w) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      next[u] = make_float4(ninf, ninf, ninf, ninf);
+      const int rd = rd0 + 8 * w + u, e = rd * 256 + lane * 4;
+      if (rd < rd1 && e < n) next[u] = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(row) + (uint32_t)e * 4u);
+    }
+  };
+  fetch(0);
+  for (int sub = 1; sub < a.n_sub; ++sub) {
+    uint64_t more[kBins1 / kTpThreads];
+    load_bins_of<kBins1, THREADS>(hrow + level1_copy_offset(sub), more);
+#pragma unroll
+    for (int i = 0; i < kBins1 / kTpThreads; ++i) bins[i] += more[i];
+  }
+  fill_exp_table(tab);
+  if (tid == 0) sh_n = 0;
+  auto clear_lh = [&]() __attribute__((always_inline)) {
+    for (int i = tid; i < kBins1; i += THREADS) lh[i] = 0;
+  };
+  clear_lh();
+  __syncthreads();
+
+  // one word after the other, the next one's scores in flight (behind the last one the first again, for the walk after this)
+  auto walk = [&](auto&& work) __attribute__((always_inline)) {
+#pragma unroll 1
+    for (int w = 0; w < words; ++w) {
+      float4 v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int left = n - (rd0 + 8 * w + u) * 256 - lane * 4;   // (a vector may straddle the row's end)
+        v[u].x = next[u].x;
+        v[u].y = left > 1 ? next[u].y : ninf;
+        v[u].z = left > 2 ? next[u].z : ninf;
+        v[u].w = left > 3 ? next[u].w : ninf;
+      }
+      fetch(w + 1 < words ? w + 1 : 0);
+      work(w, rd0 + 8 * w, v);
+    }
+  };
+  auto at = [](const float4& v, int k) __attribute__((always_inline)) { return k == 0 ? v.x : (k == 1 ? v.y : (k == 2 ? v.z : v.w)); };
+
+  int flags = pr >= 1.f ? 1 : (pr > 0.f ? 0 : -1);
+  const int shift = fixed_shift(n_row);
+  uint32_t prefix = 0;
+  float ref = 0.f;
+  uint64_t target = 1;
+  double above_base = 0.0, total_d = 1.0;
+  if (n <= 0) {
+    flags = 2;
+  } else if (flags == 0) {
+    // (a score pass that was given a bound of at most kTpChunk scores has left no level 1, see topp_common.h)
+    if (__builtin_expect(n <= kTpChunk, 0)) {
+      uint64_t some = 0;
+#pragma unroll
+      for (int i = 0; i < kBins1 / kTpThreads; ++i) some |= bins[i];
+      if (some) sh_n = 1;
+      __syncthreads();
+      const bool missing = sh_n == 0;
+      __syncthreads();
+      if (tid == 0) sh_n = 0;
+      if (missing) {
+        for (int i = tid; i < n; i += THREADS) level1_add(lh, row[i], shift, tab);
+        __syncthreads();
+        load_bins_of<kBins1, THREADS>(lh, bins);
+        __syncthreads();
+        clear_lh();
+      }
+      __syncthreads();
+    }
+    const Scan1Result s1 = scan_level1(bins, pr, sh_d, sh_i, sh_dres, tab);
+    if (s1.bin < 0) flags = 2;
+    else if (level1_bin_is_wide(s1.top)) flags = -2;
+    else { prefix = (uint32_t)s1.bin; ref = s1.ref; target = s1.target; above_base = s1.above_base; total_d = s1.total_d; }
+  }
+
+  float res_tau = ninf, res_mass = flags == 1 ? 1.f : 0.f;
+  uint32_t keep[WORDS];                                         // bit 31 - (4 u + k) of word w: score (first + u) * 256 + 4 lane + k
+#pragma unroll
+  for (int w = 0; w < WORDS; ++w) keep[w] = 0;
+  auto keep_word = [&](int w, uint32_t bits) __attribute__((always_inline)) {      // (w: the same for the whole wave)
+#pragma unroll
+    for (int i = 0; i < WORDS; ++i) keep[i] = i == w ? bits : keep[i];
+  };
+  if (flags == 0) {
+    // ---- level 2 ----
+    {
+      const KeyRange in = key_range(prefix << 21, (prefix << 21) | 0x1fffffu);
+      const uint32_t span = (uint32_t)in.hi - (uint32_t)in.lo;
+      float* const q = queue[wave];
+      int qn = 0;
+      auto weigh = [&](float s) __attribute__((always_inline)) {
+        const uint64_t w = fixed_weight(s, ref, shift, tab);
+        if (w) atomicAdd((unsigned long long*)&lh[(float_key(s) >> 10) & (kBins2 - 1)], (unsigned long long)w);
+      };
+      walk([&](int, int, const float4* v) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const float s = at(v[u], k);
+            const bool member = (__float_as_uint(s) ^ in.flip) - (uint32_t)in.lo <= span;
+            const uint64_t bal = __ballot(member);
+            if (member) q[qn + __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0))] = s;
+            qn += __popcll(bal);
+          }
+          if (u & 1) {
+            while (qn >= 64) {
+              qn -= 64;
+              weigh(q[qn + lane]);
+            }
+          }
+          __builtin_amdgcn_sched_barrier(0);      // (one round at a time: the ballots of all of them run out of scalar registers)
+        }
+      });
+      if (lane < qn) weigh(q[lane]);
+    }
+    __syncthreads();
+    load_bins_of<kBins2, THREADS>(lh, bins);
+    const ScanResult s2 = scan_from_top<kBins2>(bins, 0, target, sh_part, sh_res);
+    prefix = (prefix << 11) | (uint32_t)s2.bin;
+    clear_lh();
+    __syncthreads();
+    // ---- level 3 ----
+    {
+      const KeyRange in = key_range(prefix << 10, (prefix << 10) | 0x3ffu);
+      walk([&](int w, int first, const float4* v) __attribute__((always_inline)) {
+        uint32_t bits = 0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const float s = at(v[u], k);
+            const int32_t x = (int32_t)(__float_as_uint(s) ^ in.flip);
+            const bool ge = x >= in.lo;
+            bits = bits * 2u + (ge ? 1u : 0u);
+            if (ge && x <= in.hi) {                                 // (a handful per row)
+              const int slot = atomicAdd(&sh_n, 1);
+              if (slot < kEqCap) eq[slot] = make_uint2(float_key(s), (uint32_t)((first + u) * 256 + lane * 4 + k));
+            }
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        keep_word(w, bits);
+      });
+    }
+    __syncthreads();
+    const int listed = sh_n;
+    auto weigh3 = [&](uint32_t key) __attribute__((always_inline)) {
+      const uint64_t w = fixed_weight(key_float(key), ref, shift, tab);
+      if (w) atomicAdd((unsigned long long*)&lh[key & (kBins3 - 1)], (unsigned long long)w);
+    };
+    if (listed <= kEqCap) {
+      for (int i = tid; i < listed; i += THREADS) weigh3(eq[i].x);
+    } else {                                                        // hundreds of scores equal in their top 22 key bits
+      for (int i = tid; i < n; i += THREADS) {
+        const uint32_t key = float_key(row[i]);
+        if ((key >> 10) == prefix && row[i] != ninf) weigh3(key);
+      }
+    }
+    __syncthreads();
+    uint64_t bins3[kBins3 / kTpThreads];
+    load_bins_of<kBins3, THREADS>(lh, bins3);
+    const ScanResult s3 = scan_from_top<kBins3>(bins3, s2.above, target, sh_part, sh_res);
+    const uint32_t tkey = (prefix << 10) | (uint32_t)s3.bin;
+    res_tau = key_float(tkey);
+    res_mass = (float)((above_base + (double)(s3.above + s3.bin_mass)) / total_d);
+    // strike off the listed ones below the threshold
+    if (listed <= kEqCap) {
+      for (int i = 0; i < listed; ++i) {
+        const uint2 e = eq[i];
+        const int rd = (int)(e.y >> 8) - rd0, bit = 31 - (((rd & 7) << 2) | (int)(e.y & 3u));
+        if (e.x >= tkey || rd < 0 || rd0 + rd >= rd1 || (int)((e.y >> 2) & 63u) != lane) continue;
+#pragma unroll
+        for (int w = 0; w < WORDS; ++w)
+          if ((rd >> 3) == w) keep[w] &= ~(1u << bit);
+      }
+    } else {
+      const KeyRange in = key_range(tkey, 0xffffffffu);
+      walk([&](int w, int, const float4* v) __attribute__((always_inline)) {
+        uint32_t bits = 0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+#pragma unroll
+          for (int k = 0; k < 4; ++k) bits = bits * 2u + ((int32_t)(__float_as_uint(at(v[u], k)) ^ in.flip) >= in.lo ? 1u : 0u);
+        keep_word(w, bits);
+      });
+    }
+  } else if (flags == 1) {
+    walk([&](int w, int, const float4* v) __attribute__((always_inline)) {
+      uint32_t bits = 0;
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) bits = bits * 2u + (at(v[u], k) != ninf ? 1u : 0u);
+      keep_word(w, bits);
+    });
+  }
+
+  // ---- the kept positions, ascending: the waves' parts are in order, so is a wave's walk through its own ----
+  int mine = 0;
+#pragma unroll
+  for (int w = 0; w < WORDS; ++w) mine += __popc(keep[w]);
+  const int in_wave = wave_sum(mine);
+  if (lane == 0) sh_i[wave] = in_wave;
+  __syncthreads();
+  int base = 0, kept = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    if (w < wave) base += sh_i[w];
+    kept += sh_i[w];
+  }
+  int32_t* const out = a.sel_idx + (int64_t)r * a.sel_stride;
+#pragma unroll 1
+  for (int w = 0; w < words; ++w) {
+    const int first = rd0 + 8 * w;
+    uint32_t kw = 0;
+#pragma unroll
+    for (int i = 0; i < WORDS; ++i) kw = i == w ? keep[i] : kw;
+    uint64_t lo = 0, hi = 0;                                        // the rounds' counts, 16 bits each
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      lo |= (uint64_t)__popc((kw >> (28 - 4 * u)) & 0xFu) << (16 * u);
+      hi |= (uint64_t)__popc((kw >> (12 - 4 * u)) & 0xFu) << (16 * u);
+    }
+    const uint64_t ilo = wave_incl_scan(lo), ihi = wave_incl_scan(hi);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int sh = 16 * (u & 3);
+      const int incl = (int)(((u < 4 ? ilo : ihi) >> sh) & 0xFFFFu);
+      const uint32_t bits = (kw >> (28 - 4 * u)) & 0xFu;
+      int pos = base + incl - __popc(bits);
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (bits & (8u >> k)) out[pos++] = (first + u) * 256 + lane * 4 + k;
+      base += wave_last(incl);
+    }
+  }
+  if (tid == 0) {
+    a.sel_count[r] = (flags < 0 && n > 0) ? flags : kept;
+    if (a.tau) a.tau[r] = (flags < 0 && n > 0) ? __builtin_nanf("") : res_tau;
+    if (a.mass) a.mass[r] = res_mass;
+  }
+  if (a.rezero) {
+    for (int sub = 0; sub < a.n_sub; ++sub)
+      for (int i = tid; i < kBins1; i += THREADS) hrow[level1_copy_offset(sub) + i] = 0;
+  }
+}
+
+// Alone in its launch: 1024 threads, rows of up to 32 chunks.
+constexpr int kRowThreads = 1024, kRowWords = 8, kRowRideWords = 4;
+__global__ __launch_bounds__(kRowThreads) void topp_select_rows_kernel(const TopPArgs a) { select_row<kRowThreads, kRowWords>(a, blockIdx.x); }
+
+// The same with the local heads' work items behind the rows' workgroups (rtp_decode_attention); register budgets as in
+// topp_level_ride_kernel.
+template <int G, bool F16 = false, bool PAGED = false>
+__global__ __launch_bounds__(kTpThreads, G == 8 ? 2 : 4) void topp_select_rows_ride_kernel(const TopPArgs a, const AttnDecodeArgs la,
+                                                                                          const int n_ride, const int n_items) {
+  const int bid = blockIdx.x;
+  if (bid < a.R) select_row<kTpThreads, kRowRideWords>(a, bid);
+  else gqa_decode_items<G, kSrcLocal, kTpThreads, 1, F16, PAGED>(la, bid - a.R, n_ride, n_items);
+}
+
+// Attention over finished lists: a row's workgroups take equal shares of its kept positions (at most kTpChunk each, since
+// there are at least as many as the row has chunks) and leave one partial each for select_attend_combine_kernel.
+template <bool F16, bool PAGED>
+__global__ __launch_bounds__(kTpThreads) void gather_lists_kernel(const TopPArgs a, const GatherArgs ga) {
+  const int r = blockIdx.y, tid = threadIdx.x, part = blockIdx.x;
+  __shared__ int32_t sh_list[kTpChunk];
+  __shared__ int32_t sh_rows[PAGED ? kTpChunk : 1];
+  const int n = a.row_len[r];
+  const int parts = n > 0 ? (n + kTpChunk - 1) / kTpChunk * a.n_copy : 0;
+  if (part >= parts) return;
+  const int64_t kept = max(a.sel_count[r], 0);
+  const int lo = (int)(kept * part / parts), n_here = (int)(kept * (part + 1) / parts) - lo;
+  const int32_t* src = a.sel_idx + (int64_t)r * a.sel_stride + lo;
+  for (int i = tid; i < n_here; i += kTpThreads) sh_list[i] = src[i];
+  float M = -__builtin_huge_valf(), L = 0.f, A = 0.f;
+  attend_list<F16, PAGED>(ga, r, sh_list, sh_rows, n_here, M, L, A);
+  if (tid < kHeadDim) {
+    float* pout = ga.part + ((int64_t)r * gridDim.x + part) * kSaPart;
+    pout[4 + tid] = A;
+    if (tid == 0) { pout[0] = M; pout[1] = L; }
+  }
+}
+
 }  // namespace rtp
 
 using namespace rtp;
@@ -1340,6 +1687,62 @@ static int32_t launch_rows(const char* who, const TopPArgs& a, const GatherArgs*
   return check_launch(who);
 }
 
+static void launch_row_combine(const TopPArgs& a, const GatherArgs& ga, const AttnDecodeArgs* ride, int ride_G, hipStream_t s) {
+  if (!ride) {
+    RTP_LAUNCH(select_attend_combine_kernel<0>, dim3((unsigned)a.R), dim3(256), 0, s, a, ga, AttnDecodeArgs{});
+    return;
+  }
+  const dim3 grid((unsigned)(a.R + ride->units * ride_G));
+  if (ride_G == 2) RTP_LAUNCH(select_attend_combine_kernel<2>, grid, dim3(256), 0, s, a, ga, *ride);
+  else if (ride_G == 4) RTP_LAUNCH(select_attend_combine_kernel<4>, grid, dim3(256), 0, s, a, ga, *ride);
+  else RTP_LAUNCH(select_attend_combine_kernel<8>, grid, dim3(256), 0, s, a, ga, *ride);
+}
+
+// Rows whose level 1 is there: see select_row.
+// One workgroup goes through a row in about 0.5 us per 1000 scores with 512 threads (what the local heads' items allow beside
+// it), however many there are, where a launch per level spreads all rows over the chip: worth it where the rows are short or
+// fill the chip by themselves.  Whole steps, us, launches per level / whole rows: 4 rows of 16384 36.0 / 31.3, of 24000
+// 36.3 / 35.6, of 32768 36.1 / 36.7 (49000: 36.6 / 43.0); 32 rows of 32768 52.9 / 48.3, of 49000 58.8 / 59.7; 48 ragged rows
+// to 30011, paged, groups of 8 69.8 / 54.3, to 49000 62.2 / 58.2; 64 of 65536 110.9 / 101.8, but 64 ragged rows to 131072
+// 93.5 / 115; 160 of 131072 391 / 368; 256 ragged rows to 262144 1435 / 1346.  (The gather gains by equal shares of
+// each row's kept tokens in place of what its chunk holds: 32.5 -> 26.9 us on batch 8 x 131072.)
+static bool whole_rows(int32_t R, int64_t n_chunks, bool ride) {
+  const int64_t most = (int64_t)32 * (ride ? kRowRideWords * kTpThreads : kRowWords * kRowThreads) / kTpChunk;
+  return n_chunks <= most && (n_chunks <= 3 || R >= 8 * n_chunks);
+}
+static int32_t launch_whole_rows(const char* who, TopPArgs& a, const GatherArgs* attend, const AttnDecodeArgs* ride, int ride_G,
+                                 hipStream_t s) {
+  const dim3 block(kTpThreads);
+  const bool f16 = attend && attend->f16, paged = attend && attend->page_table;
+  if (ride) {
+    const int n_items = ride->units * ride->n_splits, n_ride = std::min(n_items, 256);
+    const dim3 grid((unsigned)(a.R + n_ride));
+#define RTP_RIDE(GG)                                                                                                         \
+  do {                                                                                                                        \
+    if (f16 && paged) RTP_LAUNCH((topp_select_rows_ride_kernel<GG, true, true>), grid, block, 0, s, a, *ride, n_ride, n_items);    \
+    else if (f16) RTP_LAUNCH((topp_select_rows_ride_kernel<GG, true, false>), grid, block, 0, s, a, *ride, n_ride, n_items);       \
+    else if (paged) RTP_LAUNCH((topp_select_rows_ride_kernel<GG, false, true>), grid, block, 0, s, a, *ride, n_ride, n_items);     \
+    else RTP_LAUNCH(topp_select_rows_ride_kernel<GG>, grid, block, 0, s, a, *ride, n_ride, n_items);                           \
+  } while (0)
+    if (ride_G == 2) RTP_RIDE(2);
+    else if (ride_G == 4) RTP_RIDE(4);
+    else RTP_RIDE(8);
+#undef RTP_RIDE
+  } else {
+    RTP_LAUNCH(topp_select_rows_kernel, dim3((unsigned)a.R), dim3(kRowThreads), 0, s, a);
+  }
+  if (attend) {
+    a.n_copy = attend->max_copy;
+    const dim3 grid((unsigned)(a.n_chunks * a.n_copy), (unsigned)a.R);
+    if (f16 && paged) RTP_LAUNCH((gather_lists_kernel<true, true>), grid, block, 0, s, a, *attend);
+    else if (f16) RTP_LAUNCH((gather_lists_kernel<true, false>), grid, block, 0, s, a, *attend);
+    else if (paged) RTP_LAUNCH((gather_lists_kernel<false, true>), grid, block, 0, s, a, *attend);
+    else RTP_LAUNCH((gather_lists_kernel<false, false>), grid, block, 0, s, a, *attend);
+    launch_row_combine(a, *attend, ride, ride_G, s);
+  }
+  return check_launch(who);
+}
+
 // Shared body of rtp_topp_select (p != NULL) and rtp_topk_select (kcount != NULL).
 static int32_t run_select(const char* who, const float* scores, int64_t score_stride, const int32_t* row_len,
                           const float* p, const int32_t* kcount, int32_t R, int64_t max_len,
@@ -1389,6 +1792,7 @@ static int32_t run_select(const char* who, const float* scores, int64_t score_st
   hipStream_t s = (hipStream_t)stream;
   if (a.n_chunks == 1) return launch_rows(who, a, attend, ride, ride_G, s);
   dim3 grid((unsigned)a.n_chunks, (unsigned)R), block(kTpThreads);
+  if (level1_ready && whole_rows(R, a.n_chunks, ride != nullptr)) return launch_whole_rows(who, a, attend, ride, ride_G, s);
   if (!level1_ready) {
     const int64_t nz = (int64_t)R * l.hist_stride;
     RTP_LAUNCH(topp_zero_kernel, dim3((unsigned)((nz + kTpThreads - 1) / kTpThreads)), block, 0, s, a.hist, nz);
@@ -1426,14 +1830,7 @@ static int32_t run_select(const char* who, const float* scores, int64_t score_st
     else if (attend->f16) RTP_LAUNCH((topp_write_kernel<true, true>), ggrid, block, 0, s, a, *attend);
     else if (paged) RTP_LAUNCH((topp_write_kernel<true, false, true>), ggrid, block, 0, s, a, *attend);
     else RTP_LAUNCH(topp_write_kernel<true>, ggrid, block, 0, s, a, *attend);
-    if (ride) {
-      const dim3 cgrid((unsigned)(R + ride->units * ride_G));
-      if (ride_G == 2) RTP_LAUNCH(select_attend_combine_kernel<2>, cgrid, dim3(256), 0, s, a, *attend, *ride);
-      else if (ride_G == 4) RTP_LAUNCH(select_attend_combine_kernel<4>, cgrid, dim3(256), 0, s, a, *attend, *ride);
-      else RTP_LAUNCH(select_attend_combine_kernel<8>, cgrid, dim3(256), 0, s, a, *attend, *ride);
-    } else {
-      RTP_LAUNCH(select_attend_combine_kernel<0>, dim3((unsigned)R), dim3(256), 0, s, a, *attend, AttnDecodeArgs{});
-    }
+    launch_row_combine(a, *attend, ride, ride_G, s);
   } else {
     RTP_LAUNCH(topp_write_kernel<false>, grid, block, 0, s, a, GatherArgs{});
   }

@@ -691,3 +691,63 @@ def test_level1_with_bounds_on_either_side_of_one_chunk(score_bound, select_boun
         for r in range(run.R):
             n = int(run.sel_count[r])
             assert n > 0 and torch.equal(run.sel_idx[r, :n], ref.sel_idx[r, :n]), (a, b, r)
+
+
+@pytest.mark.parametrize("n_ret,ctx", [
+    (2, (8193, 300, 16384, 1)),                                             # 2 chunks: rows that end on, before and behind a chunk
+    (2, (24576, 8192, 255, 257, 24575)),                                    # 3 chunks, the most that any number of rows may have
+    (8, (32768, 30001, 513, 9000)),                                         # 4 chunks, 32 rows
+    (16, (36870, 36864, 2049, 20000, 64))])                                 # 5 chunks, 80 rows
+def test_whole_row_selection_equals_the_levels_by_launch(n_ret, ctx):
+    """Rows that one workgroup selects behind the score pass's level 1 against the launches per level (level1_ready = 0), which
+    the oracle tests above hold: every output bit, twice over the same workspace, and once more as one call with the attention.
+    Scores are sums of two bf16 values, chosen row by row: broad, tied in thousands, all equal, below zero, tiny, with minus
+    infinity, with one spike, beyond what the selector accepts; p from 0 (refused) to 1."""
+    print(f"[case] whole rows, {n_ret} heads, {ctx}", flush=True)
+    g = torch.Generator().manual_seed(sum(ctx))
+    w = wl.small_decode("cpu", seed=241, n_q_heads=32, n_kv_heads=8, ret_heads=tuple(range(0, 32, 32 // n_ret)), ctx=ctx, p=(0.9,))
+    w.qI.zero_()
+    w.qI[..., :2] = 1.0
+    laws = [lambda n: torch.randn(n, generator=g) * 2, lambda n: (torch.randn(n, generator=g) * 4).round() / 4,
+            lambda n: torch.full((n,), -3.0), lambda n: torch.randn(n, generator=g) - 20, lambda n: torch.randn(n, generator=g) * 1e-3,
+            lambda n: torch.randn(n, generator=g).masked_fill_(torch.rand(n, generator=g) < 0.3, -np.inf),
+            lambda n: torch.cat([torch.full((1,), 30.0), torch.randn(n - 1, generator=g)]), lambda n: torch.randn(n, generator=g) * 100]
+    ps = [0.9, 0.3, 0.99, 1.0, 0.0, 0.99999]
+    w.kI.zero_()
+    for b in range(w.B):
+        for j in range(n_ret):
+            r = b * n_ret + j
+            n, t0 = ctx[b], w.seq_start[b]
+            s = laws[r % len(laws)](n)
+            hi = s.to(torch.bfloat16)
+            w.kI[j, t0:t0 + n, 0] = hi
+            w.kI[j, t0:t0 + n, 1] = torch.where(torch.isinf(s), torch.zeros(()), s - hi.float()).to(torch.bfloat16)
+            w.p_rows[r] = ps[r % len(ps)]
+    w = w.to(DEV)
+    ref = DecodeRun(w, fuse_level1=False)
+    ref.index_score()
+    ref.topp()
+    ref.sparse_attn()
+    run = DecodeRun(w)
+
+    def same(rep):
+        torch.cuda.synchronize()
+        assert torch.equal(run.sel_count, ref.sel_count), rep
+        assert torch.equal(run.tau.view(torch.int32), ref.tau.view(torch.int32)), rep
+        assert torch.equal(run.mass.view(torch.int32), ref.mass.view(torch.int32)), rep
+        for r in range(run.R):
+            n = max(int(run.sel_count[r]), 0)
+            assert torch.equal(run.sel_idx[r, :n], ref.sel_idx[r, :n]), (rep, r)
+            assert (run.sel_idx[r, n:] == -7).all(), (rep, r)
+
+    for rep in range(3):
+        run.sel_idx.fill_(-7)
+        run.sel_count.fill_(-9)
+        run.index_score()
+        if rep < 2:
+            run.topp()
+        else:
+            run.decode_attention()
+        same(rep)
+    a, b = run.out[:, w.layer.ret_heads].float(), ref.out[:, w.layer.ret_heads].float()
+    assert ((a - b).abs() <= 2.0 ** -7 * torch.maximum(a.abs(), b.abs()) + 1e-5).all()
