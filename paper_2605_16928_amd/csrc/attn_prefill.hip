@@ -152,11 +152,15 @@ __device__ __forceinline__ float max16_nn(const float (&v)[16]) {
 // and maxima in two short chains: 4096 queries at 128K, 28 heads: 241 -> 175 to 205 us (590 to 690 TFLOP/s); 333 queries: 89 -> 82 us; a
 // prompt of 2037 with 6 heads: 31.5 -> 29 us.  Measured without gain: four buffers, three tiles ahead (92 and 32 us: memory
 // latency is not the limit); the band on the wide kernel (twice as long: its masked blocks leave the pipelined path).
-template <bool F16>
-__global__ __launch_bounds__(kPfThreads, 2) void flash_prefill_local_kernel(const PrefillArgs a) {
-  __shared__ __attribute__((aligned(16))) unsigned char smem[2 * kPfTileBytes];
+// GROUPS = 2, for launches of at most one workgroup per compute unit: a second group of four waves takes every other tile of the
+// same queries, with buffers and a running maximum of its own, and the first one merges the two at the end.
+template <bool F16, int GROUPS>
+__global__ __launch_bounds__(kPfThreads * GROUPS, 2) void flash_prefill_local_kernel(const PrefillArgs a) {
+  __shared__ __attribute__((aligned(16))) unsigned char smem_all[GROUPS * 2 * kPfTileBytes];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int grp = GROUPS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / kPfThreads);
+  unsigned char* const smem = smem_all + grp * 2 * kPfTileBytes;
+  const int tid = (int)threadIdx.x - grp * kPfThreads, lane = tid & 63, wave = tid >> 6;
   const int g = lane >> 5, r = lane & 31;
   const int h = a.heads[blockIdx.x];
   const int b = blockIdx.z;
@@ -334,25 +338,48 @@ __global__ __launch_bounds__(kPfThreads, 2) void flash_prefill_local_kernel(cons
   };
 
   {
-    // Software pipeline: the loads of tile it + 1 are in flight while tile it is computed from the other buffer.
+    // Software pipeline: the loads of the group's next tile are in flight while this one is computed from the other buffer.
+    // (Steps are counted alike in both groups: the barriers are the workgroup's.)
+    const int steps = (n_tiles + GROUPS - 1) / GROUPS;
+    auto tile_of = [&](int i) { return i * GROUPS + grp; };
     auto tile_n0 = [&](int it) { return (it < ks_end ? it : kt_w0 + (it - ks_end)) * kPfK; };
-    auto landed = [&](int it) __attribute__((always_inline)) {       // publishes tile it
+    auto landed = [&](int i) __attribute__((always_inline)) {        // publishes the tiles of step i
       loads_landed();
       __syncthreads();
-      const int n0 = tile_n0(it);
-      if (n0 + kPfK - 1 > m_hi) {
-        zero_past(n0, it & 1);
+      const int n0 = tile_n0(tile_of(i));
+      // (the last tile alone, in the last step)
+      if (GROUPS == 1 ? n0 + kPfK - 1 > m_hi : i == steps - 1) {
+        if (tile_of(i) < n_tiles) zero_past(n0, i & 1);
         __syncthreads();
       }
     };
-    if (n_tiles > 0) {
-      load_tile(tile_n0(0), 0);
-      landed(0);
+    if (tile_of(0) < n_tiles) load_tile(tile_n0(tile_of(0)), 0);
+    if (n_tiles > 0) landed(0);
+    for (int i = 0; i < steps; ++i) {
+      if (tile_of(i + 1) < n_tiles) load_tile(tile_n0(tile_of(i + 1)), (i + 1) & 1);
+      if (GROUPS == 1 || tile_of(i) < n_tiles) compute_tile(i & 1, tile_n0(tile_of(i)));
+      if (i + 1 < steps) landed(i + 1);
     }
-    for (int it = 0; it < n_tiles; ++it) {
-      if (it + 1 < n_tiles) load_tile(tile_n0(it + 1), (it + 1) & 1);
-      compute_tile(it & 1, tile_n0(it));
-      if (it + 1 < n_tiles) landed(it + 1);
+  }
+  if constexpr (GROUPS == 2) {
+    // group 1 leaves its state, register by register, in the tile buffers; group 0 goes on with both
+    __syncthreads();
+    float* const sh = reinterpret_cast<float*>(smem_all) + tid;
+    if (grp == 1) {
+      sh[0] = mrow;
+      sh[kPfThreads] = lrow;
+#pragma unroll
+      for (int i = 0; i < 64; ++i) sh[(2 + i) * kPfThreads] = O[i >> 4][i & 15];
+    }
+    __syncthreads();
+    if (grp == 1) return;
+    const float m1 = sh[0], l1 = sh[kPfThreads], mnew = fmaxf(mrow, m1);
+    if (mnew != ninf) {
+      const float c0 = fast_exp2((mrow - mnew) * c), c1 = fast_exp2((m1 - mnew) * c);
+      lrow = lrow * c0 + l1 * c1;
+#pragma unroll
+      for (int i = 0; i < 64; ++i) O[i >> 4][i & 15] = O[i >> 4][i & 15] * c0 + sh[(2 + i) * kPfThreads] * c1;
+      mrow = mnew;
     }
   }
 
@@ -1862,8 +1889,11 @@ static int32_t launch_prefill(const char* who, bool local, PrefillArgs& a, int32
   dim3 grid((unsigned)a.n_heads, (unsigned)((a.n_q + qt - 1) / qt), (unsigned)(B * (local ? 1 : a.n_splits * a.n_sub)));
   if (grid.y > 65535 || grid.z > 65535) return fail(RTP_ERR_INVALID_ARG, "%s: n_q / B too large for one launch", who);
   if (local) {
-    if (a.f16) RTP_LAUNCH(flash_prefill_local_kernel<true>, grid, dim3(kPfThreads), 0, s, a);
-    else RTP_LAUNCH(flash_prefill_local_kernel<false>, grid, dim3(kPfThreads), 0, s, a);
+    if ((int64_t)grid.x * grid.y * grid.z <= compute_units()) {
+      if (a.f16) RTP_LAUNCH((flash_prefill_local_kernel<true, 2>), grid, dim3(2 * kPfThreads), 0, s, a);
+      else RTP_LAUNCH((flash_prefill_local_kernel<false, 2>), grid, dim3(2 * kPfThreads), 0, s, a);
+    } else if (a.f16) RTP_LAUNCH((flash_prefill_local_kernel<true, 1>), grid, dim3(kPfThreads), 0, s, a);
+    else RTP_LAUNCH((flash_prefill_local_kernel<false, 1>), grid, dim3(kPfThreads), 0, s, a);
   } else if (a.f16) RTP_LAUNCH((flash_prefill_wide_kernel<kModeDense, true>), grid, dim3(kPwThreads), 0, s, a);
   else RTP_LAUNCH(flash_prefill_wide_kernel<kModeDense>, grid, dim3(kPwThreads), 0, s, a);
   if (!local && a.n_splits * a.n_sub > 1) launch_prefill_combine(a, s);

@@ -527,3 +527,27 @@ def test_short_chunk_in_the_workspace_of_a_whole_chunk(p):
     if p >= 1.0:
         names, o, l, _ = go(one_range - 256)
         assert len(names) == 1 and (l - own[2]).abs().max() < 1e-4
+
+
+@pytest.mark.parametrize("T,heads", [(1, 64), (130, 64), (600, 64), (560, 128)])
+@pytest.mark.parametrize("kv_dtype", ["bf16", "fp16"])
+def test_local_prefill_one_and_two_wave_groups(T, heads, kv_dtype):
+    """Launches of at most one workgroup per compute unit give a query's band to two groups of waves, larger ones (600 and 560
+    queries of 60 and 120 heads: more than 256 workgroups) to one: odd and even numbers of key tiles, ragged ends, sinks outside
+    the band."""
+    print(f"[case] local prefill, T {T}, {heads} heads, {kv_dtype}", flush=True)
+    w = wl.small_prefill(DEV, chunk_start=777, T=T, n_q_heads=heads, n_kv_heads=heads // 8, ret_heads=tuple(range(0, heads, heads // 4)),
+                         sink=4, window=300, seed=191 + T, kv_dtype=kv_dtype)
+    L = w.layer
+    run = PrefillRun(w)
+    run.out.fill_(5.0)
+    run.local_attn()
+    torch.cuda.synchronize()
+    local = [h for h in range(heads) if h not in L.ret_heads]
+    rows = [(t, h) for t in sorted({0, 1, 31, 32, 127, 128, 129, T // 2, T - 2, T - 1} & set(range(T))) for h in local[::17] + local[-1:]]
+    ref = orc.prefill_rows(rows=rows, p=1.0, **prefill_oracle_inputs(w))
+    got, lse = run.out.float().cpu().numpy().astype(np.float64), run.lse.cpu().numpy()
+    for r in ref:
+        check_out(got[r["t"], r["h"]], r["out"], f"t{r['t']} h{r['h']}", tight="mfma")
+        assert abs(lse[r["t"], r["h"]] - r["lse"]) < 3e-3
+    assert (run.out[:, list(L.ret_heads)] == 5.0).all()
