@@ -1105,10 +1105,12 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
 // and every stream began by waiting for its first LDS operands, all eight waves at once; in the loop a stream reads
 // the next one's first operands.  Attention launch of 4 heads x 4096 queries at 128K tokens: 1300 -> 1066 us selecting,
 // 1250 -> 918 us dense (1.18 PFLOP/s); last 8192-query chunk of 1M tokens, selecting: 20.3 -> 17.3 to 17.7 ms (operands three
-// and two steps ahead instead of five and four: 17.7 and 1141 us).  What bounds it now is the sum of what the
-// two waves of a SIMD issue -- per 32 x 32 block 16 MFMAs of 32 cycles, 24 LDS reads and, by the counters, 64 (dense) or 122
-// (selecting) other vector instructions --, with the matrix pipe busy 59 and 48 % of the cycles and the LDS, at the rates
-// of these reads, about half of them.
+// and two steps ahead instead of five and four: 17.7 and 1141 us).  Per 32 x 32 block the two waves of a SIMD issue 16 MFMAs
+// of 32 cycles, 24 LDS reads and, by the counters, 64 (dense) or 122 (selecting) other vector instructions each, with the matrix
+// pipe busy 59 and 48 % of the cycles and the LDS, at the rates of these reads, about half of them.  Spreading a block's softmax
+// over both streams (it used to run beside the PV MFMAs alone) took the dense call of this shape from 1132 to 1124 us, 333
+// queries' launch from 132 to 129 and left the last chunk of 1M as it was: at a die clock of 1.75 GHz, against 2.4 when idle,
+// the launch has come to what the chip's power allows.
 constexpr int kPwQ = 256;
 constexpr int kPwThreads = 512;
 constexpr int kPwStages = 3;
@@ -1296,11 +1298,10 @@ __global__ __launch_bounds__(kPwThreads, 2) void flash_prefill_wide_kernel(const
       S = mfma32<F16>(ka, qreg[kk], S);
     }
   };
-  // The same MFMAs with their K operands read kAheadK steps ahead and a slice of other work (issuing the loads of a
-  // later tile) between every pair; scheduling fences keep the order.  In the steady loop the first operands were
-  // read during the stream before (ka_first; likewise va_first for the PV stream): with every wave of the workgroup at
-  // the same place (the barrier in every tile) nothing else covers their LDS latency.
-  constexpr int kAheadK = 5, kAheadV = 4;
+  // In the steady loop K operands are read kAheadK steps ahead, V operands kAheadV, the first ones during the stream before
+  // (ka_first, va_first): with every wave of the workgroup at the same place (the barrier in every tile) nothing else covers
+  // their LDS latency.
+  constexpr int kAheadK = 5, kAheadV = 4, kPairsPV = 4;
   u32x4 ka_first[kAheadK];
   s16x8 va_first[kAheadV];
   auto first_k = [&](const unsigned char* tile, int kb) __attribute__((always_inline)) {
@@ -1310,20 +1311,6 @@ __global__ __launch_bounds__(kPwThreads, 2) void flash_prefill_wide_kernel(const
   auto first_v = [&](const unsigned char* tile, int kb) __attribute__((always_inline)) {
 #pragma unroll
     for (int k = 0; k < kAheadV; ++k) va_first[k] = read_v(tile, kb, k >> 2, k & 3);
-  };
-  auto scores_beside = [&](const unsigned char* tile, int kb, f32x16& S, auto&& work) __attribute__((always_inline)) {
-    u32x4 ka[8];
-#pragma unroll
-    for (int kk = 0; kk < kAheadK; ++kk) ka[kk] = ka_first[kk];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) S[i] = 0.f;
-#pragma unroll
-    for (int kk = 0; kk < 8; ++kk) {
-      if (kk + kAheadK < 8) ka[kk + kAheadK] = read_k(tile, kb, kk + kAheadK);
-      S = mfma32<F16>(ka[kk], qreg[kk], S);
-      work(kk);
-      __builtin_amdgcn_sched_barrier(0);
-    }
   };
   // O^T += V^T P^T for key block kb of the staged tile
   auto mfma_PV = [&](const unsigned char* tile, int kb, const uint32_t (&P)[8]) __attribute__((always_inline)) {
@@ -1381,20 +1368,35 @@ __global__ __launch_bounds__(kPwThreads, 2) void flash_prefill_wide_kernel(const
     }
     lrow += lsum;
   };
-  // The steady-state step: the PV MFMAs of the previous block and the softmax of the current block as
-  // ONE hand-interleaved instruction sequence -- per MFMA (32 cycles of the matrix pipe) one pair of
-  // probabilities (2 fma, 2 exp, 1 convert, 1 packed dot product on the vector ALU); scheduling fences
-  // keep the compiler from regrouping it, V^T operands are read kAheadV steps ahead (the first ones are in va_first)
-  // and, at its end, the first K operands of the score MFMAs that follow (block next_kb of next_tile).  SEL (the
-  // selecting mode): the block's index-score MFMAs in front and every probability gated by its query's keep test
-  // (one compare, one select, one add for the count per probability).
+  // The steady-state step, two hand-interleaved streams over which the block's 16 probabilities are spread, so that each MFMA
+  // (32 cycles of the matrix pipe) has about one of them beside it (1 fma, 1 exp, half a convert and half a packed dot product on
+  // the vector ALU): pv_beside_softmax runs the PV MFMAs of the previous block and the first pairs, scores_beside_softmax
+  // the score MFMAs of the next block and the rest.  Scheduling fences keep the compiler from regrouping them; V^T operands are
+  // read kAheadV steps ahead (the first ones are in va_first) and, at the first stream's end, the first K operands of
+  // the second (block next_kb of next_tile).  SEL (the selecting mode): the block's index-score MFMA in front and every
+  // probability gated by its query's keep test (one compare, one select, one add for the count per probability).
+  f32x16 SI;
+  float mc, l_blk;
+  int cnt_blk;
+  auto pair = [&](auto sel_tag, int k, const f32x16& S, uint32_t (&Pout)[8]) __attribute__((always_inline)) {
+    constexpr bool SEL = decltype(sel_tag)::value;
+    float p0 = fast_exp2(fmaf(S[2 * k], c, -mc));
+    float p1 = fast_exp2(fmaf(S[2 * k + 1], c, -mc));
+    if (SEL) {
+      const bool k0 = SI[2 * k] >= selThr, k1 = SI[2 * k + 1] >= selThr;
+      p0 = k0 ? p0 : 0.f;
+      p1 = k1 ? p1 : 0.f;
+      cnt_blk += (k0 ? 1 : 0) + (k1 ? 1 : 0);
+    }
+    Pout[k] = pack16<F16>(p0, p1);
+    row_sum_add(l_blk, Pout[k]);
+  };
   auto pv_beside_softmax = [&](auto sel_tag, const unsigned char* tile, int kb, const uint32_t (&Pin)[8], const f32x16& S,
                                uint32_t (&Pout)[8], const u32x4 ki, const unsigned char* next_tile, int next_kb) __attribute__((always_inline)) {
     constexpr bool SEL = decltype(sel_tag)::value;
-    f32x16 SI;
-    const float mc = mrow * c;
-    float l = 0.f;
-    int cnt = 0;
+    mc = mrow * c;
+    l_blk = 0.f;
+    cnt_blk = 0;
     if (SEL) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) SI[i] = 0.f;
@@ -1411,23 +1413,29 @@ __global__ __launch_bounds__(kPwThreads, 2) void flash_prefill_wide_kernel(const
       if (k == 8 - kAheadV) first_k(next_tile, next_kb);
       const u32x4 pb = (u32x4){Pin[4 * tt], Pin[4 * tt + 1], Pin[4 * tt + 2], Pin[4 * tt + 3]};
       O[db] = mfma32<F16>(__builtin_bit_cast(u32x4, va[k]), pb, O[db]);
-      {
-        float p0 = fast_exp2(fmaf(S[2 * k], c, -mc));
-        float p1 = fast_exp2(fmaf(S[2 * k + 1], c, -mc));
-        if (SEL) {
-          const bool k0 = SI[2 * k] >= selThr, k1 = SI[2 * k + 1] >= selThr;
-          p0 = k0 ? p0 : 0.f;
-          p1 = k1 ? p1 : 0.f;
-          cnt += (k0 ? 1 : 0) + (k1 ? 1 : 0);
-        }
-        Pout[k] = pack16<F16>(p0, p1);
-        row_sum_add(l, Pout[k]);
-      }
+      if (k & 1) { if (k / 2 < kPairsPV) pair(sel_tag, k / 2, S, Pout); }
       __builtin_amdgcn_sched_barrier(0);
     }
-    row_sum_settled(l);
-    lrow += l;
-    if (SEL) sel_cnt += cnt;
+  };
+  auto scores_beside_softmax = [&](auto sel_tag, const unsigned char* tile, int kb, f32x16& Snext, const f32x16& S, uint32_t (&Pout)[8],
+                                   auto&& work) __attribute__((always_inline)) {
+    constexpr bool SEL = decltype(sel_tag)::value;
+    u32x4 ka[8];
+#pragma unroll
+    for (int kk = 0; kk < kAheadK; ++kk) ka[kk] = ka_first[kk];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) Snext[i] = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) {
+      if (kk + kAheadK < 8) ka[kk + kAheadK] = read_k(tile, kb, kk + kAheadK);
+      Snext = mfma32<F16>(ka[kk], qreg[kk], Snext);
+      work(kk);
+      if (kk & 1) { if (kPairsPV + kk / 2 < 8) pair(sel_tag, kPairsPV + kk / 2, S, Pout); }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    row_sum_settled(l_blk);
+    lrow += l_blk;
+    if (SEL) sel_cnt += cnt_blk;
   };
   // does the 32-key block starting at nb0 need per-element masks for some query of this wave?
   auto needs_mask = [&](int nb0) __attribute__((always_inline)) {
@@ -1545,20 +1553,23 @@ __global__ __launch_bounds__(kPwThreads, 2) void flash_prefill_wide_kernel(const
     auto steady = [&]() __attribute__((always_inline)) { return it < it_hi && n_t0 + kPfK - 1 <= m_lo && n_t2 + kPfK - 1 <= m_hi; };
     if (steady()) {
       if (m_w_hi >= m_w_lo) {
+        f32x16 S1;
         first_v(tile_at(it - 1), 1);
         do {
-          pv_beside_softmax(std::integral_constant<bool, SPARSE>{}, tile_at(it - 1), 1, P1, S, P0, ki0, tile_at(it), 1);
-          scores_beside(tile_at(it), 1, S, [&](int) __attribute__((always_inline)) {});
+          constexpr std::integral_constant<bool, SPARSE> sel{};
+          pv_beside_softmax(sel, tile_at(it - 1), 1, P1, S, P0, ki0, tile_at(it), 1);
+          scores_beside_softmax(sel, tile_at(it), 1, S1, S, P0, [&](int) __attribute__((always_inline)) {});
           first_v(tile_at(it), 0);
           loads_landed();
           __syncthreads();
-          pv_beside_softmax(std::integral_constant<bool, SPARSE>{}, tile_at(it), 0, P0, S, P1, ki1, tile_at(it + 1), 0);
+          pv_beside_softmax(sel, tile_at(it), 0, P0, S1, P1, ki1, tile_at(it + 1), 0);
           if (SPARSE) {                                    // the next tile's index keys: a tile's time to arrive
             ki0 = load_ki(n_t1);
             ki1 = load_ki(n_t1 + 32);
           }
           const int n2 = n_t2, s2 = slot_of(it + 2);
-          scores_beside(tile_at(it + 1), 0, S, [&](int kk) __attribute__((always_inline)) { if (kk < 2 * GH) load_piece_full(n2, s2, kk); });
+          scores_beside_softmax(sel, tile_at(it + 1), 0, S, S1, P1,
+                                [&](int kk) __attribute__((always_inline)) { if (kk < 2 * GH) load_piece_full(n2, s2, kk); });
           first_v(tile_at(it), 1);
           next_tiles(it);
           ++it;
