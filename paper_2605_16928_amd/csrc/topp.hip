@@ -131,26 +131,16 @@ __device__ __forceinline__ void load_bins_of(const uint64_t* __restrict__ h, uin
   }
 }
 
-__device__ __forceinline__ Scan1Result scan_level1(const uint64_t (&loc)[kBins1 / kTpThreads], float p, double* sh_d /*[4]*/,
-                                                   int* sh_i /*[4]*/, double* sh_res /*[3]*/,
-                                                   const double* __restrict__ tab /* filled by the caller */) {
+// `top`: the highest bin that holds a score (-1: none).  The caller puts a barrier before the next use of sh_d and sh_res.
+__device__ __forceinline__ Scan1Result scan_level1_from(const uint64_t (&loc)[kBins1 / kTpThreads], const int top, float p,
+                                                        double* sh_d /*[waves]*/, double* sh_res /*[3]*/,
+                                                        const double* __restrict__ tab /* filled by the caller */) {
   constexpr int per = kBins1 / kTpThreads;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int first = (kTpThreads - 1 - tid) * per;     // this thread's lowest bin
-  int top = -1;
-#pragma unroll
-  for (int i = 0; i < per; ++i) {
-    if (loc[i]) top = first + i;
-  }
-  top = wave_max_ge_m1(top);
-  if (lane == 0 && wave < kTpThreads / 64) sh_i[wave] = top;
-  __syncthreads();
-  top = sh_i[0];
-#pragma unroll
-  for (int w = 1; w < kTpThreads / 64; ++w) top = max(top, sh_i[w]);
   Scan1Result res;
   res.bin = -1; res.top = top; res.above_base = 0.0; res.total_d = 0.0; res.target = 1; res.ref = 0.f;
-  if (top < 0) { __syncthreads(); return res; }       // uniform: every thread sees the same `top`
+  if (top < 0) return res;                            // uniform: every thread sees the same `top`
   const double R = (double)bin_ref(top);
   double md[per];
   double sum = 0.0;
@@ -220,6 +210,27 @@ __device__ __forceinline__ Scan1Result scan_level1(const uint64_t (&loc)[kBins1 
   res.total_d = total * scale;
   res.target = tgt;
   res.ref = ref1;
+  return res;
+}
+
+__device__ __forceinline__ Scan1Result scan_level1(const uint64_t (&loc)[kBins1 / kTpThreads], float p, double* sh_d /*[4]*/,
+                                                   int* sh_i /*[4]*/, double* sh_res /*[3]*/,
+                                                   const double* __restrict__ tab /* filled by the caller */) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int per = kBins1 / kTpThreads;
+  const int first = (kTpThreads - 1 - tid) * per;     // this thread's lowest bin
+  int top = -1;
+#pragma unroll
+  for (int i = 0; i < per; ++i) {
+    if (loc[i]) top = first + i;
+  }
+  top = wave_max_ge_m1(top);
+  if (lane == 0 && wave < kTpThreads / 64) sh_i[wave] = top;
+  __syncthreads();
+  top = sh_i[0];
+#pragma unroll
+  for (int w = 1; w < kTpThreads / 64; ++w) top = max(top, sh_i[w]);
+  const Scan1Result res = scan_level1_from(loc, top, p, sh_d, sh_res, tab);
   __syncthreads();
   return res;
 }
@@ -609,9 +620,9 @@ __device__ __forceinline__ int write_ranked(uint32_t keep, int before, int32_t* 
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
     lo |= (uint64_t)__popc((keep >> (u * 4)) & 0xFu) << (16 * u);
-    hi |= (uint64_t)__popc((keep >> (16 + u * 4)) & 0xFu) << (16 * u);
+    if (kTpVec > 4) hi |= (uint64_t)__popc((keep >> (16 + u * 4)) & 0xFu) << (16 * u);
   }
-  const uint64_t ilo = wave_incl_scan(lo), ihi = wave_incl_scan(hi);
+  const uint64_t ilo = wave_incl_scan(lo), ihi = kTpVec > 4 ? wave_incl_scan(hi) : 0;
   if ((tid & 63) == 63) { sh_tot[tid >> 6][0] = ilo; sh_tot[tid >> 6][1] = ihi; }
   __syncthreads();
   int round_base = before;
@@ -676,11 +687,26 @@ constexpr int kSaInFlight = 8;             // K/V rows in flight per 16-lane gro
                                            // or more rows, measured no faster: the gather is bandwidth-bound)
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
+// What a row's attention needs beside its list, fetched at the start of a launch: behind the list it would be two more round
+// trips (a step of 4096 tokens 20.0 -> 19.4 us).
+struct AttendRow {
+  int64_t seq0;              // first token of the row's sequence (0 with pages)
+  u32x4 q;                   // this lane's 8 dims
+};
+template <bool PAGED>
+__device__ __forceinline__ AttendRow attend_row(const GatherArgs& ga, const int r) {
+  const int b = r / ga.n_ret, h = ga.ret_heads[r - b * ga.n_ret];
+  AttendRow ar;
+  ar.seq0 = PAGED ? 0 : ga.seq_start[b];
+  ar.q = *reinterpret_cast<const u32x4*>(ga.q + ((int64_t)b * ga.n_q_heads + h) * kHeadDim + (threadIdx.x & 15) * 8);
+  return ar;
+}
+
 // Attention of row r over the `kept_here` positions in `list` (LDS; complete once the barrier in here is passed): groups of
 // 16 lanes, one K/V row (256 bytes) per group and load, kSaInFlight rows per group in flight; a lane owns 8 of the
 // 128 dims.  Threads 0 .. 127 get the softmax state (M, L) and their dim's unnormalised output A (in as -inf, 0, 0).
 template <bool F16, bool PAGED>
-__device__ __forceinline__ void attend_list(const GatherArgs& ga, const int r, const int32_t* list, int32_t* rows_lds,
+__device__ __forceinline__ void attend_list(const GatherArgs& ga, const AttendRow& ar, const int r, const int32_t* list, int32_t* rows_lds,
                                             const int kept_here, float& M, float& L, float& A) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const float ninf = -__builtin_huge_valf();
@@ -689,11 +715,9 @@ __device__ __forceinline__ void attend_list(const GatherArgs& ga, const int r, c
   __syncthreads();                           // the list is complete
   const int grp = wave * 4 + (lane >> 4), piece = lane & 15;
   const int b = r / ga.n_ret;
-  const int h = ga.ret_heads[r - b * ga.n_ret];
-  const int kvh = h / (ga.n_q_heads / ga.n_kv_heads);
-  const int64_t seq0 = PAGED ? 0 : ga.seq_start[b];
-  const uint16_t* Kb = ga.K + (int64_t)kvh * ga.head_stride + seq0 * ga.row_stride + piece * 8;
-  const uint16_t* Vb = ga.V + (int64_t)kvh * ga.head_stride + seq0 * ga.row_stride + piece * 8;
+  const int kvh = ga.ret_heads[r - b * ga.n_ret] / (ga.n_q_heads / ga.n_kv_heads);
+  const uint16_t* Kb = ga.K + (int64_t)kvh * ga.head_stride + ar.seq0 * ga.row_stride + piece * 8;
+  const uint16_t* Vb = ga.V + (int64_t)kvh * ga.head_stride + ar.seq0 * ga.row_stride + piece * 8;
   if (PAGED) {
     const int32_t* pt = ga.page_table + (int64_t)b * ga.pt_stride;
     const int mask = (1 << ga.page_shift) - 1;
@@ -705,7 +729,7 @@ __device__ __forceinline__ void attend_list(const GatherArgs& ga, const int r, c
   }
   const int32_t* rows = PAGED ? rows_lds : list;
   float qv[8];
-  unpack8<F16>(*reinterpret_cast<const u32x4*>(ga.q + ((int64_t)b * ga.n_q_heads + h) * kHeadDim + piece * 8), qv);
+  unpack8<F16>(ar.q, qv);
 #pragma unroll
   for (int d = 0; d < 8; ++d) qv[d] *= ga.scale_log2;
   float m = ninf, l = 0.f, acc[8];
@@ -1005,7 +1029,7 @@ __global__ __launch_bounds__(kTpThreads) void topp_write_kernel(const TopPArgs a
 
   // ---- attention over this chunk's kept positions ----
   float M = ninf, L = 0.f, A = 0.f;
-  attend_list<F16, PAGED>(ga, r, sh_list + list_lo, sh_rows, kept_here, M, L, A);
+  attend_list<F16, PAGED>(ga, attend_row<PAGED>(ga, r), r, sh_list + list_lo, sh_rows, kept_here, M, L, A);
   if (tid < kHeadDim) {
     float* pout = ga.part + ((int64_t)r * gridDim.x + blockIdx.x) * kSaPart;
     pout[4 + tid] = A;
@@ -1122,21 +1146,30 @@ __global__ __launch_bounds__(kTpThreads) void topp_row_kernel(const TopPArgs a, 
   const float ninf = -__builtin_huge_valf();
   const bool by_count = a.kcount != nullptr;
   const int n = max(min(a.row_len[r], kTpChunk), 0);
+  // a thread owns `per` consecutive scores: shorter rows take shorter loops, and a kept position's rank is one prefix sum
+  const int per = (n + 4 * kTpThreads - 1) / (4 * kTpThreads) * 4, own = tid * per;
   float4 v[kTpVec];
-  load_chunk(reinterpret_cast<const float4*>(a.scores + (int64_t)r * a.score_stride), n, tid, v);
+#pragma unroll
+  for (int u = 0; u < kTpVec; ++u) {
+    v[u] = make_float4(ninf, ninf, ninf, ninf);
+    if (u * 4 < per && own + u * 4 < n) v[u] = *reinterpret_cast<const float4*>(a.scores + (int64_t)r * a.score_stride + own + u * 4);
+  }
+  AttendRow ar = {};
+  if constexpr (ATTEND) ar = attend_row<PAGED>(ga, r);
   uint64_t bins[kBins1 / kTpThreads];
   __shared__ uint64_t lh[kBins1];
   __shared__ int32_t sh_list[kTpChunk];              // level 2: the members' scores; then the kept positions
   __shared__ int32_t sh_rows[(ATTEND && PAGED) ? kTpChunk : 1];
-  __shared__ uint64_t sh_part[kTpThreads / 64], sh_res[3], sh_tot[kTpThreads / 64][2];
+  __shared__ uint64_t sh_part[kTpThreads / 64], sh_res[3];
   __shared__ double sh_d[kTpThreads / 64], sh_dres[3], tab[256];
-  __shared__ int sh_i[kTpThreads / 64], sh_n;
+  __shared__ int sh_i[kTpThreads / 64], sh_n, sh_neq, sh_top;
+  __shared__ uint32_t sh_eq[64];
   fill_exp_table(tab);
   auto clear_bins = [&]() {
     for (int i = tid; i < kBins1; i += kTpThreads) lh[i] = 0;
   };
   clear_bins();
-  if (tid == 0) sh_n = 0;
+  if (tid == 0) { sh_n = 0; sh_neq = 0; sh_top = -1; }
   const float pr = by_count ? 0.5f : a.p[r];
   const int kc = by_count ? a.kcount[r] : 1;
   int flags = by_count ? (kc > 0 ? 0 : -1) : (pr >= 1.f ? 1 : (pr > 0.f ? 0 : -1));
@@ -1150,16 +1183,23 @@ __global__ __launch_bounds__(kTpThreads) void topp_row_kernel(const TopPArgs a, 
   uint64_t target = 1, left_there = 0;
   double above_base = 0.0, total_d = 1.0;
   if (flags == 0) {
+    int top = -1;                                     // the highest bin, for the scan
 #pragma unroll
-    for (int u = 0; u < kTpVec; ++u)
+    for (int u = 0; u < kTpVec; ++u) {
+      if (u * 4 >= per) continue;
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const float s = score(u, k);
-        if ((u * kTpThreads + tid) * 4 + k >= n) continue;
+        if (own + u * 4 + k >= n || s == ninf) continue;
+        top = max(top, (int)(float_key(s) >> 21));
         if (!by_count) level1_add(lh, s, shift, tab);
-        else if (s != ninf) atomicAdd((unsigned long long*)&lh[float_key(s) >> 21], 1ull);
+        else atomicAdd((unsigned long long*)&lh[float_key(s) >> 21], 1ull);
       }
+    }
+    top = wave_max_ge_m1(top);
+    if (lane == 0) atomicMax(&sh_top, top);
     __syncthreads();
+    top = sh_top;
     load_bins<kBins1>(lh, bins);
     if (by_count) {
       const ScanResult s1 = scan_from_top<kBins1>(bins, 0, (uint64_t)kc, sh_part, sh_res);
@@ -1167,7 +1207,7 @@ __global__ __launch_bounds__(kTpThreads) void topp_row_kernel(const TopPArgs a, 
       else if ((uint64_t)kc >= s1.total) flags = 1;
       else { prefix = (uint32_t)s1.bin; target = (uint64_t)kc - s1.above; }
     } else {
-      const Scan1Result s1 = scan_level1(bins, pr, sh_d, sh_i, sh_dres, tab);
+      const Scan1Result s1 = scan_level1_from(bins, top, pr, sh_d, sh_dres, tab);
       if (s1.bin < 0) flags = 2;
       else if (level1_bin_is_wide(s1.top)) flags = -2;
       else { prefix = (uint32_t)s1.bin; ref = s1.ref; target = s1.target; above_base = s1.above_base; total_d = s1.total_d; }
@@ -1183,23 +1223,27 @@ __global__ __launch_bounds__(kTpThreads) void topp_row_kernel(const TopPArgs a, 
     clear_bins();
     uint32_t member = 0;
 #pragma unroll
-    for (int u = 0; u < kTpVec; ++u)
+    for (int u = 0; u < kTpVec; ++u) {
+      if (u * 4 >= per) continue;
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const float s = score(u, k);
-        const bool in = (u * kTpThreads + tid) * 4 + k < n && (float_key(s) >> 21) == prefix && s != ninf;
+        const bool in = own + u * 4 + k < n && (float_key(s) >> 21) == prefix && s != ninf;
         member |= (in ? 1u : 0u) << (u * 4 + k);
       }
+    }
     const int cnt = __popc(member), incl = wave_incl_scan(cnt);
     int base = 0;
     if (lane == 63 && incl > 0) base = atomicAdd(&sh_n, incl);
     int pos = wave_last(base) + incl - cnt;
     float* packed = reinterpret_cast<float*>(sh_list);
 #pragma unroll
-    for (int u = 0; u < kTpVec; ++u)
+    for (int u = 0; u < kTpVec; ++u) {
+      if (u * 4 >= per) continue;
 #pragma unroll
       for (int k = 0; k < 4; ++k)
         if (member & (1u << (u * 4 + k))) packed[pos++] = score(u, k);
+    }
     __syncthreads();
     const int n_member = sh_n;
     for (int i = tid; i < n_member; i += kTpThreads) {
@@ -1211,28 +1255,89 @@ __global__ __launch_bounds__(kTpThreads) void topp_row_kernel(const TopPArgs a, 
     load_bins<kBins2>(lh, bins);
     const ScanResult s2 = scan_from_top<kBins2>(bins, 0, target, sh_part, sh_res);
     prefix = (prefix << 11) | (uint32_t)s2.bin;
-    // ---- level 3: the few that share the 22-bit prefix ----
-    clear_bins();
-    __syncthreads();
+    // ---- level 3: the few that share the 22-bit prefix, hardly ever more than a wave has lanes.  Every wave takes all of
+    // them, a lane each, adds up the mass at or above its own key and finds the highest key that reaches the target: what
+    // a histogram and its scan give, without their barriers ----
     for (int i = tid; i < n_member; i += kTpThreads) {
-      const float s = packed[i];
-      const uint32_t key = float_key(s);
+      const uint32_t key = float_key(packed[i]);
       if ((key >> 10) != prefix) continue;
-      const uint64_t w = by_count ? 1ull : fixed_weight(s, ref, shift, tab);
-      if (w) atomicAdd((unsigned long long*)&lh[key & (kBins3 - 1)], (unsigned long long)w);
+      const int slot = atomicAdd(&sh_neq, 1);
+      if (slot < 64) sh_eq[slot] = key;
     }
     __syncthreads();
-    uint64_t bins3[kBins3 / kTpThreads];
-    load_bins<kBins3>(lh, bins3);
-    const ScanResult s3 = scan_from_top<kBins3>(bins3, s2.above, target, sh_part, sh_res);
-    tkey = (prefix << 10) | (uint32_t)s3.bin;
+    const int n_eq = sh_neq;
+    uint64_t reached = s2.above;                       // mass at or above the threshold key
+    tkey = prefix << 10;
+    if (n_eq <= 64) {
+      const uint32_t key = lane < n_eq ? sh_eq[lane] : 0u;
+      const uint64_t w = lane >= n_eq ? 0ull : (by_count ? 1ull : fixed_weight(key_float(key), ref, shift, tab));
+      uint64_t from_top = s2.above;
+      for (int j = 0; j < n_eq; ++j) {
+        const uint32_t kj = (uint32_t)__builtin_amdgcn_readlane((int)key, j);
+        const uint64_t wj = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(w >> 32), j) << 32) |
+                            (uint32_t)__builtin_amdgcn_readlane((int)w, j);
+        from_top += kj >= key ? wj : 0ull;
+      }
+      uint64_t todo = __ballot(lane < n_eq && from_top >= target);
+      if (todo == 0) {                                 // (beyond reach by a rounding: the prefix's lowest key)
+        for (uint64_t low = __ballot(lane < n_eq && key == tkey); low != 0; low &= low - 1) {
+          const int j = __builtin_ctzll(low);
+          reached += ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(w >> 32), j) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)w, j);
+        }
+      }
+      for (bool first = true; todo != 0; todo &= todo - 1, first = false) {
+        const int j = __builtin_ctzll(todo);
+        const uint32_t kj = (uint32_t)__builtin_amdgcn_readlane((int)key, j);
+        if (first || kj > tkey) {
+          tkey = kj;
+          reached = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(from_top >> 32), j) << 32) |
+                    (uint32_t)__builtin_amdgcn_readlane((int)from_top, j);
+        }
+      }
+    } else {
+      clear_bins();
+      __syncthreads();
+      for (int i = tid; i < n_member; i += kTpThreads) {
+        const float s = packed[i];
+        const uint32_t key = float_key(s);
+        if ((key >> 10) != prefix) continue;
+        const uint64_t w = by_count ? 1ull : fixed_weight(s, ref, shift, tab);
+        if (w) atomicAdd((unsigned long long*)&lh[key & (kBins3 - 1)], (unsigned long long)w);
+      }
+      __syncthreads();
+      uint64_t bins3[kBins3 / kTpThreads];
+      load_bins<kBins3>(lh, bins3);
+      const ScanResult s3 = scan_from_top<kBins3>(bins3, s2.above, target, sh_part, sh_res);
+      tkey = (prefix << 10) | (uint32_t)s3.bin;
+      reached = s3.above + s3.bin_mass;
+    }
     res_tau = key_float(tkey);
-    res_mass = by_count ? __builtin_nanf("") : (float)((above_base + (double)(s3.above + s3.bin_mass)) / total_d);
+    res_mass = by_count ? __builtin_nanf("") : (float)((above_base + (double)reached) / total_d);
   }
   int kept = 0;
   if (n > 0 && (flags == 0 || flags == 1)) {
-    const uint32_t keep = keep_mask(v, n, tid, flags == 1, tkey);
-    kept = write_ranked(keep, 0, ATTEND ? nullptr : a.sel_idx + (int64_t)r * a.sel_stride, 0, sh_tot, ATTEND ? sh_list : nullptr);
+    uint32_t keep = 0;
+#pragma unroll
+    for (int u = 0; u < kTpVec; ++u) {
+      if (u * 4 >= per) continue;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float s = score(u, k);
+        const bool sel = own + u * 4 + k < n && s != ninf && (flags == 1 || float_key(s) >= tkey);
+        keep |= (sel ? 1u : 0u) << (u * 4 + k);
+      }
+    }
+    const int mine = __popc(keep), incl = wave_incl_scan(mine);
+    if (lane == 63) sh_i[tid >> 6] = incl;
+    __syncthreads();
+    int pos = incl - mine;
+#pragma unroll
+    for (int w = 0; w < kTpThreads / 64; ++w) {
+      if (w < (tid >> 6)) pos += sh_i[w];
+      kept += sh_i[w];
+    }
+    int32_t* const to = ATTEND ? sh_list : a.sel_idx + (int64_t)r * a.sel_stride;
+    for (uint32_t left = keep; left != 0; left &= left - 1) to[pos++] = own + __builtin_ctz(left);
   } else {
     res_tau = (flags < 0 && n > 0) ? __builtin_nanf("") : ninf;
     res_mass = 0.f;
@@ -1241,7 +1346,7 @@ __global__ __launch_bounds__(kTpThreads) void topp_row_kernel(const TopPArgs a, 
     // this copy's share of the kept positions
     const int k_lo = kept * copy / a.n_copy, k_hi = kept * (copy + 1) / a.n_copy;
     float M = ninf, L = 0.f, A = 0.f;
-    attend_list<F16, PAGED>(ga, r, sh_list + k_lo, sh_rows, k_hi - k_lo, M, L, A);
+    attend_list<F16, PAGED>(ga, ar, r, sh_list + k_lo, sh_rows, k_hi - k_lo, M, L, A);
     if (tid < kHeadDim) {
       if (a.n_copy > 1) {
         float* pout = ga.part + ((int64_t)r * a.n_copy + copy) * kSaPart;
@@ -1590,6 +1695,7 @@ __global__ __launch_bounds__(kTpThreads) void gather_lists_kernel(const TopPArgs
   const int r = blockIdx.y, tid = threadIdx.x, part = blockIdx.x;
   __shared__ int32_t sh_list[kTpChunk];
   __shared__ int32_t sh_rows[PAGED ? kTpChunk : 1];
+  const AttendRow ar = attend_row<PAGED>(ga, r);
   const int n = a.row_len[r];
   const int parts = n > 0 ? (n + kTpChunk - 1) / kTpChunk * a.n_copy : 0;
   if (part >= parts) return;
@@ -1598,7 +1704,7 @@ __global__ __launch_bounds__(kTpThreads) void gather_lists_kernel(const TopPArgs
   const int32_t* src = a.sel_idx + (int64_t)r * a.sel_stride + lo;
   for (int i = tid; i < n_here; i += kTpThreads) sh_list[i] = src[i];
   float M = -__builtin_huge_valf(), L = 0.f, A = 0.f;
-  attend_list<F16, PAGED>(ga, r, sh_list, sh_rows, n_here, M, L, A);
+  attend_list<F16, PAGED>(ga, ar, r, sh_list, sh_rows, n_here, M, L, A);
   if (tid < kHeadDim) {
     float* pout = ga.part + ((int64_t)r * gridDim.x + part) * kSaPart;
     pout[4 + tid] = A;
