@@ -430,8 +430,8 @@ __global__ __launch_bounds__(kPfThreads * GROUPS, 2) void flash_prefill_local_ke
 __device__ __forceinline__ float sel_t(float M, float x, float index_scale) { return __builtin_fmaf(-x, index_scale, M); }
 
 // Smallest float x (as a raw product) with sel_t(M, x) < bound; -inf if every finite x qualifies.
-// sel_t is non-increasing in x, so the predicate flips once from false to true.  The exact-arithmetic solution is a few
-// ulps of the larger operand away from the flip: two probes on either side of it usually leave a handful of
+// sel_t is non-increasing in x, so the predicate flips once from false to true.  The exact-arithmetic solution is an
+// ulp or two of the larger operand away from the flip: a probe on either side of it usually leaves three or four
 // bisection steps of the 32 (a probe only ever narrows the bracket, so a poor guess costs time and nothing else).
 __device__ __forceinline__ float sel_first_below(float M, float index_scale, float bound) {
   if (bound == __builtin_huge_valf()) return -__builtin_huge_valf();
@@ -439,14 +439,11 @@ __device__ __forceinline__ float sel_first_below(float M, float index_scale, flo
   auto probe = [&](uint32_t k) {
     if (sel_t(M, key_float(k), index_scale) < bound) hi = k; else lo = k + 1;
   };
-  const float guess = (M - bound) / index_scale;
+  const float guess = (M - bound) / index_scale, off = fmaxf(fabsf(M), bound) * 0x1p-21f / index_scale;
   if (fabsf(guess) < 1e30f) {
-    const uint32_t kg = float_key(guess);
-#pragma unroll
-    for (uint32_t d = 4096; d >= 32; d >>= 7) {
-      if (kg - d > lo && kg - d < hi) probe(kg - d);
-      if (kg + d > lo && kg + d < hi) probe(kg + d);
-    }
+    const uint32_t below = float_key(guess - off), above = float_key(guess + off);
+    if (below > lo && below < hi) probe(below);
+    if (above > lo && above < hi) probe(above);
   }
   while (lo < hi) probe(lo + ((hi - lo) >> 1));
   return key_float(lo);
@@ -634,15 +631,15 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
         const int n = nb + (i >> 2) * 8 + g * 4 + (i & 3);
         // 8 * (M - x * scale) straight from 8 M and 8 * scale: scaling by a power of two commutes with both
         // roundings, so this IS 8 * sel_t(M, x, scale), one multiplication less per pair
-        const float tt8 = sel_t(selM8, SI[i], cs8);
+        float tt8 = sel_t(selM8, SI[i], cs8);
         // a repeated sweep takes the candidates at or below the lowered reference only (the others were
-        // counted above the open-ended bin); a query that does not repeat has reference -inf and takes none
-        if (!masked || (n <= m && tt8 >= t_least)) {
-          // first digit of q: floor(min(tt * 2^17, 2^21 - 1)) >> 14 == floor(min(tt * 8, (2^21 - 1) / 2^14))
-          const int bin = (int)fminf(tt8, 127.99993896484375f);
-          // exp(s - M) = exp2(tt * -log2(e)); the constant carries the 1/8, again exactly
-          atomicAdd(&hist[bin][r], (double)fast_exp2(tt8 * -0.18033688011112042f));
-        }
+        // counted above the open-ended bin); a query that does not repeat has reference -inf and takes none.  What is left
+        // out adds a weight of zero to the last bin: no branch per pair
+        if (masked) tt8 = n <= m && tt8 >= t_least ? tt8 : 1e9f;
+        // first digit of q: floor(min(tt * 2^17, 2^21 - 1)) >> 14 == floor(min(tt * 8, (2^21 - 1) / 2^14))
+        const int bin = (int)fminf(tt8, 127.99993896484375f);
+        // exp(s - M) = exp2(tt * -log2(e)); the constant carries the 1/8, again exactly
+        atomicAdd(&hist[bin][r], (double)fast_exp2(tt8 * -0.18033688011112042f));
       }
     } else {
       // Members of the digit prefix (about one pair in a hundred in sweep 2, one in ten thousand in
@@ -789,8 +786,8 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
   const int plain_lo = min(round_lo, plain_rounds) * kSelRing, plain_hi = min(round_hi, plain_rounds) * kSelRing;
   const int edge_lo = max(round_lo, plain_rounds) * kSelRing, edge_hi = round_hi * kSelRing;
   // Sweeps 2 and 3 over the mask-free range, 512 tiles (256 entries of the maximum table) at a time: where at most
-  // a quarter of the tile pairs can hold a member, only those are fetched and looked at -- with a peaked score
-  // law that is a handful of pairs in a million keys --; otherwise the streaming sweep above runs over the stretch,
+  // a quarter of a stretch's tile pairs can hold a member, only those are fetched and looked at, one after the other -- with a
+  // peaked score law that is a handful of pairs in a million keys --; otherwise the streaming sweep above runs over the stretch,
   // consulting the table per pair unless that can skip next to nothing and, in sweep 3, nine in ten of the pairs
   // the wave has looked at turned out to hold a product some query can keep (a group with one moderately hard query
   // among easy ones is not such a case: looking tells which pairs that query really keeps a key in).
@@ -806,9 +803,9 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
       int n_on = 0;
 #pragma unroll
       for (int k = 0; k < 4; ++k) n_on += __popcll(__ballot(entry(k) >= xlo_wave));
-      if (n_on > 64) {
+      if (4 * n_on > (te - tb) >> 1) {
         // next to nothing to skip, and (sweep 3) the pairs looked at so far nearly all turned out to be needed: do not look
-        const bool no_look = n_on > 240 && (phase_ == 2 || (n_looked >= 64 && 10 * n_needed >= 9 * n_looked));
+        const bool no_look = 16 * n_on > 15 * ((te - tb) >> 1) && (phase_ == 2 || (n_looked >= 64 && 10 * n_needed >= 9 * n_looked));
         sweep(PH, std::false_type{}, tb, te, no_look);
         continue;
       }
