@@ -15,7 +15,7 @@
 //
 // Load balance without host knowledge of the set sizes: a persistent grid; every workgroup derives
 // the same plan from the device-side counts -- split length ST = total tokens / grid size (rounded
-// up to 128), unit u contributes ceil(n_u / ST) work items -- and walks the items blockIdx.x,
+// up to 128, see build_plan), unit u contributes ceil(n_u / ST) work items -- and walks the items blockIdx.x,
 // blockIdx.x + gridDim.x, ...  Each item leaves a partial (m, l, acc[128]) per head; a second small
 // kernel merges the partials of a unit (the split-KV reduction of Sec. 3.4, as a separate launch).
 // Algorithmic traffic: 512 B per attended token and KV head (+ 4 B per token for the index list).
@@ -46,6 +46,12 @@ __device__ __forceinline__ int block_excl_scan(int v, int* sh_w /*[4]*/, int* to
   return off + incl - v;
 }
 
+// Shortest item of a selected-token plan, in blocks of 128 tokens (one round of loads): 5, since shorter items spend their time
+// in the prologue and the merge -- but no longer than it takes to give one item to each of 256 compute units: with fewer, the
+// launch lasts as long as the rounds of one item.  Both launches, us, items of 640 / this: 12 rows of 4096 tokens 18.1 / 13.9, of
+// 512 15.2 / 11.7, 4 of 4096 16.2 / 13.0, 48 of 1000 18.2 / 13.8; 128 of 1500 25.2 / 25.5 (the same plan).
+constexpr int kMinSplitBlocks = 5, kFewItems = 256;
+
 // Every workgroup computes the same plan: split length and the exclusive item prefix per unit.
 template <int SRC>
 __device__ __forceinline__ void build_plan(const AttnDecodeArgs& a, int* sh_prefix /*[kAdMaxUnits+1]*/, int* sh_w,
@@ -61,9 +67,9 @@ __device__ __forceinline__ void build_plan(const AttnDecodeArgs& a, int* sh_pref
   }
   int total128;
   block_excl_scan(mine, sh_w, &total128);
-  // at least kMinSplitBlocks * 128 tokens per item: shorter items spend their time in the prologue and the merge
   int st = (total128 + a.target_items - 1) / max(a.target_items, 1);
-  st = max(st, a.min_split_blocks) * 128;
+  if (SRC == kSrcSparse) st = max(st, min(kMinSplitBlocks, (total128 + kFewItems - 1) / kFewItems));
+  st = max(st, 1) * 128;
   int items = 0;
 #pragma unroll
   for (int i = 0; i < kAdMaxUnits / kAdThreads; ++i) {
@@ -524,7 +530,6 @@ int32_t decode_range_prepare(const char* who, bool dense, const rtp_layer_desc* 
   fill_common(a, L, ht, q, K, V, row_stride, head_stride, seq_start, ctx_len, out, lse, ws);
   a.units = p.units;
   a.target_items = 0;
-  a.min_split_blocks = 1;
   a.split_tokens = p.split_tokens;
   a.n_splits = p.n_splits;
   if (pages) {
@@ -634,7 +639,6 @@ static int32_t sparse_attn_decode_impl(const char* who, const rtp_layer_desc* la
   a.sel_count = sel_count;
   a.units = p.units;
   a.target_items = p.target_items;
-  a.min_split_blocks = 5;
   a.split_tokens = 0;
   a.n_splits = 0;
   a.page_table = page_table;

@@ -28,7 +28,6 @@ struct AttnDecodeArgs {
   int32_t n_q_heads, n_kv_heads, n_ret, sink, window;
   int32_t units;           // B * n_ret (sparse) or B * n_kv_heads
   int32_t target_items;    // sparse: host hint, aim for this many work items
-  int32_t min_split_blocks;  // sparse: shortest split, in blocks of 128 tokens
   int32_t split_tokens;    // local / dense: tokens per work item, fixed by the host
   int32_t n_splits;        // local / dense: work items per unit
   float scale_log2;        // softmax scale * log2(e)

@@ -751,3 +751,27 @@ def test_whole_row_selection_equals_the_levels_by_launch(n_ret, ctx):
         same(rep)
     a, b = run.out[:, w.layer.ret_heads].float(), ref.out[:, w.layer.ret_heads].float()
     assert ((a - b).abs() <= 2.0 ** -7 * torch.maximum(a.abs(), b.abs()) + 1e-5).all()
+
+
+@pytest.mark.parametrize("sizes", [
+    (1, 127, 128, 129, 255, 256, 257, 0),             # items of 128 tokens: fewer of them than compute units
+    (8192, 8191, 8193, 8192),                         # 256 and 257 blocks of 128 tokens in all: items of 128 and 256
+    (8192, 8192, 8192, 8192),
+    (36000, 30001, 33333, 32769),                     # more than 4 x 256 blocks: items of 640, the longest that the rule asks for
+    (40000, 39999, 1, 641)])                          # items of 384, one row of a single token
+def test_sparse_attn_item_lengths(sizes):
+    """Sets on either side of the lengths where the plan's shortest item changes, against the oracle's attention over them."""
+    print(f"[case] sparse item lengths {sizes}", flush=True)
+    n = max(sizes) + 5
+    w = wl.small_decode(DEV, seed=251, n_q_heads=8, n_kv_heads=2, ret_heads=(1, 6), ctx=(n,) * (len(sizes) // 2), p=(0.9,) * (len(sizes) // 2))
+    run = DecodeRun(w)
+    rng = np.random.default_rng(7)
+    sets = [np.sort(rng.choice(n, size=k, replace=False)) for k in sizes]
+    idx = torch.zeros((run.R, run.stride), dtype=torch.int32)
+    for r, s in enumerate(sets):
+        idx[r, :len(s)] = torch.from_numpy(s.astype(np.int32))
+    run.sparse_attn(idx.to(DEV), i32(list(sizes)))
+    out, lse = run.out_f64(), run.lse.cpu().numpy()
+    for (b, h), (o, l) in attend_reference(w, oracle_inputs(w), sets).items():
+        check_out(out[b, h], o, f"b{b} h{h}")
+        assert abs(lse[b, h] - l) < 1e-4              # fp32 sums of up to 40000 terms of one sign: 2e-5
