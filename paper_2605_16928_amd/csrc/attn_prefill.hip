@@ -73,7 +73,7 @@ struct PrefillArgs {
   // a threshold search cut into launches, n_slice workgroups per 32-query group (short chunks; see prefill_select_kernel)
   int32_t n_slice;
   float* sl_max;                // [groups, n_slice, 32]: the slices' row maxima
-  double* sl_hist;              // [2, groups, n_slice, 128, 32]: the slices' histograms, of the current sweep and the one before
+  double* sl_hist;              // [2, groups, n_slice, 128, 32]: the slices' histograms (running sums), of the current sweep and the one before
   struct SelState* sl_state;    // [2, groups, 32]: what a scan found, read by the next launch
   int32_t* sl_again;            // [groups]: 1 = some query's threshold lies in the open-ended bin, the last launch searches the group
 };
@@ -465,10 +465,11 @@ __device__ __forceinline__ float sel_first_below(float M, float index_scale, flo
 // the load out.
 // A chunk of few groups leaves most of the chip idle that way (333 queries of 4 heads: 44 workgroups, 0.88 ms at 128K
 // tokens).  Then the search runs as five launches with n_slice workgroups per group, each sweeping a slice of the
-// group's keys: STEP = 0 .. 3 are the sweeps -- a launch first merges what the slices of the launch before left
-// (maxima, histograms: plain stores and sums in slice order, no atomics) and repeats the scan in every slice -- and
+// group's keys: STEP = 0 .. 3 are the sweeps -- a launch first scans what the slices of the launch before left
+// (maxima, histograms as running sums: plain stores and sums in slice order, no atomics), the same in every slice -- and
 // kSelFinish scans the last histogram; the kernel boundaries are the only synchronisation.  Every sum has the same
-// terms as in one workgroup, in fp64.  0.88 -> 0.20 ms there.  (A group with a query whose threshold lies in the open-ended
+// terms as in one workgroup, in fp64.  0.88 -> 0.19 ms there (0.20 with whole histograms added up by every slice: 32 KB times
+// the slices, twice; sweeps 2 and 3 with their scans 61.7 -> 57.5 and 47.1 -> 43.1 us).  (A group with a query whose threshold lies in the open-ended
 // bin, see below, leaves that form: its sweeps 0 and 1 are thrown away and one workgroup of the last launch searches it as a whole.)
 //
 // A threshold inside the open-ended last coarse bin (candidates 15.875 or more below the row maximum) is not
@@ -974,20 +975,52 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
 
   // a sliced search: the histogram of the group from what its slices left in the launch before
   const int groups = a.n_heads * n_qtiles, grp = j * n_qtiles + qtile;
-  constexpr int kHistN = kSelBins * 32, kHistPer = kHistN / kSelThreads;
-  auto merge_slices = [&](int n) __attribute__((always_inline)) {
-    const double* old = a.sl_hist + ((int64_t)(1 - (STEP & 1)) * groups + grp) * n * kHistN + tid;
-    double sum[kHistPer];
+  constexpr int kHistN = kSelBins * 32;
+  // A slice leaves every run of a histogram as its running sums, so that the run's sum is its last entry.  Each slice of the next
+  // launch then fetches the runs' sums and, of each query, the one run that crosses, where adding up all 128 bins is 32 KB per
+  // slice in every slice.  Sums of running sums are running sums again (rounding keeps their order).
+  static_assert(kSelThreads == kRuns * 32, "one thread per run and query");
+  const int my_run = wave * 2 + g;
+  auto leave_runs = [&](double* own) __attribute__((always_inline)) {
+    double c = 0.0;
 #pragma unroll
-    for (int i = 0; i < kHistPer; ++i) sum[i] = 0.0;
-#pragma unroll 4
-    for (int k = 0; k < n; ++k) {
-#pragma unroll
-      for (int i = 0; i < kHistPer; ++i) sum[i] += old[(int64_t)k * kHistN + i * kSelThreads];
+    for (int i = 0; i < kRunBins; ++i) {
+      c += hist[my_run * kRunBins + i][r];
+      own[(my_run * kRunBins + i) * 32 + r] = c;
     }
-#pragma unroll
-    for (int i = 0; i < kHistPer; ++i) (&hist[0][0])[tid + i * kSelThreads] = sum[i];
+  };
+  auto scan_slices = [&](int n, bool whole) __attribute__((always_inline)) {
+    const double* const old = a.sl_hist + ((int64_t)(1 - (STEP & 1)) * groups + grp) * n * kHistN + r;
+    double (*crossing)[32] = run_sum + kRuns;                       // running sums of each query's crossing run
+    static_assert(sizeof(double) * 32 * (kRuns + kRunBins) <= sizeof(list_all), "both fit the lists' memory");
+    auto over_slices = [&](int bin) __attribute__((always_inline)) {
+      double sum = 0.0;
+#pragma unroll 8
+      for (int k = 0; k < n; ++k) sum += old[(int64_t)k * kHistN + bin * 32];
+      return sum;
+    };
+    run_sum[my_run][r] = over_slices(my_run * kRunBins + kRunBins - 1);
     __syncthreads();
+    double rs[kRuns];
+#pragma unroll
+    for (int i = 0; i < kRuns; ++i) rs[i] = run_sum[i][r];
+    if (whole) {
+      Z = 0.0;
+#pragma unroll
+      for (int i = 0; i < kRuns; ++i) Z += rs[i];
+    }
+    const double target = (double)a.p * Z;
+    const ThresholdRun run = threshold_run<kRuns>(above, target, rs);
+    if (my_run < kRunBins) crossing[my_run][r] = over_slices(run.run * kRunBins + my_run);
+    __syncthreads();
+    double c[kRunBins];
+#pragma unroll
+    for (int i = 0; i < kRunBins; ++i) c[i] = crossing[i][r];
+    const ThresholdBin t = threshold_in_run<kRuns, kRunBins>(run, target, c);
+    bsel = t.bin;
+    cum = t.above;
+    hsel = t.mass;
+    __syncthreads();                                                // the sums are read: the lists' memory is free again
   };
   if constexpr (kSliced) {
     const int64_t mine_at = (int64_t)grp * n_slice + slice;
@@ -1007,7 +1040,6 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
       sweep_all(std::integral_constant<int, 1>{});
     } else if constexpr (STEP >= 2) {
       if (STEP == 3 && a.sl_again[grp] != 0) return;                  // (the same for the whole workgroup)
-      merge_slices(n_slice);
       if (STEP == 2) {
         x_max = ninf;
         for (int k = 0; k < n_slice; ++k) x_max = fmaxf(x_max, a.sl_max[((int64_t)grp * n_slice + k) * 32 + r]);
@@ -1016,7 +1048,7 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
         const SelState st = a.sl_state[(int64_t)grp * 32 + r];
         Z = st.Z; above = st.above; selM = st.selM; x_max = st.x_max; prefix = st.prefix;
       }
-      scan(STEP == 2, true);
+      scan_slices(n_slice, STEP == 2);
       if (STEP == 2) {
         const bool again = any_of(in_open_bin());
         if (slice == 0 && tid == 0) a.sl_again[grp] = again ? 1 : 0;
@@ -1025,22 +1057,20 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
       prefix = STEP == 2 ? bsel : (prefix << 7) | bsel;
       above = cum;
       if (slice == 0 && tid < 32) a.sl_state[((int64_t)(STEP - 2) * groups + grp) * 32 + r] = SelState{Z, above, selM, x_max, prefix, 0};
-      __syncthreads();                                              // every wave has read the histogram
       member_range(STEP);
       zero_hist();
       __syncthreads();
       sweep_all(std::integral_constant<int, STEP>{});
     }
     __syncthreads();
-    for (int i = tid; i < kHistN; i += kSelThreads) own[i] = (&hist[0][0])[i];
+    leave_runs(own);
     return;
   }
 
   if (STEP == kSelFinish && a.sl_again[grp] == 0) {
     const SelState st = a.sl_state[((int64_t)groups + grp) * 32 + r];
     Z = st.Z; above = st.above; selM = st.selM; x_max = st.x_max; prefix = st.prefix;
-    merge_slices(a.n_slice);
-    scan(false, true);
+    scan_slices(a.n_slice, false);
     prefix = (prefix << 7) | bsel;
   } else {
     row_maxima();
@@ -1959,7 +1989,7 @@ int32_t prefill_range_attn(const char* who, bool dense, const rtp_layer_desc* L,
 }
 
 // Workgroups per 32-query group of the threshold search: as many as fill two workgroups per compute unit, each with at
-// least 4096 keys of the longest range, at most 16.  The five launches cost about 60 us beside the sweeps, what one
+// least 4096 keys of the longest range, at most 16.  The five launches cost about 50 us beside the sweeps, what one
 // workgroup needs for 9000 keys of a broad score law: the slices have to save more than that (1 to 64 queries behind
 // 60000 tokens: 82 to 93 us against some 400 in one launch; 1000 queries behind 5000 tokens stay at 62 in one).
 // `room`: bytes there are for what the launches hand on; fewer slices where it holds no more.
