@@ -649,40 +649,28 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
       // and the atomic for one or two active lanes at a time.
       // Membership x_lo <= x <= x_top is one median and one comparison, which switches the other lanes off for the
       // store at the list's end and the step of the end: three vector instructions per pair.
-      auto member = [&](int i) {
+      // MASKED: a key that the query does not see is taken as -inf, which no finite lower end lets in.
+      float v[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
         const int n = nb + (i >> 2) * 8 + g * 4 + (i & 3);
-        const bool in = __builtin_amdgcn_fmed3f(SI[i], x_lo, x_top) == SI[i];
-        return masked ? (in && n <= m) : in;
-      };
+        v[i] = (!masked || n <= m) ? SI[i] : ninf;
+      }
+      const float lo = masked ? fmaxf(x_lo, -3.4028234663852886e38f) : x_lo;
       bool go = true;
       float reach = 0.f;
       if (phase == 3) {
         // does any lane have a member in this tile?  Its products' smallest distance from the middle of the lane's
         // range says so, one and a half vector instructions per pair (rounding is monotone, so a member is
         // never further away than the range's ends as subtracted the same way; a tile let through for nothing is harmless)
-        if (masked) {
-          uint64_t any = 0;
+        float d = pinf;
 #pragma unroll
-          for (int i = 0; i < 16; ++i) any |= __ballot(member(i));
-          go = any != 0ull;
-        } else {
-          float d = pinf;
-#pragma unroll
-          for (int i = 0; i < 16; i += 2) d = fminf(fminf(fabsf(SI[i] - x_mid), fabsf(SI[i + 1] - x_mid)), d);
-          go = __ballot(d <= x_half) != 0ull;
-        }
+        for (int i = 0; i < 16; i += 2) d = fminf(fminf(fabsf(v[i] - x_mid), fabsf(v[i + 1] - x_mid)), d);
+        go = __ballot(d <= x_half) != 0ull;
         // can some query of the wave keep a key of this tile?  Its final threshold is at or above x_lo, so a
         // tile whose largest visible product is below x_lo for every query holds no kept pair
         reach = 1.f;
-        if (!reach_known) {
-          float v[16];
-#pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const int n = nb + (i >> 2) * 8 + g * 4 + (i & 3);
-            v[i] = (!masked || n <= m) ? SI[i] : ninf;
-          }
-          reach = __ballot(max16_nn(v) >= x_lo) != 0ull ? 1.f : 0.f;
-        }
+        if (!reach_known) reach = __ballot(max16_nn(v) >= x_lo) != 0ull ? 1.f : 0.f;
       }
       if (go) {
         // A half tile adds at most 8 entries, so the lists are emptied when some lane has no room for 8 more.  The list's
@@ -692,14 +680,7 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
           if (__ballot(lcnt > kSelListCap - 8) != 0ull) drain_list();
           uint32_t end = lst_base + (uint32_t)lcnt * 256u;
 #pragma unroll
-          for (int i = hf * 8; i < hf * 8 + 8; ++i) {
-            if (masked) {
-              *reinterpret_cast<float __attribute__((address_space(3)))*>(end) = SI[i];
-              end += member(i) ? 256u : 0u;
-            } else {
-              append_if_member(end, SI[i], __builtin_amdgcn_fmed3f(SI[i], x_lo, x_top));
-            }
-          }
+          for (int i = hf * 8; i < hf * 8 + 8; ++i) append_if_member(end, v[i], __builtin_amdgcn_fmed3f(v[i], lo, x_top));
           lcnt = (int)((end - lst_base) >> 8);
         }
       }
