@@ -450,7 +450,7 @@ __device__ __forceinline__ float sel_first_below(float M, float index_scale, flo
 }
 
 // A workgroup is the eight waves of one group, which split its key range between them; 128 vector registers and 80 KB of
-// LDS let two workgroups share a compute unit: four waves per SIMD (3.5 on average, by the counters) issue under each other's latencies (with two, 221 registers and loads two rounds of eight tiles ahead, the search
+// LDS let two workgroups share a compute unit (of a launch that leaves it one, some have sixteen waves): four waves per SIMD (3.5 on average, by the counters) issue under each other's latencies (with two, 221 registers and loads two rounds of eight tiles ahead, the search
 // took 23.7 ms on the last 8192-query chunk of a 1,048,576-token context, 18.4 to 19.5 now; the same code held to 128
 // registers 19.4).  The waves add into ONE histogram (LDS atomics; 32 KB); the per-lane member
 // lists of sweeps 2 and 3 are emptied when a half tile might overrun one.  All waves meet at
@@ -477,16 +477,17 @@ __device__ __forceinline__ float sel_first_below(float M, float index_scale, flo
 // concerned -- the mass above that bin is already known, the bin's members are spread over 128 new coarse bins --
 // until the threshold bin is an ordinary one (or 24 rounds, about 380 score units, are used up).
 constexpr int kSelThreads = 512;
+constexpr int kSelThreadsFew = 1024;               // alone on its compute unit: see rtp_sparse_attn_prefill
 constexpr float kSelLumpT = 15.875f;               // (kSelBins - 1) / 8: where the open-ended bin starts
 constexpr double kSelLumpScale = 7843180.797657975;   // exp(15.875)
 constexpr int kSelMaxRounds = 24;
 constexpr int kSelAll = -1, kSelFinish = 4;        // STEP of prefill_select_kernel beside the sweeps 0 .. 3
 
-template <int STEP>
-__global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const PrefillArgs a) {
+template <int STEP, int THREADS = kSelThreads>
+__global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const PrefillArgs a) {
   constexpr bool kSliced = STEP >= 0 && STEP < kSelFinish;             // this launch sweeps a slice of the group's keys
   constexpr bool kWhole = STEP == kSelAll || STEP == kSelFinish;       // ... or can run the whole search
-  constexpr int NW = kSelThreads / 64;                             // waves of the workgroup
+  constexpr int NW = THREADS / 64;                             // waves of the workgroup
   __shared__ double hist[kSelBins][32];                            // 32 KB
   __shared__ float list_all[NW][kSelListCap][64];                  // per-lane member lists of sweeps 2 and 3 (48 KB)
   float (*max_all)[32] = reinterpret_cast<float (*)[32]>(&list_all[0][0][0]);   // sweep 0: the waves' row maxima
@@ -561,7 +562,7 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
   // the group's waves clear their histogram together (followed by a barrier at the call sites)
   auto zero_hist = [&]() __attribute__((always_inline)) {
     double* h = &hist[0][0];
-    for (int i = tid; i < kSelBins * 32; i += kSelThreads) h[i] = 0.0;
+    for (int i = tid; i < kSelBins * 32; i += THREADS) h[i] = 0.0;
   };
   // One candidate's mass into bin `bin` of this lane's query.
   auto add_mass = [&](int bin, float tt) __attribute__((always_inline)) {
@@ -835,11 +836,11 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
   // runs' sums and the bins of the run that crosses, on the same numbers in the same order.  (All of them going through
   // all 128 bins is a chain of LDS reads and additions of 32000 cycles, three times per workgroup.)  One barrier; the
   // sums live in the lists' memory, idle between sweeps.  `whole`: the histogram holds all candidates, take Z from it.
-  constexpr int kRuns = 2 * NW, kRunBins = kSelBins / kRuns;
+  constexpr int kRuns = kSelThreads / 32, kRunBins = kSelBins / kRuns;
   double (*run_sum)[32] = reinterpret_cast<double (*)[32]>(&list_all[0][0][0]);
   static_assert(kSelBins % kRuns == 0 && sizeof(double) * 32 * kRuns + sizeof(int) * NW <= sizeof(list_all), "runs of equal length");
   auto scan = [&](bool whole, bool take) __attribute__((always_inline)) {
-    {
+    if (THREADS == kSelThreads || tid < kSelThreads) {
       double h[kRunBins], sum = 0.0;
 #pragma unroll
       for (int i = 0; i < kRunBins; ++i) h[i] = hist[(wave * 2 + g) * kRunBins + i][r];
@@ -960,7 +961,7 @@ __global__ __launch_bounds__(kSelThreads, 4) void prefill_select_kernel(const Pr
   // A slice leaves every run of a histogram as its running sums, so that the run's sum is its last entry.  Each slice of the next
   // launch then fetches the runs' sums and, of each query, the one run that crosses, where adding up all 128 bins is 32 KB per
   // slice in every slice.  Sums of running sums are running sums again (rounding keeps their order).
-  static_assert(kSelThreads == kRuns * 32, "one thread per run and query");
+  static_assert(STEP == kSelAll || THREADS == kRuns * 32, "one thread per run and query");
   const int my_run = wave * 2 + g;
   auto leave_runs = [&](double* own) __attribute__((always_inline)) {
     double c = 0.0;
@@ -2199,7 +2200,15 @@ extern "C" int32_t rtp_sparse_attn_prefill(const rtp_layer_desc* layer, const vo
     RTP_LAUNCH(prefill_select_kernel<3>, grid, dim3(kSelThreads), 0, s, a);
     RTP_LAUNCH(prefill_select_kernel<kSelFinish>, search_grid(1), dim3(kSelThreads), 0, s, a);
   } else {
-    RTP_LAUNCH(prefill_select_kernel<kSelAll>, search_grid(1), dim3(kSelThreads), 0, s, a);
+    // At most one workgroup per compute unit: sixteen waves each, four per SIMD, where eight leave it two.  Below about 5000
+    // keys the waves have too few rounds for that to show (one group of 32 queries and 5000 keys 79.6 / 80.4 us a call with
+    // eight / sixteen, a prompt of 2037, 2 heads, 68.1 / 70.1); beyond: 1024 queries of 4 heads at 5100 keys 104.9 / 100.9, at
+    // 12000 154 / 139; 100 at 12000 132 / 115; 2000 at 18000 233 / 208.
+    const int64_t groups = (int64_t)layer->n_ret * n_qtiles, rounds = (chunk_start + T + 32 * kSelRing - 1) / (32 * kSelRing);
+    if (groups <= compute_units() && rounds > 40)
+      RTP_LAUNCH((prefill_select_kernel<kSelAll, kSelThreadsFew>), search_grid(1), dim3(kSelThreadsFew), 0, s, a);
+    else
+      RTP_LAUNCH(prefill_select_kernel<kSelAll>, search_grid(1), dim3(kSelThreads), 0, s, a);
   }
   const unsigned n_wide = (unsigned)((T + kPwQ - 1) / kPwQ);
   RTP_LAUNCH(prefill_active_tiles_kernel, dim3(n_wide, (unsigned)a.n_heads), dim3(256), 0, (hipStream_t)stream, a);
