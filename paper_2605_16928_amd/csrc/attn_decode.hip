@@ -20,6 +20,7 @@
 // kernel merges the partials of a unit (the split-KV reduction of Sec. 3.4, as a separate launch).
 // Algorithmic traffic: 512 B per attended token and KV head (+ 4 B per token for the index list).
 #include "attn_decode_shared.h"
+#include "split_plan.h"
 
 #include <stdlib.h>
 
@@ -46,30 +47,31 @@ __device__ __forceinline__ int block_excl_scan(int v, int* sh_w /*[4]*/, int* to
   return off + incl - v;
 }
 
-// Shortest item of a selected-token plan, in blocks of 128 tokens (one round of loads): 5, since shorter items spend their time
-// in the prologue and the merge -- but no longer than it takes to give one item to each of 256 compute units: with fewer, the
-// launch lasts as long as the rounds of one item.  Both launches, us, items of 640 / this: 12 rows of 4096 tokens 18.1 / 13.9, of
-// 512 15.2 / 11.7, 4 of 4096 16.2 / 13.0, 48 of 1000 18.2 / 13.8; 128 of 1500 25.2 / 25.5 (the same plan).
-constexpr int kMinSplitBlocks = 5, kFewItems = 256;
-
 // Every workgroup computes the same plan: split length and the exclusive item prefix per unit.
 template <int SRC>
-__device__ __forceinline__ void build_plan(const AttnDecodeArgs& a, int* sh_prefix /*[kAdMaxUnits+1]*/, int* sh_w,
+__device__ __forceinline__ void build_plan(const AttnDecodeArgs& a, int* sh_prefix /*[kAdMaxUnits+1]*/, int* sh_w /*[2 * waves]*/,
                                            int* split_tokens, int* n_items) {
   const int tid = threadIdx.x;
   int cnt[kAdMaxUnits / kAdThreads];
-  int mine = 0;
+  int total128 = 0, longest128 = 0;       // in blocks of 128 tokens, so the total cannot overflow int
 #pragma unroll
   for (int i = 0; i < kAdMaxUnits / kAdThreads; ++i) {
     const int u = tid * (kAdMaxUnits / kAdThreads) + i;
     cnt[i] = u < a.units ? unit_tokens<SRC>(a, u) : 0;
-    mine += (cnt[i] + 127) >> 7;          // in blocks of 128 tokens, so the total cannot overflow int
+    total128 += (cnt[i] + 127) >> 7;
+    longest128 = max(longest128, (cnt[i] + 127) >> 7);
   }
-  int total128;
-  block_excl_scan(mine, sh_w, &total128);
-  int st = (total128 + a.target_items - 1) / max(a.target_items, 1);
-  if (SRC == kSrcSparse) st = max(st, min(kMinSplitBlocks, (total128 + kFewItems - 1) / kFewItems));
-  st = max(st, 1) * 128;
+  total128 = wave_sum(total128);
+  longest128 = wave_max_ge_m1(longest128);
+  if ((tid & 63) == 0) { sh_w[2 * (tid >> 6)] = total128; sh_w[2 * (tid >> 6) + 1] = longest128; }
+  __syncthreads();
+  total128 = longest128 = 0;
+#pragma unroll
+  for (int w = 0; w < kAdThreads / 64; ++w) {
+    total128 += sh_w[2 * w];
+    longest128 = max(longest128, sh_w[2 * w + 1]);
+  }
+  const int st = split_blocks(total128, longest128, a.target_items) * 128;
   int items = 0;
 #pragma unroll
   for (int i = 0; i < kAdMaxUnits / kAdThreads; ++i) {
@@ -119,7 +121,7 @@ template <int G, int SRC, int U, bool PAGED = false, bool F16 = false>
 __global__ __launch_bounds__(kAdThreads) void attn_decode_kernel(const AttnDecodeArgs a) {
   static_assert(!PAGED || SRC != kSrcDense, "paging is implemented for the selected-token and the local source");
   __shared__ int sh_prefix[kAdMaxUnits + 1];
-  __shared__ int sh_w[kAdThreads / 64];
+  __shared__ int sh_w[2 * (kAdThreads / 64)];
   __shared__ float sh_m[kAdThreads / 64][G], sh_l[kAdThreads / 64][G];
   __shared__ float sh_acc[kAdThreads / 64][G][kHeadDim];
 
@@ -354,7 +356,7 @@ __global__ __launch_bounds__(kAdThreads) void attn_decode_gqa_kernel(const AttnD
 template <int G, int SRC>
 __global__ __launch_bounds__(kAdThreads) void attn_decode_combine_kernel(const AttnDecodeArgs a) {
   __shared__ int sh_prefix[SRC == kSrcSparse ? kAdMaxUnits + 1 : 1];
-  __shared__ int sh_w[kAdThreads / 64];
+  __shared__ int sh_w[2 * (kAdThreads / 64)];
   const int unit = blockIdx.x / G, hh = blockIdx.x - unit * G;
   int b, h, i0, i1;
   if (SRC == kSrcSparse) {

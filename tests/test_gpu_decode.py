@@ -758,7 +758,8 @@ def test_whole_row_selection_equals_the_levels_by_launch(n_ret, ctx):
     (8192, 8191, 8193, 8192),                         # 256 and 257 blocks of 128 tokens in all: items of 128 and 256
     (8192, 8192, 8192, 8192),
     (36000, 30001, 33333, 32769),                     # more than 4 x 256 blocks: items of 640, the longest that the rule asks for
-    (40000, 39999, 1, 641)])                          # items of 384, one row of a single token
+    (40000, 39999, 1, 641),                           # items of 640 by the longest rows' partials, one row of a single token
+    (16385, 0), (32768, 1), (33000, 129)])            # one row alone: 43, 64 and 52 items
 def test_sparse_attn_item_lengths(sizes):
     """Sets on either side of the lengths where the plan's shortest item changes, against the oracle's attention over them."""
     print(f"[case] sparse item lengths {sizes}", flush=True)
