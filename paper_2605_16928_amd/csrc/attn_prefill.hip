@@ -152,8 +152,10 @@ __device__ __forceinline__ float max16_nn(const float (&v)[16]) {
 // and maxima in two short chains: 4096 queries at 128K, 28 heads: 241 -> 175 to 205 us (590 to 690 TFLOP/s); 333 queries: 89 -> 82 us; a
 // prompt of 2037 with 6 heads: 31.5 -> 29 us.  Measured without gain: four buffers, three tiles ahead (92 and 32 us: memory
 // latency is not the limit); the band on the wide kernel (twice as long: its masked blocks leave the pipelined path).
-// GROUPS = 2, for launches of at most one workgroup per compute unit: a second group of four waves takes every other tile of the
-// same queries, with buffers and a running maximum of its own, and the first one merges the two at the end.
+// GROUPS = 2, for launches of at most one workgroup per compute unit whose bands may have four tiles: a second group of four waves
+// takes every other tile of the same queries, with buffers and a running maximum of its own, and the first one merges the two at the
+// end.  Launch, us (GPU time alone), one group / two: 28 heads, 333 queries behind 131072 tokens, window 2048: 70.3 / 49.3; 200
+// behind 5000, window 512: 28.4 / 22.2; 256 of a prompt (four tiles) 12.4 / 12.2, but 128 to 192 (two, three) 9.3 / 10.2, 64 (one) 6.0 / 7.9.
 template <bool F16, int GROUPS>
 __global__ __launch_bounds__(kPfThreads * GROUPS, 2) void flash_prefill_local_kernel(const PrefillArgs a) {
   __shared__ __attribute__((aligned(16))) unsigned char smem_all[GROUPS * 2 * kPfTileBytes];
@@ -1898,7 +1900,14 @@ static int choose_sub(int n_heads, int32_t T, int64_t chunk_start, int n_base, i
   return s > 1 ? (int)s : 1;
 }
 
-static int32_t launch_prefill(const char* who, bool local, PrefillArgs& a, int32_t B, hipStream_t s) {
+// The most key tiles that the band of a query tile can have: sinks apart from the window, and no position from max_ctx on.  (Where
+// max_ctx is far above the contexts there are, the bands of their first 192 queries take two groups all the same: 1 to 2 us.)
+static int64_t band_tiles(const PrefillArgs& a, int64_t max_ctx) {
+  const int64_t span = std::max<int64_t>(a.window, 1) - 1 + std::min(a.n_q, kPfQ);       // window of the first query to the last query
+  return std::min((max_ctx + kPfK - 1) / kPfK, ((int64_t)a.sink + kPfK - 1) / kPfK + (span + kPfK - 2) / kPfK + 1);
+}
+
+static int32_t launch_prefill(const char* who, bool local, PrefillArgs& a, int32_t B, int64_t max_ctx, hipStream_t s) {
   if (a.n_heads == 0) return RTP_OK;
   if (a.n_splits < 1) a.n_splits = 1;
   if (a.n_sub < 1) a.n_sub = 1;
@@ -1909,7 +1918,7 @@ static int32_t launch_prefill(const char* who, bool local, PrefillArgs& a, int32
   dim3 grid((unsigned)a.n_heads, (unsigned)((a.n_q + qt - 1) / qt), (unsigned)(B * (local ? 1 : a.n_splits * a.n_sub)));
   if (grid.y > 65535 || grid.z > 65535) return fail(RTP_ERR_INVALID_ARG, "%s: n_q / B too large for one launch", who);
   if (local) {
-    if ((int64_t)grid.x * grid.y * grid.z <= compute_units()) {
+    if ((int64_t)grid.x * grid.y * grid.z <= compute_units() && band_tiles(a, max_ctx) >= 4) {
       if (a.f16) RTP_LAUNCH((flash_prefill_local_kernel<true, 2>), grid, dim3(2 * kPfThreads), 0, s, a);
       else RTP_LAUNCH((flash_prefill_local_kernel<false, 2>), grid, dim3(2 * kPfThreads), 0, s, a);
     } else if (a.f16) RTP_LAUNCH((flash_prefill_local_kernel<true, 1>), grid, dim3(kPfThreads), 0, s, a);
@@ -1967,7 +1976,7 @@ int32_t prefill_range_attn(const char* who, bool dense, const rtp_layer_desc* L,
   a.n_heads = 0;
   for (int h = 0; h < L->n_q_heads; ++h)
     if (dense || !ht.is_ret[h]) a.heads[a.n_heads++] = (uint8_t)h;
-  return launch_prefill(who, !dense, a, B, s);
+  return launch_prefill(who, !dense, a, B, max_ctx, s);
 }
 
 // Workgroups per 32-query group of the threshold search: as many as fill two workgroups per compute unit, each with at
@@ -2137,7 +2146,7 @@ extern "C" int32_t rtp_sparse_attn_prefill(const rtp_layer_desc* layer, const vo
     a.n_splits = split ? ranges.dense : 1;
     a.n_sub = split ? (int32_t)std::min<size_t>(ranges.dense_sub, room / ranges.dense) : 1;
     a.part = (float*)ws;
-    return launch_prefill(who, false, a, 1, (hipStream_t)stream);
+    return launch_prefill(who, false, a, 1, chunk_start + T, (hipStream_t)stream);
   }
 
   // index queries: given, or projected in fp64 into the workspace first

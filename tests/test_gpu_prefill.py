@@ -566,3 +566,21 @@ def test_local_prefill_one_and_two_wave_groups(T, heads, kv_dtype):
         check_out(got[r["t"], r["h"]], r["out"], f"t{r['t']} h{r['h']}", tight="mfma")
         assert abs(lse[r["t"], r["h"]] - r["lse"]) < 3e-3
     assert (run.out[:, list(L.ret_heads)] == 5.0).all()
+
+
+@pytest.mark.parametrize("chunk_start,T,sink,window,groups", [
+    (0, 192, 4, 512, 1), (0, 193, 4, 512, 2),                              # three and four tiles of keys in all
+    (5000, 1, 4, 65, 1), (5000, 1, 4, 66, 2), (5000, 1, 0, 129, 1),        # by the window: one sink tile and two or three of the band
+    (5000, 128, 4, 2, 2), (100, 64, 64, 16, 1), (6, 3, 0, 0x7fffffff, 1)])
+def test_local_prefill_groups_by_the_tiles_of_a_band(chunk_start, T, sink, window, groups):
+    """Bands that cannot have four key tiles are left to one group of waves."""
+    print(f"[case] band of {T} queries behind {chunk_start}, {sink} + {window}", flush=True)
+    w = wl.small_prefill(DEV, chunk_start=chunk_start, T=T, n_q_heads=8, n_kv_heads=2, ret_heads=(1,), sink=sink, window=window, seed=311)
+    run = PrefillRun(w)
+    names = _launches(run.local_attn)
+    assert len(names) == 1 and names[0].strip("()").endswith(f", {groups}>"), names
+    torch.cuda.synchronize()
+    rows = [(t, h) for t in sorted({0, T // 2, T - 1}) for h in (0, 7)]
+    got = run.out.float().cpu().numpy().astype(np.float64)
+    for r in orc.prefill_rows(rows=rows, p=1.0, **prefill_oracle_inputs(w)):
+        check_out(got[r["t"], r["h"]], r["out"], f"t{r['t']} h{r['h']}", tight="mfma")
