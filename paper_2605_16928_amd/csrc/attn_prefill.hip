@@ -479,7 +479,8 @@ __device__ __forceinline__ float sel_first_below(float M, float index_scale, flo
 // concerned -- the mass above that bin is already known, the bin's members are spread over 128 new coarse bins --
 // until the threshold bin is an ordinary one (or 24 rounds, about 380 score units, are used up).
 constexpr int kSelThreads = 512;
-constexpr int kSelThreadsFew = 1024;               // alone on its compute unit: see rtp_sparse_attn_prefill
+constexpr int kSelThreadsFew = 1024;               // alone on its compute unit, keys for more than kSelFewRounds rounds of
+constexpr int kSelFewRounds = 90;                  // 32 * kSelRing: see rtp_sparse_attn_prefill
 constexpr float kSelLumpT = 15.875f;               // (kSelBins - 1) / 8: where the open-ended bin starts
 constexpr double kSelLumpScale = 7843180.797657975;   // exp(15.875)
 constexpr int kSelMaxRounds = 24;
@@ -2209,12 +2210,14 @@ extern "C" int32_t rtp_sparse_attn_prefill(const rtp_layer_desc* layer, const vo
     RTP_LAUNCH(prefill_select_kernel<3>, grid, dim3(kSelThreads), 0, s, a);
     RTP_LAUNCH(prefill_select_kernel<kSelFinish>, search_grid(1), dim3(kSelThreads), 0, s, a);
   } else {
-    // At most one workgroup per compute unit: sixteen waves each, four per SIMD, where eight leave it two.  Below about 5000
-    // keys the waves have too few rounds for that to show (one group of 32 queries and 5000 keys 79.6 / 80.4 us a call with
-    // eight / sixteen, a prompt of 2037, 2 heads, 68.1 / 70.1); beyond: 1024 queries of 4 heads at 5100 keys 104.9 / 100.9, at
-    // 12000 154 / 139; 100 at 12000 132 / 115; 2000 at 18000 233 / 208.
+    // At most one workgroup per compute unit: sixteen waves each, four per SIMD, where eight leave it two.  What every wave does
+    // by itself (its first loads, the ends of the member ranges) then takes twice the issue slots, which a peaked score law, whose
+    // last two sweeps are a few tiles, does not win back on short contexts: the line lies where no law lost by them.  Calls of 4
+    // heads, us, eight waves (as they were when sixteen came) / sixteen, clusters and a peaked law: 1000 queries at 6200 keys 111.0 / 104.8
+    // and 70.4 / 73.0, at 9000 130.1 / 120.2 and 77.3 / 78.8, 200 at 11200 133.1 / 121.6 and 68.8 / 70.4; beyond the line, 200 at 11600
+    // 139.9 / 122.6 and 71.9 / 70.7, 1000 at 12400 160.5 / 143.4 and 88.3 / 87.1, 2000 at 17000 230.8 / 205.8 and 99.7 / 98.5.
     const int64_t groups = (int64_t)layer->n_ret * n_qtiles, rounds = (chunk_start + T + 32 * kSelRing - 1) / (32 * kSelRing);
-    if (groups <= compute_units() && rounds > 40)
+    if (groups <= compute_units() && rounds > kSelFewRounds)
       RTP_LAUNCH((prefill_select_kernel<kSelAll, kSelThreadsFew>), search_grid(1), dim3(kSelThreadsFew), 0, s, a);
     else
       RTP_LAUNCH(prefill_select_kernel<kSelAll>, search_grid(1), dim3(kSelThreads), 0, s, a);

@@ -429,17 +429,22 @@ def test_sparse_prefill_sliced_search(chunk_start, T, kw, p):
 
 @pytest.mark.parametrize("chunk_start,T,kw,p", [
     (5087, 33, {}, 0.9), (5120, 1, {}, 0.8), (5121, 65, dict(own_frac=0.99, pick_run=32), 0.9), (8200, 97, dict(index_mode="proj"), 0.95),
-    (6000, 40, dict(index_scale=2.5), 0.999999)])
+    (6000, 40, dict(index_scale=2.5), 0.999999),
+    (11487, 33, {}, 0.9), (11520, 1, {}, 0.8), (11521, 65, dict(own_frac=0.99, pick_run=32), 0.9), (12000, 97, dict(index_mode="proj"), 0.95),
+    (11600, 40, dict(index_scale=2.5), 0.999999)])
 def test_sparse_prefill_search_in_large_workgroups(chunk_start, T, kw, p):
-    """Few query groups with keys for more rounds than eight waves take in five each: workgroups of sixteen waves, on either side
-    of the first such length, and with thresholds in the open-ended bin."""
+    """Few query groups with keys for more than 90 rounds of tiles: workgroups of sixteen waves, on either side of the first such
+    length, and with thresholds in the open-ended bin."""
     print(f"[case] search in large workgroups, T {T} behind {chunk_start}", flush=True)
     kw = dict(kw)
     scale = kw.pop("index_scale", None)
     w = wl.small_prefill("cpu", p=p, chunk_start=chunk_start, T=T, seed=161 + T, n_q_heads=4, n_kv_heads=2, ret_heads=(1,), **kw)
     if scale:
         w.layer.index_scale = scale
-    _check_sparse_prefill(w.to(DEV), f"large_{chunk_start}_{T}", p)
+    w = w.to(DEV)
+    names = _launches(PrefillRun(w).sparse_prefill)
+    assert any("kSelThreadsFew" in n for n in names) == (chunk_start + T > 90 * 128) and not any("<0>" in n for n in names), names
+    _check_sparse_prefill(w, f"large_{chunk_start}_{T}", p)
 
 
 def test_sparse_prefill_sliced_search_with_a_threshold_in_the_open_ended_bin():
