@@ -1674,9 +1674,11 @@ __device__ __forceinline__ void select_row(const TopPArgs& a, const int r) {
   }
 }
 
-// Alone in its launch: 1024 threads, rows of up to 32 chunks.
-constexpr int kRowThreads = 1024, kRowWords = 8, kRowRideWords = 4;
-__global__ __launch_bounds__(kRowThreads) void topp_select_rows_kernel(const TopPArgs a) { select_row<kRowThreads, kRowWords>(a, blockIdx.x); }
+// Alone in its launch: 1024 threads, rows of up to 8 chunks.
+constexpr int kRowThreads = 1024, kRowChunks = 8, kRowRideChunks = 6;
+__global__ __launch_bounds__(kRowThreads) void topp_select_rows_kernel(const TopPArgs a) {
+  select_row<kRowThreads, kRowChunks * kTpChunk / (32 * kRowThreads)>(a, blockIdx.x);
+}
 
 // The same with the local heads' work items behind the rows' workgroups (rtp_decode_attention); register budgets as in
 // topp_level_ride_kernel.
@@ -1684,7 +1686,7 @@ template <int G, bool F16 = false, bool PAGED = false>
 __global__ __launch_bounds__(kTpThreads, G == 8 ? 2 : 4) void topp_select_rows_ride_kernel(const TopPArgs a, const AttnDecodeArgs la,
                                                                                           const int n_ride, const int n_items) {
   const int bid = blockIdx.x;
-  if (bid < a.R) select_row<kTpThreads, kRowRideWords>(a, bid);
+  if (bid < a.R) select_row<kTpThreads, kRowRideChunks * kTpChunk / (32 * kTpThreads)>(a, bid);
   else gqa_decode_items<G, kSrcLocal, kTpThreads, 1, F16, PAGED>(la, bid - a.R, n_ride, n_items);
 }
 
@@ -1804,17 +1806,28 @@ static void launch_row_combine(const TopPArgs& a, const GatherArgs& ga, const At
   else RTP_LAUNCH(select_attend_combine_kernel<8>, grid, dim3(256), 0, s, a, ga, *ride);
 }
 
-// Rows whose level 1 is there: see select_row.
-// One workgroup goes through a row in about 0.5 us per 1000 scores with 512 threads (what the local heads' items allow beside
-// it), however many there are, where a launch per level spreads all rows over the chip: worth it where the rows are short or
-// fill the chip by themselves.  Whole steps, us, launches per level / whole rows: 4 rows of 16384 36.0 / 31.3, of 24000
-// 36.3 / 35.6, of 32768 36.1 / 36.7 (49000: 36.6 / 43.0); 32 rows of 32768 52.9 / 48.3, of 49000 58.8 / 59.7; 48 ragged rows
-// to 30011, paged, groups of 8 69.8 / 54.3, to 49000 62.2 / 58.2; 64 of 65536 110.9 / 101.8, but 64 ragged rows to 131072
-// 93.5 / 115; 160 of 131072 391 / 368; 256 ragged rows to 262144 1435 / 1346.  (The gather gains by equal shares of
-// each row's kept tokens in place of what its chunk holds: 32.5 -> 26.9 us on batch 8 x 131072.)
-static bool whole_rows(int32_t R, int64_t n_chunks, bool ride) {
-  const int64_t most = (int64_t)32 * (ride ? kRowRideWords * kTpThreads : kRowWords * kRowThreads) / kTpChunk;
-  return n_chunks <= most && (n_chunks <= 3 || R >= 8 * n_chunks);
+// Rows whose level 1 is there: see select_row.  One workgroup goes through a row however many there are, where a launch per level
+// spreads all rows over the chip.  The host knows the number of rows and a bound of their lengths, not how the lengths are
+// spread, so the lines lie where one long row among short ones does not lose either: whole rows where rows are short, or where
+// they fill the chip by themselves.  Whole steps, us (GPU time alone), launches per level / whole rows:
+//  * alone in the launch, 1024 threads, one row per compute unit, about 0.3 us per 1000 scores.  1 row of 24576 34.2 / 34.0, 128 ragged
+//    to 20483 55.3 / 49.0, 256 68.2 / 61.6, but 257 (a second round for one row) 68.0 / 71.5, 512 107 / 101, 1024 82.4 / 90.4.  Up to 32768,
+//    32 rows, one long 35.1 / 33.4.  Five to eight chunks: 40 rows, one of 40960, 38.0 / 42.1; 160, two of 36867, 55.3 / 57.3 (the selector
+//    alone wins from there on: 32.4 / 31.3 with one of 36867); 256, three of 53251, 65.4 / 65.6, ragged 104 / 94; 450 161 / 152; 512, two of
+//    36867, 84.0 / 87.5.  Longer rows: 256 ragged to 216181 260.6 / 254.1, but with one that long 78.2 / 103.5.
+//  * beside carried local heads, 512 threads, 0.5 us per 1000 scores.  One row of 16384 32.3 / 29.6, 512 to 12291 115 / 94 (8/2 heads).
+//    Beyond two chunks the longest row sets the time of the launch, which is hidden where a launch that carries the local rows takes
+//    as long anyway.  Three and four: 2 rows of 24576 32.3 / 34.9; 32 rows, one of 32768, with 640 carried tokens a row (8/2 heads, window
+//    512) 35.6 / 37.1, with 2560 (32/4 heads, window 2048) 40.5 / 37.6; 128 with few 46.1 / 43.1 and 52.2 / 44.5; 512 183 / 193.  Five and six, groups of
+//    up to 4: 48 rows, one of 45059, 3072 carried tokens a row 47.7 / 50.4, 5120 57.7 / 51.0; groups of 8 73.0 / 78.1.  Seven: 56 rows 53.9 / 56.6.
+static bool whole_rows(int32_t R, int64_t n_chunks, bool attend, const AttnDecodeArgs* ride, int ride_G) {
+  if (!ride) {
+    if (R > 256 && (R < 384 || R > 512)) return false;
+    return n_chunks <= ((attend ? R >= 240 && R <= 480 : R >= 160) ? kRowChunks : (R >= 32 ? 4 : 3));
+  }
+  const int64_t carried = (int64_t)ride->units * ride->n_splits * ride->split_tokens / R;
+  if (R < 32 || R > 256) return n_chunks == 2 && R <= 512;
+  return n_chunks <= (ride_G <= 4 && carried >= 4096 && R >= 48 ? kRowRideChunks : (R >= 128 || carried >= 2048 ? 4 : 2));
 }
 static int32_t launch_whole_rows(const char* who, TopPArgs& a, const GatherArgs* attend, const AttnDecodeArgs* ride, int ride_G,
                                  hipStream_t s) {
@@ -1898,7 +1911,7 @@ static int32_t run_select(const char* who, const float* scores, int64_t score_st
   hipStream_t s = (hipStream_t)stream;
   if (a.n_chunks == 1) return launch_rows(who, a, attend, ride, ride_G, s);
   dim3 grid((unsigned)a.n_chunks, (unsigned)R), block(kTpThreads);
-  if (level1_ready && whole_rows(R, a.n_chunks, ride != nullptr)) return launch_whole_rows(who, a, attend, ride, ride_G, s);
+  if (level1_ready && whole_rows(R, a.n_chunks, attend != nullptr, ride, ride_G)) return launch_whole_rows(who, a, attend, ride, ride_G, s);
   if (!level1_ready) {
     const int64_t nz = (int64_t)R * l.hist_stride;
     RTP_LAUNCH(topp_zero_kernel, dim3((unsigned)((nz + kTpThreads - 1) / kTpThreads)), block, 0, s, a.hist, nz);

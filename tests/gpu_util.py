@@ -30,6 +30,16 @@ def oracle_inputs(w: wl.DecodeWorkload) -> dict:
     return d
 
 
+def launches(call):
+    """Names of the kernels that `call` launches."""
+    rtp.rtp_profile_start(64)
+    try:
+        call()
+    finally:
+        recorded = rtp.rtp_profile_stop(64)
+    return [name for name, _ in recorded]
+
+
 # ---- comparators ------------------------------------------------------------------------------
 def check_scores(s_gpu: np.ndarray, s_ref: np.ndarray, qI_bits, kI_bits, what=""):
     q = orc.bf16_to_f64(qI_bits)

@@ -6,7 +6,7 @@ import torch
 
 from oracle import rtp_oracle as orc
 from paper_2605_16928_amd import rtp, workloads as wl
-from gpu_util import (DEV, DecodeRun, oracle_inputs, check_scores, check_selection, check_selection_valid, check_out,
+from gpu_util import (DEV, DecodeRun, launches, oracle_inputs, check_scores, check_selection, check_selection_valid, check_out,
                       check_layer, attend_reference, i32, ws_alloc)
 
 pytestmark = pytest.mark.gpu
@@ -693,19 +693,26 @@ def test_level1_with_bounds_on_either_side_of_one_chunk(score_bound, select_boun
             assert n > 0 and torch.equal(run.sel_idx[r, :n], ref.sel_idx[r, :n]), (a, b, r)
 
 
-@pytest.mark.parametrize("n_ret,ctx", [
-    (2, (8193, 300, 16384, 1)),                                             # 2 chunks: rows that end on, before and behind a chunk
-    (2, (24576, 8192, 255, 257, 24575)),                                    # 3 chunks, the most that any number of rows may have
-    (8, (32768, 30001, 513, 9000)),                                         # 4 chunks, 32 rows
-    (16, (36870, 36864, 2049, 20000, 64))])                                 # 5 chunks, 80 rows
-def test_whole_row_selection_equals_the_levels_by_launch(n_ret, ctx):
+@pytest.mark.parametrize("n_ret,ctx,window,alone,attend,carried", [
+    # 2 chunks: rows that end on, before and behind a chunk
+    (2, (8193, 300, 16384, 1), 96, True, True, True),
+    (2, (24576, 8192, 255, 257, 24575), 96, True, True, False),             # 3 chunks, the most that any number of rows may have
+    (8, (32768, 30001, 513, 9000), 96, True, True, False),                  # 4 chunks, 32 rows
+    (8, (32768, 30001, 513, 9000), 4096, True, True, True),                 # ... with thousands of local tokens a row carried
+    (4, (49152, 49151, 40961, 24577, 2000, 300, 1, 8193, 64, 255, 16385, 40960), 2048, False, False, True),    # 6 chunks, 48 rows
+    (16, (36870, 36864, 2049, 20000, 64), 96, False, False, False),         # 5 chunks, 80 rows: launches per level
+    (16, (65536, 65535, 57345, 49153, 8193, 300, 1, 40961, 255, 64000), 96, True, False, False),               # 8 chunks, 160 rows
+    (32, (65536, 65533, 57344, 8192, 300, 2, 40963, 61441), 96, True, True, True)])                            # 256 rows, no local head
+def test_whole_row_selection_equals_the_levels_by_launch(n_ret, ctx, window, alone, attend, carried):
     """Rows that one workgroup selects behind the score pass's level 1 against the launches per level (level1_ready = 0), which
     the oracle tests above hold: every output bit, twice over the same workspace, and once more as one call with the attention.
     Scores are sums of two bf16 values, chosen row by row: broad, tied in thousands, all equal, below zero, tiny, with minus
-    infinity, with one spike, beyond what the selector accepts; p from 0 (refused) to 1."""
+    infinity, with one spike, beyond what the selector accepts; p from 0 (refused) to 1.  `alone`, `attend` and `carried`: whether
+    the selector, the selector with the gather and the call that carries the local heads take whole rows."""
     print(f"[case] whole rows, {n_ret} heads, {ctx}", flush=True)
     g = torch.Generator().manual_seed(sum(ctx))
-    w = wl.small_decode("cpu", seed=241, n_q_heads=32, n_kv_heads=8, ret_heads=tuple(range(0, 32, 32 // n_ret)), ctx=ctx, p=(0.9,))
+    w = wl.small_decode("cpu" if sum(ctx) < 100000 else DEV, seed=241, n_q_heads=32, n_kv_heads=8, ret_heads=tuple(range(0, 32, 32 // n_ret)),
+                        ctx=ctx, p=(0.9,), window=window)
     w.qI.zero_()
     w.qI[..., :2] = 1.0
     laws = [lambda n: torch.randn(n, generator=g) * 2, lambda n: (torch.randn(n, generator=g) * 4).round() / 4,
@@ -740,17 +747,53 @@ def test_whole_row_selection_equals_the_levels_by_launch(n_ret, ctx):
             assert torch.equal(run.sel_idx[r, :n], ref.sel_idx[r, :n]), (rep, r)
             assert (run.sel_idx[r, n:] == -7).all(), (rep, r)
 
-    for rep in range(3):
+    whole = lambda names: any("topp_select_rows" in n for n in names)
+    for rep, (call, expected) in enumerate(((run.topp, alone), (run.topp, alone), (run.select_attend, attend), (run.decode_attention, carried))):
         run.sel_idx.fill_(-7)
         run.sel_count.fill_(-9)
         run.index_score()
-        if rep < 2:
-            run.topp()
-        else:
-            run.decode_attention()
+        names = launches(call)
+        assert whole(names) == expected, (rep, names)
         same(rep)
     a, b = run.out[:, w.layer.ret_heads].float(), ref.out[:, w.layer.ret_heads].float()
     assert ((a - b).abs() <= 2.0 ** -7 * torch.maximum(a.abs(), b.abs()) + 1e-5).all()
+
+
+@pytest.mark.parametrize("form,heads,window,B,bound,whole", [
+    ("topp", (32, 8, 4), 2048, 10, 40960, False), ("topp", (32, 8, 8), 2048, 32, 216181, False), ("topp", (32, 8, 1), 2048, 257, 9000, False),
+    ("topp", (32, 8, 4), 2048, 8, 32768, True), ("topp", (32, 8, 4), 2048, 7, 32768, False), ("topp", (32, 8, 8), 2048, 48, 60533, True),
+    ("attend", (32, 8, 4), 2048, 12, 49152, False), ("attend", (32, 8, 4), 2048, 40, 36867, False), ("attend", (32, 8, 8), 2048, 32, 60533, True),
+    ("attend", (32, 8, 4), 2048, 32, 131072, False), ("attend", (32, 8, 8), 2048, 64, 36867, False), ("attend", (32, 8, 8), 2048, 64, 24000, True),
+    ("one", (8, 2, 2), 512, 1, 24576, False), ("one", (8, 2, 2), 512, 1, 16384, True), ("one", (8, 2, 2), 512, 16, 32768, False),
+    ("one", (8, 2, 2), 512, 64, 32768, True), ("one", (32, 4, 4), 2048, 12, 30011, True), ("one", (32, 4, 1), 2048, 48, 49152, False),
+    ("one", (32, 8, 4), 2048, 12, 49152, True), ("one", (32, 8, 4), 2048, 12, 49153, False), ("one", (16, 8, 2), 700, 24, 49152, False),
+    ("one", (16, 8, 4), 700, 128, 20000, False), ("one", (16, 8, 4), 700, 128, 16384, True), ("one", (8, 2, 4), 700, 129, 16384, False)])
+def test_route_of_rows_by_their_number_and_bound(form, heads, window, B, bound, whole):
+    """Whole rows only where one long row among short ones does not lose by it, on either side of each line: the call goes by the
+    bound it is given (the rows here are short), and either route selects the same."""
+    print(f"[case] route of {form}, {heads}, {B} x {heads[2]} rows, bound {bound}", flush=True)
+    hq, hkv, n_ret = heads
+    w = wl.small_decode(DEV, seed=261, n_q_heads=hq, n_kv_heads=hkv, ret_heads=tuple(range(0, hq, hq // n_ret)),
+                        ctx=tuple(40 + 7 * (b % 11) for b in range(B)), p=(0.9,), window=window)
+    ref = DecodeRun(w, fuse_level1=False)
+    ref.index_score()
+    ref.topp()
+    run = DecodeRun(w)
+    run.max_ctx, run.stride = bound, (bound + 3) // 4 * 4
+    run.scores = torch.full((run.R, run.stride), float("nan"), device=DEV)
+    run.sel_idx = torch.full((run.R, run.stride), -7, dtype=torch.int32, device=DEV)
+    run.ws_topp = ws_alloc(rtp.rtp_topp_workspace_bytes(run.R, bound))
+    rtp.rtp_topp_workspace_init(run.ws_topp)
+    run.ws_fused = ws_alloc(rtp.rtp_select_attend_decode_workspace_bytes(run.desc, run.B, bound))
+    run.ws_local = ws_alloc(rtp.rtp_local_attn_workspace_bytes(run.desc, run.B, 1, bound))
+    run.index_score()
+    names = launches({"topp": run.topp, "attend": run.select_attend, "one": run.decode_attention}[form])
+    assert any("topp_select_rows" in n for n in names) == whole, names
+    torch.cuda.synchronize()
+    assert torch.equal(run.sel_count, ref.sel_count) and torch.equal(run.tau, ref.tau) and torch.equal(run.mass, ref.mass)
+    for r in range(0, run.R, max(1, run.R // 37)):
+        n = int(run.sel_count[r])
+        assert n > 0 and torch.equal(run.sel_idx[r, :n], ref.sel_idx[r, :n]), r
 
 
 @pytest.mark.parametrize("sizes", [
