@@ -161,6 +161,14 @@ def _ptr(t) -> Optional[int]:
 _raw_stream = None
 
 
+def _forget_raw_stream():
+    global _raw_stream
+    _raw_stream = None
+
+
+os.register_at_fork(after_in_child=_forget_raw_stream)      # (torch refuses the device in a child: ask it again there)
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
         # torch's current stream as a bare handle: a Stream object per call costs more than the rest of the marshalling
@@ -168,9 +176,12 @@ def _stream(stream) -> Optional[int]:
         global _raw_stream
         if _raw_stream is None:
             import torch
-            torch.cuda.current_stream()                     # (initialises the device, or raises where there is none)
+            handle = torch.cuda.current_stream().cuda_stream     # (initialises the device, or raises where there is none)
+            if not (hasattr(torch._C, "_cuda_getCurrentRawStream") and hasattr(torch._C, "_cuda_getDevice")):
+                return handle                                    # (not part of torch's interface)
             _raw_stream = (torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice)
-        return _raw_stream[0](_raw_stream[1]())
+        raw, device = _raw_stream
+        return raw(device())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream

@@ -383,3 +383,34 @@ def test_prefill_workspace_of_a_chunk_covers_shorter_chunks(hq, hkv, n_ret, T0, 
     whole = need(L, T0, N - T0)
     over = [t for t in range(1, T0) if need(L, t, N - t) > whole]
     assert not over, (len(over), over[:3])
+
+
+def test_a_forked_child_asks_torch_for_the_stream_again(monkeypatch):
+    """torch refuses a device that the parent initialised: the handle kept for the parent's calls must not hide that."""
+    import torch
+    monkeypatch.setattr(rtp, "_raw_stream", (lambda device: 11 + device, lambda: 3))
+
+    def refuse():
+        raise RuntimeError("Cannot re-initialize CUDA in forked subprocess")
+    monkeypatch.setattr(torch.cuda, "current_stream", refuse)
+    assert rtp._stream(None) == 14
+    pid = os.fork()
+    if pid == 0:
+        code = 1
+        try:
+            rtp._stream(None)
+        except RuntimeError:
+            code = 0
+        finally:
+            os._exit(code)
+    assert os.waitstatus_to_exitcode(os.waitpid(pid, 0)[1]) == 0
+    assert rtp._stream(None) == 14 and rtp._stream(5) == 5
+
+
+def test_stream_without_torch_s_unpublished_functions(monkeypatch):
+    import torch
+    import types
+    monkeypatch.setattr(rtp, "_raw_stream", None)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=23))
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    assert rtp._stream(None) == 23 and rtp._raw_stream is None
