@@ -487,14 +487,16 @@ def test_decode_attention_in_one_call_matches_oracle(name):
         check_layer(out, lse, w, oi, ref, sets, f"{name} layer")
 
 
-def test_decode_step_replays_from_a_hip_graph():
+@pytest.mark.parametrize("ctx,batch,kernel", [(20000, 3, "topp_level_ride_kernel"), (9000, 2, "topp_select_rows_ride_kernel"), (5000, 2, "topp_row_kernel")])
+def test_decode_step_replays_from_a_hip_graph(ctx, batch, kernel):
     """The step (score pass + rtp_decode_attention) captured once and replayed: every replay, with eager steps
     of another copy and synchronisations in between, must reproduce the eager result bit for bit (the library
     records kernel launches only: no memset nodes, no allocation, no host synchronisation)."""
-    print("[case] decode step in a HIP graph", flush=True)
-    w = wl.c2(DEV, ctx=20000, batch=3, p=0.9)
-    run, other = DecodeRun(w), DecodeRun(wl.c2(DEV, seed=5, ctx=9000, batch=2, p=0.8))
-    run.step_one_stream()
+    print(f"[case] decode step in a HIP graph, {batch} x {ctx}", flush=True)
+    w = wl.c2(DEV, ctx=ctx, batch=batch, p=0.9)
+    run, other = DecodeRun(w), DecodeRun(wl.c2(DEV, seed=5, ctx=29000 - ctx, batch=5 - batch, p=0.8))
+    names = launches(run.step_one_stream)
+    assert any(kernel in n for n in names), names
     torch.cuda.synchronize()
     want = (run.out.clone(), run.lse.clone(), run.sel_idx.clone(), run.sel_count.clone(), run.tau.clone())
     side = torch.cuda.Stream()
@@ -664,28 +666,31 @@ def test_gather_shared_by_several_workgroups(ctx, clustered):
     assert (run.lse[:, L.ret_heads] - two.lse[:, L.ret_heads]).abs().max() < 1e-4
 
 
-@pytest.mark.parametrize("score_bound,select_bound", [(5000, 20000), (20000, 5000)])
+@pytest.mark.parametrize("score_bound,select_bound", [(5000, 20000), (20000, 5000), (5000, 40000), (40000, 5000)])
 @pytest.mark.parametrize("R", [2, 20])
 def test_level1_with_bounds_on_either_side_of_one_chunk(score_bound, select_bound, R):
     """The bound handed to the score pass and the selector's differ, one of them at most 8192: rows of one chunk are selected all
-    the same, and the workspace of the first step serves the steps behind it, whichever bound they name."""
+    the same, and the workspace of the first step serves the steps behind it, whichever bound they name.  (A selector bound of 20000
+    takes whole rows, one of 40000 the launches per level.)"""
     print(f"[case] score pass bound {score_bound}, selector bound {select_bound}, {R} rows", flush=True)
     w = wl.small_decode("cpu", seed=231 + R, ctx=(5000, 4097, 300, 1, 2049, 4999, 777, 5000, 64, 4000)[:R // 2], p=(0.9,), ret_heads=(0, 5)).to(DEV)
     ref = DecodeRun(w, fuse_level1=False)
     ref.index_score()
     ref.topp()
     run = DecodeRun(w)
-    run.stride = 20000
+    bound = max(score_bound, select_bound)
+    run.stride = bound
     run.scores = torch.full((run.R, run.stride), float("nan"), device=DEV)
     run.sel_idx = torch.full((run.R, run.stride), -7, dtype=torch.int32, device=DEV)
-    run.ws_topp = ws_alloc(rtp.rtp_topp_workspace_bytes(run.R, 20000))
+    run.ws_topp = ws_alloc(rtp.rtp_topp_workspace_bytes(run.R, bound))
     rtp.rtp_topp_workspace_init(run.ws_topp)
-    for a, b in ((score_bound, select_bound), (20000, 20000), (score_bound, select_bound), (score_bound, score_bound)):
+    for a, b in ((score_bound, select_bound), (bound, bound), (score_bound, select_bound), (score_bound, score_bound)):
         run.sel_count.fill_(-7)
         run.max_ctx = a
         run.index_score()
         run.max_ctx = b
-        run.topp()
+        names = launches(run.topp)
+        assert any("topp_level_kernel" in n for n in names) == (b == 40000), names
         torch.cuda.synchronize()
         assert torch.equal(run.sel_count, ref.sel_count) and torch.equal(run.tau, ref.tau) and torch.equal(run.mass, ref.mass), (a, b)
         for r in range(run.R):

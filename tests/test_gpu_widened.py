@@ -7,7 +7,7 @@ import torch
 
 from oracle import rtp_oracle as orc
 from paper_2605_16928_amd import rtp, workloads as wl
-from gpu_util import DEV, DecodeRun, oracle_inputs, i32, i64, ws_alloc, layer_desc_of
+from gpu_util import DEV, DecodeRun, launches, oracle_inputs, i32, i64, ws_alloc, layer_desc_of
 
 pytestmark = pytest.mark.gpu
 
@@ -394,24 +394,33 @@ def test_paged_sparse_attention_matches_contiguous_and_oracle(page_size, kv_dtyp
             assert abs(float(lse[b, h]) - l) < 2e-3
 
 
-@pytest.mark.parametrize("case", ["g4", "g8_f16", "g1", "g2_bigbatch"])
+@pytest.mark.parametrize("case", ["g4", "g8_f16", "g1", "g2_bigbatch", "levels_g2", "levels_g2_f16", "levels_g4", "levels_g4_f16", "levels_g8",
+                                  "levels_g8_f16"])
 def test_decode_attention_from_a_paged_cache(case):
     """Everything after the score pass with the whole K/V cache in pages (retrieval heads' gather and the local
     heads' sink + window rows through the page table): selections and outputs bit-identical to the contiguous
     call, and every head against the oracle's attention read through the table.  The cases cover the carried
-    form (G = 2, 4, 8), the fall-back that runs the parts in turn (G = 1) and fp16 rows."""
+    form (G = 2, 4, 8), the fall-back that runs the parts in turn (G = 1), fp16 rows, and few rows of more than two chunks, which take
+    the launches per level."""
     print(f"[case] decode attention from a paged cache, {case}", flush=True)
+    levels = case.startswith("levels")
     kw = {"g4": dict(),
           "g8_f16": dict(n_q_heads=16, n_kv_heads=2, ret_heads=(3, 8), sink=4, window=700, kv_dtype="fp16"),
           "g1": dict(n_q_heads=4, n_kv_heads=4, ret_heads=(1, 3)),
-          "g2_bigbatch": dict(n_q_heads=8, n_kv_heads=4, ret_heads=(0, 1, 6))}[case]
-    ctx = (700, 1531, 64, 2048, 9000, 13) if case != "g2_bigbatch" else tuple(int(x) for x in
+          "g2_bigbatch": dict(n_q_heads=8, n_kv_heads=4, ret_heads=(0, 1, 6)),
+          "levels_g2": dict(n_q_heads=4, n_kv_heads=2, ret_heads=(0, 3)),
+          "levels_g4": dict(n_q_heads=8, n_kv_heads=2, ret_heads=(1, 2)),
+          "levels_g8": dict(n_q_heads=16, n_kv_heads=2, ret_heads=(5, 8), window=700)}[case if case in ("g8_f16",) else case.replace("_f16", "")]
+    if levels and case.endswith("_f16"):
+        kw["kv_dtype"] = "fp16"
+    ctx = (25000, 700, 8193, 16384) if levels else (700, 1531, 64, 2048, 9000, 13) if case != "g2_bigbatch" else tuple(int(x) for x in
                                                                              np.random.default_rng(3).integers(5, 3000, size=40))
     page_size = 64 if case != "g1" else 16
     w = wl.small_decode(DEV, seed=71, ctx=ctx, **kw)
     L = w.layer
     run = DecodeRun(w)
-    run.step_one_stream()
+    names = launches(run.step_one_stream)
+    assert any("topp_level_ride_kernel" in n for n in names) == levels, names
     torch.cuda.synchronize()
     want = (run.out.clone(), run.lse.clone(), run.sel_idx.clone(), run.sel_count.clone(), run.tau.clone(), run.mass.clone())
     # one shuffled pool for all sequences and KV heads
