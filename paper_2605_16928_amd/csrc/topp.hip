@@ -1337,7 +1337,22 @@ __global__ __launch_bounds__(kTpThreads) void topp_row_kernel(const TopPArgs a, 
       kept += sh_i[w];
     }
     int32_t* const to = ATTEND ? sh_list : a.sel_idx + (int64_t)r * a.sel_stride;
-    for (uint32_t left = keep; left != 0; left &= left - 1) to[pos++] = own + __builtin_ctz(left);
+    if (ATTEND || kept * 2 <= n) {
+      for (uint32_t left = keep; left != 0; left &= left - 1) to[pos++] = own + __builtin_ctz(left);
+    } else {
+      // A list of more than half of the scores that goes to memory: a thread's stores lie up to 64 bytes from its neighbours'.  The
+      // wave goes through its scores 64 at a time instead, each lane with the owner's mask and rank.  Selector alone, us, a loop over
+      // a thread's own / this: 512 rows of 8192 that keep 44 % 49.8 / 49.4, 93 % 61.9 / 51.5, all 54.2 / 39.4; 4 rows 17.2 / 17.9, 19.8 / 18.2
+      // and 12.1 / 10.0.
+      static_assert(kTpVec * 4 <= 16 && kTpChunk < 65536, "mask and rank in one word");
+      const uint32_t inverse = 65536u / per + (65536 % per != 0 ? 1 : 0);          // i / per for i < 64 * 16
+      const int packed_keep = (int)(keep | (uint32_t)pos << 16);
+      for (int it = 0; it < per; ++it) {
+        const int i = it * 64 + lane, owner = (int)((uint32_t)i * inverse >> 16), bit = i - owner * per;
+        const uint32_t of = (uint32_t)__shfl(packed_keep, owner);
+        if (of >> bit & 1u) to[(of >> 16) + __popc(of & ((1u << bit) - 1u))] = (tid & ~63) * per + i;
+      }
+    }
   } else {
     res_tau = (flags < 0 && n > 0) ? __builtin_nanf("") : ninf;
     res_mass = 0.f;

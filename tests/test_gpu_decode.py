@@ -698,6 +698,37 @@ def test_level1_with_bounds_on_either_side_of_one_chunk(score_bound, select_boun
             assert n > 0 and torch.equal(run.sel_idx[r, :n], ref.sel_idx[r, :n]), (a, b, r)
 
 
+@pytest.mark.parametrize("n", [1, 63, 257, 2047, 2048, 2049, 4095, 4100, 6143, 6144, 6145, 8191, 8192])
+@pytest.mark.parametrize("call", ["topp", "decode_attention"])
+def test_one_chunk_rows_that_keep_few_and_many(n, call):
+    """Lists of rows of one chunk on either side of half of the scores kept, where they are written in another order, at every
+    number of scores per thread: exactly the finite scores at or above the reported threshold, ascending, nothing behind them."""
+    print(f"[case] one chunk, {n} scores, {call}", flush=True)
+    g = torch.Generator().manual_seed(n)
+    w = wl.small_decode("cpu", seed=271, n_q_heads=16, n_kv_heads=4, ret_heads=tuple(range(0, 16, 2)), ctx=(n, n), p=(0.9,), window=32).to(DEV)
+    run = DecodeRun(w)
+    p = torch.tensor([0.05, 0.3, 0.5, 0.9, 0.97, 0.999, 0.999999, 1.0], dtype=torch.float32).repeat(2)
+    w.p_rows.copy_(p)
+    for rep in range(2):
+        run.index_score()
+        s = torch.randn((run.R, n), generator=g) * (0.3 if rep else 1.5)
+        s[8:].masked_fill_(torch.rand((8, n), generator=g) < 0.2, -np.inf)
+        s[:, 0] = 0.5
+        run.scores[:, :n] = s.to(DEV)
+        run.sel_idx.fill_(-7)
+        getattr(run, call)()
+        torch.cuda.synchronize()
+        tau, cnt, idx = run.tau.cpu(), run.sel_count.cpu(), run.sel_idx.cpu()
+        for r in range(run.R):
+            want = torch.nonzero((s[r] >= tau[r]) & (s[r] > -np.inf)).squeeze(1).to(torch.int32)
+            assert int(cnt[r]) == len(want) and torch.equal(idx[r, :len(want)], want) and (idx[r, len(want):] == -7).all(), r
+            wgt = torch.exp(s[r].double() - s[r].max().double())
+            assert wgt[want.long()].sum() >= (float(p[r]) - 1e-6) * wgt.sum()
+            kept = s[r][want.long()]
+            if p[r] < 1:
+                assert wgt[want.long()][kept > kept.min()].sum() < (float(p[r]) + 1e-6) * wgt.sum(), r
+
+
 @pytest.mark.parametrize("n_ret,ctx,window,alone,attend,carried", [
     # 2 chunks: rows that end on, before and behind a chunk
     (2, (8193, 300, 16384, 1), 96, True, True, True),
