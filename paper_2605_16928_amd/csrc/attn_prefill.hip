@@ -478,6 +478,10 @@ __device__ __forceinline__ float sel_first_below(float M, float index_scale, flo
 // taken as "keep everything": the workgroup repeats sweep 1 with the reference lowered by 15.875 for the queries
 // concerned -- the mass above that bin is already known, the bin's members are spread over 128 new coarse bins --
 // until the threshold bin is an ordinary one (or 24 rounds, about 380 score units, are used up).
+//
+// At the limit of 128 registers the forms that run the whole search keep 68 to 84 bytes per lane in scratch, the slices of sweep 3
+// eight: addresses and ends of ranges that are stored before a sweep and read back at the start of the next one or behind it, none of it inside
+// the loops over tiles.
 constexpr int kSelThreads = 512;
 constexpr int kSelThreadsFew = 1024;               // alone on its compute unit, keys for more than kSelFewRounds rounds of
 constexpr int kSelFewRounds = 90;                  // 32 * kSelRing: see rtp_sparse_attn_prefill
@@ -1121,8 +1125,9 @@ __global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const Prefil
 // of 32 cycles, 24 LDS reads and, by the counters, 64 (dense) or 122 (selecting) other vector instructions each, with the matrix
 // pipe busy 59 and 48 % of the cycles and the LDS, at the rates of these reads, about half of them.  Spreading a block's softmax
 // over both streams (it used to run beside the PV MFMAs alone) took the dense call of this shape from 1132 to 1124 us, 333
-// queries' launch from 132 to 129 and left the last chunk of 1M as it was: at a die clock of 1.75 GHz, against 2.4 when idle,
-// the launch has come to what the chip's power allows.
+// queries' launch from 132 to 129 and left the selecting last chunk of 1M as it was.  The dense launch runs at a die clock of 1.71 to
+// 1.75 GHz, against 2.4 when idle: it has come to what the chip's power allows.  The selecting one (1.98 GHz, matrix pipe busy 51 %) has
+// not; it issues twice the other vector instructions.
 constexpr int kPwQ = 256;
 constexpr int kPwThreads = 512;
 constexpr int kPwStages = 3;

@@ -8,6 +8,12 @@
 // descending cumulative mass crosses p * Z.  After three levels the threshold key is exact.
 // Masses are integers (see topp_common.h), so the result does not depend on atomic ordering.
 //
+// Three forms, chosen by the number of rows and the bound of their lengths:
+//  * rows of one chunk (kTpChunk scores): one launch, from the scores alone (topp_row_kernel);
+//  * rows of a few chunks behind a score pass that has left level 1: one workgroup per row walks it (select_row), the gather, if
+//    asked for, is a launch of its own over the finished lists (gather_lists_kernel); whole_rows() says which rows;
+//  * everything else, and every top-k of more than one chunk: launches per level, as follows.
+//
 // Launches: [zero] -> level 1 -> level 2 -> level 3 -> write.  The first two disappear when
 // the score pass has already accumulated level 1 (level1_ready).  Level 3 also leaves, per chunk, the
 // number of scores strictly above the 22-bit prefix (certainly kept) and appends the few scores that
@@ -1126,11 +1132,13 @@ __global__ __launch_bounds__(256) void select_attend_combine_kernel(const TopPAr
 // A row of at most kTpChunk scores is one workgroup's chunk, so nothing has to cross a launch: the scores stay in
 // registers through all three levels, the histograms never leave LDS (the score pass leaves the workspace alone for such
 // rows: a level-1 histogram by the way costs it more than it costs the 512 threads here), the chunk's offset is 0 and,
-// with ATTEND, its partial softmax state is the row's result.  The same bins, weights, scans and compaction as in the
-// launches above give the same numbers.  RIDE_G > 0: the last n_ride workgroups run the local heads' work items of the
+// with ATTEND, its partial softmax state is the row's result.  Levels 1 and 2 have the bins, weights and scans of the launches
+// above; level 3 adds up the same integer weights in registers where at most 64 scores share the 22-bit prefix, and the kept
+// positions are ranked by one prefix sum over consecutive scores: the same numbers.  RIDE_G > 0: the last n_ride workgroups run the local heads' work items of the
 // step (rtp_decode_attention).  n_copy workgroups per row repeat the selection and share the gather where a merge launch
 // follows for the local heads anyway.
-// Latency-bound throughout: a step of one sequence of 4096 tokens 38.7 -> 23 us of kernels, the selector alone 27 -> 11 us.
+// Latency-bound throughout: a step of one sequence of 4096 tokens 38.3 us by launches per level, 20 with this launch, 17.2 since
+// its scores are consecutive per thread and level 3 has no histogram (13.9 of them in here, by a kernel trace).
 template <bool ATTEND, int RIDE_G, bool F16 = false, bool PAGED = false>
 __global__ __launch_bounds__(kTpThreads) void topp_row_kernel(const TopPArgs a, const GatherArgs ga, const AttnDecodeArgs la,
                                                               const int n_ride, const int direct) {
@@ -1760,7 +1768,9 @@ constexpr int kDirectTokens = 1024;
 // More chunks: four while they leave the chip a quarter full (1 x 32768, 4 heads: 15.3 -> 11.0 us; 3 x 32768: 15.5 -> 12.5),
 // fewer where a row would have more partials than the merge's short form reads in one round, 32 (1 x 131072: write and merge
 // 19.4 us with one, 18.2 with two, 18.7 with four).  Beyond 64 workgroups the copies only compete for the memory (5 x 65536:
-// 17.7 us with one, 19.8 with two; 12 ragged rows to 30011: 15.3 and 18.0).
+// 17.7 us with one, 19.8 with two; 12 ragged rows to 30011: 15.3 and 18.0).  Those are times of the launches per level; behind
+// whole rows the copies are equal shares of a list: a step of 1 x 16384, 4 heads, p = 0.9 / 0.98 30.3 / 39.2 us with four, 32.2 / 47.7
+// with two, 34.1 / 65.8 with one, of 8 x 16384 36.3 / 56.1, 37.6 / 57.2 and 40.0 / 74.4.
 static int gather_copies(int64_t R, int64_t n_chunks) {
   if (n_chunks == 1) return R <= 64 ? 4 : (R <= 128 ? 2 : 1);
   return R * n_chunks > 64 ? 1 : (n_chunks <= 8 ? 4 : (n_chunks <= 16 ? 2 : 1));

@@ -16,8 +16,8 @@ namespace rtp {
 
 // Scores of a row per workgroup of the selector.  Rows of at most that many are selected in one launch, from the scores
 // alone: the score pass then leaves the selector's workspace untouched.  Each of the two goes by the bound it was given.  Where
-// only the score pass's is that small, the level-2 launch makes up for the missing level 1; where only the selector's is, its
-// one launch clears the level 1 it has no use for.
+// only the score pass's is that small, the selector makes up for the missing level 1 (select_row, or the level-2 launch); where only
+// the selector's is, its one launch clears the level 1 it has no use for.
 constexpr int kTpChunk = 8192;
 
 constexpr int kBins1 = 2048, kBins2 = 2048, kBins3 = 1024;
