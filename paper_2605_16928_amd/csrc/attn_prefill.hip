@@ -26,6 +26,7 @@ namespace rtp {
 
 constexpr int kPfThreads = 256;
 constexpr int kPfQ = 128;          // queries per workgroup
+constexpr int kPwQ = 256;          // of the wide kernel
 constexpr int kPfK = 64;           // keys per tile
 constexpr int kPfPart = kHeadDim + 4;   // floats per partial row: max, sum, 2 pad, unnormalised output[128]
 
@@ -74,14 +75,33 @@ struct PrefillArgs {
   int32_t n_slice;
   float* sl_max;                // [groups, n_slice, 32]: the slices' row maxima
   double* sl_hist;              // [2, groups, n_slice, 128, 32]: the slices' histograms (running sums), of the current sweep and the one before
-  struct SelState* sl_state;    // [2, groups, 32]: what a scan found, read by the next launch
-  int32_t* sl_again;            // [groups]: 1 = some query's threshold lies in the open-ended bin, the last launch searches the group
+  struct SelState* sl_state;    // [2, n_ret, n_q]: what a scan found, read by the next launch
+  int32_t* sl_again;            // [groups]: 1 = some query's threshold lies in the open-ended bin, the last launch searches the group;
+                                // 2 = the group's search is complete
+  // queries regrouped by how much they keep (prefill_order_kernel); NULL: every launch takes them by position
+  int32_t* order;               // [n_ret, n_q]: the query of every place
+  int32_t* order_on;            // [n_ret, blocks]: how the block's queries stand, kOrder...
+  int32_t order_block;          // queries per block, a multiple of kPwQ
+  int32_t one_round;            // workgroups of a search launch that run at the same time
+  int32_t order_whole;          // the first digits came from whole rows: kOrderOwnAlike asks for whole groups too
+  // the attention launch's work, cut by the lists' lengths (prefill_plan_kernel); NULL: n_splits ranges of every list.  A query tile has two
+  // lists then: list i of its first waves (the ordinary act_list), and of the others, where they keep little, list n_lists + i, which is
+  // in more_list: queries in the order of what they keep have one such tile to a block at the most
+  int32_t* n_units;             // how many there are; 0: nothing is regrouped, n_splits ranges of every list all the same
+  int2* units;                  // [n_units]: {list, range | ranges << 8 | first wave << 16 | past the last << 20 | kUnitExact}
+  int2* list_info;              // [2 * n_lists]: {tiles, the same waves << 16 | kUnitExact}, n_lists = n_ret * ceil(n_q / 256)
+  int2* list_ranges;            // [2 * n_lists]: {ranges | past the last wave << 16, where the first one's partials are}, in 256-row pieces of `part`
+  int32_t* more_list;           // [n_ret, blocks, n_t64]
+  int32_t part_cap;             // pieces there is room for
 };
 
-struct SelState {               // one query between two launches of a sliced search
+enum { kOrderOwnAlike = 0, kOrderOwn = 1, kOrderByKept = 2 };  // by position, their last sweeps about equally long; by position; regrouped
+constexpr int kUnitExact = 1 << 30, kFewKept = 64;
+enum { kSelRebased = 1, kSelOpen = 2, kSelClassShift = 8 };   // SelState::flags; the class of prefill_order_kernel above them
+struct SelState {               // one query between two launches of a search
   double Z, above;
   float selM, x_max;
-  int32_t prefix, pad;
+  int32_t prefix, flags;
 };
 
 // Key ranges a selecting launch behind a threshold search really uses: the grid is sized for lists that differ
@@ -90,6 +110,11 @@ struct SelState {               // one query between two launches of a sliced se
 __device__ __forceinline__ int listed_splits(const PrefillArgs& a) {
   const int longest = a.act_range[0], shortest = a.act_range[1];
   return (2 * shortest >= longest) ? min(a.n_splits_even, a.n_splits) : a.n_splits;
+}
+
+__device__ __forceinline__ int32_t* more_list_of(const PrefillArgs& a, int j, int q_tile) {
+  const int blocks = (a.n_q + a.order_block - 1) / a.order_block;
+  return a.more_list + ((int64_t)j * blocks + q_tile * kPwQ / a.order_block) * a.n_t64;
 }
 
 enum { kModeDense = 0, kModeSparse = 1 };
@@ -488,9 +513,134 @@ constexpr int kSelFewRounds = 90;                  // 32 * kSelRing: see rtp_spa
 constexpr float kSelLumpT = 15.875f;               // (kSelBins - 1) / 8: where the open-ended bin starts
 constexpr double kSelLumpScale = 7843180.797657975;   // exp(15.875)
 constexpr int kSelMaxRounds = 24;
-constexpr int kSelAll = -1, kSelFinish = 4;        // STEP of prefill_select_kernel beside the sweeps 0 .. 3
+// STEP of prefill_select_kernel beside the sweeps 0 .. 3: the whole search; its end after sliced sweeps; the first digit of whole
+// rows, and of sliced ones, left to prefill_order_kernel
+constexpr int kSelAll = -1, kSelFinish = 4, kSelFirst = 5, kSelScan = 6;
 
-template <int STEP, int THREADS = kSelThreads>
+// ---- queries regrouped by how much they keep ----
+// A 32-query group of the search's last sweeps and a 256-query tile of the attention launch have to visit every key tile that one
+// of their queries keeps a key in.  Where queries that keep a few tokens stand among queries that keep tenths of the context, that
+// is nearly every tile for every group.  So, once the first digit of every threshold is known (and with it, from the histogram, about how many candidates
+// a query keeps), the queries of a block are brought into the order of that number, in half octaves, those that keep most first, and by position within a class; the
+// sweeps behind, the tile lists and the attention launch take them in this order.  No result depends on it but for the order
+// of fp32 sums.  Share of the key tiles that 256-query tiles visit, by position / regrouped: last 8192 queries of 1M tokens with Zipf
+// clusters 0.996 / 0.46, 4096 queries at 128K with clusters of 32 at p = 0.9 and 0.8 0.985 / 0.66 and 0.985 / 0.37, with a few hard
+// queries among easy ones 0.18 / 0.064; ten classes per decade or whole octaves instead change little (0.455, 0.48 on the first).
+// A block's order is left alone unless, for queries that keep more than 1/64, 1/256 or 1/1024 of the context, a sixteenth of its tiles
+// would be spared a query that does: sweep 2 then finds the tiles' maxima as sweep 0 left them, for these groups.  If then none
+// or a quarter of them and more keep more than 1/2048, a group's last sweeps are not cut into slices (4096 queries at 128K tokens that all keep a
+// sixth: sweeps 2 and 3 640 us in slices, 590 without; one that keeps 800 of 1M among 8191 that keep 20: 670 and 1550).
+constexpr int kOrderThreads = 1024;
+constexpr int kOrderMax = 8192;                    // queries of a block
+constexpr int kOrderClasses = 64;
+constexpr int kFewClass = 12;                      // below it: fewer than kFewKept kept
+static_assert(kFewKept == 1 << (kFewClass / 2), "half octaves");
+__global__ __launch_bounds__(kOrderThreads) void prefill_order_kernel(const PrefillArgs a) {
+  constexpr int NW = kOrderThreads / 64, ROUNDS = kOrderMax / kOrderThreads, TILES = kOrderMax / kPwQ;
+  __shared__ int at[kOrderClasses][ROUNDS * NW];   // places of a wave's round within a class, then before it
+  __shared__ int class_at[kOrderClasses];
+  __shared__ uint32_t tile_has[3];                 // which tiles hold a query of a class from here on
+  __shared__ int n_hard[4];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int j = blockIdx.y, first = blockIdx.x * a.order_block, n = min(a.order_block, a.n_q - first);
+  const SelState* const st = a.sl_state + (int64_t)j * a.n_q + first;
+  int32_t* const order = a.order + (int64_t)j * a.n_q + first;
+  for (int i = tid; i < kOrderClasses * ROUNDS * NW; i += kOrderThreads) (&at[0][0])[i] = 0;
+  for (int i = tid; i < (n + kPwQ - 1) / kPwQ; i += kOrderThreads) a.act_count[(int64_t)j * ((a.n_q + kPwQ - 1) / kPwQ) + first / kPwQ + i] = 0;
+  if (tid < 4) { if (tid < 3) tile_has[tid] = 0; n_hard[tid] = 0; }
+  __syncthreads();
+  const float keys = (float)(a.q_start_host + first + n);
+  int cls[ROUNDS], rank[ROUNDS];
+#pragma unroll
+  for (int k = 0; k < ROUNDS; ++k) {
+    const int i = k * kOrderThreads + tid;
+    const bool on = i < n;
+    cls[k] = on ? kOrderClasses - 1 - (st[i].flags >> kSelClassShift) : kOrderClasses - 1;      // (the class that keeps most comes first)
+    uint64_t same = __ballot(on);
+#pragma unroll
+    for (int b = 0; b < 6; ++b) {
+      const uint64_t bit = __ballot((cls[k] >> b) & 1);
+      same &= (cls[k] >> b) & 1 ? bit : ~bit;
+    }
+    rank[k] = __popcll(same & ((1ull << lane) - 1ull));
+    if (on && rank[k] == 0) at[cls[k]][k * NW + wave] = __popcll(same);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {                                  // 1/64, 1/256, 1/1024 of the context
+      const float least = 2.f * (__builtin_amdgcn_logf(keys) - (6.f + 2.f * q));
+      const uint64_t hard = __ballot(on && (float)(kOrderClasses - 1 - cls[k]) >= least);
+      if (lane == 0 && hard != 0ull) {
+        atomicOr(&tile_has[q], 1u << (i / kPwQ));
+        atomicAdd(&n_hard[q], __popcll(hard));
+      }
+    }
+    const uint64_t deep = __ballot(on && (float)(kOrderClasses - 1 - cls[k]) >= 2.f * (__builtin_amdgcn_logf(keys) - 11.f));
+    if (lane == 0 && deep != 0ull) atomicAdd(&n_hard[3], __popcll(deep));
+  }
+  __syncthreads();
+  const int n_tiles = (n + kPwQ - 1) / kPwQ;
+  bool on = false;
+#pragma unroll
+  for (int q = 0; q < 3; ++q) on = on || 16 * (__popc(tile_has[q]) - (n_hard[q] + kPwQ - 1) / kPwQ) >= n_tiles;
+  if (tid == 0) a.order_on[j * gridDim.x + blockIdx.x] = on ? kOrderByKept : n_hard[3] > 0 && 4 * n_hard[3] < n ? kOrderOwn : kOrderOwnAlike;
+  if (!on) {                                                        // (the same for the whole workgroup)
+    for (int i = tid; i < n; i += kOrderThreads) order[i] = first + i;
+    return;
+  }
+  // sixteen threads go through a class, eight entries each
+  constexpr int PER = ROUNDS * NW / 16;
+  static_assert(kOrderThreads == 16 * kOrderClasses && PER * 16 == ROUNDS * NW && TILES <= 32, "one run of entries per thread, one bit per tile");
+  {
+    const int c = tid >> 4, e0 = (tid & 15) * PER;
+    int sum = 0;
+#pragma unroll
+    for (int e = 0; e < PER; ++e) sum += at[c][e0 + e];
+    int incl = sum;
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) {
+      const int up = __shfl_up(incl, o, 16);
+      if ((tid & 15) >= o) incl += up;
+    }
+    int run = incl - sum;
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+      const int v = at[c][e0 + e];
+      at[c][e0 + e] = run;
+      run += v;
+    }
+    if ((tid & 15) == 15) class_at[c] = incl;
+  }
+  __syncthreads();
+  if (wave == 0) {
+    const int v = class_at[lane];
+    int incl = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int up = __shfl_up(incl, o);
+      if (lane >= o) incl += up;
+    }
+    class_at[lane] = incl - v;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < ROUNDS; ++k) {
+    const int i = k * kOrderThreads + tid;
+    if (i < n) order[class_at[cls[k]] + at[cls[k]][k * NW + wave] + rank[k]] = first + i;
+  }
+}
+
+// Least and greatest of 32 positions, lane and lane ^ 32 holding the same one.
+__device__ __forceinline__ void position_range(int m, int& lo, int& hi) {
+  lo = hi = m;
+#pragma unroll
+  for (int o = 16; o > 0; o >>= 1) {
+    lo = min(lo, __shfl_xor(lo, o));
+    hi = max(hi, __shfl_xor(hi, o));
+  }
+  lo = __builtin_amdgcn_readfirstlane(lo);
+  hi = __builtin_amdgcn_readfirstlane(hi);
+}
+
+template <int STEP, int THREADS = kSelThreads, bool ORDERED = false>
 __global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const PrefillArgs a) {
   constexpr bool kSliced = STEP >= 0 && STEP < kSelFinish;             // this launch sweeps a slice of the group's keys
   constexpr bool kWhole = STEP == kSelAll || STEP == kSelFinish;       // ... or can run the whole search
@@ -520,24 +670,43 @@ __global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const Prefil
     a.act_range[1] = 0x7fffffff;
   }
   if (qtile >= n_qtiles * n_slice) return;                         // (the whole workgroup)
-  const int slice = qtile / n_qtiles;
-  qtile -= slice * n_qtiles;
-  const int t0 = (n_qtiles - 1 - qtile) * 32;                      // first query of the group; long rows first
+  int slice = qtile / n_qtiles;
+  if (ORDERED && (int)gridDim.x <= a.one_round) {
+    // one round of two workgroups per compute unit: all slices of what keeps most first, and the second half in reverse, so that the second workgroup
+    // of a compute unit has the less to do the more the first one has
+    const int n_here = n_qtiles * n_slice, half = (n_here + 1) / 2;
+    if (qtile >= half) qtile = n_here - 1 - (qtile - half);
+    slice = qtile % n_slice;
+    qtile /= n_slice;
+  } else {
+    qtile -= slice * n_qtiles;
+  }
+  // first query of the group; long rows first, or what keeps most
+  const int t0 = (ORDERED ? qtile : n_qtiles - 1 - qtile) * 32;
   const int pos0 = (int)a.q_start_host;
   // The lanes past the last query of a partial group repeat that query (their results are not stored): every lane
   // then has a causal range that ends where its group's does, and the group's interior tiles need no mask.  (Masking
   // those lanes instead puts the whole range of a partial group on the masked path of one wave: the search takes 10.7 against 0.9 ms
   // for a chunk of 333 queries behind 131072 tokens.)
   const bool qok = t0 + r < a.n_q;
-  const int t = min(t0 + r, a.n_q - 1);
+  int t = min(t0 + r, a.n_q - 1);
+  if (ORDERED) t = a.order[(int64_t)j * a.n_q + t];
   const int m = pos0 + t;
   const float ninf = -__builtin_huge_valf(), pinf = __builtin_huge_valf();
   const float cs = a.index_scale;
   const uint16_t* kIg = a.kI + (int64_t)j * a.kI_head_stride;
   const u32x4 qIreg = *reinterpret_cast<const u32x4*>(a.qI + ((int64_t)j * a.n_q + t) * kIndexDim + g * 8);
   const int n_rows = pos0 + a.n_q;                                 // index-key rows that exist
-  const int m_lo = pos0 + t0;
-  const int m_hi = pos0 + min(t0 + 32, a.n_q) - 1;
+  int m_lo = pos0 + t0;
+  int m_hi = pos0 + min(t0 + 32, a.n_q) - 1;
+  // whether the table holds the group's maxima; where its queries were brought together after sweep 0, sweep 2 makes its row
+  bool own_table = true;
+  int order_mode = kOrderOwn;
+  if (ORDERED) {
+    position_range(m, m_lo, m_hi);
+    order_mode = a.order_on[j * ((a.n_q + a.order_block - 1) / a.order_block) + t0 / a.order_block];
+    own_table = order_mode != kOrderByKept;
+  }
   const int n_tiles = m_hi / 32 + 1;
   const int n_interior = (m_lo + 1) / 32;                          // tiles with nb + 31 <= m_lo
   float (*lst)[64] = list_all[wave];
@@ -550,7 +719,8 @@ __global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const Prefil
   float xlo_wave = ninf;            // smallest x_lo over the wave's queries
   float xlo_wave_top = ninf;        // and the largest
   bool reach_known = false;         // sweep 3: the tile in hand is certain to hold a product at or above its query's x_lo
-  int n_looked = 0, n_needed = 0;   // sweep 3: tile pairs whose reach was worked out, and those found within reach
+  bool kept_much = false;           // regrouped queries that keep so much that few pairs will be without a kept key
+  int n_looked = 0, n_needed = 0;   // sweep 3 (and 2, if it makes the table): tile pairs whose reach was worked out, and those found within reach
   int lcnt = 0;                     // entries in this lane's member list
   const uint32_t lst_base = (uint32_t)(size_t)(__attribute__((address_space(3))) float*)&lst[0][lane];
 
@@ -679,6 +849,9 @@ __global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const Prefil
         // tile whose largest visible product is below x_lo for every query holds no kept pair
         reach = 1.f;
         if (!reach_known) reach = __ballot(max16_nn(v) >= x_lo) != 0ull ? 1.f : 0.f;
+      } else if (ORDERED && !reach_known) {
+        go = __ballot(max16_nn(v) >= x_lo) != 0ull;
+        reach = go ? 1.f : 0.f;
       }
       if (go) {
         // A half tile adds at most 8 entries, so the lists are emptied when some lane has no room for 8 more.  The list's
@@ -704,6 +877,7 @@ __global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const Prefil
   // Sweeps 2 and 3 consult the maximum table pair by pair: skip what cannot hold a member, and in sweep 3 note which
   // pairs a query can keep a key in.  no_look: nearly every pair can hold a member and is needed (see sweep_picked);
   // the pairs keep their maxima in the table, which is the conservative answer.
+  // Regrouped queries that keep much (kept_much): of 64 pairs the first 8 are looked at, and the others if one of these was not needed.
   auto sweep = [&](auto PH, auto MASKED, int tile_begin, int tile_end, bool no_look = false) __attribute__((always_inline)) {
     if (tile_begin >= tile_end) return;
     constexpr int phase_ = decltype(PH)::value;
@@ -725,11 +899,13 @@ __global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const Prefil
       for (int hb = 0; hb < kSelRing; hb += kSelMfma) {            // kSelMfma MFMAs in flight at a time
         // no member possible in this pair of tiles: only the prefetches for the next round are issued
         bool skip = false;
+        if (ORDERED && kSkip && kept_much && (((first + hb) >> 1) & 63) == 0) no_look = false;
         if (kSkip) {
           const float pair_max = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(tm[hb / 2])));
-          skip = !no_look && pair_max < xlo_wave;
+          const bool maxima = !ORDERED || own_table;               // (else +-inf, from sweep 2, and nothing before it)
+          skip = !no_look && pair_max < xlo_wave && (maxima || phase_ == 3);
           // a maximum at or above EVERY query's x_lo is at or above its own query's: no need to look
-          reach_known = no_look || pair_max >= xlo_wave_top;
+          reach_known = no_look || (maxima && (phase_ == 2 || pair_max >= xlo_wave_top));
           tm[hb / 2] = tmx[((first + kSelRing + hb) >> 1)];
         }
         if (skip) {
@@ -759,10 +935,17 @@ __global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const Prefil
         }
         // the last sweep knows better than the maximum: can one of the wave's queries keep a key of the pair?
         // (a pair known to reach keeps its maximum, which says the same)
-        if (phase_ == 3 && !reach_known) {
+        // (and sweep 2 finds the first answer where sweep 0 saw the queries in other groups)
+        if ((phase_ == 3 || (ORDERED && phase_ == 2)) && !reach_known) {
           n_looked += 1;
           n_needed += tmax > 0.f ? 1 : 0;
           if (lane == 0) tmx[(first + hb) >> 1] = tmax > 0.f ? pinf : ninf;
+          if (ORDERED && kept_much) {
+            if ((((first + hb) >> 1) & 63) == 7) no_look = n_needed >= 8;
+            if (tmax <= 0.f) n_needed = 0;                         // (here: how many of the last pairs in a row were needed)
+          }
+        } else if (ORDERED && phase_ == 2 && !own_table) {
+          if (lane == 0) tmx[(first + hb) >> 1] = pinf;
         }
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -771,7 +954,10 @@ __global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const Prefil
   const int n_plain = n_interior / kSelRing * kSelRing;            // whole rounds of interior tiles run without masks
   // this wave's share: an equal run of the rounds, the masked ones of the edge (one or two) at the end
   const int plain_rounds = n_plain / kSelRing, rounds = (n_tiles + kSelRing - 1) / kSelRing;
-  const int share = slice * NW + wave, shares = n_slice * NW;
+  // (ORDERED: where the last sweeps will take about equally long everywhere, the rest of a group's search is left to its first workgroup)
+  const bool rest_whole = STEP == 2 && ORDERED && order_mode == kOrderOwnAlike && a.order_whole != 0;
+  if (rest_whole && slice != 0) return;
+  const int share = (rest_whole ? 0 : slice * NW) + wave, shares = (rest_whole ? 1 : n_slice) * NW;
   const int round_lo = (int)((int64_t)rounds * share / shares), round_hi = (int)((int64_t)rounds * (share + 1) / shares);
   const int plain_lo = min(round_lo, plain_rounds) * kSelRing, plain_hi = min(round_hi, plain_rounds) * kSelRing;
   const int edge_lo = max(round_lo, plain_rounds) * kSelRing, edge_hi = round_hi * kSelRing;
@@ -786,6 +972,10 @@ __global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const Prefil
 #pragma unroll 1
     for (int tb = tile_begin; tb < tile_end; tb += 512) {
       const int te = min(tb + 512, tile_end);
+      if (ORDERED && phase_ == 2 && !own_table) {
+        sweep(PH, std::false_type{}, tb, te);
+        continue;
+      }
       auto entry = [&](int k) {
         const int pair = (tb >> 1) + k * 64 + lane;
         return pair < (te >> 1) ? tmx[pair] : ninf;
@@ -795,7 +985,7 @@ __global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const Prefil
       for (int k = 0; k < 4; ++k) n_on += __popcll(__ballot(entry(k) >= xlo_wave));
       if (4 * n_on > (te - tb) >> 1) {
         // next to nothing to skip, and (sweep 3) the pairs looked at so far nearly all turned out to be needed: do not look
-        const bool no_look = 16 * n_on > 15 * ((te - tb) >> 1) && (phase_ == 2 || (n_looked >= 64 && 10 * n_needed >= 9 * n_looked));
+        const bool no_look = (!ORDERED || own_table) && 16 * n_on > 15 * ((te - tb) >> 1) && (phase_ == 2 || (n_looked >= 64 && 10 * n_needed >= 9 * n_looked));
         sweep(PH, std::false_type{}, tb, te, no_look);
         continue;
       }
@@ -807,7 +997,7 @@ __global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const Prefil
           const int pl = __builtin_ctzll(todo);
           todo &= todo - 1ull;
           const int tile = tb + 2 * (k * 64 + pl);
-          reach_known = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(tmv), pl)) >= xlo_wave_top;
+          reach_known = (!ORDERED || own_table) && (phase_ == 2 || __int_as_float(__builtin_amdgcn_readlane(__float_as_int(tmv), pl)) >= xlo_wave_top);
           f32x16 SI[2];
 #pragma unroll
           for (int u = 0; u < 2; ++u) {
@@ -846,6 +1036,20 @@ __global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const Prefil
   constexpr int kRuns = kSelThreads / 32, kRunBins = kSelBins / kRuns;
   double (*run_sum)[32] = reinterpret_cast<double (*)[32]>(&list_all[0][0][0]);
   static_assert(kSelBins % kRuns == 0 && sizeof(double) * 32 * kRuns + sizeof(int) * NW <= sizeof(list_all), "runs of equal length");
+  // About how many candidates the query keeps: the mass of every bin by the weight of its middle, run by run above the run that crosses.
+  float kept_about = 0.f;
+  auto count_kept = [&](const double (&rs)[kRuns], double target, auto&& bin_mass) __attribute__((always_inline)) {
+    const int run = bsel / kRunBins;
+    kept_about = 0.f;
+#pragma unroll
+    for (int i = 0; i < kRuns; ++i) kept_about += i < run ? (float)rs[i] * fast_exp2(((float)i + 0.5f) * 1.44269504f) : 0.f;
+#pragma unroll
+    for (int i = 0; i < kRunBins; ++i) {
+      const int b = run * kRunBins + i;
+      const float share = b < bsel ? 1.f : (b > bsel ? 0.f : fminf((float)((target - cum) / hsel), 1.f));
+      kept_about += share * (float)bin_mass(i) * fast_exp2(((float)b + 0.5f) * 0.18033688f);
+    }
+  };
   auto scan = [&](bool whole, bool take) __attribute__((always_inline)) {
     if (THREADS == kSelThreads || tid < kSelThreads) {
       double h[kRunBins], sum = 0.0;
@@ -870,6 +1074,7 @@ __global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const Prefil
     bsel = t.bin;
     cum = t.above;
     hsel = t.mass;
+    if (STEP == kSelFirst) count_kept(rs, target, [&](int i) __attribute__((always_inline)) { return hist[bsel / kRunBins * kRunBins + i][r]; });
   };
 
   // ---- sweep 0: the row maxima ----
@@ -889,7 +1094,7 @@ __global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const Prefil
     selM = mx * cs;
     __syncthreads();                                                // the maxima are read: the lists' memory is free again
   };
-  bool rebased = false;
+  bool rebased = false;             // the reference is not the row maximum
   // after a scan of sweep 1: is this query's threshold in the open-ended bin?
   auto in_open_bin = [&]() __attribute__((always_inline)) { return bsel == kSelBins - 1 && hsel > 0.0; };
   // the same for any query of the workgroup (flags in the lists' memory, idle in this phase; the barrier also says
@@ -969,6 +1174,7 @@ __global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const Prefil
   // launch then fetches the runs' sums and, of each query, the one run that crosses, where adding up all 128 bins is 32 KB per
   // slice in every slice.  Sums of running sums are running sums again (rounding keeps their order).
   static_assert(STEP == kSelAll || THREADS == kRuns * 32, "one thread per run and query");
+  static_assert((kSelScan & 1) == 0 && (kSelFinish & 1) == 0, "histograms alternate between launches");
   const int my_run = wave * 2 + g;
   auto leave_runs = [&](double* own) __attribute__((always_inline)) {
     double c = 0.0;
@@ -979,7 +1185,7 @@ __global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const Prefil
     }
   };
   auto scan_slices = [&](int n, bool whole) __attribute__((always_inline)) {
-    const double* const old = a.sl_hist + ((int64_t)(1 - (STEP & 1)) * groups + grp) * n * kHistN + r;
+    const double* const old = a.sl_hist + ((int64_t)(1 - (STEP & 1)) * groups + grp) * n * kHistN + r;   // (kSelScan and sweep 2: of sweep 1)
     double (*crossing)[32] = run_sum + kRuns;                       // running sums of each query's crossing run
     static_assert(sizeof(double) * 32 * (kRuns + kRunBins) <= sizeof(list_all), "both fit the lists' memory");
     auto over_slices = [&](int bin) __attribute__((always_inline)) {
@@ -1009,61 +1215,31 @@ __global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const Prefil
     bsel = t.bin;
     cum = t.above;
     hsel = t.mass;
+    if (STEP == kSelScan) count_kept(rs, target, [&](int i) __attribute__((always_inline)) { return i == 0 ? c[0] : c[i] - c[i > 0 ? i - 1 : 0]; });
     __syncthreads();                                                // the sums are read: the lists' memory is free again
   };
-  if constexpr (kSliced) {
-    const int64_t mine_at = (int64_t)grp * n_slice + slice;
-    double* const own = a.sl_hist + ((int64_t)(STEP & 1) * groups * n_slice + mine_at) * kHistN;          // written by this launch
-    if constexpr (STEP == 0) {
-      row_maxima();
-      if (tid < 32) a.sl_max[mine_at * 32 + r] = x_max;
-      return;
-    }
-    if constexpr (STEP == 1) {
-      x_max = ninf;
-      for (int k = 0; k < n_slice; ++k) x_max = fmaxf(x_max, a.sl_max[((int64_t)grp * n_slice + k) * 32 + r]);
-      selM = x_max * cs;
-      selM8 = selM * 8.0f;
-      zero_hist();
-      __syncthreads();
-      sweep_all(std::integral_constant<int, 1>{});
-    } else if constexpr (STEP >= 2) {
-      if (STEP == 3 && a.sl_again[grp] != 0) return;                  // (the same for the whole workgroup)
-      if (STEP == 2) {
-        x_max = ninf;
-        for (int k = 0; k < n_slice; ++k) x_max = fmaxf(x_max, a.sl_max[((int64_t)grp * n_slice + k) * 32 + r]);
-        selM = x_max * cs;
-      } else {
-        const SelState st = a.sl_state[(int64_t)grp * 32 + r];
-        Z = st.Z; above = st.above; selM = st.selM; x_max = st.x_max; prefix = st.prefix;
-      }
-      scan_slices(n_slice, STEP == 2);
-      if (STEP == 2) {
-        const bool again = any_of(in_open_bin());
-        if (slice == 0 && tid == 0) a.sl_again[grp] = again ? 1 : 0;
-        if (again) return;
-      }
-      prefix = STEP == 2 ? bsel : (prefix << 7) | bsel;
-      above = cum;
-      if (slice == 0 && tid < 32) a.sl_state[((int64_t)(STEP - 2) * groups + grp) * 32 + r] = SelState{Z, above, selM, x_max, prefix, 0};
-      member_range(STEP);
-      zero_hist();
-      __syncthreads();
-      sweep_all(std::integral_constant<int, STEP>{});
-    }
-    __syncthreads();
-    leave_runs(own);
-    return;
-  }
-
-  if (STEP == kSelFinish && a.sl_again[grp] == 0) {
-    const SelState st = a.sl_state[((int64_t)groups + grp) * 32 + r];
+  // what a launch hands to the next one, per query
+  SelState* const state0 = a.sl_state + (int64_t)j * a.n_q + t;
+  SelState* const state1 = state0 + (int64_t)a.n_heads * a.n_q;
+  auto take = [&](const SelState& st) __attribute__((always_inline)) {
     Z = st.Z; above = st.above; selM = st.selM; x_max = st.x_max; prefix = st.prefix;
-    scan_slices(a.n_slice, false);
-    prefix = (prefix << 7) | bsel;
-  } else {
-    row_maxima();
-    first_digit();
+    rebased = (st.flags & kSelRebased) != 0;
+  };
+  // (48 kept keys a pair on the average: 1/43 of the context per query, more than a run of tokens that a query keeps for itself)
+  auto see_how_much = [&](int flags) __attribute__((always_inline)) {
+    float kept = fast_exp2(0.5f * (float)(flags >> kSelClassShift));
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1) kept += __shfl_xor(kept, o);
+    kept_much = !own_table && __builtin_amdgcn_readfirstlane(kept * 64.f >= 48.f * (float)n_rows ? 1 : 0) != 0;
+  };
+  auto leave = [&](SelState* st, int flags) __attribute__((always_inline)) {
+    *st = SelState{Z, above, selM, x_max, prefix, (rebased ? kSelRebased : 0) | flags};
+  };
+  // the class of prefill_order_kernel: half octaves of the kept count
+  auto class_of_kept = [&]() __attribute__((always_inline)) {
+    return (int)fminf(fmaxf(2.f * __builtin_amdgcn_logf(kept_about), 0.f), (float)(kOrderClasses - 2));
+  };
+  auto last_digits = [&]() __attribute__((always_inline)) {
 #pragma unroll 1
     for (int phase = 2; phase < 4; ++phase) {
       member_range(phase);
@@ -1077,17 +1253,110 @@ __global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const Prefil
       above = cum;
       __syncthreads();                                              // every wave has read the histograms
     }
+  };
+  auto results = [&]() __attribute__((always_inline)) {
+    // a threshold inside the open-ended last coarse bin (only after the last repeat) keeps every candidate
+    const bool lump = (prefix >> 14) == kSelBins - 1;
+    cut = lump ? pinf : (float)(prefix + 1) * (1.0f / kSelScale);
+    sel_mass = (lump || !(Z > 0.0)) ? 1.f : (float)((cum + hsel) / Z);
+    if (!qok || g != 0 || wave != 0) return;
+    const int64_t o = (int64_t)j * a.n_q + t;
+    a.sel_thr[o] = sel_first_below(selM, cs, cut);
+    if (a.mass) a.mass[o] = sel_mass;
+    // kept: candidates with floor((M - s) * 2^17) <= the threshold's digit string, i.e. s > M - cut
+    if (a.tau) a.tau[o] = cut != pinf ? selM - cut : ninf;
+  };
+  auto row_max_of_slices = [&]() __attribute__((always_inline)) {
+    x_max = ninf;
+    for (int k = 0; k < a.n_slice; ++k) x_max = fmaxf(x_max, a.sl_max[((int64_t)grp * a.n_slice + k) * 32 + r]);
+    selM = x_max * cs;
+  };
+  if constexpr (STEP == kSelFirst) {
+    row_maxima();
+    first_digit();
+    if (qok && g == 0 && wave == 0) leave(state0, class_of_kept() << kSelClassShift);
+    return;
   }
-  // a threshold inside the open-ended last coarse bin (only after the last repeat) keeps every candidate
-  const bool lump = (prefix >> 14) == kSelBins - 1;
-  cut = lump ? pinf : (float)(prefix + 1) * (1.0f / kSelScale);
-  sel_mass = (lump || !(Z > 0.0)) ? 1.f : (float)((cum + hsel) / Z);
-  if (!qok || g != 0 || wave != 0) return;
-  const int64_t o = (int64_t)j * a.n_q + t;
-  a.sel_thr[o] = sel_first_below(selM, cs, cut);
-  if (a.mass) a.mass[o] = sel_mass;
-  // kept: candidates with floor((M - s) * 2^17) <= the threshold's digit string, i.e. s > M - cut
-  if (a.tau) a.tau[o] = cut != pinf ? selM - cut : ninf;
+  if constexpr (STEP == kSelScan) {
+    row_max_of_slices();
+    scan_slices(a.n_slice, true);
+    prefix = bsel;
+    above = cum;
+    const int open = in_open_bin() ? kSelOpen | ((kOrderClasses - 1) << kSelClassShift) : class_of_kept() << kSelClassShift;
+    if (qok && g == 0 && wave == 0) leave(state0, open);
+    return;
+  }
+  if constexpr (kSliced) {
+    const int64_t mine_at = (int64_t)grp * n_slice + slice;
+    double* const own = a.sl_hist + ((int64_t)(STEP & 1) * groups * n_slice + mine_at) * kHistN;          // written by this launch
+    if constexpr (STEP == 0) {
+      row_maxima();
+      if (tid < 32) a.sl_max[mine_at * 32 + r] = x_max;
+      return;
+    }
+    if constexpr (STEP == 1) {
+      row_max_of_slices();
+      selM8 = selM * 8.0f;
+      zero_hist();
+      __syncthreads();
+      sweep_all(std::integral_constant<int, 1>{});
+    } else if constexpr (STEP >= 2) {
+      if (STEP == 3 && a.sl_again[grp] != 0) return;                  // (the same for the whole workgroup)
+      int again = 0;
+      if (STEP == 2 && ORDERED) {
+        const SelState st = *state0;
+        take(st);
+        see_how_much(st.flags);
+        again = any_of((st.flags & kSelOpen) != 0) ? 1 : 0;
+        if (rest_whole) {
+          if (tid == 0) a.sl_again[grp] = 2;
+          __syncthreads();
+          last_digits();
+          results();
+          return;
+        }
+      } else if (STEP == 2) {
+        row_max_of_slices();
+        scan_slices(n_slice, true);
+        again = any_of(in_open_bin()) ? 1 : 0;
+        prefix = bsel;
+        above = cum;
+      } else {
+        const SelState st = *state0;
+        take(st);
+        if (ORDERED) see_how_much(st.flags);
+        scan_slices(n_slice, false);
+        prefix = (prefix << 7) | bsel;
+        above = cum;
+      }
+      if (STEP == 2) {
+        if (slice == 0 && tid == 0) a.sl_again[grp] = again;
+        if (again) return;
+      }
+      if (slice == 0 && tid < 32 && !(STEP == 2 && ORDERED)) leave(STEP == 2 ? state0 : state1, 0);
+      member_range(STEP);
+      zero_hist();
+      __syncthreads();
+      sweep_all(std::integral_constant<int, STEP>{});
+    }
+    __syncthreads();
+    leave_runs(own);
+    return;
+  }
+
+  const int again = STEP == kSelFinish ? a.sl_again[grp] : 1;
+  if (again == 2) return;
+  if (again == 0) {
+    take(*state1);
+    scan_slices(a.n_slice, false);
+    prefix = (prefix << 7) | bsel;
+  } else {
+    own_table = true;
+    row_maxima();
+    first_digit();
+    last_digits();
+  }
+  results();
 }
 
 // ---- the wide kernel: dense and selecting modes ------------------------------------------------------
@@ -1128,7 +1397,6 @@ __global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const Prefil
 // queries' launch from 132 to 129 and left the selecting last chunk of 1M as it was.  The dense launch runs at a die clock of 1.71 to
 // 1.75 GHz, against 2.4 when idle: it has come to what the chip's power allows.  The selecting one (1.98 GHz, matrix pipe busy 51 %) has
 // not; it issues twice the other vector instructions.
-constexpr int kPwQ = 256;
 constexpr int kPwThreads = 512;
 constexpr int kPwStages = 3;
 // One staged tile: 64 K rows then 64 V rows, 256 bytes each, no padding -- the tiles are written by
@@ -1161,29 +1429,54 @@ __global__ __launch_bounds__(kPwThreads, 2) void flash_prefill_wide_kernel(const
   // The grid of such a launch is sized for the finer cut; the ranges really used (listed_splits) take the
   // first workgroups of the grid in the same (key range, query tile, head slot) order, the others leave.
   constexpr bool listed = SPARSE;
-  const int n_parts = listed ? listed_splits(a) : a.n_splits, n_sub = a.n_sub;
-  const int n_splits = n_parts * n_sub;
+  const int n_wide = (a.n_q + kPwQ - 1) / kPwQ;
+  const int n_units = listed && a.units ? *a.n_units : 0;
+  int n_parts = listed && n_units == 0 ? listed_splits(a) : a.n_splits;
+  int n_sub = a.n_sub;
+  int n_splits = n_parts * n_sub;
   int hslot = blockIdx.x, split, qt_rev = blockIdx.y, b = 0;
-  if (listed) {
+  bool exact_only = false, more = false;
+  int list = 0, wave_lo = 0, wave_hi = NW;            // the unit's list and the waves whose queries it is for
+  if (listed && n_units > 0) {
+    if ((int)blockIdx.x >= n_units) return;
+    const int2 unit = a.units[blockIdx.x];
+    const int what = __builtin_amdgcn_readfirstlane(unit.y);
+    list = __builtin_amdgcn_readfirstlane(unit.x);
+    const int n_lists = a.n_heads * n_wide;
+    more = list >= n_lists;
+    const int tile = more ? list - n_lists : list;
+    hslot = tile / n_wide;
+    qt_rev = tile - hslot * n_wide;
+    split = what & 0xff;
+    n_splits = n_parts = (what >> 8) & 0xff;
+    n_sub = 1;
+    wave_lo = (what >> 16) & 0xf;
+    wave_hi = (what >> 20) & 0xf;
+    exact_only = (what & kUnitExact) != 0;
+  } else if (listed) {
     const int lin = (int)blockIdx.x + (int)gridDim.x * ((int)blockIdx.y + (int)gridDim.y * (int)blockIdx.z);
     split = lin % n_splits;
-    qt_rev = (lin / n_splits) % (int)gridDim.y;
-    hslot = lin / (n_splits * (int)gridDim.y);
-    if (hslot >= (int)gridDim.z) return;
+    qt_rev = (lin / n_splits) % n_wide;
+    hslot = lin / (n_splits * n_wide);
+    if (hslot >= a.n_heads) return;
   } else {
     b = blockIdx.z / n_splits;
     split = (int)blockIdx.z - b * n_splits;
   }
   const int h = a.heads[hslot];
-  const int t0 = ((int)gridDim.y - 1 - qt_rev) * kPwQ;
+  const bool ordered = SPARSE && a.order != nullptr;    // (hard queries first, their tiles have the long lists)
+  const int t0 = (ordered ? qt_rev : n_wide - 1 - qt_rev) * kPwQ;
   const int kvh = h / (a.n_q_heads / a.n_kv_heads);
   const int pos0 = a.q_start ? a.q_start[b] : (int)a.q_start_host;
   const int64_t tok0 = a.seq_start ? a.seq_start[b] : 0;
   const float ninf = -__builtin_huge_valf();
 
   // ---- this lane's query (column r of the wave's 32) ----
-  const int tq = t0 + wave * 32 + r;
-  const bool qok = tq < a.n_q;
+  const bool my_wave = wave >= wave_lo && wave < wave_hi;
+  const bool qok = my_wave && t0 + wave * 32 + r < a.n_q;
+  const int32_t* const order = ordered ? a.order + (int64_t)hslot * a.n_q : nullptr;
+  int tq = t0 + wave * 32 + r;
+  if (ordered) tq = order[min(tq, a.n_q - 1)];
   const int mq = pos0 + tq;
   const int64_t qrow = (((int64_t)b * a.n_q + tq) * a.n_q_heads + h) * kHeadDim;
   u32x4 qreg[8];
@@ -1192,14 +1485,28 @@ __global__ __launch_bounds__(kPwThreads, 2) void flash_prefill_wide_kernel(const
     qreg[kk] = qok ? *reinterpret_cast<const u32x4*>(a.q + qrow + kk * 16 + g * 8) : (u32x4){0u, 0u, 0u, 0u};
 
   // ---- key tiles this workgroup needs ----
-  const int m_lo = pos0 + t0;
-  const int m_hi = pos0 + min(t0 + kPwQ, a.n_q) - 1;
+  int m_lo = pos0 + t0;
+  int m_hi = pos0 + min(t0 + kPwQ, a.n_q) - 1;
+  if (ordered) {
+    int lo = 0x7fffffff, hi = 0;
+#pragma unroll
+    for (int k = 0; k < kPwQ / 64; ++k) {
+      const int m = pos0 + order[min(t0 + k * 64 + lane, a.n_q - 1)];
+      lo = min(lo, m);
+      hi = max(hi, m);
+    }
+    lo = min(lo, __shfl_xor(lo, 32));
+    hi = max(hi, __shfl_xor(hi, 32));
+    int unused;
+    position_range(lo, m_lo, unused);
+    position_range(hi, unused, m_hi);
+  }
   const int kt_end = m_hi / kPfK;                       // inclusive
   // selecting mode with a threshold search in front: only the tiles on this query tile's list (ascending
   // 64-key tile numbers, written by prefill_active_tiles_kernel) can hold a kept pair
-  const int qt_list = (int)gridDim.y - 1 - qt_rev;
-  const int32_t* const alist = listed ? a.act_list + ((int64_t)hslot * gridDim.y + qt_list) * a.n_t64 : nullptr;
-  const int n_tiles = listed ? a.act_count[(int64_t)hslot * gridDim.y + qt_list] : kt_end + 1;
+  const int qt_list = t0 / kPwQ;
+  const int32_t* const alist = !listed ? nullptr : more ? more_list_of(a, hslot, qt_list) : a.act_list + ((int64_t)hslot * n_wide + qt_list) * a.n_t64;
+  const int n_tiles = !listed ? kt_end + 1 : n_units > 0 ? a.list_info[list].x : a.act_count[(int64_t)hslot * n_wide + qt_list];
   const uint16_t* Kg = a.K + (int64_t)kvh * a.head_stride + tok0 * a.row_stride;
   const uint16_t* Vg = a.V + (int64_t)kvh * a.head_stride + tok0 * a.row_stride;
 
@@ -1207,8 +1514,12 @@ __global__ __launch_bounds__(kPwThreads, 2) void flash_prefill_wide_kernel(const
   float mrow = ninf, lrow = 0.f;
   const float c = a.scale_log2;
   const int q_last = pos0 + a.n_q - 1;
-  const int m_w_lo = pos0 + t0 + wave * 32;                      // the wave's first query position
-  const int m_w_hi = min(m_w_lo + 31, q_last);          // and its last (< m_w_lo: the wave has no queries)
+  // the wave's first query position and its last; -1 for a wave without queries
+  int m_w_lo = -1, m_w_hi = -1;
+  if (my_wave && t0 + wave * 32 < a.n_q) {
+    m_w_lo = ordered ? m_lo : pos0 + t0 + wave * 32;
+    m_w_hi = ordered ? m_hi : min(m_w_lo + 31, q_last);
+  }
 
   // ---- selecting mode: a key is kept by a query iff the raw index product reaches the query's
   // threshold (found by prefill_select_kernel; -inf keeps every candidate).  The index-score block of
@@ -1456,11 +1767,11 @@ __global__ __launch_bounds__(kPwThreads, 2) void flash_prefill_wide_kernel(const
   };
   // does the 32-key block starting at nb0 need per-element masks for some query of this wave?
   auto needs_mask = [&](int nb0) __attribute__((always_inline)) {
-    return m_w_hi < m_w_lo || nb0 + 31 > m_w_lo;
+    return nb0 + 31 > m_w_lo;
   };
   // can some query of this wave see a key of the block at all?
   auto is_active = [&](int nb0) __attribute__((always_inline)) {
-    return !(m_w_hi < m_w_lo || nb0 > m_w_hi);
+    return nb0 <= m_w_hi;
   };
 
   auto tile_n0 = [&](int it) __attribute__((always_inline)) {
@@ -1473,8 +1784,8 @@ __global__ __launch_bounds__(kPwThreads, 2) void flash_prefill_wide_kernel(const
   auto slot_of = [&](int it) __attribute__((always_inline)) { return (it - it_lo) % kPwStages; };
   auto tile_at = [&](int it) __attribute__((always_inline)) { return Ls + slot_of(it) * kPwTileBytes; };
 
-  bool redo = false;
-  if (it_lo < it_hi) {
+  bool redo = exact_only;
+  if (it_lo < it_hi && !exact_only) {
     f32x16 S;
     uint32_t P0[8], P1[8];
     lrow = 0.f;
@@ -1569,7 +1880,7 @@ __global__ __launch_bounds__(kPwThreads, 2) void flash_prefill_wide_kernel(const
     // fetches its share of the tiles.
     auto steady = [&]() __attribute__((always_inline)) { return it < it_hi && n_t0 + kPfK - 1 <= m_lo && n_t2 + kPfK - 1 <= m_hi; };
     if (steady()) {
-      if (m_w_hi >= m_w_lo) {
+      if (m_w_hi >= 0) {
         f32x16 S1;
         first_v(tile_at(it - 1), 1);
         do {
@@ -1621,9 +1932,12 @@ __global__ __launch_bounds__(kPwThreads, 2) void flash_prefill_wide_kernel(const
   }
 
   if (redo) {
-    // ---- exact pass: running maximum, accumulators rescaled in place; no pipelining (rare) ----
+    // ---- exact pass: running maximum, accumulators rescaled in place; only the next tile's loads are in flight.  For queries that
+    // keep few keys (their tiles' lists are short once they stand together) and references out of reach (rare).  In bf16 the probabilities are multiplied
+    // in two parts, rounded and the rest: a sum of a few terms does not average a rounding to 8 bits. ----
+    constexpr bool kParts = SPARSE && !F16;
     f32x16 S;
-    uint32_t P[8];
+    uint32_t P[8], Q[kParts ? 8 : 1];
     mrow = ninf;
     lrow = 0.f;
     sel_cnt = 0;
@@ -1631,15 +1945,18 @@ __global__ __launch_bounds__(kPwThreads, 2) void flash_prefill_wide_kernel(const
     for (int db = 0; db < 4; ++db)
 #pragma unroll
       for (int i = 0; i < 16; ++i) O[db][i] = 0.f;
+    __syncthreads();
+    if (it_lo < it_hi) load_tile(tile_n0(it_lo), 0);
     for (int it = it_lo; it < it_hi; ++it) {
-      __syncthreads();
-      load_tile(tile_n0(it), 0);
+      const int buf = (it - it_lo) & 1;
+      const unsigned char* const tile = Ls + buf * kPwTileBytes;
       loads_landed();
       __syncthreads();
+      if (it + 1 < it_hi) load_tile(tile_n0(it + 1), buf ^ 1);
       for (int kb = 0; kb < 2; ++kb) {
         const int nb0 = tile_n0(it) + kb * 32;
         if (!is_active(nb0)) continue;
-        if (kb == 0) mfma_S(Ls, 0, S); else mfma_S(Ls, 1, S);
+        if (kb == 0) mfma_S(tile, 0, S); else mfma_S(tile, 1, S);
         mask_block(S, nb0);
         if (SPARSE) select_block(S, load_ki(nb0));
         float mx = S[0];
@@ -1647,6 +1964,7 @@ __global__ __launch_bounds__(kPwThreads, 2) void flash_prefill_wide_kernel(const
         for (int i = 1; i < 16; ++i) mx = fmaxf(mx, S[i]);
         mx = fmaxf(mx, __shfl_xor(mx, 32));
         const float mnew = fmaxf(mrow, mx);
+        if (SPARSE && __ballot(mx != ninf) == 0ull) continue;     // no query of the wave keeps a key of the block
         const float msafe = mnew == ninf ? 0.f : mnew;
         const float mc = msafe * c;
         float lsum = 0.f;
@@ -1656,6 +1974,7 @@ __global__ __launch_bounds__(kPwThreads, 2) void flash_prefill_wide_kernel(const
           const float p1 = fast_exp2(fmaf(S[i + 1], c, -mc));
           lsum += p0 + p1;
           P[i >> 1] = pack16<F16>(p0, p1);
+          if constexpr (kParts) Q[i >> 1] = pack16<F16>(p0 - bf16_lo(P[i >> 1]), p1 - bf16_hi(P[i >> 1]));
         }
         const float corr = fast_exp2((mrow - msafe) * c);
         lrow = lrow * corr + lsum;
@@ -1664,7 +1983,8 @@ __global__ __launch_bounds__(kPwThreads, 2) void flash_prefill_wide_kernel(const
 #pragma unroll
           for (int i = 0; i < 16; ++i) O[db][i] *= corr;
         mrow = mnew;
-        if (kb == 0) mfma_PV(Ls, 0, P); else mfma_PV(Ls, 1, P);
+        if (kb == 0) mfma_PV(tile, 0, P); else mfma_PV(tile, 1, P);
+        if constexpr (kParts) { if (kb == 0) mfma_PV(tile, 0, Q); else mfma_PV(tile, 1, Q); }
       }
     }
   }
@@ -1681,7 +2001,9 @@ __global__ __launch_bounds__(kPwThreads, 2) void flash_prefill_wide_kernel(const
     if (a.count) a.count[o] = mq + 1;
   }
   if (n_splits > 1) {
-    float* prow = a.part + (((int64_t)split * a.n_heads + hslot) * a.n_q + tq) * kPfPart;
+    const int64_t at = listed && n_units > 0 ? (int64_t)(a.list_ranges[list].y + split) * kPwQ + wave * 32 + r
+                                         : ((int64_t)split * a.n_heads + hslot) * a.n_q + tq;
+    float* prow = a.part + at * kPfPart;
     if (g == 0) { prow[0] = mfin; prow[1] = ltot; prow[2] = __int_as_float(kept); }
 #pragma unroll
     for (int db = 0; db < 4; ++db)
@@ -1710,54 +2032,229 @@ __global__ __launch_bounds__(kPwThreads, 2) void flash_prefill_wide_kernel(const
   if (SPARSE && a.count && g == 0) a.count[(int64_t)hslot * a.n_q + tq] = kept;
 }
 
+// The first digit of a sliced search, for prefill_order_kernel.
+static constexpr auto prefill_first_digit = prefill_select_kernel<kSelScan>;
+
 // The 64-key tiles a 256-query tile of the selecting attention launch has to visit: tile n is on the list iff, for
 // one of the tile's eight 32-query groups, the group's largest index product in the tile (tile_max, written by the
 // first sweep of prefill_select_kernel) reaches the group's smallest threshold.  Every other tile holds no kept
 // pair -- the keep test is product >= threshold -- so leaving it out changes no output, count or sum.
-// Grid (query tiles, retrieval heads), 256 threads; the list is ascending.
-__global__ __launch_bounds__(256) void prefill_active_tiles_kernel(const PrefillArgs a) {
+// Grid (query tiles, retrieval heads); the list is ascending.  A thread takes one tile at a time and the eight groups' entries of it at
+// once: a chain of dependent loads, and few workgroups, is all there is to this launch (with 256 threads, a group's entry loaded only if the
+// groups before had none: 67 us where every tile is on the list, 245 where few are, for 8192 queries behind 1M tokens; 22 now).
+// Regrouped queries, grid (.., .., 2): the groups whose queries all keep few keys get a list of their own, which the attention launch walks
+// with more exact probabilities; they are all of the query tile's groups, or its last ones (the second list then) in one tile of a block.
+constexpr int kListThreads = 1024, kListThreadsFew = 256;    // (up to 32768 keys: two rounds of 256 threads, 4.0 us for 2037 against 5.1)
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void prefill_active_tiles_kernel(const PrefillArgs a) {
+  constexpr int G = kPwQ / 32;
   const int j = blockIdx.y, qt = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int t0 = qt * kPwQ;
-  __shared__ float thr[kPwQ / 32];
-  __shared__ int wave_n[4];
-  {
-    const int t = t0 + tid;
-    float v = t < a.n_q ? a.sel_thr[(int64_t)j * a.n_q + t] : __builtin_huge_valf();
+  const bool second = blockIdx.z != 0;
+  __shared__ float thr[G];
+  __shared__ int last[G];                               // the last position of every group (-1: a group past the chunk)
+  __shared__ int many[G];                               // some query of the group keeps more than few keys
+  __shared__ int wave_n[2][THREADS / 64];
+  const int pos0 = (int)a.q_start_host;
+  const bool by_kept = a.units && a.order_on[j * ((a.n_q + a.order_block - 1) / a.order_block) + t0 / a.order_block] == kOrderByKept;
+  if (tid < kPwQ) {
+    int t = t0 + tid;
+    const bool qok = t < a.n_q;
+    if (a.order && qok) t = a.order[(int64_t)j * a.n_q + t];
+    float v = qok ? a.sel_thr[(int64_t)j * a.n_q + t] : __builtin_huge_valf();
+    int m = qok ? pos0 + t : -1;
+    int cls = by_kept && qok ? a.sl_state[(int64_t)j * a.n_q + t].flags >> kSelClassShift : 0;
 #pragma unroll
-    for (int o = 16; o > 0; o >>= 1) v = fminf(v, __shfl_xor(v, o));
-    if ((tid & 31) == 0) thr[tid >> 5] = v;
+    for (int o = 16; o > 0; o >>= 1) {
+      v = fminf(v, __shfl_xor(v, o));
+      m = max(m, __shfl_xor(m, o));
+      cls = max(cls, __shfl_xor(cls, o));
+    }
+    if ((tid & 31) == 0) {
+      thr[tid >> 5] = v;
+      last[tid >> 5] = m;
+      many[tid >> 5] = cls >= kFewClass ? 1 : 0;
+    }
   }
   __syncthreads();
-  const int pos0 = (int)a.q_start_host;
-  const int n_pairs = (pos0 + min(t0 + kPwQ, a.n_q) - 1) / kPfK + 1;
+  // this list's groups
+  int n_many = by_kept ? 0 : G;
+#pragma unroll
+  for (int i = 0; i < G; ++i) if (by_kept && many[i]) n_many = i + 1;
+  const bool exact = n_many == 0 || second;
+  const int lo = second ? n_many : 0, hi = second || n_many == 0 ? G : n_many;
+  const int n_wide = gridDim.x, list_no = (second ? (int)gridDim.y * n_wide : 0) + j * n_wide + qt;
+  if (second && (n_many == 0 || n_many == G)) {
+    if (tid == 0) a.list_info[list_no] = make_int2(0, 0);
+    return;
+  }
+  // the groups' rows of the table, each as far as the group's last query sees
+  float least[G];
+  int n_of[G], n_pairs = 0;
+#pragma unroll
+  for (int i = 0; i < G; ++i) {
+    least[i] = thr[i];
+    n_of[i] = last[i] < 0 || i < lo || i >= hi ? 0 : last[i] / kPfK + 1;
+    n_pairs = max(n_pairs, n_of[i]);
+  }
   const float* tm = a.tile_max + ((int64_t)j * ((a.n_q + 31) / 32) + t0 / 32) * a.n_t64;
-  int32_t* list = a.act_list + ((int64_t)j * gridDim.x + qt) * a.n_t64;
+  int32_t* list = second ? more_list_of(a, j, qt) : a.act_list + ((int64_t)j * n_wide + qt) * a.n_t64;
+  auto entries = [&](int p, float (&v)[G]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < G; ++i) v[i] = p < n_of[i] ? tm[(int64_t)i * a.n_t64 + p] : -__builtin_huge_valf();
+  };
   int base = 0;
-  for (int p0 = 0; p0 < n_pairs; p0 += 256) {
+  float v[G];
+  entries(tid, v);
+  for (int p0 = 0, odd = 0; p0 < n_pairs; p0 += THREADS, odd ^= 1) {
     const int p = p0 + tid;
     bool on = false;
-    if (p < n_pairs) {
 #pragma unroll
-      for (int i = 0; i < kPwQ / 32; ++i) {
-        const int tw = t0 + 32 * i;
-        // the group's row of the table reaches as far as its last query sees
-        if (tw < a.n_q && p * kPfK <= pos0 + min(tw + 32, a.n_q) - 1) on = on || tm[(int64_t)i * a.n_t64 + p] >= thr[i];
-      }
-    }
+    for (int i = 0; i < G; ++i) on = on || (p < n_of[i] && v[i] >= least[i]);
+    entries(p + THREADS, v);
     const uint64_t bal = __ballot(on);
-    if (lane == 0) wave_n[wave] = __popcll(bal);
+    if (lane == 0) wave_n[odd][wave] = __popcll(bal);
     __syncthreads();
     int before = base;
-    for (int w = 0; w < wave; ++w) before += wave_n[w];
+#pragma unroll
+    for (int w = 0; w < THREADS / 64; ++w) {
+      const int n = wave_n[odd][w];
+      if (w < wave) before += n;
+      base += n;
+    }
     if (on) list[before + __popcll(bal & ((1ull << lane) - 1ull))] = p;
-    base += wave_n[0] + wave_n[1] + wave_n[2] + wave_n[3];
-    __syncthreads();
   }
   if (tid == 0) {
-    a.act_count[(int64_t)j * gridDim.x + qt] = base;
-    atomicMax(&a.act_range[0], base);
-    atomicMin(&a.act_range[1], base);
+    if (a.units) {
+      a.list_info[list_no] = make_int2(base, lo << 16 | hi << 20 | (exact ? kUnitExact : 0));
+      atomicAdd(&a.act_count[(int64_t)j * n_wide + qt], base);      // (of both lists; prefill_order_kernel has cleared it)
+    } else {
+      a.act_count[(int64_t)j * n_wide + qt] = base;
+    }
+    if (!second) {
+      atomicMax(&a.act_range[0], base);
+      atomicMin(&a.act_range[1], base);
+    }
+  }
+}
+
+// Cuts the attention launch's work over lists of very different lengths (regrouped queries: hundreds of tiles beside a handful) into
+// units of about equal length: every list into equal ranges of at most U tiles, U the least for which there are k units per compute unit,
+// which holds one workgroup; the k of 1 to 4 that makes k * (U + kUnitTiles) least, kUnitTiles being what a unit costs beside its tiles: its
+// start, a partial result to write and one to merge.  Units of half of U or more come first, by head, range and tile, an eighth of them
+// for each die, so that the workgroups of a die walk the same keys at the same time and meet in its L2; the short ones fill up behind.
+// Attention launch of 4 heads over regrouped queries, ranges of 512 tiles of each list / planned, us: 4096 queries at 128K tokens, clusters at
+// p = 0.9 and 0.8 1060 / 860 and 1044 / 516, a few hard queries among easy ones 1060 / 129, 333 queries 159 / 106.
+constexpr int kUnitTiles = 12, kUnitLeast = 16, kUnitRounds = 4, kUnitRanges = 64;
+constexpr int kExactTiles = 2;                     // what a tile of the exact pass takes
+constexpr int kPlanThreads = 1024, kPlanLists = 4096;
+__global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(const PrefillArgs a, const int n_cu) {
+  constexpr int NW = kPlanThreads / 64;
+  __shared__ int len[kPlanLists], cut[kPlanLists];     // a list's tiles; its ranges if they are long units, else 0
+  __shared__ int waves[kPlanLists];
+  __shared__ int best_u[kUnitRounds], longest[NW];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n_wide = (a.n_q + kPwQ - 1) / kPwQ, n = 2 * a.n_heads * n_wide;
+  // (a second list is there only if it has tiles)
+  auto ranges_of = [&](int i, int u) __attribute__((always_inline)) { return max((len[i] + u - 1) / u, 2 * i < n ? 1 : 0); };
+  int most = 1;
+  {
+    const int blocks = (a.n_q + a.order_block - 1) / a.order_block * a.n_heads;
+    bool on = false;
+    for (int i = tid; i < blocks; i += kPlanThreads) on = on || a.order_on[i] == kOrderByKept;
+    if (__syncthreads_or(on ? 1 : 0) == 0) {            // nothing is regrouped
+      if (tid == 0) *a.n_units = 0;
+      return;
+    }
+  }
+  for (int i = tid; i < n; i += kPlanThreads) {
+    const int2 info = a.list_info[i];
+    len[i] = info.y & kUnitExact ? info.x * kExactTiles : info.x;
+    waves[i] = info.y;
+    most = max(most, len[i]);
+  }
+  most = wave_max_ge_m1(most);
+  if (lane == 0) longest[wave] = most;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < NW; ++w) most = max(most, longest[w]);
+  int n_more = 0;
+  for (int i = n / 2 + lane; i < n; i += 64) n_more += len[i] > 0 ? 1 : 0;
+  n_more = wave_sum(n_more);
+  if (wave < kUnitRounds) {                             // one k for each of the first waves
+    const int limit = max(min((wave + 1) * n_cu, a.part_cap), n / 2 + n_more);
+    int lo = min(max(kUnitLeast, (most + kUnitRanges - 1) / kUnitRanges), most), hi = most;
+    while (lo < hi) {
+      const int u = (lo + hi) >> 1;
+      int units = 0;
+      for (int i = lane; i < n; i += 64) units += ranges_of(i, u);
+      if (wave_sum(units) <= limit) hi = u;
+      else lo = u + 1;
+    }
+    if (lane == 0) best_u[wave] = lo;
+  }
+  __syncthreads();
+  int u = 0, cost = 0x7fffffff;
+#pragma unroll
+  for (int k = 0; k < kUnitRounds; ++k) {
+    const int c = (k + 1) * (best_u[k] + kUnitTiles);
+    if (c < cost) { cost = c; u = best_u[k]; }
+  }
+  // prefix sums over the lists: ranges (for the partials), ranges of long units, short units
+  __shared__ int3 wave_tot[NW];
+  __shared__ int long_before[kPlanLists];
+  int3 carry = make_int3(0, 0, 0);
+  for (int i0 = 0; i0 < n; i0 += kPlanThreads) {
+    const int i = i0 + tid;
+    const int r = i < n ? ranges_of(i, u) : 0;
+    const bool is_long = r > 0 && 2 * len[i] >= u * r;
+    const int3 mine = make_int3(r, is_long ? r : 0, r > 0 && !is_long ? 1 : 0);
+    int3 upto = make_int3(wave_incl_scan(mine.x), wave_incl_scan(mine.y), wave_incl_scan(mine.z));
+    if (lane == 63) wave_tot[wave] = upto;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const int3 t = wave_tot[w];
+      if (w < wave) { upto.x += t.x; upto.y += t.y; upto.z += t.z; }
+    }
+    if (i < n) {
+      cut[i] = is_long ? r : 0;
+      long_before[i] = carry.y + upto.y - mine.y;
+      len[i] = carry.z + upto.z - mine.z;               // (from here on: the short units before)
+      a.list_ranges[i] = make_int2(r | ((waves[i] >> 20) & 0xf) << 16, carry.x + upto.x - mine.x);
+      if (r == 0) waves[i] = -1;                        // no list
+    }
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const int3 t = wave_tot[w];
+      carry.x += t.x; carry.y += t.y; carry.z += t.z;
+    }
+    __syncthreads();
+  }
+  const int n_long = carry.y, per_die = n_long / 8, rest = n_long % 8;
+  if (tid == 0) *a.n_units = n_long + carry.z;
+  const int share = max(kPlanThreads / n, 1), stride = n > kPlanThreads ? kPlanThreads : n;     // threads per list
+  for (int i = tid / share; i < n; i += stride) {
+    const int sub = tid % share, h = i / n_wide;        // (the second lists as so many heads more)
+    if (waves[i] == -1) continue;
+    if (cut[i] == 0) {
+      if (sub == 0) a.units[n_long + len[i]] = make_int2(i, 1 << 8 | waves[i]);
+      continue;
+    }
+    const int before = long_before[h * n_wide];
+    for (int s = sub; s < cut[i]; s += share) {
+      int p = before;
+      for (int k = h * n_wide; k < (h + 1) * n_wide; ++k) {
+        const int c = cut[k];
+        p += min(c, s) + (k < i && c > s ? 1 : 0);
+      }
+      const bool more = p < rest * (per_die + 1);       // the first `rest` dies have one more
+      const int p1 = p - rest * (per_die + 1);
+      const int die = more ? p / (per_die + 1) : rest + p1 / max(per_die, 1);
+      const int at = more ? p % (per_die + 1) : p1 % max(per_die, 1);
+      a.units[at * 8 + die] = make_int2(i, s | cut[i] << 8 | waves[i]);
+    }
   }
 }
 
@@ -1771,12 +2268,26 @@ __global__ __launch_bounds__(256) void prefill_combine_kernel(const PrefillArgs 
   __shared__ int sh_kept[8];
   __shared__ __attribute__((aligned(16))) float sh_acc[8][kHeadDim];
   const int tid = threadIdx.x, d4 = tid & 31, grp = tid >> 5, slice = grp % SLICES, hs = blockIdx.y;
-  const int t = blockIdx.x * (8 / SLICES) + grp / SLICES;
-  const bool row = t < a.n_q;
+  const int place = blockIdx.x * (8 / SLICES) + grp / SLICES;
+  const bool row = place < a.n_q;
+  int t = place, n_splits;
+  const float* part = a.part;
+  int64_t step;                                                         // from one range's partials to the next
+  if (a.units && *a.n_units > 0) {
+    const int n_wide = (a.n_q + kPwQ - 1) / kPwQ, at = min(place, a.n_q - 1), list = hs * n_wide + at / kPwQ;
+    int2 ranges = a.list_ranges[list];
+    if (at % kPwQ / 32 >= ranges.x >> 16) ranges = a.list_ranges[a.n_heads * n_wide + list];
+    n_splits = ranges.x & 0xffff;
+    if (n_splits == 1) return;                           // (the same for the whole workgroup: the attention launch has written the rows)
+    part += ((int64_t)ranges.y * kPwQ + place % kPwQ) * kPfPart;
+    step = (int64_t)kPwQ * kPfPart;
+  } else {
+    n_splits = (a.act_range ? listed_splits(a) : a.n_splits) * a.n_sub;   // (a listed launch decides on the device)
+    part += ((int64_t)hs * a.n_q + (row ? t : 0)) * kPfPart;
+    step = (int64_t)a.n_heads * a.n_q * kPfPart;
+  }
+  if (a.order && row) t = a.order[(int64_t)hs * a.n_q + t];
   const float ninf = -__builtin_huge_valf();
-  const int n_splits = (a.act_range ? listed_splits(a) : a.n_splits) * a.n_sub;   // (a listed launch decides on the device)
-  const int64_t step = (int64_t)a.n_heads * a.n_q * kPfPart;            // from one range's partials to the next
-  const float* part = a.part + ((int64_t)hs * a.n_q + (row ? t : 0)) * kPfPart;
   float M = ninf, L = 0.f;
   float4 A = make_float4(0.f, 0.f, 0.f, 0.f);
   int kept = 0;
@@ -1837,11 +2348,6 @@ __global__ __launch_bounds__(256) void prefill_combine_kernel(const PrefillArgs 
   if (a.act_range && a.count) a.count[(int64_t)hs * a.n_q + t] = kept;   // selecting mode: kept keys over all key ranges
 }
 
-static void launch_prefill_combine(const PrefillArgs& a, hipStream_t s) {
-  if (a.n_splits * a.n_sub > 8) RTP_LAUNCH(prefill_combine_kernel<8>, dim3((unsigned)a.n_q, (unsigned)a.n_heads), dim3(256), 0, s, a);
-  else RTP_LAUNCH(prefill_combine_kernel<2>, dim3((unsigned)((a.n_q + 3) / 4), (unsigned)a.n_heads), dim3(256), 0, s, a);
-}
-
 // Compute units of the current device (256 on the target; also the answer where no device is visible,
 // as when only a workspace size is asked for).
 static int compute_units() {
@@ -1854,6 +2360,13 @@ static int compute_units() {
     return n;
   }();
   return v;
+}
+
+static void launch_prefill_combine(const PrefillArgs& a, hipStream_t s) {
+  // (planned ranges: two units per compute unit over lists of about equal length; the partials there can be are far more)
+  const int expected = a.units ? std::min<int>(kUnitRanges, 2 * compute_units() / (a.n_heads * ((a.n_q + kPwQ - 1) / kPwQ))) : a.n_splits * a.n_sub;
+  if (expected > 8) RTP_LAUNCH(prefill_combine_kernel<8>, dim3((unsigned)a.n_q, (unsigned)a.n_heads), dim3(256), 0, s, a);
+  else RTP_LAUNCH(prefill_combine_kernel<2>, dim3((unsigned)((a.n_q + 3) / 4), (unsigned)a.n_heads), dim3(256), 0, s, a);
 }
 
 // Number of key-range splits for a dense launch with few workgroups (long context, few heads).  A
@@ -1998,7 +2511,7 @@ static SearchWs search_ws(int64_t groups, int64_t workgroups) {
   SearchWs w = {};
   w.max_bytes = align_up((size_t)workgroups * 32 * sizeof(float), 256);
   w.hist_bytes = align_up((size_t)workgroups * 2 * kSelBins * 32 * sizeof(double), 256);
-  w.state_bytes = align_up((size_t)groups * 2 * 32 * sizeof(SelState), 256);
+  w.state_bytes = align_up((size_t)groups * 2 * 32 * sizeof(SelState), 256);       // (two per query)
   w.again_bytes = align_up((size_t)groups * sizeof(int32_t), 256);
   return w;
 }
@@ -2007,6 +2520,24 @@ static int search_slices(int n_ret, int32_t T, int64_t chunk_start, size_t room)
   int64_t s = std::min(2 * (int64_t)compute_units() / groups, std::min(keys / 4096, (int64_t)16));
   while (s >= 2 && search_ws(groups, groups * s).total() > room) --s;
   return s >= 2 && keys - keys / s > 9000 ? (int)s : 1;
+}
+
+// Queries that prefill_order_kernel may regroup together (0: none).  A group's masked tiles reach from its first query to its last, so
+// the block is at most a sixteenth of what lies before the chunk; below 65536 keys or 512 queries the three launches
+// more cost about what the tiles spared give (333 queries behind 131072 tokens: call 360 -> 345 us), and short chunks keep one result whatever their
+// workspace: by position or by kept count, the probabilities are rounded to 16 bits against different references.
+static int order_block(int32_t T, int64_t chunk_start) {
+  if (chunk_start + T < 65536 || T < 2 * kPwQ) return 0;
+  const int64_t most = std::min<int64_t>(chunk_start / 16 / kPwQ * kPwQ, kOrderMax);
+  return T <= most ? (T + kPwQ - 1) / kPwQ * kPwQ : most >= 1024 ? (int)most : 0;
+}
+// Workgroups per group of the last sweeps behind regrouped queries whose first sweeps took whole rows: their lengths differ by two orders of
+// magnitude, so two rounds of workgroups for the chip's dispatcher to even out, of at most 262144 keys (a lone hard group's time is all of the
+// launch's).  Sweeps 2 and 3 of 4096 queries at 128K tokens, p = 0.9 and 0.8, one round / two / four: 411 + 226 and 373 + 200 us / 384 + 217
+// and 276 + 146 / 360 + 220 and 271 + 155.  A search that is sliced from the start keeps its one round: a workgroup's start (the order, the state, the ends
+// of the member ranges: some 10 us) costs more than the evener end gives.
+static int order_slices(int64_t groups, int64_t keys) {
+  return (int)std::min<int64_t>(std::max<int64_t>({std::min(4 * (int64_t)compute_units() / groups, keys / 4096), keys / 262144, (int64_t)1}), 16);
 }
 
 // Sizes of the tile bookkeeping of a selecting launch.  A table row has one entry per 64 keys of the context, plus
@@ -2025,6 +2556,23 @@ static PrefillTileWs prefill_tile_ws(int32_t n_ret, int32_t T, int64_t chunk_sta
   return w;
 }
 
+// The order, a flag per block, and the attention launch's units with their number and the lists' ranges.
+struct OrderWs {
+  size_t order, flags, units, info, ranges, more;
+  size_t total() const { return order + flags + units + info + ranges + more; }
+};
+static int order_blocks(int32_t T) { return (T + 1023) / 1024 + 1; }     // at most
+static int max_units(int n_ret, int32_t T) { return std::max(kUnitRounds * compute_units(), n_ret * ((T + kPwQ - 1) / kPwQ + order_blocks(T))); }
+static OrderWs order_ws(int n_ret, int32_t T, int64_t chunk_start) {
+  OrderWs w;
+  w.order = align_up((size_t)n_ret * T * sizeof(int32_t), 256);
+  const size_t lists = (size_t)n_ret * ((T + kPwQ - 1) / kPwQ);
+  w.flags = align_up((size_t)n_ret * order_blocks(T) * sizeof(int32_t), 256);
+  w.units = align_up(((size_t)max_units(n_ret, T) + 1) * sizeof(int2), 256);
+  w.info = w.ranges = align_up(2 * lists * sizeof(int2), 256);
+  w.more = align_up((size_t)n_ret * order_blocks(T) * prefill_tile_ws(n_ret, T, chunk_start).n_t64 * sizeof(int32_t), 256);
+  return w;
+}
 // Key ranges of a launch for the retrieval heads under either rule.
 struct PrefillRanges {
   int dense, dense_sub, listed, listed_sub;
@@ -2078,7 +2626,12 @@ static size_t prefill_scratch(int n_ret, int32_t T, int64_t chunk_start) {
     most = std::max(most, partial_bytes(ranges, n_ret, last));
   }
   const int64_t cus = compute_units(), wgs = std::min(groups * std::min(end / 4096, (int64_t)16), 2 * cus);
-  return std::max(most, end > 9000 ? search_ws(std::min(groups, cus), wgs).total() : 0);
+  most = std::max(most, end > 9000 ? search_ws(std::min(groups, cus), wgs).total() : 0);
+  if (end >= 65536 && T >= 2 * kPwQ) {
+    const int64_t regrouped = std::max(groups * std::min(std::max(end / 262144, (int64_t)1), (int64_t)16), std::min(groups * std::min(end / 4096, (int64_t)16), 4 * cus));
+    most = std::max(most, search_ws(groups, regrouped).total()) + order_ws(n_ret, T, chunk_start).total();
+  }
+  return most;
 }
 
 }  // namespace rtp
@@ -2177,16 +2730,49 @@ extern "C" int32_t rtp_sparse_attn_prefill(const rtp_layer_desc* layer, const vo
   a.index_scale = index_scale_of(layer);
   const PrefillWs w = prefill_ws(layer->n_ret, T, chunk_start);
   char* const tiles = (char*)ws + w.proj + w.state;
-  char* const scratch = (char*)ws + w.front();
-  const size_t room = ws_bytes - w.front();
+  char* scratch = (char*)ws + w.front();
+  size_t room = ws_bytes - w.front();
+  const int64_t groups = (int64_t)layer->n_ret * ((T + 31) / 32), keys = chunk_start + T;
   a.sel_thr = (float*)((char*)ws + w.proj);
-  a.part = (float*)scratch;
   a.n_splits = ranges.listed;
-  a.n_sub = (int32_t)std::max<size_t>(std::min<size_t>(ranges.listed_sub, room / range_bytes(layer->n_ret, T) / ranges.listed), 1);
   a.n_slice = search_slices(layer->n_ret, T, chunk_start, room);
+  // regrouped queries: where the scratch has room for the order beside the partials of the ranges and what the sweeps leave
+  int last_slices = a.n_slice;
+  if (const int block = order_block(T, chunk_start)) {
+    const OrderWs ow = order_ws(layer->n_ret, T, chunk_start);
+    const size_t ob = ow.total();
+    // (the sweeps before the order keep their slices as well, for which there is room already without it)
+    const size_t parts = partial_bytes(ranges.listed, layer->n_ret, T);
+    int first = a.n_slice, last = a.n_slice > 1 ? a.n_slice : order_slices(groups, keys);
+    while (first > 1 && search_ws(groups, groups * first).total() + ob > room) --first;
+    while (last > 1 && search_ws(groups, groups * last).total() + ob > room) --last;
+    if (std::max({search_ws(groups, groups * std::max(first, last)).total(), parts}) + ob <= room && (first > 1 || a.n_slice == 1)) {
+      last_slices = last;
+      a.order_whole = a.n_slice == 1;
+      a.n_slice = first;
+      a.order = (int32_t*)scratch;
+      a.order_on = (int32_t*)(scratch + ow.order);
+      if (2 * layer->n_ret * ((T + kPwQ - 1) / kPwQ) <= kPlanLists) {
+        char* const at = scratch + ow.order + ow.flags;
+        a.units = (int2*)at + 1;
+        a.n_units = (int32_t*)at;
+        a.list_info = (int2*)(at + ow.units);
+        a.list_ranges = (int2*)(at + ow.units + ow.info);
+        a.more_list = (int32_t*)(at + ow.units + ow.info + ow.ranges);
+      }
+      a.order_block = block;
+      a.one_round = 2 * compute_units();
+      scratch += ob;
+      room -= ob;
+    }
+  }
+  a.part = (float*)scratch;
+  a.n_sub = (int32_t)std::max<size_t>(std::min<size_t>(ranges.listed_sub, room / range_bytes(layer->n_ret, T) / ranges.listed), 1);
+  if (a.units) {
+    a.part_cap = (int32_t)std::min<size_t>(room / ((size_t)kPwQ * kPfPart * sizeof(float)), kUnitRounds * compute_units());
+  }
   {
-    const int64_t groups = (int64_t)layer->n_ret * ((T + 31) / 32);
-    const SearchWs sw = search_ws(groups, groups * a.n_slice);
+    const SearchWs sw = search_ws(groups, groups * std::max(a.n_slice, last_slices));
     a.sl_max = (float*)scratch;
     a.sl_hist = (double*)(scratch + sw.max_bytes);
     a.sl_state = (SelState*)(scratch + sw.max_bytes + sw.hist_bytes);
@@ -2211,25 +2797,39 @@ extern "C" int32_t rtp_sparse_attn_prefill(const rtp_layer_desc* layer, const vo
     const dim3 grid = search_grid((unsigned)a.n_slice);
     RTP_LAUNCH(prefill_select_kernel<0>, grid, dim3(kSelThreads), 0, s, a);
     RTP_LAUNCH(prefill_select_kernel<1>, grid, dim3(kSelThreads), 0, s, a);
-    RTP_LAUNCH(prefill_select_kernel<2>, grid, dim3(kSelThreads), 0, s, a);
-    RTP_LAUNCH(prefill_select_kernel<3>, grid, dim3(kSelThreads), 0, s, a);
-    RTP_LAUNCH(prefill_select_kernel<kSelFinish>, search_grid(1), dim3(kSelThreads), 0, s, a);
-  } else {
+    if (!a.order) {
+      RTP_LAUNCH(prefill_select_kernel<2>, grid, dim3(kSelThreads), 0, s, a);
+      RTP_LAUNCH(prefill_select_kernel<3>, grid, dim3(kSelThreads), 0, s, a);
+      RTP_LAUNCH(prefill_select_kernel<kSelFinish>, search_grid(1), dim3(kSelThreads), 0, s, a);
+    }
+  } else if (!a.order) {
     // At most one workgroup per compute unit: sixteen waves each, four per SIMD, where eight leave it two.  What every wave does
     // by itself (its first loads, the ends of the member ranges) then takes twice the issue slots, which a peaked score law, whose
     // last two sweeps are a few tiles, does not win back on short contexts: the line lies where no law lost by them.  Calls of 4
     // heads, us, eight waves (as they were when sixteen came) / sixteen, clusters and a peaked law: 1000 queries at 6200 keys 111.0 / 104.8
     // and 70.4 / 73.0, at 9000 130.1 / 120.2 and 77.3 / 78.8, 200 at 11200 133.1 / 121.6 and 68.8 / 70.4; beyond the line, 200 at 11600
     // 139.9 / 122.6 and 71.9 / 70.7, 1000 at 12400 160.5 / 143.4 and 88.3 / 87.1, 2000 at 17000 230.8 / 205.8 and 99.7 / 98.5.
-    const int64_t groups = (int64_t)layer->n_ret * n_qtiles, rounds = (chunk_start + T + 32 * kSelRing - 1) / (32 * kSelRing);
+    const int64_t rounds = (keys + 32 * kSelRing - 1) / (32 * kSelRing);
     if (groups <= compute_units() && rounds > kSelFewRounds)
       RTP_LAUNCH((prefill_select_kernel<kSelAll, kSelThreadsFew>), search_grid(1), dim3(kSelThreadsFew), 0, s, a);
     else
       RTP_LAUNCH(prefill_select_kernel<kSelAll>, search_grid(1), dim3(kSelThreads), 0, s, a);
   }
+  if (a.order) {
+    if (a.n_slice > 1) RTP_LAUNCH(prefill_first_digit, search_grid(1), dim3(kSelThreads), 0, s, a);
+    else RTP_LAUNCH(prefill_select_kernel<kSelFirst>, search_grid(1), dim3(kSelThreads), 0, s, a);
+    RTP_LAUNCH(prefill_order_kernel, dim3((unsigned)((T + a.order_block - 1) / a.order_block), (unsigned)a.n_heads), dim3(kOrderThreads), 0, s, a);
+    a.n_slice = last_slices;
+    const dim3 grid = search_grid((unsigned)last_slices);
+    RTP_LAUNCH((prefill_select_kernel<2, kSelThreads, true>), grid, dim3(kSelThreads), 0, s, a);
+    RTP_LAUNCH((prefill_select_kernel<3, kSelThreads, true>), grid, dim3(kSelThreads), 0, s, a);
+    RTP_LAUNCH((prefill_select_kernel<kSelFinish, kSelThreads, true>), search_grid(1), dim3(kSelThreads), 0, s, a);
+  }
   const unsigned n_wide = (unsigned)((T + kPwQ - 1) / kPwQ);
-  RTP_LAUNCH(prefill_active_tiles_kernel, dim3(n_wide, (unsigned)a.n_heads), dim3(256), 0, (hipStream_t)stream, a);
-  const dim3 grid((unsigned)(a.n_splits * a.n_sub), n_wide, (unsigned)a.n_heads);
+  if (keys > 128 * kListThreadsFew) RTP_LAUNCH(prefill_active_tiles_kernel<kListThreads>, dim3(n_wide, (unsigned)a.n_heads, a.units ? 2u : 1u), dim3(kListThreads), 0, s, a);
+  else RTP_LAUNCH(prefill_active_tiles_kernel<kListThreadsFew>, dim3(n_wide, (unsigned)a.n_heads), dim3(kListThreadsFew), 0, s, a);
+  if (a.units) RTP_LAUNCH(prefill_plan_kernel, dim3(1), dim3(kPlanThreads), 0, s, a, compute_units());
+  const dim3 grid = a.units ? dim3(std::max((unsigned)max_units(a.n_heads, T), (unsigned)(a.n_splits * a.n_sub * a.n_heads) * n_wide)) : dim3((unsigned)(a.n_splits * a.n_sub), n_wide, (unsigned)a.n_heads);
   if (a.f16) RTP_LAUNCH((flash_prefill_wide_kernel<kModeSparse, true>), grid, dim3(kPwThreads), 0, (hipStream_t)stream, a);
   else RTP_LAUNCH(flash_prefill_wide_kernel<kModeSparse>, grid, dim3(kPwThreads), 0, (hipStream_t)stream, a);
   if (a.n_splits * a.n_sub > 1) launch_prefill_combine(a, (hipStream_t)stream);

@@ -589,3 +589,54 @@ def test_local_prefill_groups_by_the_tiles_of_a_band(chunk_start, T, sink, windo
     got = run.out.float().cpu().numpy().astype(np.float64)
     for r in orc.prefill_rows(rows=rows, p=1.0, **prefill_oracle_inputs(w)):
         check_out(got[r["t"], r["h"]], r["out"], f"t{r['t']} h{r['h']}", tight="mfma")
+
+
+@pytest.mark.parametrize("chunk_start,T,heads,kw,kv_dtype", [
+    (65280, 513, (1,), {}, "bf16"),                                        # one query past two tiles of 256; a sliced search
+    (70001, 777, (0, 2, 3), dict(own_frac=0.99, pick_run=32), "fp16"),     # three heads; a ragged last tile and group
+    (65536, 2113, (0, 1, 2, 3), dict(zipf=1.1, cluster_len=32), "bf16"),   # whole rows, more groups than compute units
+    (62000, 4200, (1, 2), {}, "bf16"),                                     # two blocks, the second one short
+    (65000, 600, (1,), dict(index_mode="proj"), "bf16"),                   # every query keeps much: nothing to regroup
+    (66000, 2100, (0, 1, 2, 3), dict(own_frac=0.97, pick_run=64, tokens_per_cluster=32768, q_noise=0.1), "bf16"),   # every one little
+    (65536, 530, (2,), dict(index_scale=2.5, p=0.999999), "bf16"),         # thresholds in the open-ended bin, sliced
+    (65536, 2081, (0, 1, 2, 3), dict(index_scale=2.5, p=0.999999), "bf16")])   # and in whole rows
+def test_sparse_prefill_with_regrouped_queries(chunk_start, T, heads, kw, kv_dtype):
+    """Chunks behind a long prefix take their queries by how much they keep.  In the least workspace there is, they take them by
+    position: the same selection, and outputs that differ by the order of fp32 sums and the rounding of probabilities to 16 bits
+    against other references (2^-8 each, of which a row's sum averages some: 2^-7 of the value, and 2^-7 of a unit-variance value
+    where they cancel)."""
+    print(f"[case] regrouped queries, T {T} behind {chunk_start}, {heads}, {kw}, {kv_dtype}", flush=True)
+    kw = dict(kw)
+    scale, p = kw.pop("index_scale", None), kw.pop("p", 0.9)
+    w = wl.make_prefill("regrouped", wl.Layer(8, 4, list(heads), sink=4, window=256, kv_dtype=kv_dtype), chunk_start, T, p, 211 + T, DEV, **kw)
+    if scale:
+        w.layer.index_scale = scale
+    run = PrefillRun(w)
+    need = rtp.rtp_sparse_attn_prefill_workspace_bytes(run.desc, T, chunk_start)
+
+    def go(n_bytes):
+        ws = torch.full((n_bytes,), 0xAB, dtype=torch.uint8, device=DEV)
+        o, l = torch.zeros_like(run.out), torch.zeros_like(run.lse)
+        st = [torch.full_like(t, -5) for t in (run.tau, run.count, run.mass)]
+        q_in = w.q_pre if w.WQ is not None else w.qI
+        names = _launches(lambda: rtp.rtp_sparse_attn_prefill(run.desc, q_in, w.q, w.WQ, w.kI, w.N * 16, run.Kp, run.Vp, run.rs, run.hs,
+                                                              chunk_start, T, p, o, l, *st, ws))
+        torch.cuda.synchronize()
+        return names, o[:, w.layer.ret_heads].float(), l[:, w.layer.ret_heads], st
+
+    lo, hi = 0, need // 256
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        try:
+            go(mid * 256)
+            hi = mid
+        except rtp.RtpError as e:
+            assert e.code == rtp.RTP_ERR_WORKSPACE
+            lo = mid
+    names, o, l, st = go(need)
+    plain, o1, l1, st1 = go(hi * 256)
+    assert any("order_kernel" in n for n in names) and not any("order_kernel" in n for n in plain), (names, plain)
+    assert torch.equal(st[0], st1[0]) and torch.equal(st[1], st1[1]) and (st[2] - st1[2]).abs().max() < 1e-6
+    assert ((o - o1).abs() <= 2.0 ** -7 * torch.maximum(o.abs(), o1.abs()) + 2.0 ** -7).all()
+    assert (l - l1).abs().max() < 6e-3
+    assert st[1].min() >= 1
