@@ -128,7 +128,7 @@ constexpr int kSelQMax = (1 << 21) - 1;
 constexpr int kPfTileBytes = kPfK * kHeadDim * 2 * 2;                 // one staged K + V tile
 constexpr int kSelListCap = 24;      // entries per lane of the member lists: with the histogram 80 KB, two workgroups per compute unit
 constexpr int kSelMfma = 2;          // index-score MFMAs of a wave in flight (the SIMD's other waves cover their latency)
-constexpr int kSelRing = 4;          // index-key tiles in flight per wave during the threshold search
+constexpr int kSelRing = 4, kSelRingWide = 8;   // index-key tiles in flight per wave during the threshold search; where only some of its sweeps run
 
 __device__ __forceinline__ int sel_q_of_t(float tt) {       // tt = M - s >= 0
   return (int)fminf(tt * kSelScale, (float)kSelQMax);
@@ -645,6 +645,7 @@ __global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const Prefil
   constexpr bool kSliced = STEP >= 0 && STEP < kSelFinish;             // this launch sweeps a slice of the group's keys
   constexpr bool kWhole = STEP == kSelAll || STEP == kSelFinish;       // ... or can run the whole search
   constexpr int NW = THREADS / 64;                             // waves of the workgroup
+  constexpr int RING = STEP == kSelAll || STEP == kSelFinish ? kSelRing : kSelRingWide;
   __shared__ double hist[kSelBins][32];                            // 32 KB
   __shared__ float list_all[NW][kSelListCap][64];                  // per-lane member lists of sweeps 2 and 3 (48 KB)
   float (*max_all)[32] = reinterpret_cast<float (*)[32]>(&list_all[0][0][0]);   // sweep 0: the waves' row maxima
@@ -754,9 +755,7 @@ __global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const Prefil
   float x_max = ninf;               // the row's largest raw product
   float x_mid = 0.f, x_half = 0.f;  // sweep 3: middle of [x_lo, min(x_top, x_max)] and the larger distance of its ends from it
   int shift = 0;
-  float mxs[kSelMfma];
-#pragma unroll
-  for (int u = 0; u < kSelMfma; ++u) mxs[u] = ninf;
+  float mx_lane = ninf;             // sweep 0: the lane's largest product
 
   // Weighs the listed members of every lane: lane-private lists, so the only cross-lane step is the loop bound.
   // Four entries at a time: their reads, exponentials and atomics overlap (one by one, a drain is a chain of LDS round
@@ -790,7 +789,7 @@ __global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const Prefil
   // the lowered reference --, 2 / 3: members of the digit prefix): SI = its 32 x 32 index products, nb = its first
   // key.  MASKED: causality and the lowered reference are tested pair by pair.
   float t_least = ninf;             // masked sweep 1: candidates have 8 (M - s) >= t_least
-  auto tile_work = [&](auto PH, auto MASKED, const f32x16& SI, int nb, float& mxacc) __attribute__((always_inline)) -> float {
+  auto tile_work = [&](auto PH, auto MASKED, const f32x16& SI, int nb) __attribute__((always_inline)) -> float {
     constexpr int phase = decltype(PH)::value;
     constexpr bool masked = decltype(MASKED)::value;
     if (phase == 0) {
@@ -801,9 +800,7 @@ __global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const Prefil
         const int n = nb + (i >> 2) * 8 + g * 4 + (i & 3);
         v[i] = (!masked || n <= m) ? SI[i] : ninf;
       }
-      const float top = max16_nn(v);
-      mxacc = fmaxf(mxacc, top);
-      return top;
+      return max16_nn(v);
     } else if (phase == 1) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
@@ -870,7 +867,31 @@ __global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const Prefil
     return 0.f;
   };
 
-  // One sweep over the tiles [tile_begin, tile_end) in rounds of kSelRing: a round's index-key registers are refilled
+  // Sweep 0: the maxima of a round's tile pairs over the wave's 32 queries x 64 keys, to the table.  The pairs share the steps across
+  // lanes: the halves of two are swapped into one register, the rows of two such into one, then four steps inside the rows.
+  auto swapped = [](float a, float b) __attribute__((always_inline)) {
+    const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return max_nn(__uint_as_float(x[0]), __uint_as_float(x[1]));
+  };
+  auto pair_maxima = [&](const float (&top)[RING / 2], float* to) __attribute__((always_inline)) {
+    float x = swapped(top[0], top[1]);                             // lanes 0 .. 31: of pair 0, the others: of pair 1
+    int at = lane >> 5;
+    if constexpr (RING == 8) {
+      const auto y = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(swapped(top[2], top[3])), false, false);
+      x = max_nn(__uint_as_float(y[0]), __uint_as_float(y[1]));    // rows of 16 lanes: pairs 0, 2, 1, 3
+      at = (lane >> 5) | ((lane >> 3) & 2);
+    }
+#define RTP_STEP(CTRL) x = max_nn(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true)));
+    RTP_STEP(0xB1) RTP_STEP(0x4E) RTP_STEP(0x141) RTP_STEP(0x140)  // quad_perm [1,0,3,2] and [2,3,0,1], row_half_mirror, row_mirror
+#undef RTP_STEP
+    if constexpr (RING == 4) {
+      const auto y = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+      x = max_nn(__uint_as_float(y[0]), __uint_as_float(y[1]));
+    }
+    if ((lane & (RING == 8 ? 15 : 31)) == 0) to[at] = x;
+  };
+
+  // One sweep over the tiles [tile_begin, tile_end) in rounds of RING: a round's index-key registers are refilled
   // (for the next round) as soon as its MFMAs have read them, so a load has a round's arithmetic -- of this wave and
   // of the SIMD's three others -- to land in.  No tail test: the mask-free range is a whole number of rounds, and in
   // the masked range a tile past the last one holds only keys n > m, which the causal mask drops.
@@ -885,18 +906,19 @@ __global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const Prefil
     static_assert(kSelMfma == 2, "a batch of MFMAs is one 64-key tile of the maximum table");
     constexpr bool masked_ = decltype(MASKED)::value;
     auto fetch = [&](int tile) { return masked_ ? load_k(tile) : load_k_whole(tile); };
-    u32x4 ring[kSelRing];
-    float tm[kSelRing / 2];                                        // the table entries of the tile pairs in the ring
+    u32x4 ring[RING];
+    float top[RING / 2];                                           // sweep 0: the lanes' maxima of the round's pairs
+    float tm[RING / 2];                                        // the table entries of the tile pairs in the ring
 #pragma unroll
-    for (int u = 0; u < kSelRing; ++u) ring[u] = fetch(tile_begin + u);
+    for (int u = 0; u < RING; ++u) ring[u] = fetch(tile_begin + u);
     if (kSkip) {
 #pragma unroll
-      for (int u = 0; u < kSelRing / 2; ++u) tm[u] = tmx[(tile_begin >> 1) + u];
+      for (int u = 0; u < RING / 2; ++u) tm[u] = tmx[(tile_begin >> 1) + u];
     }
 #pragma unroll 1
-    for (int first = tile_begin; first < tile_end; first += kSelRing) {
+    for (int first = tile_begin; first < tile_end; first += RING) {
 #pragma unroll
-      for (int hb = 0; hb < kSelRing; hb += kSelMfma) {            // kSelMfma MFMAs in flight at a time
+      for (int hb = 0; hb < RING; hb += kSelMfma) {            // kSelMfma MFMAs in flight at a time
         // no member possible in this pair of tiles: only the prefetches for the next round are issued
         bool skip = false;
         if (ORDERED && kSkip && kept_much && (((first + hb) >> 1) & 63) == 0) no_look = false;
@@ -906,11 +928,11 @@ __global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const Prefil
           skip = !no_look && pair_max < xlo_wave && (maxima || phase_ == 3);
           // a maximum at or above EVERY query's x_lo is at or above its own query's: no need to look
           reach_known = no_look || (maxima && (phase_ == 2 || pair_max >= xlo_wave_top));
-          tm[hb / 2] = tmx[((first + kSelRing + hb) >> 1)];
+          tm[hb / 2] = tmx[((first + RING + hb) >> 1)];
         }
         if (skip) {
 #pragma unroll
-          for (int u = 0; u < kSelMfma; ++u) ring[hb + u] = fetch(first + kSelRing + hb + u);
+          for (int u = 0; u < kSelMfma; ++u) ring[hb + u] = fetch(first + RING + hb + u);
           continue;
         }
         f32x16 SI[kSelMfma];
@@ -922,16 +944,17 @@ __global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const Prefil
                                                           __builtin_bit_cast(bf16x8, qIreg), SI[u], 0, 0, 0);
         }
 #pragma unroll
-        for (int u = 0; u < kSelMfma; ++u) ring[hb + u] = fetch(first + kSelRing + hb + u);
+        for (int u = 0; u < kSelMfma; ++u) ring[hb + u] = fetch(first + RING + hb + u);
         float tmax = ninf;
 #pragma unroll
         for (int u = 0; u < kSelMfma; ++u) {
           __builtin_amdgcn_sched_barrier(0);       // one tile at a time: hoisting four tiles' operands runs out of registers
-          tmax = fmaxf(tmax, tile_work(PH, MASKED, SI[u], (first + hb + u) * 32, mxs[u]));
+          const float v = tile_work(PH, MASKED, SI[u], (first + hb + u) * 32);
+          tmax = phase_ == 0 ? (u == 0 ? v : max_nn(tmax, v)) : fmaxf(tmax, v);
         }
-        if (phase_ == 0) {                         // the pair's maximum over the wave's 32 queries x 64 keys
-          const float wm = wave_max_f32(tmax);
-          if (lane == 0) tmx[(first + hb) >> 1] = wm;
+        if (phase_ == 0) {
+          mx_lane = max_nn(mx_lane, tmax);
+          top[hb / 2] = tmax;
         }
         // the last sweep knows better than the maximum: can one of the wave's queries keep a key of the pair?
         // (a pair known to reach keeps its maximum, which says the same)
@@ -949,18 +972,19 @@ __global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const Prefil
         }
         __builtin_amdgcn_sched_barrier(0);
       }
+      if (phase_ == 0) pair_maxima(top, tmx + (first >> 1));
     }
   };
-  const int n_plain = n_interior / kSelRing * kSelRing;            // whole rounds of interior tiles run without masks
+  const int n_plain = n_interior / RING * RING;            // whole rounds of interior tiles run without masks
   // this wave's share: an equal run of the rounds, the masked ones of the edge (one or two) at the end
-  const int plain_rounds = n_plain / kSelRing, rounds = (n_tiles + kSelRing - 1) / kSelRing;
+  const int plain_rounds = n_plain / RING, rounds = (n_tiles + RING - 1) / RING;
   // (ORDERED: where the last sweeps will take about equally long everywhere, the rest of a group's search is left to its first workgroup)
   const bool rest_whole = STEP == 2 && ORDERED && order_mode == kOrderOwnAlike && a.order_whole != 0;
   if (rest_whole && slice != 0) return;
   const int share = (rest_whole ? 0 : slice * NW) + wave, shares = (rest_whole ? 1 : n_slice) * NW;
   const int round_lo = (int)((int64_t)rounds * share / shares), round_hi = (int)((int64_t)rounds * (share + 1) / shares);
-  const int plain_lo = min(round_lo, plain_rounds) * kSelRing, plain_hi = min(round_hi, plain_rounds) * kSelRing;
-  const int edge_lo = max(round_lo, plain_rounds) * kSelRing, edge_hi = round_hi * kSelRing;
+  const int plain_lo = min(round_lo, plain_rounds) * RING, plain_hi = min(round_hi, plain_rounds) * RING;
+  const int edge_lo = max(round_lo, plain_rounds) * RING, edge_hi = round_hi * RING;
   // Sweeps 2 and 3 over the mask-free range, 512 tiles (256 entries of the maximum table) at a time: where at most
   // a quarter of a stretch's tile pairs can hold a member, only those are fetched and looked at, one after the other -- with a
   // peaked score law that is a handful of pairs in a million keys --; otherwise the streaming sweep above runs over the stretch,
@@ -1008,7 +1032,7 @@ __global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const Prefil
           }
           float tmax = ninf;
 #pragma unroll
-          for (int u = 0; u < 2; ++u) tmax = fmaxf(tmax, tile_work(PH, std::false_type{}, SI[u], (tile + u) * 32, mxs[u]));
+          for (int u = 0; u < 2; ++u) tmax = fmaxf(tmax, tile_work(PH, std::false_type{}, SI[u], (tile + u) * 32));
           if (phase_ == 3 && !reach_known && lane == 0) tmx[tile >> 1] = tmax > 0.f ? pinf : ninf;
         }
       }
@@ -1081,10 +1105,7 @@ __global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const Prefil
   // (of this workgroup's share of the keys, in every wave)
   auto row_maxima = [&]() __attribute__((always_inline)) {
     sweep_all(std::integral_constant<int, 0>{});
-    float mx = mxs[0];
-#pragma unroll
-    for (int u = 1; u < kSelMfma; ++u) mx = fmaxf(mx, mxs[u]);
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    float mx = fmaxf(mx_lane, __shfl_xor(mx_lane, 32));
     if (g == 0) max_all[wave][r] = mx;
     zero_hist();
     __syncthreads();
@@ -2541,7 +2562,7 @@ static int order_slices(int64_t groups, int64_t keys) {
 }
 
 // Sizes of the tile bookkeeping of a selecting launch.  A table row has one entry per 64 keys of the context, plus
-// the entries the threshold search touches past a group's last tile (its sweeps run in whole rounds of kSelRing tiles of
+// the entries the threshold search touches past a group's last tile (its sweeps run in whole rounds of four or eight tiles of
 // 32 keys and read the table one round ahead: four entries at most, sixteen are there).
 struct PrefillTileWs {
   int32_t n_t64;
