@@ -14,7 +14,7 @@
 //    asked for, is a launch of its own over the finished lists (gather_lists_kernel); whole_rows() says which rows;
 //  * everything else, and every top-k of more than one chunk: launches per level, as follows.
 //
-// Launches: [zero] -> level 1 -> level 2 -> level 3 -> write.  The first two disappear when
+// Launches: [zero] -> level 1 -> level 2 -> level 3 -> write.  The first one disappears for a top-k of rows of a few chunks, the first two when
 // the score pass has already accumulated level 1 (level1_ready).  Level 3 also leaves, per chunk, the
 // number of scores strictly above the 22-bit prefix (certainly kept) and appends the few scores that
 // share the prefix to a short per-row list; the write launch finds the exact threshold from the
@@ -306,6 +306,14 @@ __device__ __forceinline__ void load_chunk(const float4* __restrict__ src, int n
   }
 }
 
+// A chunk's level-1 counts fit 16 bits, so a copy of level 1 (2048 x 64 bits) has room for four chunks' counts, stored side by
+// side: nothing to clear before the level-1 launch, no global atomics in it, and the level-2 prologue adds up the row's chunks.  Rows of up to
+// four chunks per copy go this way (12 rows of 50021 scores: the clearing launch, 4.0 us and the gap behind it, falls away).
+static_assert(kTpChunk < 65536, "counts of a chunk in 16 bits");
+__device__ __forceinline__ uint64_t* own_counts_slice(uint64_t* hrow, int c) {
+  return hrow + level1_copy_offset(c >> 2) + (c & 3) * (kBins1 / 4);       // four bins to a word
+}
+
 // ---- launch 0 (only when level 1 is not supplied): zero the histograms -------------------------------
 __global__ __launch_bounds__(kTpThreads) void topp_zero_kernel(uint64_t* hist, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * kTpThreads + threadIdx.x;
@@ -327,7 +335,8 @@ __device__ __forceinline__ void block_count_to(int cnt, int32_t* dst, int* sh_i 
 }
 
 // ---- launches 1-3: one histogram level each ----------------------------------------------------
-template <int LEVEL>
+// OWN_COUNTS: a static top-k whose level-1 launch stores every chunk's counts in a slice of its own.
+template <int LEVEL, bool OWN_COUNTS = false>
 __device__ __forceinline__ void level_body(const TopPArgs& a, const int c, const int r) {
   constexpr int kBins = LEVEL == 1 ? kBins1 : (LEVEL == 2 ? kBins2 : kBins3);
   constexpr int kShift = LEVEL == 1 ? 21 : (LEVEL == 2 ? 10 : 0);     // key bits below this level's field
@@ -337,8 +346,16 @@ __device__ __forceinline__ void level_body(const TopPArgs& a, const int c, const
   // histogram of the level before in their prologue)
   static_assert(kBins1 == kBins2, "one register array serves the scans of levels 2 and 3");
   uint64_t prev_bins[kBins1 / kTpThreads];
-  if (LEVEL >= 2) load_bins<kBins1>(a.hist + (int64_t)r * a.hist_stride + (LEVEL == 3 ? kBins1 : 0), prev_bins);
-  if (LEVEL == 2) {      // level 1 may be spread over several copies
+  constexpr bool own_counts = LEVEL == 2 && OWN_COUNTS;
+  if (LEVEL >= 2 && !own_counts) load_bins<kBins1>(a.hist + (int64_t)r * a.hist_stride + (LEVEL == 3 ? kBins1 : 0), prev_bins);
+  uint64_t counts[own_counts ? 8 : 1];    // of the first eight chunks (those past the row's end are left out below)
+  if constexpr (own_counts) {
+    static_assert(kBins1 / kTpThreads == 4, "a thread's bins are one word of a slice");
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      counts[i] = own_counts_slice(a.hist + (int64_t)r * a.hist_stride, min(i, a.n_chunks - 1))[kTpThreads - 1 - (int)threadIdx.x];
+  }
+  if (LEVEL == 2 && !own_counts) {      // level 1 may be spread over several copies
     for (int sub = 1; sub < a.n_sub; ++sub) {
       uint64_t more[kBins1 / kTpThreads];
       load_bins<kBins1>(a.hist + (int64_t)r * a.hist_stride + level1_copy_offset(sub), more);
@@ -352,6 +369,24 @@ __device__ __forceinline__ void level_body(const TopPArgs& a, const int c, const
   const int n_here = (int)min((int64_t)kTpChunk, (int64_t)n - n0);
   float4 v[kTpVec];
   load_chunk(reinterpret_cast<const float4*>(a.scores + (int64_t)r * a.score_stride + n0), n_here, tid, v);
+  if constexpr (own_counts) {
+    const int active = (n + kTpChunk - 1) / kTpChunk;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) prev_bins[k] = 0;
+    for (int i0 = 0; i0 < active; i0 += 8) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const uint64_t w = i0 + i < active ? counts[i] : 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) prev_bins[k] += (w >> (16 * k)) & 0xffffu;
+      }
+      if (i0 + 8 < active) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          counts[i] = own_counts_slice(a.hist + (int64_t)r * a.hist_stride, min(i0 + 8 + i, active - 1))[kTpThreads - 1 - tid];
+      }
+    }
+  }
 
   __shared__ uint64_t lh[kBins];
   __shared__ uint64_t sh_part[kTpThreads / 64];
@@ -565,13 +600,22 @@ __device__ __forceinline__ void level_body(const TopPArgs& a, const int c, const
     }
   }
   __syncthreads();
+  if constexpr (LEVEL == 1 && OWN_COUNTS) {
+    uint64_t w = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) w |= lh[tid * 4 + k] << (16 * k);
+    own_counts_slice(hrow, c)[tid] = w;
+    const int active = (n + kTpChunk - 1) / kTpChunk;                // level 2's histogram, for the next launch
+    for (int i = c * kTpThreads + tid; i < kBins2; i += active * kTpThreads) hrow[kBins1 + i] = 0;
+    return;
+  }
   flush_hist(lh, hrow + (LEVEL == 1 ? level1_copy_offset(c % a.n_sub) : kOff), kBins, kTpThreads);
   clear_level3();
 }
 
-template <int LEVEL>
+template <int LEVEL, bool OWN_COUNTS = false>
 __global__ __launch_bounds__(kTpThreads) void topp_level_kernel(const TopPArgs a) {
-  level_body<LEVEL>(a, blockIdx.x, blockIdx.y);
+  level_body<LEVEL, OWN_COUNTS>(a, blockIdx.x, blockIdx.y);
 }
 
 // A level-2 or level-3 launch with local heads of the same decode step on board (rtp_decode_attention): the
@@ -1937,7 +1981,10 @@ static int32_t run_select(const char* who, const float* scores, int64_t score_st
   if (a.n_chunks == 1) return launch_rows(who, a, attend, ride, ride_G, s);
   dim3 grid((unsigned)a.n_chunks, (unsigned)R), block(kTpThreads);
   if (level1_ready && whole_rows(R, a.n_chunks, attend != nullptr, ride, ride_G)) return launch_whole_rows(who, a, attend, ride, ride_G, s);
-  if (!level1_ready) {
+  const bool own_counts = kcount && a.n_chunks <= 4 * l.n_sub;
+  if (own_counts) {
+    RTP_LAUNCH((topp_level_kernel<1, true>), grid, block, 0, s, a);
+  } else if (!level1_ready) {
     const int64_t nz = (int64_t)R * l.hist_stride;
     RTP_LAUNCH(topp_zero_kernel, dim3((unsigned)((nz + kTpThreads - 1) / kTpThreads)), block, 0, s, a.hist, nz);
     RTP_LAUNCH(topp_level_kernel<1>, grid, block, 0, s, a);
@@ -1963,7 +2010,8 @@ static int32_t run_select(const char* who, const float* scores, int64_t score_st
 #undef RTP_RIDE
     RTP_LAUNCH(topp_level_kernel<3>, grid, block, 0, s, a);
   } else {
-    RTP_LAUNCH(topp_level_kernel<2>, grid, block, 0, s, a);
+    if (own_counts) RTP_LAUNCH((topp_level_kernel<2, true>), grid, block, 0, s, a);
+    else RTP_LAUNCH(topp_level_kernel<2>, grid, block, 0, s, a);
     RTP_LAUNCH(topp_level_kernel<3>, grid, block, 0, s, a);
   }
   if (attend) {

@@ -475,3 +475,39 @@ def test_decode_attention_from_a_paged_cache(case):
             err = np.abs(out[b, h] - o)
             assert (err <= 1e-3 + 2.0 ** -8 * np.abs(o)).all(), f"b{b} h{h}: {err.max()}"
             assert abs(float(run.lse[b, h]) - l) < 2e-3
+
+
+@pytest.mark.parametrize("R,n_max,own", [(2, 262144, True), (2, 262145, False), (5, 131072, True), (5, 131073, False), (12, 65536, True),
+                                         (12, 65537, False), (12, 50021, True), (17, 32768, True), (17, 32769, False), (17, 8193, True)])
+def test_topk_select_counts_of_chunks(R, n_max, own):
+    """Rows of up to four chunks per copy of the first level store the chunks' counts side by side instead of adding them up: on
+    either side of that line, rows of one chunk to all of them, in a workspace full of other bits."""
+    print(f"[case] top-k counts, {R} rows to {n_max}", flush=True)
+    rng = np.random.default_rng(R * 1000003 + n_max)
+    lens = [[n_max, 1, 8191, 8192, 8193, n_max - 1][i % 6] for i in range(R)]
+    ks = [min(n, [4096, 1, 17, n, max(n - 1, 1)][i % 5]) for i, n in enumerate(lens)]
+    stride = (n_max + 3) // 4 * 4
+    sc = torch.full((R, stride), float("nan"), dtype=torch.float32)
+    for i, n in enumerate(lens):
+        row = rng.standard_normal(n).astype(np.float32) * (1.0 + 3.0 * (i % 3))
+        if i % 4 == 3:
+            # ties at the threshold; + 0.0: the selector's keys order minus zero below zero, the comparison below does not
+            row = np.round(row * 4.0) / 4.0 + 0.0
+        sc[i, :n] = torch.from_numpy(row.astype(np.float32))
+    ws = torch.full((rtp.rtp_topp_workspace_bytes(R, n_max),), 0xAB, dtype=torch.uint8, device=DEV)
+    sel = torch.full((R, stride), -1, dtype=torch.int32, device=DEV)
+    cnt, tau = torch.full((R,), -9, dtype=torch.int32, device=DEV), torch.zeros(R, device=DEV)
+    dev = sc.to(DEV)
+    for rep in range(2):
+        rtp.rtp_profile_start(16)
+        rtp.rtp_topk_select(dev, stride, i32(lens), i32(ks), R, n_max, sel, stride, cnt, tau, ws)
+        names = [n for n, _ in rtp.rtp_profile_stop(16)]
+        assert any("zero" in n for n in names) == (not own), names
+        torch.cuda.synchronize()
+        for i, (n, k) in enumerate(zip(lens, ks)):
+            row = sc[i, :n]
+            th = torch.topk(row, k).values[-1]
+            want = torch.nonzero(row >= th).squeeze(1).to(torch.int32)
+            assert torch.equal(sel[i, :int(cnt[i])].cpu(), want), (i, n, k)
+            if k < n:
+                assert tau[i].item() == th.item()
