@@ -645,7 +645,9 @@ __global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const Prefil
   constexpr bool kSliced = STEP >= 0 && STEP < kSelFinish;             // this launch sweeps a slice of the group's keys
   constexpr bool kWhole = STEP == kSelAll || STEP == kSelFinish;       // ... or can run the whole search
   constexpr int NW = THREADS / 64;                             // waves of the workgroup
-  constexpr int RING = STEP == kSelAll || STEP == kSelFinish ? kSelRing : kSelRingWide;
+  // (the sweeps of a sliced search that stay with their slices' keys for a few rounds only are quicker with the short one: 333 queries
+  // behind 131072 tokens, sweeps 1 and 2 60.2 and 55.2 us against 61.9 and 56.3)
+  constexpr int RING = STEP == 0 || STEP == kSelFirst || (ORDERED && kSliced) ? kSelRingWide : kSelRing;
   __shared__ double hist[kSelBins][32];                            // 32 KB
   __shared__ float list_all[NW][kSelListCap][64];                  // per-lane member lists of sweeps 2 and 3 (48 KB)
   float (*max_all)[32] = reinterpret_cast<float (*)[32]>(&list_all[0][0][0]);   // sweep 0: the waves' row maxima
@@ -1433,7 +1435,8 @@ constexpr int kPwTileBytes = 2 * kPfK * kHeadDim * 2;
 constexpr int kSmemWide = kPwTileBytes * kPwStages;
 
 
-template <int MODE, bool F16 = false>
+// ORDERED: a selecting launch over regrouped queries, planned or not.
+template <int MODE, bool F16 = false, bool ORDERED = false>
 __global__ __launch_bounds__(kPwThreads, 2) void flash_prefill_wide_kernel(const PrefillArgs a) {
   constexpr int NW = kPwThreads / 64;        // waves per workgroup; each owns 32 queries
   constexpr int RG = 4 * NW;                 // tile rows one load instruction of the whole workgroup covers
@@ -1451,14 +1454,15 @@ __global__ __launch_bounds__(kPwThreads, 2) void flash_prefill_wide_kernel(const
   // first workgroups of the grid in the same (key range, query tile, head slot) order, the others leave.
   constexpr bool listed = SPARSE;
   const int n_wide = (a.n_q + kPwQ - 1) / kPwQ;
-  const int n_units = listed && a.units ? *a.n_units : 0;
+  static_assert(!ORDERED || SPARSE, "only behind a search");
+  const int n_units = ORDERED && a.units ? *a.n_units : 0;
   int n_parts = listed && n_units == 0 ? listed_splits(a) : a.n_splits;
   int n_sub = a.n_sub;
   int n_splits = n_parts * n_sub;
   int hslot = blockIdx.x, split, qt_rev = blockIdx.y, b = 0;
   bool exact_only = false, more = false;
   int list = 0, wave_lo = 0, wave_hi = NW;            // the unit's list and the waves whose queries it is for
-  if (listed && n_units > 0) {
+  if (ORDERED && n_units > 0) {
     if ((int)blockIdx.x >= n_units) return;
     const int2 unit = a.units[blockIdx.x];
     const int what = __builtin_amdgcn_readfirstlane(unit.y);
@@ -1485,7 +1489,7 @@ __global__ __launch_bounds__(kPwThreads, 2) void flash_prefill_wide_kernel(const
     split = (int)blockIdx.z - b * n_splits;
   }
   const int h = a.heads[hslot];
-  const bool ordered = SPARSE && a.order != nullptr;    // (hard queries first, their tiles have the long lists)
+  constexpr bool ordered = ORDERED;                     // (hard queries first, their tiles have the long lists)
   const int t0 = (ordered ? qt_rev : n_wide - 1 - qt_rev) * kPwQ;
   const int kvh = h / (a.n_q_heads / a.n_kv_heads);
   const int pos0 = a.q_start ? a.q_start[b] : (int)a.q_start_host;
@@ -1493,7 +1497,7 @@ __global__ __launch_bounds__(kPwThreads, 2) void flash_prefill_wide_kernel(const
   const float ninf = -__builtin_huge_valf();
 
   // ---- this lane's query (column r of the wave's 32) ----
-  const bool my_wave = wave >= wave_lo && wave < wave_hi;
+  const bool my_wave = !ORDERED || (wave >= wave_lo && wave < wave_hi);
   const bool qok = my_wave && t0 + wave * 32 + r < a.n_q;
   const int32_t* const order = ordered ? a.order + (int64_t)hslot * a.n_q : nullptr;
   int tq = t0 + wave * 32 + r;
@@ -1960,7 +1964,7 @@ __global__ __launch_bounds__(kPwThreads, 2) void flash_prefill_wide_kernel(const
     // ---- exact pass: running maximum, accumulators rescaled in place; only the next tile's loads are in flight.  For queries that
     // keep few keys (their tiles' lists are short once they stand together) and references out of reach (rare).  In bf16 the probabilities are multiplied
     // in two parts, rounded and the rest: a sum of a few terms does not average a rounding to 8 bits. ----
-    constexpr bool kParts = SPARSE && !F16;
+    constexpr bool kParts = ORDERED && !F16;
     f32x16 S;
     uint32_t P[8], Q[kParts ? 8 : 1];
     mrow = ninf;
@@ -2026,7 +2030,7 @@ __global__ __launch_bounds__(kPwThreads, 2) void flash_prefill_wide_kernel(const
     if (a.count) a.count[o] = mq + 1;
   }
   if (n_splits > 1) {
-    const int64_t at = listed && n_units > 0 ? (int64_t)(a.list_ranges[list].y + split) * kPwQ + wave * 32 + r
+    const int64_t at = ORDERED && n_units > 0 ? (int64_t)(a.list_ranges[list].y + split) * kPwQ + wave * 32 + r
                                          : ((int64_t)split * a.n_heads + hslot) * a.n_q + tq;
     float* prow = a.part + at * kPfPart;
     if (g == 0) { prow[0] = mfin; prow[1] = ltot; prow[2] = __int_as_float(kept); }
@@ -2287,7 +2291,7 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(const Prefil
 // four partials in flight each, a lane owns 4 of the 128 output dims; LDS merges the slices.  8 / SLICES rows per
 // workgroup: two slices where there are few ranges (24 us for 16384 rows of 4 ranges with a thread per dim going through
 // the ranges one by one, 11 now), all eight where a short chunk's keys are cut into dozens (43 and 5 us for 256 rows of 64).
-template <int SLICES>
+template <int SLICES, bool ORDERED = false>
 __global__ __launch_bounds__(256) void prefill_combine_kernel(const PrefillArgs a) {
   __shared__ float sh_m[8], sh_l[8];
   __shared__ int sh_kept[8];
@@ -2298,7 +2302,7 @@ __global__ __launch_bounds__(256) void prefill_combine_kernel(const PrefillArgs 
   int t = place, n_splits;
   const float* part = a.part;
   int64_t step;                                                         // from one range's partials to the next
-  if (a.units && *a.n_units > 0) {
+  if (ORDERED && a.units && *a.n_units > 0) {
     const int n_wide = (a.n_q + kPwQ - 1) / kPwQ, at = min(place, a.n_q - 1), list = hs * n_wide + at / kPwQ;
     int2 ranges = a.list_ranges[list];
     if (at % kPwQ / 32 >= ranges.x >> 16) ranges = a.list_ranges[a.n_heads * n_wide + list];
@@ -2311,7 +2315,7 @@ __global__ __launch_bounds__(256) void prefill_combine_kernel(const PrefillArgs 
     part += ((int64_t)hs * a.n_q + (row ? t : 0)) * kPfPart;
     step = (int64_t)a.n_heads * a.n_q * kPfPart;
   }
-  if (a.order && row) t = a.order[(int64_t)hs * a.n_q + t];
+  if (ORDERED && row) t = a.order[(int64_t)hs * a.n_q + t];
   const float ninf = -__builtin_huge_valf();
   float M = ninf, L = 0.f;
   float4 A = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -2390,8 +2394,11 @@ static int compute_units() {
 static void launch_prefill_combine(const PrefillArgs& a, hipStream_t s) {
   // (planned ranges: two units per compute unit over lists of about equal length; the partials there can be are far more)
   const int expected = a.units ? std::min<int>(kUnitRanges, 2 * compute_units() / (a.n_heads * ((a.n_q + kPwQ - 1) / kPwQ))) : a.n_splits * a.n_sub;
-  if (expected > 8) RTP_LAUNCH(prefill_combine_kernel<8>, dim3((unsigned)a.n_q, (unsigned)a.n_heads), dim3(256), 0, s, a);
-  else RTP_LAUNCH(prefill_combine_kernel<2>, dim3((unsigned)((a.n_q + 3) / 4), (unsigned)a.n_heads), dim3(256), 0, s, a);
+  const dim3 grid8((unsigned)a.n_q, (unsigned)a.n_heads), grid2((unsigned)((a.n_q + 3) / 4), (unsigned)a.n_heads);
+  if (a.order && expected > 8) RTP_LAUNCH((prefill_combine_kernel<8, true>), grid8, dim3(256), 0, s, a);
+  else if (a.order) RTP_LAUNCH((prefill_combine_kernel<2, true>), grid2, dim3(256), 0, s, a);
+  else if (expected > 8) RTP_LAUNCH(prefill_combine_kernel<8>, grid8, dim3(256), 0, s, a);
+  else RTP_LAUNCH(prefill_combine_kernel<2>, grid2, dim3(256), 0, s, a);
 }
 
 // Number of key-range splits for a dense launch with few workgroups (long context, few heads).  A
@@ -2855,9 +2862,11 @@ extern "C" int32_t rtp_sparse_attn_prefill(const rtp_layer_desc* layer, const vo
   else RTP_LAUNCH(prefill_active_tiles_kernel<kListThreadsFew>, dim3(n_wide, (unsigned)a.n_heads), dim3(kListThreadsFew), 0, s, a);
   if (a.units) RTP_LAUNCH(prefill_plan_kernel, dim3(1), dim3(kPlanThreads), 0, s, a, compute_units());
   const dim3 grid = a.units ? dim3(std::max((unsigned)max_units(a.n_heads, T), (unsigned)(a.n_splits * a.n_sub * a.n_heads) * n_wide)) : dim3((unsigned)(a.n_splits * a.n_sub), n_wide, (unsigned)a.n_heads);
-  if (a.f16) RTP_LAUNCH((flash_prefill_wide_kernel<kModeSparse, true>), grid, dim3(kPwThreads), 0, (hipStream_t)stream, a);
+  if (a.order && a.f16) RTP_LAUNCH((flash_prefill_wide_kernel<kModeSparse, true, true>), grid, dim3(kPwThreads), 0, s, a);
+  else if (a.order) RTP_LAUNCH((flash_prefill_wide_kernel<kModeSparse, false, true>), grid, dim3(kPwThreads), 0, s, a);
+  else if (a.f16) RTP_LAUNCH((flash_prefill_wide_kernel<kModeSparse, true>), grid, dim3(kPwThreads), 0, (hipStream_t)stream, a);
   else RTP_LAUNCH(flash_prefill_wide_kernel<kModeSparse>, grid, dim3(kPwThreads), 0, (hipStream_t)stream, a);
-  if (a.n_splits * a.n_sub > 1) launch_prefill_combine(a, (hipStream_t)stream);
+  if (a.units || a.n_splits * a.n_sub > 1) launch_prefill_combine(a, (hipStream_t)stream);
   return check_launch(who);
 }
 
