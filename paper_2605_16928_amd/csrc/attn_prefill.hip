@@ -50,7 +50,8 @@ struct PrefillArgs {
   uint16_t* out;
   float* lse;
   int32_t n_heads;
-  uint8_t heads[128];           // query heads this launch computes
+  int32_t n_seq;                // sequences (local band)
+  uint8_t heads[128];           // query heads this launch computes, ascending
   int32_t n_splits;             // wide kernel: key range of every query tile cut into this many parts
   int32_t n_sub;                // ... and every part into this many sub-ranges that share the part's reference maxima
   float* part;                  // n_splits * n_sub > 1: partial results [range, head slot, query, kPfPart]
@@ -189,10 +190,33 @@ __global__ __launch_bounds__(kPfThreads * GROUPS, 2) void flash_prefill_local_ke
   unsigned char* const smem = smem_all + grp * 2 * kPfTileBytes;
   const int tid = (int)threadIdx.x - grp * kPfThreads, lane = tid & 63, wave = tid >> 6;
   const int g = lane >> 5, r = lane & 31;
-  const int h = a.heads[blockIdx.x];
-  const int b = blockIdx.z;
-  const int t0 = ((int)gridDim.y - 1 - (int)blockIdx.y) * kPfQ;
-  const int kvh = h / (a.n_q_heads / a.n_kv_heads);
+  int h, b, t0, split = 0;
+  const int group = a.n_q_heads / a.n_kv_heads;
+  if (GROUPS == 2) {
+    h = a.heads[blockIdx.x];
+    b = a.n_splits > 1 ? 0 : (int)blockIdx.z;
+    split = a.n_splits > 1 ? (int)blockIdx.z : 0;
+    t0 = ((int)gridDim.y - 1 - (int)blockIdx.y) * kPfQ;
+  } else {
+    // Workgroups go to the eight dies in turn, each with an L2 of its own, and every die takes an eighth of the work in one piece: KV head by
+    // KV head, within one the query tiles of a sequence (late ones first), within a tile the query heads, so that the workgroups a die runs at a
+    // time read one KV head's rows of a few thousand tokens.  With the heads side by side in the grid a die read all KV heads' windows
+    // at once: 4096 queries at 128K tokens 180 -> 171 us, the last 8192 of 1M (window 4096) 625 -> 595.  (Launches of few workgroups lose the
+    // microsecond that finding the place takes.)
+    const int n_qt = (a.n_q + kPfQ - 1) / kPfQ, per_head = n_qt * a.n_seq, n_unit = a.n_heads * per_head;
+    const int die = (int)blockIdx.x & 7, chunk = (n_unit + 7) >> 3;
+    const int unit = die * chunk + ((int)blockIdx.x >> 3);
+    if (unit >= n_unit) return;
+    const int any = unit / per_head, kv = a.heads[any] / group;
+    int first = any, last = any;                              // the KV head's slots
+    while (first > 0 && a.heads[first - 1] / group == kv) --first;
+    while (last + 1 < a.n_heads && a.heads[last + 1] / group == kv) ++last;
+    const int in_group = unit - first * per_head, n_in = last - first + 1;
+    h = a.heads[first + in_group % n_in];
+    b = in_group / n_in / n_qt;
+    t0 = (n_qt - 1 - in_group / n_in % n_qt) * kPfQ;
+  }
+  const int kvh = h / group;
   const int pos0 = a.q_start ? a.q_start[b] : (int)a.q_start_host;
   const int64_t tok0 = a.seq_start ? a.seq_start[b] : 0;
   const float ninf = -__builtin_huge_valf();
@@ -214,7 +238,9 @@ __global__ __launch_bounds__(kPfThreads * GROUPS, 2) void flash_prefill_local_ke
   const int kt_end = m_hi / kPfK;                       // inclusive
   const int kt_w0 = max(a.sink, m_lo - a.window + 1) / kPfK;
   const int ks_end = min((a.sink + kPfK - 1) / kPfK, kt_w0);    // sink tiles not already inside the band
-  const int n_tiles = ks_end + (kt_end - kt_w0 + 1);
+  const int n_band = ks_end + (kt_end - kt_w0 + 1);
+  const int it_lo = GROUPS == 2 ? n_band * split / a.n_splits : 0;    // this workgroup's range of them
+  const int n_tiles = (GROUPS == 2 ? n_band * (split + 1) / a.n_splits : n_band) - it_lo;
 
   const uint16_t* Kg = a.K + (int64_t)kvh * a.head_stride + tok0 * a.row_stride;
   const uint16_t* Vg = a.V + (int64_t)kvh * a.head_stride + tok0 * a.row_stride;
@@ -369,7 +395,7 @@ __global__ __launch_bounds__(kPfThreads * GROUPS, 2) void flash_prefill_local_ke
     // (Steps are counted alike in both groups: the barriers are the workgroup's.)
     const int steps = (n_tiles + GROUPS - 1) / GROUPS;
     auto tile_of = [&](int i) { return i * GROUPS + grp; };
-    auto tile_n0 = [&](int it) { return (it < ks_end ? it : kt_w0 + (it - ks_end)) * kPfK; };
+    auto tile_n0 = [&](int i) { const int it = it_lo + i; return (it < ks_end ? it : kt_w0 + (it - ks_end)) * kPfK; };
     auto landed = [&](int i) __attribute__((always_inline)) {        // publishes the tiles of step i
       loads_landed();
       __syncthreads();
@@ -413,6 +439,17 @@ __global__ __launch_bounds__(kPfThreads * GROUPS, 2) void flash_prefill_local_ke
   // ---- normalise and store ----
   const float ltot = lrow + __shfl_xor(lrow, 32);
   if (!qok) return;
+  if (GROUPS == 2 && a.n_splits > 1) {
+    float* prow = a.part + (((int64_t)split * a.n_heads + blockIdx.x) * a.n_q + t) * kPfPart;
+    if (g == 0) { prow[0] = mrow; prow[1] = ltot; prow[2] = 0.f; }
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+#pragma unroll
+      for (int i4 = 0; i4 < 4; ++i4)
+        *reinterpret_cast<float4*>(prow + 4 + db * 32 + i4 * 8 + g * 4) =
+            make_float4(O[db][i4 * 4], O[db][i4 * 4 + 1], O[db][i4 * 4 + 2], O[db][i4 * 4 + 3]);
+    return;
+  }
   const float inv = ltot > 0.f ? 1.f / ltot : 0.f;
   uint16_t* orow = a.out + qrow;
 #pragma unroll
@@ -2458,6 +2495,17 @@ static int64_t band_tiles(const PrefillArgs& a, int64_t max_ctx) {
   return std::min((max_ctx + kPfK - 1) / kPfK, ((int64_t)a.sink + kPfK - 1) / kPfK + (span + kPfK - 2) / kPfK + 1);
 }
 
+// Ranges of a band's key tiles, of at least eight tiles each, for launches of one sequence that leave compute units idle: a workgroup's way
+// through its tiles is a chain of 2.5 us a step, whoever else is there.  28 heads, window 2048, behind 131072 tokens, launch / with the merge: 32
+// queries 44 / 21 us, 256 (four ranges) 54 / 31, 333 (three) 57 / 36, 512 (two) 54 / 44.
+static int band_splits(const PrefillArgs& a, int32_t B, int64_t max_ctx) {
+  const int64_t units = (int64_t)a.n_heads * ((a.n_q + kPfQ - 1) / kPfQ);
+  if (B != 1 || units <= 0) return 1;
+  const int64_t s = std::min(compute_units() / units, band_tiles(a, max_ctx) / 8);
+  return s > 1 ? (int)std::min<int64_t>(s, 8) : 1;
+}
+static size_t band_bytes(int n_heads, int32_t n_q, int splits) { return align_up((size_t)splits * n_heads * n_q * kPfPart * sizeof(float), 256); }
+
 static int32_t launch_prefill(const char* who, bool local, PrefillArgs& a, int32_t B, int64_t max_ctx, hipStream_t s) {
   if (a.n_heads == 0) return RTP_OK;
   if (a.n_splits < 1) a.n_splits = 1;
@@ -2469,11 +2517,19 @@ static int32_t launch_prefill(const char* who, bool local, PrefillArgs& a, int32
   dim3 grid((unsigned)a.n_heads, (unsigned)((a.n_q + qt - 1) / qt), (unsigned)(B * (local ? 1 : a.n_splits * a.n_sub)));
   if (grid.y > 65535 || grid.z > 65535) return fail(RTP_ERR_INVALID_ARG, "%s: n_q / B too large for one launch", who);
   if (local) {
-    if ((int64_t)grid.x * grid.y * grid.z <= compute_units() && band_tiles(a, max_ctx) >= 4) {
+    const int64_t n_unit = (int64_t)grid.x * grid.y * grid.z;
+    if (n_unit <= compute_units() && band_tiles(a, max_ctx) >= 4) {
+      grid.z *= a.n_splits;
       if (a.f16) RTP_LAUNCH((flash_prefill_local_kernel<true, 2>), grid, dim3(2 * kPfThreads), 0, s, a);
       else RTP_LAUNCH((flash_prefill_local_kernel<false, 2>), grid, dim3(2 * kPfThreads), 0, s, a);
-    } else if (a.f16) RTP_LAUNCH((flash_prefill_local_kernel<true, 1>), grid, dim3(kPfThreads), 0, s, a);
-    else RTP_LAUNCH((flash_prefill_local_kernel<false, 1>), grid, dim3(kPfThreads), 0, s, a);
+      if (a.n_splits > 1) launch_prefill_combine(a, s);
+    } else {
+      if (n_unit > 0x7fffffff - 8) return fail(RTP_ERR_INVALID_ARG, "%s: n_q / B too large for one launch", who);
+      a.n_seq = B;
+      grid = dim3((unsigned)((n_unit + 7) / 8 * 8));
+      if (a.f16) RTP_LAUNCH((flash_prefill_local_kernel<true, 1>), grid, dim3(kPfThreads), 0, s, a);
+      else RTP_LAUNCH((flash_prefill_local_kernel<false, 1>), grid, dim3(kPfThreads), 0, s, a);
+    }
   } else if (a.f16) RTP_LAUNCH((flash_prefill_wide_kernel<kModeDense, true>), grid, dim3(kPwThreads), 0, s, a);
   else RTP_LAUNCH(flash_prefill_wide_kernel<kModeDense>, grid, dim3(kPwThreads), 0, s, a);
   if (!local && a.n_splits * a.n_sub > 1) launch_prefill_combine(a, s);
@@ -2496,7 +2552,7 @@ static int32_t check_prefill_common(const char* who, const void* q, const void* 
 int32_t prefill_range_attn(const char* who, bool dense, const rtp_layer_desc* L, const void* q, const void* K,
                            const void* V, int64_t row_stride, int64_t head_stride, const int64_t* seq_start,
                            const int32_t* ctx_len, const int32_t* q_start, int32_t B, int32_t n_q, int64_t max_ctx,
-                           void* out, float* lse, hipStream_t s) {
+                           void* out, float* lse, void* ws, size_t ws_bytes, hipStream_t s) {
   HeadTable ht;
   int32_t rc = fill_head_table(L, &ht, who);
   if (rc != RTP_OK) return rc;
@@ -2527,7 +2583,24 @@ int32_t prefill_range_attn(const char* who, bool dense, const rtp_layer_desc* L,
   a.n_heads = 0;
   for (int h = 0; h < L->n_q_heads; ++h)
     if (dense || !ht.is_ret[h]) a.heads[a.n_heads++] = (uint8_t)h;
+  if (!dense && ws && !((uintptr_t)ws & 255)) {
+    const int splits = band_splits(a, B, max_ctx);
+    if (splits > 1 && ws_bytes >= band_bytes(a.n_heads, n_q, splits)) {
+      a.n_splits = splits;
+      a.part = (float*)ws;
+    }
+  }
   return launch_prefill(who, !dense, a, B, max_ctx, s);
+}
+size_t prefill_range_ws(const rtp_layer_desc* L, int32_t B, int32_t n_q, int64_t max_ctx) {
+  if (!L || n_q <= 1 || B != 1 || L->n_q_heads <= L->n_ret) return 0;
+  PrefillArgs a = {};
+  a.n_heads = L->n_q_heads - L->n_ret;
+  a.n_q = n_q;
+  a.sink = L->sink;
+  a.window = L->window;
+  const int splits = band_splits(a, B, max_ctx);
+  return splits > 1 ? band_bytes(a.n_heads, n_q, splits) : 0;
 }
 
 // Workgroups per 32-query group of the threshold search: as many as fill two workgroups per compute unit, each with at

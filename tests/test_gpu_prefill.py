@@ -650,3 +650,32 @@ def test_sparse_prefill_fp16_few_kept_keys_far_from_the_first_tile(scale):
     w = wl.small_prefill("cpu", chunk_start=3000, T=70, seed=231, n_q_heads=4, n_kv_heads=2, ret_heads=(1,), own_frac=0.99, pick_run=32, kv_dtype="fp16")
     w.q.mul_(scale)
     _check_sparse_prefill(w.to(DEV), f"f16_few_{scale}", 0.9)
+
+
+@pytest.mark.parametrize("chunk_start,T,sink,window,bound,kv_dtype", [
+    (5000, 1, 4, 1000, 0, "bf16"), (5000, 130, 4, 1000, 0, "fp16"), (3001, 333, 70, 2048, 0, "bf16"), (2047, 97, 0, 1025, 0, "bf16"),
+    (0, 40, 4, 2048, 4096, "bf16"),            # one tile of keys where the bound allows for thirty: empty ranges
+    (63, 257, 4, 4096, 8192, "fp16"), (1100, 64, 1200, 100, 0, "bf16")])
+def test_local_prefill_key_ranges(chunk_start, T, sink, window, bound, kv_dtype):
+    """Few workgroups and long bands: the key tiles are cut into ranges whose partial results a second launch merges.  Without room
+    for them in the workspace, one range; both against the oracle, and retrieval heads untouched."""
+    print(f"[case] local prefill in ranges, T {T} behind {chunk_start}, {sink} + {window}, {kv_dtype}", flush=True)
+    w = wl.small_prefill(DEV, chunk_start=chunk_start, T=T, n_q_heads=8, n_kv_heads=2, ret_heads=(1,), sink=sink, window=window, seed=411 + T,
+                         kv_dtype=kv_dtype)
+    L, run = w.layer, PrefillRun(w)
+    max_ctx = max(w.N, bound)
+    need = rtp.rtp_local_attn_workspace_bytes(run.desc, 1, T, max_ctx)
+    rows = [(t, h) for t in sorted({0, 1, 31, 32, 127, 128, T // 2, T - 1} & set(range(T))) for h in (0, 2, 7)]
+    ref = orc.prefill_rows(rows=rows, p=1.0, **prefill_oracle_inputs(w))
+    for n_bytes in (need, 256):
+        ws = torch.full((max(n_bytes, 256),), 0xAB, dtype=torch.uint8, device=DEV)
+        out, lse = torch.full_like(run.out, 5.0), torch.full_like(run.lse, 5.0)
+        names = _launches(lambda: rtp.rtp_local_attn(run.desc, w.q, run.Kp, run.Vp, run.rs, run.hs, run.seq_start, run.ctx_len, run.q_start,
+                                                     1, T, max_ctx, out, lse, ws))
+        torch.cuda.synchronize()
+        assert any("combine" in n for n in names) == (n_bytes == need), names
+        got, l = out.float().cpu().numpy().astype(np.float64), lse.cpu().numpy()
+        for r in ref:
+            check_out(got[r["t"], r["h"]], r["out"], f"t{r['t']} h{r['h']}", tight="mfma")
+            assert abs(l[r["t"], r["h"]] - r["lse"]) < 3e-3
+        assert (out[:, 1] == 5.0).all() and (lse[:, 1] == 5.0).all()
