@@ -590,6 +590,7 @@ __global__ __launch_bounds__(kOrderThreads) void prefill_order_kernel(const Pref
   int cls[ROUNDS], rank[ROUNDS];
 #pragma unroll
   for (int k = 0; k < ROUNDS; ++k) {
+    if (k * kOrderThreads >= n) break;                             // (the same for the whole workgroup)
     const int i = k * kOrderThreads + tid;
     const bool on = i < n;
     cls[k] = on ? kOrderClasses - 1 - (st[i].flags >> kSelClassShift) : kOrderClasses - 1;      // (the class that keeps most comes first)
@@ -2628,11 +2629,14 @@ static int search_slices(int n_ret, int32_t T, int64_t chunk_start, size_t room)
 }
 
 // Queries that prefill_order_kernel may regroup together (0: none).  A group's masked tiles reach from its first query to its last, so
-// the block is at most a sixteenth of what lies before the chunk; below 65536 keys or 512 queries the three launches
-// more cost about what the tiles spared give (333 queries behind 131072 tokens: call 360 -> 345 us), and short chunks keep one result whatever their
-// workspace: by position or by kept count, the probabilities are rounded to 16 bits against different references.
-static int order_block(int32_t T, int64_t chunk_start) {
-  if (chunk_start + T < 65536 || T < 2 * kPwQ) return 0;
+// the block is at most a sixteenth of what lies before the chunk.  Below 65536 keys, 512 queries or 4e8 pairs of query and key over all heads the three
+// launches more cost what the tiles spared give.  Calls of 4 heads, us, by position / regrouped, clusters, projected queries (nothing to
+// regroup, a sixth of the context kept by all) and a peaked law: 4096 queries at 128K tokens 2520 / 2200, 2445 / 2445, 842 / 837; 1000 there
+// 730 / 670, 699 / 716, 299 / 303; 4000 behind 65536 1240 / 1130, 1349 / 1394, 548 / 561; on the other side of the line 1024 behind 65536 441 / 446.
+// (Chunks of less than 512 queries keep one result whatever their workspace: by position or by kept count, the probabilities are rounded to 16
+// bits against different references; 333 queries behind 131072 would gain 4 %.)
+static int order_block(int n_ret, int32_t T, int64_t chunk_start) {
+  if (chunk_start + T < 65536 || T < 2 * kPwQ || (double)n_ret * T * (double)(chunk_start + T) < 4e8) return 0;
   const int64_t most = std::min<int64_t>(chunk_start / 16 / kPwQ * kPwQ, kOrderMax);
   return T <= most ? (T + kPwQ - 1) / kPwQ * kPwQ : most >= 1024 ? (int)most : 0;
 }
@@ -2843,7 +2847,7 @@ extern "C" int32_t rtp_sparse_attn_prefill(const rtp_layer_desc* layer, const vo
   a.n_slice = search_slices(layer->n_ret, T, chunk_start, room);
   // regrouped queries: where the scratch has room for the order beside the partials of the ranges and what the sweeps leave
   int last_slices = a.n_slice;
-  if (const int block = order_block(T, chunk_start)) {
+  if (const int block = order_block(layer->n_ret, T, chunk_start)) {
     const OrderWs ow = order_ws(layer->n_ret, T, chunk_start);
     const size_t ob = ow.total();
     // (the sweeps before the order keep their slices as well, for which there is room already without it)
