@@ -213,7 +213,9 @@ int32_t rtp_sparse_attn_decode(const rtp_layer_desc* layer, const void* q,
  * inside that margin.
  * For p < 1 the attention visits only the 64-key tiles in which some query of a 256-query tile can keep a key (the
  * search leaves, per 32-query group and tile, whether a product reaches the group's thresholds); outputs, counts and
- * sums are those of visiting every tile.  The workspace holds that table (4 B per group and 64 keys of context),
+ * sums are those of visiting every tile.  In a large chunk behind a long context the groups and tiles are not of
+ * neighbouring queries but of queries that keep about as much; no result depends on that but for the order of fp32 sums.
+ * The workspace holds that table (4 B per group and 64 keys of context),
  * the tile lists, and the key-range partials or, before them, what the launches of a short chunk's search hand on: about
  * 630 MB for T = 8192 at chunk_start = 1,040,384 with 4 retrieval heads, 40 MB for T = 4096 at 126,976, 35 MB for T = 333
  * at 131,072.  The size function answers what every chunk of at most T queries ending at chunk_start + T takes at full
@@ -235,7 +237,8 @@ int32_t rtp_sparse_attn_prefill(const rtp_layer_desc* layer, const void* q_pre, 
  * index score of every 32-query group in every 64-key tile, and the attention launch visits a tile only if some
  * query of its 256-query tile can keep a key there).  layer, T and chunk_start as in that call; waits for `stream`,
  * then writes two host values: tiles_visited (64-key tiles visited, summed over retrieval heads and 256-query
- * tiles) and tiles_causal (what plain causal attention visits).  ws_bytes: at least the size function's answer.
+ * tiles; of regrouped queries, a list as long as the longest-reaching one of them needs) and tiles_causal (what plain
+ * causal attention visits).  Any other call on the workspace in between ends what the figures stand on.  ws_bytes: at least the size function's answer.
  * Allocates nothing on the device.
  */
 int32_t rtp_sparse_attn_prefill_tile_stats(const rtp_layer_desc* layer, int32_t T, int64_t chunk_start,
@@ -249,6 +252,8 @@ int32_t rtp_sparse_attn_prefill_tile_stats(const rtp_layer_desc* layer, int32_t 
  * A query at position m attends tokens { n < sink } U { max(sink, m - window + 1) <= n <= m }.
  * Decode (q_start == NULL, n_q == 1) reads each needed K/V row once per KV head and serves the whole
  * GQA group from it; prefill (q_start != NULL) runs banded causal MFMA tiles.
+ * A short chunk of one sequence cuts its bands into key ranges and keeps their partials in the workspace; a smaller
+ * workspace, or none, is accepted in prefill and costs idle compute units.
  * max_ctx: host upper bound of ctx_len[].
  */
 size_t rtp_local_attn_workspace_bytes(const rtp_layer_desc* layer, int32_t B, int32_t n_q, int64_t max_ctx);

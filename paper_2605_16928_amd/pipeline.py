@@ -279,8 +279,9 @@ class PrefillRun:
         self.tau = torch.zeros((max(L.n_ret, 1), w.T), dtype=torch.float32, device=DEV)
         self.mass = torch.zeros((max(L.n_ret, 1), w.T), dtype=torch.float32, device=DEV)
         self.count = torch.zeros((max(L.n_ret, 1), w.T), dtype=torch.int32, device=DEV)
-        self.ws = ws_alloc(max(rtp.rtp_sparse_attn_prefill_workspace_bytes(self.desc, w.T, w.chunk_start),
-                               rtp.rtp_local_attn_workspace_bytes(self.desc, 1, w.T, w.N)))
+        self.ws = ws_alloc(rtp.rtp_sparse_attn_prefill_workspace_bytes(self.desc, w.T, w.chunk_start))
+        # (the local band's own: its partials must not meet a search on another stream, nor what tile_stats reads)
+        self.ws_local = ws_alloc(rtp.rtp_local_attn_workspace_bytes(self.desc, 1, w.T, w.N))
         if interleaved:
             self.kv = torch.cat([w.K, w.V], dim=2).contiguous()
             self.Kp, self.Vp, self.rs, self.hs = self.kv.data_ptr(), self.kv.data_ptr() + 256, 256, w.N * 256
@@ -291,7 +292,7 @@ class PrefillRun:
         w = self.w
         rtp.rtp_local_attn(self.desc, w.q, self.Kp, self.Vp, self.rs, self.hs, self.seq_start, self.ctx_len,
                            self.q_start, 1, w.T, w.N, self.out if out is None else out,
-                           self.lse if lse is None else lse, self.ws)
+                           self.lse if lse is None else lse, self.ws_local)
 
     def dense_attn(self, out=None, lse=None):
         w = self.w

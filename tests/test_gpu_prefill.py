@@ -679,3 +679,13 @@ def test_local_prefill_key_ranges(chunk_start, T, sink, window, bound, kv_dtype)
             check_out(got[r["t"], r["h"]], r["out"], f"t{r['t']} h{r['h']}", tight="mfma")
             assert abs(l[r["t"], r["h"]] - r["lse"]) < 3e-3
         assert (out[:, 1] == 5.0).all() and (lse[:, 1] == 5.0).all()
+
+
+def test_local_band_between_a_search_and_its_tile_stats():
+    """The local band's partials go to a workspace of their own: the figures of the search before it stay."""
+    w = wl.small_prefill(DEV, chunk_start=3001, T=333, n_q_heads=8, n_kv_heads=2, ret_heads=(1,), sink=4, window=2048, seed=417)
+    run = PrefillRun(w)
+    run.sparse_prefill(p=0.5)
+    stats = run.tile_stats()
+    assert any("combine" in n for n in _launches(run.local_attn))
+    assert 0 < stats[0] <= stats[1] and run.tile_stats() == stats
