@@ -538,7 +538,8 @@ def main() -> int:
                 "topp_tiles_visited_frac": round(visited / max(causal, 1), 5),
                 "topp_useful_flop_frac": round(kept_pairs * 512 / (t_topp * 1e-6) / MFMA_PEAK, 6),
                 "topp_attention_issued_flop_frac": round(visited * 256 * 64 * (512 + 32) / (t_topp * 1e-6) / MFMA_PEAK, 4),
-                "topp_threshold_search_ms": round(by_kernel.get("prefill_select_kernel", 0.0) / 1e3, 3),
+                "topp_threshold_search_ms": round(sum(by_kernel.get(k, 0.0) for k in (
+                    "prefill_select_kernel", "prefill_first_digit", "prefill_order_kernel")) / 1e3, 3),
                 "topp_attention_ms": round((by_kernel.get("flash_prefill_wide_kernel", 0.0)
                                             + by_kernel.get("prefill_combine_kernel", 0.0)) / 1e3, 3),
             }

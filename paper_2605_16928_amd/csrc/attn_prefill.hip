@@ -519,11 +519,12 @@ __device__ __forceinline__ float sel_first_below(float M, float index_scale, flo
 // registers 19.4).  The waves add into ONE histogram (LDS atomics; 32 KB); the per-lane member
 // lists of sweeps 2 and 3 are emptied when a half tile might overrun one.  All waves meet at
 // barriers around every scan, so the phases are uniform over the workgroup.
-// What bounds the sweeps there: sweep 0 (2.4 ms) and sweep 3 (2.0, was 4.0) their vector instructions per tile; sweep 1
-// (7.4, was 9.3) the LDS atomics -- an fp64 one holds the compute unit's LDS for 8.4 cycles, i.e. 34 per SIMD and wave of
-// 64 pairs, as many as its seven vector instructions take --; sweep 2 (6.3, was 8.2) the LDS stores (4.3 cycles
-// each whatever the number of lanes) and draining the lists.  Skipping the stores of the pairs without a member by a
-// branch measured slower (7.5).
+// What bounds the sweeps there: sweep 0 (1.9 ms, was 2.4) and sweep 3 their vector instructions per tile; sweep 1
+// (7.4, was 9.3) the LDS atomics -- an fp64 one holds the compute unit's LDS for 8.6 cycles, i.e. 34 per SIMD and wave of
+// 64 pairs, as many as its seven vector instructions take --; sweep 2 the LDS stores (4.6 cycles
+// each whatever the number of lanes) and draining the lists.  Over every tile sweeps 2 and 3 take 6.3 and 2.0 ms, over the tiles that the regrouped
+// queries of that chunk leave them (see below) 3.4 and 1.9 as launches of their own.  Skipping the stores of the pairs without a member by a
+// branch measured slower (7.5 ms over every tile); one store of a table entry per round of sweeps 2 and 3 gave 0.4 %, which the runs of one side differ by.
 // One group per workgroup: when a few queries of a chunk have their threshold deep in the
 // background while the others' sweeps 2 and 3 visit a handful of tiles, short workgroups let the dispatcher even
 // the load out.
@@ -1450,8 +1451,9 @@ __global__ __launch_bounds__(THREADS, 4) void prefill_select_kernel(const Prefil
 // interleaved.  Inside the branches that served both before, the register allocator moved accumulators at the joins,
 // and every stream began by waiting for its first LDS operands, all eight waves at once; in the loop a stream reads
 // the next one's first operands.  Attention launch of 4 heads x 4096 queries at 128K tokens: 1300 -> 1066 us selecting,
-// 1250 -> 918 us dense (1.18 PFLOP/s); last 8192-query chunk of 1M tokens, selecting: 20.3 -> 17.3 to 17.7 ms (operands three
-// and two steps ahead instead of five and four: 17.7 and 1141 us).  Per 32 x 32 block the two waves of a SIMD issue 16 MFMAs
+// 1250 -> 918 us dense (1.18 PFLOP/s); last 8192-query chunk of 1M tokens, selecting, over every tile: 20.3 -> 17.3 to 17.7 ms (operands three
+// and two steps ahead instead of five and four: 17.7 and 1141 us).  Over the 0.46 of the tiles that its queries regrouped leave (ORDERED):
+// 8.9 ms; the 4096 at 128K, 0.66 of the tiles: 825 us.  Per 32 x 32 block the two waves of a SIMD issue 16 MFMAs
 // of 32 cycles, 24 LDS reads and, by the counters, 64 (dense) or 122 (selecting) other vector instructions each, with the matrix
 // pipe busy 59 and 48 % of the cycles and the LDS, at the rates of these reads, about half of them.  Spreading a block's softmax
 // over both streams (it used to run beside the PV MFMAs alone) took the dense call of this shape from 1132 to 1124 us, 333
