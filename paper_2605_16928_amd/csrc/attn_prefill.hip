@@ -2631,14 +2631,16 @@ static int search_slices(int n_ret, int32_t T, int64_t chunk_start, size_t room)
 }
 
 // Queries that prefill_order_kernel may regroup together (0: none).  A group's masked tiles reach from its first query to its last, so
-// the block is at most a sixteenth of what lies before the chunk.  Below 65536 keys, 512 queries or 4e8 pairs of query and key over all heads the three
-// launches more cost what the tiles spared give.  Calls of 4 heads, us, by position / regrouped, clusters, projected queries (nothing to
-// regroup, a sixth of the context kept by all) and a peaked law: 4096 queries at 128K tokens 2520 / 2200, 2445 / 2445, 842 / 837; 1000 there
-// 730 / 670, 699 / 716, 299 / 303; 4000 behind 65536 1240 / 1130, 1349 / 1394, 548 / 561; on the other side of the line 1024 behind 65536 441 / 446.
+// the block is at most a sixteenth of what lies before the chunk.  The launches more take 20 to 45 us, which laws with nothing to regroup lose: below
+// 65536 keys, 512 queries or 1.2e9 pairs of query and key over all heads that is 2 to 3 % of the call, above up to 2 near the line.  Calls of 4 heads, us, by position /
+// regrouped, clusters, projected queries (a sixth of the context kept by all) and a peaked law: 4096 queries at 128K tokens 2520 / 2200, 2445 /
+// 2445, 842 / 837; 3000 there 2325 / 1853, 2232 / 2219, 831 / 814; 4096 behind 98304 1994 / 1816, 1955 / 1988, 707 / 711; 1024 behind 400000 1932 / 1743,
+// 1882 / 1892, 673 / 622; on the other side of the line 4000 behind 65536 1240 / 1130, 1349 / 1394, 548 / 561; 1000 at 128K 730 / 670, 699 / 716,
+// 299 / 303.
 // (Chunks of less than 512 queries keep one result whatever their workspace: by position or by kept count, the probabilities are rounded to 16
 // bits against different references; 333 queries behind 131072 would gain 4 %.)
 static int order_block(int n_ret, int32_t T, int64_t chunk_start) {
-  if (chunk_start + T < 65536 || T < 2 * kPwQ || (double)n_ret * T * (double)(chunk_start + T) < 4e8) return 0;
+  if (chunk_start + T < 65536 || T < 2 * kPwQ || (double)n_ret * T * (double)(chunk_start + T) < 1.2e9) return 0;
   const int64_t most = std::min<int64_t>(chunk_start / 16 / kPwQ * kPwQ, kOrderMax);
   return T <= most ? (T + kPwQ - 1) / kPwQ * kPwQ : most >= 1024 ? (int)most : 0;
 }

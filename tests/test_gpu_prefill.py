@@ -592,14 +592,14 @@ def test_local_prefill_groups_by_the_tiles_of_a_band(chunk_start, T, sink, windo
 
 
 @pytest.mark.parametrize("chunk_start,T,heads,kw,kv_dtype", [
-    (1 << 20, 513, (1,), {}, "bf16"),                                        # one query past two tiles of 256; a sliced search
-    (180001, 777, (0, 2, 3), dict(own_frac=0.99, pick_run=32), "fp16"),     # three heads; a ragged last tile and group
-    (65536, 2113, (0, 1, 2, 3), dict(zipf=1.1, cluster_len=32), "bf16"),   # whole rows, more groups than compute units
-    (62000, 4200, (1, 2), {}, "bf16"),                                     # two blocks, the second one short
-    (240000, 600, (1, 2, 3), dict(index_mode="proj"), "bf16"),                   # every query keeps much: nothing to regroup
-    (66000, 2100, (0, 1, 2, 3), dict(own_frac=0.97, pick_run=64, tokens_per_cluster=32768, q_noise=0.1), "bf16"),   # every one little
-    (270000, 530, (1, 2, 3), dict(index_scale=2.5, p=0.999999), "bf16"),         # thresholds in the open-ended bin, sliced
-    (65536, 2081, (0, 1, 2, 3), dict(index_scale=2.5, p=0.999999), "bf16")])   # and in whole rows
+    (1 << 20, 513, (1, 2, 3), {}, "bf16"),                                   # one query past two tiles of 256; a sliced search
+    (520001, 777, (0, 2, 3), dict(own_frac=0.99, pick_run=32), "fp16"),     # three heads; a ragged last tile and group
+    (150000, 2113, (0, 1, 2, 3), dict(zipf=1.1, cluster_len=32), "bf16"),   # whole rows, more groups than compute units
+    (62000, 4600, (0, 1, 2, 3), {}, "bf16"),                             # two blocks, the second one short
+    (700000, 600, (1, 2, 3), dict(index_mode="proj"), "bf16"),                   # every query keeps much: nothing to regroup
+    (150000, 2100, (0, 1, 2, 3), dict(own_frac=0.97, pick_run=64, tokens_per_cluster=32768, q_noise=0.1), "bf16"),   # every one little
+    (800000, 530, (1, 2, 3), dict(index_scale=2.5, p=0.999999), "bf16"),         # thresholds in the open-ended bin, sliced
+    (150000, 2081, (0, 1, 2, 3), dict(index_scale=2.5, p=0.999999), "bf16")])   # and in whole rows
 def test_sparse_prefill_with_regrouped_queries(chunk_start, T, heads, kw, kv_dtype):
     """Chunks behind a long prefix take their queries by how much they keep.  In the least workspace there is, they take them by
     position: the same selection, and outputs that differ by the order of fp32 sums and the rounding of probabilities to 16 bits
