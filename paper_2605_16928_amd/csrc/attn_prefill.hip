@@ -50,7 +50,7 @@ struct PrefillArgs {
   uint16_t* out;
   float* lse;
   int32_t n_heads;
-  int32_t n_seq;                // sequences (local band)
+  bool by_die;                  // local band: a KV head to a die
   uint8_t heads[128];           // query heads this launch computes, ascending
   int32_t n_splits;             // wide kernel: key range of every query tile cut into this many parts
   int32_t n_sub;                // ... and every part into this many sub-ranges that share the part's reference maxima
@@ -192,18 +192,18 @@ __global__ __launch_bounds__(kPfThreads * GROUPS, 2) void flash_prefill_local_ke
   const int g = lane >> 5, r = lane & 31;
   int h, b, t0, split = 0;
   const int group = a.n_q_heads / a.n_kv_heads;
-  if (GROUPS == 2) {
+  if (GROUPS == 2 || !a.by_die) {
     h = a.heads[blockIdx.x];
     b = a.n_splits > 1 ? 0 : (int)blockIdx.z;
     split = a.n_splits > 1 ? (int)blockIdx.z : 0;
     t0 = ((int)gridDim.y - 1 - (int)blockIdx.y) * kPfQ;
   } else {
     // Workgroups go to the eight dies in turn, each with an L2 of its own, and every die takes an eighth of the work in one piece: KV head by
-    // KV head, within one the query tiles of a sequence (late ones first), within a tile the query heads, so that the workgroups a die runs at a
+    // KV head, within one the query tiles (late ones first), within a tile the query heads, so that the workgroups a die runs at a
     // time read one KV head's rows of a few thousand tokens.  With the heads side by side in the grid a die read all KV heads' windows
     // at once: 4096 queries at 128K tokens 180 -> 171 us, the last 8192 of 1M (window 4096) 625 -> 595.  (Launches of few workgroups lose the
     // microsecond that finding the place takes.)
-    const int n_qt = (a.n_q + kPfQ - 1) / kPfQ, per_head = n_qt * a.n_seq, n_unit = a.n_heads * per_head;
+    const int per_head = (a.n_q + kPfQ - 1) / kPfQ, n_unit = a.n_heads * per_head;
     const int die = (int)blockIdx.x & 7, chunk = (n_unit + 7) >> 3;
     const int unit = die * chunk + ((int)blockIdx.x >> 3);
     if (unit >= n_unit) return;
@@ -213,8 +213,8 @@ __global__ __launch_bounds__(kPfThreads * GROUPS, 2) void flash_prefill_local_ke
     while (last + 1 < a.n_heads && a.heads[last + 1] / group == kv) ++last;
     const int in_group = unit - first * per_head, n_in = last - first + 1;
     h = a.heads[first + in_group % n_in];
-    b = in_group / n_in / n_qt;
-    t0 = (n_qt - 1 - in_group / n_in % n_qt) * kPfQ;
+    b = 0;
+    t0 = (per_head - 1 - in_group / n_in) * kPfQ;
   }
   const int kvh = h / group;
   const int pos0 = a.q_start ? a.q_start[b] : (int)a.q_start_host;
@@ -2527,9 +2527,11 @@ static int32_t launch_prefill(const char* who, bool local, PrefillArgs& a, int32
       else RTP_LAUNCH((flash_prefill_local_kernel<false, 2>), grid, dim3(2 * kPfThreads), 0, s, a);
       if (a.n_splits > 1) launch_prefill_combine(a, s);
     } else {
-      if (n_unit > 0x7fffffff - 8) return fail(RTP_ERR_INVALID_ARG, "%s: n_q / B too large for one launch", who);
-      a.n_seq = B;
-      grid = dim3((unsigned)((n_unit + 7) / 8 * 8));
+      // Query tiles whose whole window lies before the chunk take equally long; of a prompt's, the early ones are short, and an eighth in one
+      // piece is not an eighth of the work (calls with a prompt's 4096 queries, 28 local heads, window 2048: 247 us, 264 by die; 1024, 61 heads,
+      // window 512: 89 and 93).
+      a.by_die = B == 1 && max_ctx - a.n_q >= a.window;
+      if (a.by_die) grid = dim3((unsigned)((n_unit + 7) / 8 * 8));
       if (a.f16) RTP_LAUNCH((flash_prefill_local_kernel<true, 1>), grid, dim3(kPfThreads), 0, s, a);
       else RTP_LAUNCH((flash_prefill_local_kernel<false, 1>), grid, dim3(kPfThreads), 0, s, a);
     }

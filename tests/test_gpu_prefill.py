@@ -689,3 +689,22 @@ def test_local_band_between_a_search_and_its_tile_stats():
     stats = run.tile_stats()
     assert any("combine" in n for n in _launches(run.local_attn))
     assert 0 < stats[0] <= stats[1] and run.tile_stats() == stats
+
+
+@pytest.mark.parametrize("chunk_start,T,window", [(200, 1153, 200), (199, 1153, 200), (3000, 1281, 90), (0, 1281, 2048)])
+def test_local_prefill_of_more_workgroups_than_compute_units(chunk_start, T, window):
+    """A KV head to a die from the first chunk on whose window lies before it; KV heads of four local heads and of three, a last tile of
+    one query, a number of workgroups that eight does not divide."""
+    print(f"[case] local prefill of many workgroups, T {T} behind {chunk_start}, window {window}", flush=True)
+    w = wl.small_prefill(DEV, chunk_start=chunk_start, T=T, n_q_heads=32, n_kv_heads=8, ret_heads=(1, 9, 31), sink=4, window=window, seed=431 + T)
+    run = PrefillRun(w)
+    out, lse = torch.full_like(run.out, 5.0), torch.full_like(run.lse, 5.0)
+    run.local_attn(out, lse)
+    torch.cuda.synchronize()
+    got, l = out.float().cpu().numpy().astype(np.float64), lse.cpu().numpy()
+    rows = [(t, h) for t in (0, 127, 128, T // 2, T - 1) for h in (0, 3, 8, 16, 30)]
+    for r in orc.prefill_rows(rows=rows, p=1.0, **prefill_oracle_inputs(w)):
+        check_out(got[r["t"], r["h"]], r["out"], f"t{r['t']} h{r['h']}", tight="mfma")
+        assert abs(l[r["t"], r["h"]] - r["lse"]) < 3e-3
+    local = [h for h in range(32) if h not in (1, 9, 31)]
+    assert (lse[:, local] != 5.0).all() and (out[:, [1, 9, 31]] == 5.0).all()
