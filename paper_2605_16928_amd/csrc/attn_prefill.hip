@@ -79,7 +79,7 @@ struct PrefillArgs {
   struct SelState* sl_state;    // [2, n_ret, n_q]: what a scan found, read by the next launch
   int32_t* sl_again;            // [groups]: 1 = some query's threshold lies in the open-ended bin, the last launch searches the group;
                                 // 2 = the group's search is complete
-  // queries regrouped by how much they keep (prefill_order_kernel); NULL: every launch takes them by position
+  // queries regrouped by how much they keep (prefill_order_kernel); NULL: every launch takes them by position, and units is NULL too
   int32_t* order;               // [n_ret, n_q]: the query of every place
   int32_t* order_on;            // [n_ret, blocks]: how the block's queries stand, kOrder...
   int32_t order_block;          // queries per block, a multiple of kPwQ
@@ -1475,7 +1475,7 @@ constexpr int kPwTileBytes = 2 * kPfK * kHeadDim * 2;
 constexpr int kSmemWide = kPwTileBytes * kPwStages;
 
 
-// ORDERED: a selecting launch over regrouped queries, planned or not.
+// ORDERED: a selecting launch over regrouped queries, in planned units (without any where nothing is regrouped, the order being by position).
 template <int MODE, bool F16 = false, bool ORDERED = false>
 __global__ __launch_bounds__(kPwThreads, 2) void flash_prefill_wide_kernel(const PrefillArgs a) {
   constexpr int NW = kPwThreads / 64;        // waves per workgroup; each owns 32 queries
@@ -1495,7 +1495,7 @@ __global__ __launch_bounds__(kPwThreads, 2) void flash_prefill_wide_kernel(const
   constexpr bool listed = SPARSE;
   const int n_wide = (a.n_q + kPwQ - 1) / kPwQ;
   static_assert(!ORDERED || SPARSE, "only behind a search");
-  const int n_units = ORDERED && a.units ? *a.n_units : 0;
+  const int n_units = ORDERED ? *a.n_units : 0;
   int n_parts = listed && n_units == 0 ? listed_splits(a) : a.n_splits;
   int n_sub = a.n_sub;
   int n_splits = n_parts * n_sub;
@@ -2342,7 +2342,7 @@ __global__ __launch_bounds__(256) void prefill_combine_kernel(const PrefillArgs 
   int t = place, n_splits;
   const float* part = a.part;
   int64_t step;                                                         // from one range's partials to the next
-  if (ORDERED && a.units && *a.n_units > 0) {
+  if (ORDERED && *a.n_units > 0) {                       // (partials lie by place)
     const int n_wide = (a.n_q + kPwQ - 1) / kPwQ, at = min(place, a.n_q - 1), list = hs * n_wide + at / kPwQ;
     int2 ranges = a.list_ranges[list];
     if (at % kPwQ / 32 >= ranges.x >> 16) ranges = a.list_ranges[a.n_heads * n_wide + list];
@@ -2350,12 +2350,12 @@ __global__ __launch_bounds__(256) void prefill_combine_kernel(const PrefillArgs 
     if (n_splits == 1) return;                           // (the same for the whole workgroup: the attention launch has written the rows)
     part += ((int64_t)ranges.y * kPwQ + place % kPwQ) * kPfPart;
     step = (int64_t)kPwQ * kPfPart;
-  } else {
+    if (row) t = a.order[(int64_t)hs * a.n_q + place];
+  } else {                                               // (by query, which is the place)
     n_splits = (a.act_range ? listed_splits(a) : a.n_splits) * a.n_sub;   // (a listed launch decides on the device)
     part += ((int64_t)hs * a.n_q + (row ? t : 0)) * kPfPart;
     step = (int64_t)a.n_heads * a.n_q * kPfPart;
   }
-  if (ORDERED && row) t = a.order[(int64_t)hs * a.n_q + t];
   const float ninf = -__builtin_huge_valf();
   float M = ninf, L = 0.f;
   float4 A = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -2641,7 +2641,11 @@ static int search_slices(int n_ret, int32_t T, int64_t chunk_start, size_t room)
 // 299 / 303.
 // (Chunks of less than 512 queries keep one result whatever their workspace: by position or by kept count, the probabilities are rounded to 16
 // bits against different references; 333 queries behind 131072 would gain 4 %.)
+// More lists than prefill_plan_kernel holds: by position.  Without planned units the attention's ranges are as uneven as the lists, and queries that
+// keep few keys lose their exact pass; 64 heads, 8193 queries behind 60000 tokens, ms, by position / regrouped without a plan: clusters 37.5 / 32.6, Zipf
+// clusters 36.2 / 33.5, projected queries 36.9 / 37.7, peaked 9.9 / 10.9, a few hard queries 13.6 / 15.5.
 static int order_block(int n_ret, int32_t T, int64_t chunk_start) {
+  if ((int64_t)2 * n_ret * ((T + kPwQ - 1) / kPwQ) > kPlanLists) return 0;
   if (chunk_start + T < 65536 || T < 2 * kPwQ || (double)n_ret * T * (double)(chunk_start + T) < 1.2e9) return 0;
   const int64_t most = std::min<int64_t>(chunk_start / 16 / kPwQ * kPwQ, kOrderMax);
   return T <= most ? (T + kPwQ - 1) / kPwQ * kPwQ : most >= 1024 ? (int)most : 0;
@@ -2867,14 +2871,12 @@ extern "C" int32_t rtp_sparse_attn_prefill(const rtp_layer_desc* layer, const vo
       a.n_slice = first;
       a.order = (int32_t*)scratch;
       a.order_on = (int32_t*)(scratch + ow.order);
-      if (2 * layer->n_ret * ((T + kPwQ - 1) / kPwQ) <= kPlanLists) {
-        char* const at = scratch + ow.order + ow.flags;
-        a.units = (int2*)at + 1;
-        a.n_units = (int32_t*)at;
-        a.list_info = (int2*)(at + ow.units);
-        a.list_ranges = (int2*)(at + ow.units + ow.info);
-        a.more_list = (int32_t*)(at + ow.units + ow.info + ow.ranges);
-      }
+      char* const at = scratch + ow.order + ow.flags;
+      a.units = (int2*)at + 1;
+      a.n_units = (int32_t*)at;
+      a.list_info = (int2*)(at + ow.units);
+      a.list_ranges = (int2*)(at + ow.units + ow.info);
+      a.more_list = (int32_t*)(at + ow.units + ow.info + ow.ranges);
       a.order_block = block;
       a.one_round = 2 * compute_units();
       scratch += ob;

@@ -1,5 +1,7 @@
 """GPU parity of the prefill path (MFMA tiles): local sink+window attention, the dense comparison,
 and the retrieval heads' chunk kernel, against the CPU oracle row by row."""
+import re
+
 import numpy as np
 import pytest
 import torch
@@ -708,3 +710,60 @@ def test_local_prefill_of_more_workgroups_than_compute_units(chunk_start, T, win
         assert abs(l[r["t"], r["h"]] - r["lse"]) < 3e-3
     local = [h for h in range(32) if h not in (1, 9, 31)]
     assert (lse[:, local] != 5.0).all() and (out[:, [1, 9, 31]] == 5.0).all()
+
+
+def _in_least_workspace(run, p):
+    """The chunk in the smallest workspace that is accepted: the kernels launched and out, lse, tau, count, mass."""
+    w = run.w
+    o, l = torch.zeros_like(run.out), torch.zeros_like(run.lse)
+    st = [torch.full_like(t, -5) for t in (run.tau, run.count, run.mass)]
+
+    def go(n_bytes):
+        ws = torch.full((n_bytes,), 0xAB, dtype=torch.uint8, device=DEV)
+        return _launches(lambda: rtp.rtp_sparse_attn_prefill(run.desc, w.q_pre if w.WQ is not None else w.qI, w.q, w.WQ, w.kI, w.N * 16, run.Kp,
+                                                             run.Vp, run.rs, run.hs, w.chunk_start, w.T, p, o, l, *st, ws))
+
+    with pytest.raises(rtp.RtpError) as e:
+        go(256)
+    assert e.value.code == rtp.RTP_ERR_WORKSPACE
+    names = go(int(re.search(r"workspace of (\d+) bytes", str(e.value)).group(1)))
+    torch.cuda.synchronize()
+    return names, (o, l, *st)
+
+
+def _check_rounded_probabilities(o, o1):
+    """Two bf16 results [.., 128] of the same set, probabilities rounded to 8 bits against different references.  A rounding is off by at most
+    2^-8 of the value, evenly spread at the worst: the difference of two has a standard deviation of at most 2^-8 sqrt(2/3) of the probability, and a
+    sum over keys with independent values that share of the row's root mean square.  Six of these, and the results' own roundings."""
+    rms = torch.maximum(o.pow(2).mean(-1, keepdim=True), o1.pow(2).mean(-1, keepdim=True)).sqrt()
+    worst = ((o - o1).abs() - 2.0 ** -7 * torch.maximum(o.abs(), o1.abs())).div(rms).max().item()
+    print(f"   differ by {worst * 256:.2f} / 256 of a row's rms", flush=True)
+    assert worst <= 6 * (2.0 / 3.0) ** 0.5 * 2.0 ** -8
+
+
+@pytest.mark.parametrize("T,planned", [(8192, True), (8193, False)])
+def test_sparse_prefill_up_to_the_lists_that_are_planned_and_past_them(T, planned):
+    """64 retrieval heads with as many queries as the attention launch's work is planned for, and one more: that call is the one of the least
+    workspace there is, bit for bit.  Rows of either end and of the middle are the oracle's."""
+    print(f"[case] sparse prefill, 64 retrieval heads, T {T}", flush=True)
+    w = wl.make_prefill("many_lists", wl.Layer(64, 8, list(range(64)), sink=4, window=256), 60000, T, 0.9, 307, DEV, zipf=1.1)
+    run = PrefillRun(w)
+    assert any("order_kernel" in n for n in _launches(run.sparse_prefill)) == planned
+    torch.cuda.synchronize()
+    full = [t.clone() for t in (run.out, run.lse, run.tau, run.count, run.mass)]
+    names, least = _in_least_workspace(run, w.p)
+    assert not any("order_kernel" in n for n in names), names
+    for what, a, b in list(zip(("out", "lse", "tau", "count", "mass"), full, least))[2 if planned else 0:]:
+        assert torch.equal(a, b) or what == "mass" and (a - b).abs().max() < 1e-6, what
+    _check_rounded_probabilities(full[0].float(), least[0].float())
+    assert (full[1] - least[1]).abs().max() < 6e-3
+    out, lse, cnt = full[0].float().cpu().numpy().astype(np.float64), full[1].cpu().numpy(), full[3].cpu().numpy()
+    rows = [(t, h) for t in (0, 255, 4100, T - 1) for h in (0, 37, 63)]
+    for r in orc.prefill_rows(rows=rows, p=float(np.float32(w.p)), **prefill_oracle_inputs(w)):
+        t, h = r["t"], r["h"]
+        k_lo, k_hi = count_range(r["scores"], float(np.float32(w.p)))
+        # (a token within 2^-17 below the threshold is kept as well)
+        near = int((np.abs(r["scores"] - r["sel"]["tau"]) <= BAND).sum())
+        assert k_lo - near <= cnt[h, t] <= k_hi + near, (t, h, cnt[h, t], r["sel"]["count"])
+        check_out(out[t, h], r["out"], f"t{t} h{h}", tight=False)
+        assert abs(lse[t, h] - r["lse"]) < 6e-3
