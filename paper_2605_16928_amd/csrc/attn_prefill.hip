@@ -1742,7 +1742,9 @@ __global__ __launch_bounds__(kPwThreads, 2) void flash_prefill_wide_kernel(const
   };
   // probabilities against the fixed reference; masked scores are -inf and give exactly 0.  Summed as rounded to 16 bits where
   // the steady loop could have run the block, unrounded where it could not: rows of few tokens live in such blocks, and their
-  // log-sum would carry the rounding (chunk of 172 tokens at position 0: 2.2e-4 instead of 1.2e-4 off).
+  // log-sum would carry the rounding (chunk of 172 tokens at position 0: 2.2e-4 instead of 1.2e-4 off).  fp16: a probability above
+  // 65504 is rounded to infinity, which the PV product takes and the unrounded sum does not show; the sum of such a block is the rounded one,
+  // i.e. infinite, so that the range is repeated in the exact pass.
   auto softmax_fixed = [&](const f32x16& S, uint32_t (&P)[8], const bool rounded) __attribute__((always_inline)) {
     const float mc = mrow * c;
     float lsum = 0.f;
@@ -1753,11 +1755,12 @@ __global__ __launch_bounds__(kPwThreads, 2) void flash_prefill_wide_kernel(const
       lsum += p0 + p1;
       P[i >> 1] = pack16<F16>(p0, p1);
     }
-    if (rounded) {                                       // (the same for the whole wave)
-      lsum = 0.f;
+    if (F16 || rounded) {                                // (the same for the whole wave)
+      float as_rounded = 0.f;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) row_sum_add(lsum, P[i]);
-      row_sum_settled(lsum);
+      for (int i = 0; i < 8; ++i) row_sum_add(as_rounded, P[i]);
+      row_sum_settled(as_rounded);
+      if (rounded || !(as_rounded < __builtin_huge_valf())) lsum = as_rounded;
     }
     lrow += lsum;
   };

@@ -601,7 +601,8 @@ def test_local_prefill_groups_by_the_tiles_of_a_band(chunk_start, T, sink, windo
     (700000, 600, (1, 2, 3), dict(index_mode="proj"), "bf16"),                   # every query keeps much: nothing to regroup
     (150000, 2100, (0, 1, 2, 3), dict(own_frac=0.97, pick_run=64, tokens_per_cluster=32768, q_noise=0.1), "bf16"),   # every one little
     (800000, 530, (1, 2, 3), dict(index_scale=2.5, p=0.999999), "bf16"),         # thresholds in the open-ended bin, sliced
-    (150000, 2081, (0, 1, 2, 3), dict(index_scale=2.5, p=0.999999), "bf16")])   # and in whole rows
+    (150000, 2081, (0, 1, 2, 3), dict(index_scale=2.5, p=0.999999), "bf16"),    # and in whole rows
+    (150000, 2113, (0, 1, 2, 3), dict(recent=9.0), "fp16")])               # some queries find the token before them far above the rest
 def test_sparse_prefill_with_regrouped_queries(chunk_start, T, heads, kw, kv_dtype):
     """Chunks behind a long prefix take their queries by how much they keep.  In the least workspace there is, they take them by
     position: the same selection, and outputs that differ by the order of fp32 sums and the rounding of probabilities to 16 bits
@@ -609,10 +610,15 @@ def test_sparse_prefill_with_regrouped_queries(chunk_start, T, heads, kw, kv_dty
     where they cancel)."""
     print(f"[case] regrouped queries, T {T} behind {chunk_start}, {heads}, {kw}, {kv_dtype}", flush=True)
     kw = dict(kw)
-    scale, p = kw.pop("index_scale", None), kw.pop("p", 0.9)
+    scale, p, recent = kw.pop("index_scale", None), kw.pop("p", 0.9), kw.pop("recent", 0.0)
     w = wl.make_prefill("regrouped", wl.Layer(8, 4, list(heads), sink=4, window=256, kv_dtype=kv_dtype), chunk_start, T, p, 211 + T, DEV, **kw)
     if scale:
         w.layer.index_scale = scale
+    for t in range(5, T, 64) if recent else ():
+        for j, h in ((0, 0), (2, 2)):                              # (two query heads to a KV head)
+            q, n = w.q[t, h].float(), chunk_start + t - 1
+            w.K[h // 2, n] = ((4.0 + recent) * 128 ** 0.5 * q / q.dot(q)).to(w.K.dtype)
+            w.kI[j, n] = (w.kI[j].float().norm(dim=-1).max() * w.qI[j, t].float() / w.qI[j, t].float().norm()).to(torch.bfloat16)
     run = PrefillRun(w)
     need = rtp.rtp_sparse_attn_prefill_workspace_bytes(run.desc, T, chunk_start)
 
@@ -767,3 +773,27 @@ def test_sparse_prefill_up_to_the_lists_that_are_planned_and_past_them(T, planne
         assert k_lo - near <= cnt[h, t] <= k_hi + near, (t, h, cnt[h, t], r["sel"]["count"])
         check_out(out[t, h], r["out"], f"t{t} h{h}", tight=False)
         assert abs(lse[t, h] - r["lse"]) < 6e-3
+
+
+@pytest.mark.parametrize("p", [0.9, 1.0])
+@pytest.mark.parametrize("above", [2.0, 4.0, 6.0, 9.0, 12.0, 20.0])
+def test_fp16_prefill_one_recent_key_far_above_the_rest(above, p):
+    """fp16 probabilities end at 65504.  One query finds one key of its own diagonal block `above` units over anything else it sees; every
+    other query is ordinary, so that no other row makes the workgroup repeat its keys."""
+    print(f"[case] fp16, one recent key {above} above, p {p}", flush=True)
+    w = wl.small_prefill("cpu", chunk_start=3000, T=70, seed=233, n_q_heads=4, n_kv_heads=2, ret_heads=(1,), kv_dtype="fp16", p=p)
+    t, n, h = 40, 3035, 1
+    q = w.q[t, h].float()
+    best = (w.K[0].float() @ q).max() / 128 ** 0.5
+    w.K[0, n] = ((best + above) * 128 ** 0.5 * q / q.dot(q)).to(w.K.dtype)
+    w.kI[0, n] = (4.0 * w.qI[0, t].float() / w.qI[0, t].float().norm()).to(torch.bfloat16)   # (kept by the query, whoever else keeps it)
+    w = w.to(DEV)
+    if p < 1.0:
+        _check_sparse_prefill(w, f"f16_recent_{above}", p)
+        return
+    run = PrefillRun(w)
+    run.sparse_prefill()
+    torch.cuda.synchronize()
+    got = run.out.float().cpu().numpy().astype(np.float64)
+    for r in orc.prefill_rows(rows=[(i, h) for i in range(w.T)], p=1.0, **prefill_oracle_inputs(w)):
+        check_out(got[r["t"], h], r["out"], f"t{r['t']}", tight="mfma")
