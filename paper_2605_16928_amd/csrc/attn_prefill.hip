@@ -1883,10 +1883,6 @@ __global__ __launch_bounds__(kPwThreads, 2) void flash_prefill_wide_kernel(const
       for (int i = 1; i < 16; ++i) mx = fmaxf(mx, S[i]);
       mrow = fmaxf(mrow, fmaxf(mx, __shfl_xor(mx, 32)));
     }
-    // fp16: a query may keep few keys of the range, all far below this tile's best, and their probabilities would be subnormal (one such
-    // query among 256, in a few hundred tiles, nearly always: the whole range was then repeated in the exact pass).  Eight octaves of the sixteen above the
-    // reference are left to scores that lie higher.  Attention launch of 2000 and 4096 queries at 128K tokens 954 -> 430, 1387 -> 868 us.
-    if (SPARSE && F16) mrow -= 8.f / c;
     if (it_lo != p_lo) mfma_S(Ls, 0, S);                 // S now holds block (it_lo, 0)
 
     // Invariant at the start of half hf of tile it: S holds the scores of that block if it is active
@@ -1995,11 +1991,16 @@ __global__ __launch_bounds__(kPwThreads, 2) void flash_prefill_wide_kernel(const
     bool bad = false;
     const float ltot = lrow + __shfl_xor(lrow, 32);
     // selecting mode: a query that kept no key of this range legitimately sums to zero
-    const bool sees_key = SPARSE ? (sel_cnt + __shfl_xor(sel_cnt, 32) > 0)
-                                 : (qok && tile_n0(it_lo) <= mq);
+    const int n_kept = SPARSE ? sel_cnt + __shfl_xor(sel_cnt, 32) : 0;
+    const bool sees_key = SPARSE ? n_kept > 0 : (qok && tile_n0(it_lo) <= mq);
     // (fp16 probabilities: nothing above 65504 -- a larger one is infinite and shows in the sum -- and a
-    // row whose largest probability is below 2^-6 has most of its mass in subnormals or flushed to zero)
-    bad = bad || (sees_key && !(ltot > (F16 ? 0x1p-6f : 0x1p-60f) && ltot < 0x1p100f));
+    // row whose largest probability is below 2^-6 may have most of its mass in subnormals.  Few kept keys may have a smaller sum: a subnormal is
+    // off by at most 2^-25, and n of those are within 2^-11 of a sum of n * 2^-14, as the rounding of n normal probabilities is.  A query
+    // that keeps a few keys of a range, all far below its first tile's best, is one of 256 in hundreds of tiles nearly always, and the whole range was
+    // repeated for it.  Attention launch at 128K tokens, 333, 2000 and 4096 queries (clusters): 365 -> 150, 1547 -> 606, 1472 -> 939 us.)
+    float least = F16 ? 0x1p-6f : 0x1p-60f;
+    if (SPARSE && F16) least = fminf(least, (float)n_kept * 0x1p-14f);
+    bad = bad || (sees_key && !(ltot > least && ltot < 0x1p100f));
     redo = __syncthreads_or(bad ? 1 : 0) != 0;
   }
 

@@ -650,10 +650,10 @@ def test_sparse_prefill_with_regrouped_queries(chunk_start, T, heads, kw, kv_dty
     assert st[1].min() >= 1
 
 
-@pytest.mark.parametrize("scale", [1.0, 24.0])
+@pytest.mark.parametrize("scale", [1.0, 2.0, 3.0, 4.0, 6.0, 10.0, 24.0])
 def test_sparse_prefill_fp16_few_kept_keys_far_from_the_first_tile(scale):
-    """fp16 probabilities against a range's reference, eight octaves below its first tile's best: queries that keep a handful of keys, with
-    scores all around it (scale 1: within +-4; 24: far above and below, where the exact pass has to take over)."""
+    """fp16 probabilities against a range's reference, its first tile's best: queries that keep a handful of keys, with scores all around it
+    (scale 1: within +-4; 2 to 4: probabilities down to subnormals; 24: far above and below, where the exact pass has to take over)."""
     print(f"[case] fp16, few kept keys, scale {scale}", flush=True)
     w = wl.small_prefill("cpu", chunk_start=3000, T=70, seed=231, n_q_heads=4, n_kv_heads=2, ret_heads=(1,), own_frac=0.99, pick_run=32, kv_dtype="fp16")
     w.q.mul_(scale)
