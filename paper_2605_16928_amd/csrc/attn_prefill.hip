@@ -2031,13 +2031,16 @@ __global__ __launch_bounds__(kPwThreads, 2) void flash_prefill_wide_kernel(const
         if (!is_active(nb0)) continue;
         if (kb == 0) mfma_S(tile, 0, S); else mfma_S(tile, 1, S);
         mask_block(S, nb0);
-        if (SPARSE) select_block(S, load_ki(nb0));
+        if (SPARSE) {
+          const int before = sel_cnt;
+          select_block(S, load_ki(nb0));
+          if (__ballot(sel_cnt != before) == 0ull) continue;      // no query of the wave keeps a key of the block
+        }
         float mx = S[0];
 #pragma unroll
         for (int i = 1; i < 16; ++i) mx = fmaxf(mx, S[i]);
         mx = fmaxf(mx, __shfl_xor(mx, 32));
         const float mnew = fmaxf(mrow, mx);
-        if (SPARSE && __ballot(mx != ninf) == 0ull) continue;     // no query of the wave keeps a key of the block
         const float msafe = mnew == ninf ? 0.f : mnew;
         const float mc = msafe * c;
         float lsum = 0.f;
