@@ -2604,15 +2604,22 @@ int32_t prefill_range_attn(const char* who, bool dense, const rtp_layer_desc* L,
   }
   return launch_prefill(who, !dense, a, B, max_ctx, s);
 }
+// What every chunk of at most n_q queries can use: a server has one workspace, and it is the short last chunk that is cut into ranges.
+// (Of the chunks with as many query tiles the longest has the most ranges and the largest ones; beyond half a workgroup per compute unit there are none.)
 size_t prefill_range_ws(const rtp_layer_desc* L, int32_t B, int32_t n_q, int64_t max_ctx) {
   if (!L || n_q <= 1 || B != 1 || L->n_q_heads <= L->n_ret) return 0;
   PrefillArgs a = {};
   a.n_heads = L->n_q_heads - L->n_ret;
-  a.n_q = n_q;
   a.sink = L->sink;
   a.window = L->window;
-  const int splits = band_splits(a, B, max_ctx);
-  return splits > 1 ? band_bytes(a.n_heads, n_q, splits) : 0;
+  size_t most = 0;
+  for (int tiles = 1; 2 * tiles * a.n_heads <= compute_units(); ++tiles) {
+    a.n_q = (int32_t)std::min<int64_t>(n_q, (int64_t)tiles * kPfQ);
+    const int splits = band_splits(a, B, max_ctx);
+    if (splits > 1) most = std::max(most, band_bytes(a.n_heads, a.n_q, splits));
+    if (a.n_q == n_q) break;
+  }
+  return most;
 }
 
 // Workgroups per 32-query group of the threshold search: as many as fill two workgroups per compute unit, each with at

@@ -385,6 +385,18 @@ def test_prefill_workspace_of_a_chunk_covers_shorter_chunks(hq, hkv, n_ret, T0, 
     assert not over, (len(over), over[:3])
 
 
+@pytest.mark.parametrize("hq,hkv,n_ret,window,T0,N", [
+    (32, 8, 4, 2048, 4096, 131405), (32, 8, 4, 8192, 1000, 131072), (8, 2, 2, 512, 8192, 20000), (64, 8, 8, 2048, 513, 6000),
+    (8, 2, 7, 100000, 4000, 4000), (32, 8, 4, 300, 2048, 9000), (32, 8, 32, 2048, 4096, 131405)])
+def test_local_workspace_of_a_chunk_covers_shorter_chunks(hq, hkv, n_ret, window, T0, N):
+    """The same for the local heads, whose band is cut into key ranges in the short chunks alone."""
+    L = _layer(n_q_heads=hq, n_kv_heads=hkv, ret_heads=list(range(n_ret)), window=window)
+    need = [rtp.rtp_local_attn_workspace_bytes(L, 1, t, N) for t in range(1, T0 + 1)]
+    over = [t for t in range(T0 - 1) if need[t] > need[-1]]
+    assert not over, (len(over), over[:3])
+    assert need == sorted(need) and all(n % 256 == 0 for n in need)
+
+
 def test_a_forked_child_asks_torch_for_the_stream_again(monkeypatch):
     """torch refuses a device that the parent initialised: the handle kept for the parent's calls must not hide that."""
     import torch
