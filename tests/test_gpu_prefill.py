@@ -593,6 +593,17 @@ def test_local_prefill_groups_by_the_tiles_of_a_band(chunk_start, T, sink, windo
         check_out(got[r["t"], r["h"]], r["out"], f"t{r['t']} h{r['h']}", tight="mfma")
 
 
+def _check_rounded_probabilities(o, o1, kv_dtype="bf16"):
+    """Two results [.., 128] of the same set, probabilities rounded to 8 bits (fp16: 11) against different references.  A rounding is off by at most
+    2^-8 of the value, evenly spread at the worst: the difference of two has a standard deviation of at most 2^-8 sqrt(2/3) of the probability, and a
+    sum over keys with independent values that share of the row's root mean square.  Six of these, and the results' own roundings."""
+    ulp = 2.0 ** (-11 if kv_dtype == "fp16" else -8)
+    rms = torch.maximum(o.pow(2).mean(-1, keepdim=True), o1.pow(2).mean(-1, keepdim=True)).sqrt()
+    worst = ((o - o1).abs() - 2 * ulp * torch.maximum(o.abs(), o1.abs())).div(rms).max().item()
+    print(f"   differ by {worst / ulp:.2f} roundings of a row's rms", flush=True)
+    assert worst <= 6 * (2.0 / 3.0) ** 0.5 * ulp
+
+
 @pytest.mark.parametrize("chunk_start,T,heads,kw,kv_dtype", [
     (1 << 20, 513, (1, 2, 3), {}, "bf16"),                                   # one query past two tiles of 256; a sliced search
     (520001, 777, (0, 2, 3), dict(own_frac=0.99, pick_run=32), "fp16"),     # three heads; a ragged last tile and group
@@ -606,8 +617,7 @@ def test_local_prefill_groups_by_the_tiles_of_a_band(chunk_start, T, sink, windo
 def test_sparse_prefill_with_regrouped_queries(chunk_start, T, heads, kw, kv_dtype):
     """Chunks behind a long prefix take their queries by how much they keep.  In the least workspace there is, they take them by
     position: the same selection, and outputs that differ by the order of fp32 sums and the rounding of probabilities to 16 bits
-    against other references (2^-8 each, of which a row's sum averages some: 2^-7 of the value, and 2^-7 of a unit-variance value
-    where they cancel)."""
+    against other references."""
     print(f"[case] regrouped queries, T {T} behind {chunk_start}, {heads}, {kw}, {kv_dtype}", flush=True)
     kw = dict(kw)
     scale, p, recent = kw.pop("index_scale", None), kw.pop("p", 0.9), kw.pop("recent", 0.0)
@@ -645,7 +655,7 @@ def test_sparse_prefill_with_regrouped_queries(chunk_start, T, heads, kw, kv_dty
     plain, o1, l1, st1 = go(hi * 256)
     assert any("order_kernel" in n for n in names) and not any("order_kernel" in n for n in plain), (names, plain)
     assert torch.equal(st[0], st1[0]) and torch.equal(st[1], st1[1]) and (st[2] - st1[2]).abs().max() < 1e-6
-    assert ((o - o1).abs() <= 2.0 ** -7 * torch.maximum(o.abs(), o1.abs()) + 2.0 ** -7).all()
+    _check_rounded_probabilities(o, o1, kv_dtype)
     assert (l - l1).abs().max() < 6e-3
     assert st[1].min() >= 1
 
@@ -735,16 +745,6 @@ def _in_least_workspace(run, p):
     names = go(int(re.search(r"workspace of (\d+) bytes", str(e.value)).group(1)))
     torch.cuda.synchronize()
     return names, (o, l, *st)
-
-
-def _check_rounded_probabilities(o, o1):
-    """Two bf16 results [.., 128] of the same set, probabilities rounded to 8 bits against different references.  A rounding is off by at most
-    2^-8 of the value, evenly spread at the worst: the difference of two has a standard deviation of at most 2^-8 sqrt(2/3) of the probability, and a
-    sum over keys with independent values that share of the row's root mean square.  Six of these, and the results' own roundings."""
-    rms = torch.maximum(o.pow(2).mean(-1, keepdim=True), o1.pow(2).mean(-1, keepdim=True)).sqrt()
-    worst = ((o - o1).abs() - 2.0 ** -7 * torch.maximum(o.abs(), o1.abs())).div(rms).max().item()
-    print(f"   differ by {worst * 256:.2f} / 256 of a row's rms", flush=True)
-    assert worst <= 6 * (2.0 / 3.0) ** 0.5 * 2.0 ** -8
 
 
 @pytest.mark.parametrize("T,planned", [(8192, True), (8193, False)])
