@@ -36,7 +36,7 @@
  *    tokens n <= q_start[b] + t (causal), and q_start[b] + n_q <= ctx_len[b] must hold.
  *  - Queries and outputs: bf16 [B, n_q, n_q_heads, 128].  Retrieval-head entry points write only the
  *    rows of retrieval heads, rtp_local_attn only the rows of the other heads, so the two may run
- *    concurrently on two streams.  `lse` (optional, fp32 [B, n_q, n_q_heads]) receives the natural-log
+ *    concurrently on two streams, each with a workspace of its own (also in prefill, see (5)).  `lse` (optional, fp32 [B, n_q, n_q_heads]) receives the natural-log
  *    sum of exponentials of the scaled logits over the attended set.
  *  - Return value: RTP_OK or a negative error code.  Every argument check happens on the host before
  *    the first launch; on error nothing has been enqueued.  rtp_last_error() gives a thread-local
@@ -213,11 +213,14 @@ int32_t rtp_sparse_attn_decode(const rtp_layer_desc* layer, const void* q,
  * inside that margin.
  * For p < 1 the attention visits only the 64-key tiles in which some query of a 256-query tile can keep a key (the
  * search leaves, per 32-query group and tile, whether a product reaches the group's thresholds); outputs, counts and
- * sums are those of visiting every tile.  In a large chunk behind a long context the groups and tiles are not of
- * neighbouring queries but of queries that keep about as much; no result depends on that but for the order of fp32 sums.
+ * sums are those of visiting every tile.  In a large chunk behind a long context (512 queries or more) the groups and tiles are
+ * not of neighbouring queries but of queries that keep about as much, if the workspace has room for their order.  Thresholds, kept sets,
+ * counts and masses do not depend on that; out and lse do, by the order of fp32 sums and by the rounding of probabilities to 16 bits
+ * against other references (bf16: by 1e-3 to 2e-3 of out's 2-norm).
  * The workspace holds that table (4 B per group and 64 keys of context),
- * the tile lists, and the key-range partials or, before them, what the launches of a short chunk's search hand on: about
- * 630 MB for T = 8192 at chunk_start = 1,040,384 with 4 retrieval heads, 40 MB for T = 4096 at 126,976, 35 MB for T = 333
+ * the tile lists, and the key-range partials or, before them, what the launches of a search in slices hand on (a short chunk's, or the last
+ * sweeps over regrouped queries, with their order): about
+ * 630 MB for T = 8192 at chunk_start = 1,040,384 with 4 retrieval heads, 74 MB for T = 4096 at 126,976, 35 MB for T = 333
  * at 131,072.  The size function answers what every chunk of at most T queries ending at chunk_start + T takes at full
  * speed, so it never answers less for a longer chunk with the same end.  A short chunk needs far less (T = 333 at
  * 131,072: 6 MB) and uses of a smaller workspace what there is, at the price of idle compute units.  p >= 1 without
@@ -252,8 +255,10 @@ int32_t rtp_sparse_attn_prefill_tile_stats(const rtp_layer_desc* layer, int32_t 
  * A query at position m attends tokens { n < sink } U { max(sink, m - window + 1) <= n <= m }.
  * Decode (q_start == NULL, n_q == 1) reads each needed K/V row once per KV head and serves the whole
  * GQA group from it; prefill (q_start != NULL) runs banded causal MFMA tiles.
- * A short chunk of one sequence cuts its bands into key ranges and keeps their partials in the workspace; a smaller
- * workspace, or none, is accepted in prefill and costs idle compute units.
+ * A short chunk of one sequence cuts its bands into key ranges and keeps their partials in the workspace, which is therefore written in
+ * prefill too: it is not one that a call on another stream works in, nor one that rtp_sparse_attn_prefill_tile_stats is still to read.  A smaller
+ * workspace, or none, is accepted in prefill and costs idle compute units; for n_q > 1 the size function answers what every chunk of at most
+ * n_q queries can use.
  * max_ctx: host upper bound of ctx_len[].
  */
 size_t rtp_local_attn_workspace_bytes(const rtp_layer_desc* layer, int32_t B, int32_t n_q, int64_t max_ctx);

@@ -560,8 +560,9 @@ constexpr int kSelAll = -1, kSelFinish = 4, kSelFirst = 5, kSelScan = 6;
 // of their queries keeps a key in.  Where queries that keep a few tokens stand among queries that keep tenths of the context, that
 // is nearly every tile for every group.  So, once the first digit of every threshold is known (and with it, from the histogram, about how many candidates
 // a query keeps), the queries of a block are brought into the order of that number, in half octaves, those that keep most first, and by position within a class; the
-// sweeps behind, the tile lists and the attention launch take them in this order.  No result depends on it but for the order
-// of fp32 sums.  Share of the key tiles that 256-query tiles visit, by position / regrouped: last 8192 queries of 1M tokens with Zipf
+// sweeps behind, the tile lists and the attention launch take them in this order.  Thresholds, kept sets, counts and masses do not depend on it;
+// outputs do by the order of fp32 sums and the rounding of probabilities to 16 bits, against a reference from other keys or, where few are kept,
+// in two parts.  Share of the key tiles that 256-query tiles visit, by position / regrouped: last 8192 queries of 1M tokens with Zipf
 // clusters 0.996 / 0.46, 4096 queries at 128K with clusters of 32 at p = 0.9 and 0.8 0.985 / 0.66 and 0.985 / 0.37, with a few hard
 // queries among easy ones 0.18 / 0.064; ten classes per decade or whole octaves instead change little (0.455, 0.48 on the first).
 // A block's order is left alone unless, for queries that keep more than 1/64, 1/256 or 1/1024 of the context, a sixteenth of its tiles
@@ -2653,8 +2654,8 @@ static int search_slices(int n_ret, int32_t T, int64_t chunk_start, size_t room)
 // 2445, 842 / 837; 3000 there 2325 / 1853, 2232 / 2219, 831 / 814; 4096 behind 98304 1994 / 1816, 1955 / 1988, 707 / 711; 1024 behind 400000 1932 / 1743,
 // 1882 / 1892, 673 / 622; on the other side of the line 4000 behind 65536 1240 / 1130, 1349 / 1394, 548 / 561; 1000 at 128K 730 / 670, 699 / 716,
 // 299 / 303.
-// (Chunks of less than 512 queries keep one result whatever their workspace: by position or by kept count, the probabilities are rounded to 16
-// bits against different references; 333 queries behind 131072 would gain 4 %.)
+// (Which of the two it is also follows from the workspace, and the probabilities are rounded to 16 bits against different references: chunks of
+// less than 512 queries are left one result whatever their workspace; 333 queries behind 131072 would gain 4 %.)
 // More lists than prefill_plan_kernel holds: by position.  Without planned units the attention's ranges are as uneven as the lists, and queries that
 // keep few keys lose their exact pass; 64 heads, 8193 queries behind 60000 tokens, ms, by position / regrouped without a plan: clusters 37.5 / 32.6, Zipf
 // clusters 36.2 / 33.5, projected queries 36.9 / 37.7, peaked 9.9 / 10.9, a few hard queries 13.6 / 15.5.
