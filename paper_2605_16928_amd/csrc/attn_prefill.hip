@@ -2081,7 +2081,8 @@ __global__ __launch_bounds__(kPwThreads, 2) void flash_prefill_wide_kernel(const
     const int64_t at = ORDERED && n_units > 0 ? (int64_t)(a.list_ranges[list].y + split) * kPwQ + wave * 32 + r
                                          : ((int64_t)split * a.n_heads + hslot) * a.n_q + tq;
     float* prow = a.part + at * kPfPart;
-    if (g == 0) { prow[0] = mfin; prow[1] = ltot; prow[2] = __int_as_float(kept); }
+    // (a sum that is not a number comes with a maximum that the merge does not take for a range without keys)
+    if (g == 0) { prow[0] = it_lo < it_hi && ltot != ltot ? 0.f : mfin; prow[1] = ltot; prow[2] = __int_as_float(kept); }
 #pragma unroll
     for (int db = 0; db < 4; ++db)
 #pragma unroll

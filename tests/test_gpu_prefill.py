@@ -800,14 +800,15 @@ def test_fp16_prefill_one_recent_key_far_above_the_rest(above, p):
 
 
 @pytest.mark.parametrize("kv_dtype", ["bf16", "fp16"])
-def test_sparse_prefill_a_kept_key_that_is_not_a_number(kv_dtype):
+@pytest.mark.parametrize("chunk_start", [500, 3000])          # one range of keys; several, of which the first holds the key
+def test_sparse_prefill_a_kept_key_that_is_not_a_number(chunk_start, kv_dtype):
     """A kept key whose scores are not a number, alone in its block of 32: its row says so (no finite log-sum, no output), whoever else is kept."""
-    print(f"[case] sparse prefill, NaN in a kept key, {kv_dtype}", flush=True)
-    w = wl.small_prefill("cpu", chunk_start=500, T=1, seed=235, n_q_heads=4, n_kv_heads=2, ret_heads=(1,), kv_dtype=kv_dtype, p=0.9)
+    print(f"[case] sparse prefill, NaN in a kept key, {chunk_start}, {kv_dtype}", flush=True)
+    w = wl.small_prefill("cpu", chunk_start=chunk_start, T=1, seed=235, n_q_heads=4, n_kv_heads=2, ret_heads=(1,), kv_dtype=kv_dtype, p=0.9)
     kept = orc.prefill_rows(rows=[(0, 1)], p=0.9, **prefill_oracle_inputs(w))[0]["sel"]["idx"]
     alone = [n for n in kept if (np.asarray(kept) // 32 == n // 32).sum() == 1]
     assert len(kept) > 1 and alone
-    w.K[0, alone[0]] = float("nan")
+    w.K[0, min(alone)] = float("nan")
     run = PrefillRun(w.to(DEV))
     run.sparse_prefill()
     torch.cuda.synchronize()
